@@ -19,68 +19,127 @@ __device__ __forceinline__ int32_t wave_max(int32_t v)
     for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
     return v;
 }
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v)
+// Over one 16-lane DPP row (quads, then rotations by 4 and 8 within the row):
+// every lane of the row receives the row's result.
+template <class Op>
+__device__ __forceinline__ int32_t row_reduce32(int32_t x, Op op)
 {
-    for (int o = 32; o > 0; o >>= 1) {
-        uint32_t lo = __shfl_xor((uint32_t)v, o, 64);
-        uint32_t hi = __shfl_xor((uint32_t)(v >> 32), o, 64);
-        v += ((uint64_t)hi << 32) | lo;
-    }
+    x = op(x, dpp::mov<dpp::kQuad1032>(x, x));
+    x = op(x, dpp::mov<dpp::kQuad2301>(x, x));
+    x = op(x, dpp::mov<dpp::kRowRor4>(x, x));
+    x = op(x, dpp::mov<dpp::kRowRor8>(x, x));
+    return x;
+}
+__device__ __forceinline__ uint64_t row_sum_u64(uint64_t v)
+{
+    v += dpp::mov64<dpp::kQuad1032>(v, v);
+    v += dpp::mov64<dpp::kQuad2301>(v, v);
+    v += dpp::mov64<dpp::kRowRor4>(v, v);
+    v += dpp::mov64<dpp::kRowRor8>(v, v);
     return v;
 }
 
-// One wavefront per polygon: MBR by min/max reduction; twice the signed area
-// as the shoelace sum of fan terms (v - v0) x (v' - v0), each exact in 128
-// bits and summed modulo 2^64 (exact whenever |area2| < 2^63); collinear iff
-// every fan term is zero.
+// A lane's share of a polygon's staging: its vertices' box and the sum modulo
+// 2^64 of its fan terms (v - v0) x (v' - v0), and whether one is not zero,
+// which 64 bits decide while the differences stay below 2^31 (else 128).
+struct Staged {
+    int32_t mnx = INT32_MAX, mny = INT32_MAX, mxx = INT32_MIN, mxy = INT32_MIN;
+    int32_t nz = 0;
+    uint64_t acc = 0;
+
+    // lane `l` of kLanes takes every kLanes-th vertex, kU in flight
+    template <int kLanes, int kU>
+    __device__ __forceinline__ void take(const int32_t *__restrict__ xy, int64_t a, int64_t b, int l)
+    {
+        const int64_t x0 = xy[2 * a], y0 = xy[2 * a + 1];
+        for (int64_t v0 = a; v0 < b; v0 += kLanes * kU) {
+            int32_t x[kU], y[kU], xn[kU], yn[kU];
+#pragma unroll
+            for (int u = 0; u < kU; u++) {
+                // past the end: the first vertex, whose fan term is zero
+                const int64_t v = v0 + kLanes * u + l < b ? v0 + kLanes * u + l : a, w = v + 1 < b ? v + 1 : a;
+                x[u] = xy[2 * v];
+                y[u] = xy[2 * v + 1];
+                xn[u] = xy[2 * w];
+                yn[u] = xy[2 * w + 1];
+            }
+#pragma unroll
+            for (int u = 0; u < kU; u++) {
+                mnx = min(mnx, x[u]); mxx = max(mxx, x[u]);
+                mny = min(mny, y[u]); mxy = max(mxy, y[u]);
+                const int64_t dx = x[u] - x0, dy = y[u] - y0, ex = xn[u] - x0, ey = yn[u] - y0;
+                const uint64_t t = (uint64_t)dx * (uint64_t)ey - (uint64_t)ex * (uint64_t)dy;
+                acc += t;
+                bool any = t != 0;
+                if (((dx + (1ll << 31)) | (dy + (1ll << 31)) | (ex + (1ll << 31)) | (ey + (1ll << 31))) >> 32)
+                    any = (__int128)dx * ey != (__int128)ex * dy;
+                nz |= any ? 1 : 0;
+            }
+        }
+    }
+    __device__ __forceinline__ void reduce_row()
+    {
+        mnx = row_reduce32(mnx, [](int32_t u, int32_t v) { return min(u, v); });
+        mny = row_reduce32(mny, [](int32_t u, int32_t v) { return min(u, v); });
+        mxx = row_reduce32(mxx, [](int32_t u, int32_t v) { return max(u, v); });
+        mxy = row_reduce32(mxy, [](int32_t u, int32_t v) { return max(u, v); });
+        nz = row_reduce32(nz, [](int32_t u, int32_t v) { return u | v; });
+        acc = row_sum_u64(acc);
+    }
+    __device__ __forceinline__ void reduce_wave()
+    {
+        mnx = wave_min32(mnx); mny = wave_min32(mny);
+        mxx = wave_max32(mxx); mxy = wave_max32(mxy);
+        nz = __ballot(nz != 0) != 0;
+        acc = (uint64_t)wave_sum_i64((int64_t)acc);
+    }
+    __device__ __forceinline__ void write(int64_t p, int64_t m, int32_t *__restrict__ mbr, int64_t *__restrict__ area2,
+                                          uint32_t *__restrict__ flags) const
+    {
+        mbr[4 * p + 0] = m > 0 ? mnx : 0; mbr[4 * p + 1] = m > 0 ? mny : 0;
+        mbr[4 * p + 2] = m > 0 ? mxx : 0; mbr[4 * p + 3] = m > 0 ? mxy : 0;
+        if (area2) area2[p] = (int64_t)acc;
+        if (!flags) return;
+        uint32_t f = 0;
+        if (m < 3) f |= kFlagFew;
+        if (!nz) f |= kFlagCollinear;
+        if (m > 0 && ((int64_t)mxx - mnx >= (1ll << 26) || (int64_t)mxy - mny >= (1ll << 26))) f |= kFlagWide;
+        flags[p] = f;
+    }
+};
+
+// MBR, twice the signed area (exact whenever |area2| < 2^63) and flags of
+// every polygon.  Bound: the latency of the chain offsets -> vertices ->
+// reductions, so four polygons share a wavefront, a 16-lane row each; one of
+// more than kRowMost vertices is taken by the whole wavefront afterwards (a
+// row alone would need 256 round trips for 8,192 vertices).  2 M polygons of
+// 22 vertices 358 us against 878 with a wavefront each.
+constexpr int kRowMost = 128;
 __global__ __launch_bounds__(256) void k_prepare(const int32_t *__restrict__ xy,
                                                  const int64_t *__restrict__ off, int64_t n,
                                                  int32_t *__restrict__ mbr,
                                                  int64_t *__restrict__ area2,
                                                  uint32_t *__restrict__ flags)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t p = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; p < n; p += nwaves) {
-        const int64_t a = off[p], b = off[p + 1], m = b - a;
-        if (m <= 0) {
-            if (lane == 0) {
-                mbr[4 * p + 0] = mbr[4 * p + 1] = mbr[4 * p + 2] = mbr[4 * p + 3] = 0;
-                if (area2) area2[p] = 0;
-                if (flags) flags[p] = kFlagFew | kFlagCollinear;
-            }
-            continue;
-        }
-        const int64_t x0 = xy[2 * a], y0 = xy[2 * a + 1];
-        int32_t mnx = INT32_MAX, mny = INT32_MAX, mxx = INT32_MIN, mxy = INT32_MIN;
-        uint64_t acc = 0;
-        bool nz = false;
-        for (int64_t v = a + lane; v < b; v += 64) {
-            const int32_t x = xy[2 * v], y = xy[2 * v + 1];
-            const int64_t w = (v + 1 == b) ? a : v + 1;
-            const int64_t xn = xy[2 * w], yn = xy[2 * w + 1];
-            mnx = min(mnx, x); mxx = max(mxx, x);
-            mny = min(mny, y); mxy = max(mxy, y);
-            const __int128 t = (__int128)((int64_t)x - x0) * (yn - y0) -
-                               (__int128)(xn - x0) * ((int64_t)y - y0);
-            acc += (uint64_t)t;
-            nz |= (t != 0);
-        }
-        mnx = wave_min(mnx); mny = wave_min(mny);
-        mxx = wave_max(mxx); mxy = wave_max(mxy);
-        acc = wave_sum_u64(acc);
-        const bool any_nz = __ballot(nz) != 0;
-        if (lane == 0) {
-            mbr[4 * p + 0] = mnx; mbr[4 * p + 1] = mny;
-            mbr[4 * p + 2] = mxx; mbr[4 * p + 3] = mxy;
-            if (area2) area2[p] = (int64_t)acc;
-            if (flags) {
-                uint32_t f = 0;
-                if (m < 3) f |= kFlagFew;
-                if (!any_nz) f |= kFlagCollinear;
-                if ((int64_t)mxx - mnx >= (1ll << 26) || (int64_t)mxy - mny >= (1ll << 26)) f |= kFlagWide;
-                flags[p] = f;
-            }
+    const int lane = threadIdx.x & 63, rl = lane & 15;
+    const int64_t step = ((int64_t)gridDim.x * blockDim.x) >> 4;
+    for (int64_t p0 = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * 4; p0 < n; p0 += step) {
+        const int64_t p = p0 + (lane >> 4);
+        const int64_t a = p < n ? off[p] : 0, b = p < n ? off[p + 1] : 0;
+        const bool big = b - a > kRowMost;
+        Staged s;
+        if (b > a && !big) s.take<16, 2>(xy, a, b, rl);
+        s.reduce_row();
+        if (p < n && !big && rl == 0) s.write(p, b - a, mbr, area2, flags);
+        uint64_t todo = __ballot(big && rl == 0);
+        while (todo) {
+            const int r = __ffsll((unsigned long long)todo) - 1;
+            todo &= todo - 1;
+            const int64_t ra = (int64_t)dpp::readlane64((uint64_t)a, r), rb = (int64_t)dpp::readlane64((uint64_t)b, r);
+            Staged w;
+            w.take<64, 4>(xy, ra, rb, lane);
+            w.reduce_wave();
+            if (lane == 0) w.write(p0 + (r >> 4), rb - ra, mbr, area2, flags);
         }
     }
 }
@@ -92,21 +151,45 @@ __global__ void k_box_init(int32_t *acc)
     }
 }
 
-__global__ __launch_bounds__(256) void k_box_of(const int32_t *__restrict__ xy, int64_t nv,
-                                                int32_t *__restrict__ acc)
+// Bound: HBM once the atomics are few: one set a 1,024-thread workgroup and a
+// workgroup a CU (one set a wavefront from 4,096 workgroups, 65,536 atomics on
+// one line, took 750 us where the 8.6 M vertices' bytes take 15).
+constexpr int kBoxThreads = 1024;
+__global__ __launch_bounds__(kBoxThreads) void k_box_of(const int32_t *__restrict__ xy, int64_t nv,
+                                                        int32_t *__restrict__ acc)
 {
+    __shared__ int32_t s_r[4][kBoxThreads / 64];
     int32_t mnx = INT32_MAX, mny = INT32_MAX, mxx = INT32_MIN, mxy = INT32_MIN;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < nv;
-         v += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t x = xy[2 * v], y = xy[2 * v + 1];
-        mnx = min(mnx, x); mxx = max(mxx, x);
-        mny = min(mny, y); mxy = max(mxy, y);
+    constexpr int kU = 4;
+    const int64_t step = (int64_t)gridDim.x * kBoxThreads;
+    for (int64_t v0 = (int64_t)blockIdx.x * kBoxThreads + threadIdx.x; v0 < nv; v0 += step * kU) {
+        int32_t x[kU], y[kU];
+#pragma unroll
+        for (int u = 0; u < kU; u++) {
+            const int64_t v = v0 + u * step < nv ? v0 + u * step : v0;
+            x[u] = xy[2 * v];
+            y[u] = xy[2 * v + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; u++) {
+            mnx = min(mnx, x[u]); mxx = max(mxx, x[u]);
+            mny = min(mny, y[u]); mxy = max(mxy, y[u]);
+        }
     }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     mnx = wave_min(mnx); mny = wave_min(mny);
     mxx = wave_max(mxx); mxy = wave_max(mxy);
-    if ((threadIdx.x & 63) == 0) {
-        atomicMin(acc + 0, mnx); atomicMin(acc + 1, mny);
-        atomicMax(acc + 2, mxx); atomicMax(acc + 3, mxy);
+    if (lane == 0) {
+        s_r[0][wave] = mnx; s_r[1][wave] = mny;
+        s_r[2][wave] = mxx; s_r[3][wave] = mxy;
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        const int c = threadIdx.x;
+        int32_t r = s_r[c][0];
+        for (int w = 1; w < kBoxThreads / 64; w++) r = c < 2 ? min(r, s_r[c][w]) : max(r, s_r[c][w]);
+        if (c < 2) atomicMin(acc + c, r);
+        else atomicMax(acc + c, r);
     }
 }
 
@@ -213,8 +296,8 @@ polymh_status launch_prepare(const int32_t *xy, const int64_t *off, int64_t n, i
                              int64_t *area2, uint32_t *flags, hipStream_t s)
 {
     if (n == 0) return POLYMH_OK;
-    // 4 polygons (waves) per 256-thread block
-    hipLaunchKernelGGL(k_prepare, dim3(grid_for(n, 4, 1 << 16)), dim3(256), 0, s, xy, off, n, mbr,
+    // 16 polygons (rows of 16 lanes) per 256-thread block
+    hipLaunchKernelGGL(k_prepare, dim3(grid_for(n, 16, 1 << 16)), dim3(256), 0, s, xy, off, n, mbr,
                        area2, flags);
     return check_launch("prepare");
 }
@@ -223,7 +306,8 @@ polymh_status launch_box_of(const int32_t *xy, int64_t nv, int32_t *acc4, hipStr
 {
     hipLaunchKernelGGL(k_box_init, dim3(1), dim3(64), 0, s, acc4);
     if (nv > 0)
-        hipLaunchKernelGGL(k_box_of, dim3(grid_for(nv, 256, 4096)), dim3(256), 0, s, xy, nv, acc4);
+        hipLaunchKernelGGL(k_box_of, dim3(grid_for(nv, kBoxThreads, cu_count())), dim3(kBoxThreads), 0, s, xy, nv,
+                           acc4);
     return check_launch("box_of");
 }
 
