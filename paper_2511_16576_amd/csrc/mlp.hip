@@ -2,14 +2,17 @@
 // sigmoid) with BF16 weights and activations on the MFMA units, FP32
 // accumulation, MSE loss and Adam on FP32 master weights.
 //
-// Products run on v_mfma_f32_32x32x16_bf16: one wavefront owns a 32 x 32 tile
+// Products run on v_mfma_f32_32x32x16_bf16: one wavefront owns 32 x 32 tiles
 // of the output and walks K in steps of 16.  Operand fragments: lane l holds
 // row (l % 32) of A and column (l % 32) of B, for the 8 consecutive k values
 // 8*(l / 32) .. 8*(l / 32) + 7 of the step; result element r of lane l is
-// row 8*(r / 4) + 4*(l / 32) + r % 4, column l % 32.  Operands are read with
-// arbitrary strides so the forward (X W^T), the input gradient (dZ W) and the
-// weight gradient (dZ^T H) share the kernel; when k is the contiguous index
-// a lane reads its 8 values with one 16-byte load.
+// row 8*(r / 4) + 4*(l / 32) + r % 4, column l % 32.
+//
+// The layers of a 32-row tile of the batch never leave the chip between their
+// products: k_mlp_forward runs both hidden layers and the output of a tile
+// (each wavefront keeps its 32 hidden units' weights in registers, as the
+// fused inference does) and k_mlp_back the way back to the first layer's
+// pre-activations; k_wgrad then reduces the weight gradients over the batch.
 #include "internal.hpp"
 #include "scorer_common.hpp"
 
@@ -44,19 +47,14 @@ __device__ __forceinline__ bf16x8 frag(const Operand &o, int64_t row, int64_t k)
     }
 }
 
-enum Epi { kStoreF32 = 0, kBiasGelu = 1, kGeluGrad = 2, kAccF32 = 3 };
-
 struct GemmArgs {
     Operand A, B;
     int64_t M, N, K;   // M, N multiples of 32; K multiple of 16
-    int epi;
-    float *outf;       // kStoreF32/kAccF32: C; kBiasGelu: z; kGeluGrad: dz (fp32)
-    __bf16 *outb;      // kBiasGelu: h = gelu(z); kGeluGrad: dz (bf16)
-    const float *bias; // kBiasGelu
-    const float *zin;  // kGeluGrad: the pre-activation z
-    int64_t ldo;       // leading dimension of the outputs
+    float *out;
 };
 
+// C = A B with arbitrary strides (the exported product): one wavefront a
+// 32 x 32 tile, operands from memory.
 template <bool AKC, bool BKC>
 __global__ __launch_bounds__(256) void k_gemm(GemmArgs g)
 {
@@ -76,148 +74,374 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g)
 #pragma unroll
     for (int r = 0; r < 16; r++) {
         const int64_t i = i0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int64_t o = i * g.ldo + col;
-        const float c = acc[r];
-        if (g.epi == kStoreF32) {
-            g.outf[o] = c;
-        } else if (g.epi == kAccF32) {
-            g.outf[o] += c;
-        } else if (g.epi == kBiasGelu) {
-            const float z = c + g.bias[col];
-            g.outf[o] = z;
-            g.outb[o] = to_bf16(gelu(z));
-        } else {
-            const float d = c * gelu_grad(g.zin[o]);
-            g.outf[o] = d;
-            g.outb[o] = to_bf16(d);
-        }
+        g.out[i * g.N + col] = acc[r];
     }
 }
 
-// Split-K form of the product for the weight gradients, whose M x N output
-// is a few dozen tiles while K is the whole batch (one wavefront a tile
-// would leave the chip nearly idle): split s (blockIdx.y) reduces over
-// [s kc, min(K, (s + 1) kc)) and writes its partial tile to part[s][M][N];
-// k_split_sum then adds the splits in order, so the result is deterministic.
-template <bool AKC, bool BKC>
-__global__ __launch_bounds__(256) void k_gemm_part(GemmArgs g, int64_t kc, float *__restrict__ part)
+// Parameter block (FP32 master): W1[256][288], b1[256], W2[256][256], b2[256], w3[256], b3.
+constexpr int64_t kOffW1 = 0, kOffB1 = kOffW1 + (int64_t)kHid * kIn, kOffW2 = kOffB1 + kHid,
+                  kOffB2 = kOffW2 + (int64_t)kHid * kHid, kOffW3 = kOffB2 + kHid, kOffB3 = kOffW3 + kHid,
+                  kNParams = kOffB3 + 1;
+// BF16 copies: W1 then W2.
+constexpr int64_t kNBf16 = (int64_t)kHid * kIn + (int64_t)kHid * kHid;
+
+constexpr int kTile = 32;                        // batch rows of a tile
+constexpr int kTileThreads = 512, kTileWaves = kTileThreads / 64;
+constexpr int kXStride = kIn + 8, kHStride = kHid + 8;   // LDS row strides (16-byte multiples)
+constexpr int kK1 = kIn / 16, kK2 = kHid / 16;
+constexpr int kXChunks = kTile * kIn / 8, kHChunks = kTile * kHid / 8;   // 16-byte pieces of a tile
+
+// z += row tile [32][ld] (LDS) x w, a wavefront's 32 columns over K steps.
+template <int K>
+__device__ __forceinline__ f32x16 tile_product(const __bf16 *rows, int ld, const bf16x8 (&w)[K], int lane)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t tiles_n = g.N / 32;
-    const int64_t tile = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (tile >= (g.M / 32) * tiles_n) return;
-    const int64_t i0 = (tile / tiles_n) * 32, j0 = (tile % tiles_n) * 32;
-    const int64_t row = i0 + (lane & 31), col = j0 + (lane & 31);
-    const int64_t kl = 8 * (lane >> 5);
-    const int64_t k_lo = (int64_t)blockIdx.y * kc, k_hi = min(g.K, k_lo + kc);
     f32x16 acc = {};
-    for (int64_t k0 = k_lo; k0 < k_hi; k0 += 16) {
-        const bf16x8 a = frag<AKC>(g.A, row, k0 + kl);
-        const bf16x8 b = frag<BKC>(g.B, col, k0 + kl);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-    }
-    float *out = part + (int64_t)blockIdx.y * g.M * g.N;
+    const __bf16 *a = rows + (lane & 31) * ld + 8 * (lane >> 5);
 #pragma unroll
-    for (int r = 0; r < 16; r++) {
-        const int64_t i = i0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        out[i * g.N + col] = acc[r];
+    for (int ks = 0; ks < K; ks++)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(a + 16 * ks), w[ks], acc, 0, 0,
+                                                      0);
+    return acc;
+}
+// A 32 x 256 BF16 tile from LDS to rows r0 .. of out [.][256], 16 bytes a lane.
+__device__ __forceinline__ void store_tile(const __bf16 *tile, __bf16 *__restrict__ out, int64_t r0)
+{
+    for (int c = threadIdx.x; c < kHChunks; c += kTileThreads) {
+        const int r = c / (kHid / 8), k = c % (kHid / 8);
+        *reinterpret_cast<uint4 *>(out + (r0 + r) * kHid + 8 * k) =
+            *reinterpret_cast<const uint4 *>(tile + r * kHStride + 8 * k);
     }
 }
 
-__global__ __launch_bounds__(256) void k_split_sum(const float *__restrict__ part, int nsplit, int64_t M,
-                                                   int64_t N, float *__restrict__ out, int64_t ldo)
+// sum_j h[j] w3[j] over a row of 256 in LDS, one wavefront a row.
+__device__ __forceinline__ float row_dot(const __bf16 *h, const float (&w3)[kHid / 64], int lane)
 {
-    const int64_t mn = M * N;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < mn;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        float v = 0.f;
-        for (int s = 0; s < nsplit; s++) v += part[s * mn + e];
-        const int64_t i = e / N;
-        out[i * ldo + (e - i * N)] = v;
-    }
-}
-
-// Output layer and loss gradient: y = sigmoid(h2 . w3 + b3); with labels,
-// dz3 = 2 (y - J) / B * y (1 - y) and dH2 = dz3 w3^T (bf16, before GELU').
-__global__ __launch_bounds__(256) void k_head(const __bf16 *__restrict__ h2, const float *__restrict__ w3,
-                                              const float *__restrict__ b3, int64_t B,
-                                              float *__restrict__ y, const float *__restrict__ label,
-                                              float *__restrict__ dz3, float *__restrict__ loss)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (r >= B) return;
     float s = 0.f;
-    for (int j = lane; j < kHid; j += 64) s += (float)h2[r * kHid + j] * w3[j];
+#pragma unroll
+    for (int i = 0; i < kHid / 64; i++) s += (float)h[lane + 64 * i] * w3[i];
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    const float yy = 1.0f / (1.0f + expf(-(s + b3[0])));
-    if (lane == 0) {
-        y[r] = yy;
-        if (label) {
-            const float e = yy - label[r];
-            dz3[r] = 2.0f * e / (float)B * yy * (1.0f - yy);
-            atomicAdd(loss, e * e / (float)B);
+    return s;
+}
+
+// Both hidden layers and the output of 32 rows at a time: z1 = X W1^T + b1,
+// h1 = gelu(z1), z2 = h1 W2^T + b2, h2 = gelu(z2), y = sigmoid(h2 . w3 + b3),
+// all kept for the backward pass.  One workgroup a CU; the next tile's rows
+// are loaded while a tile runs.  Bound: the 512 GELUs a row (VALU) and the 3
+// KB a row that the activations take.
+__global__ __launch_bounds__(kTileThreads) void k_mlp_forward(const __bf16 *__restrict__ X, int64_t tiles,
+                                                              const float *__restrict__ params,
+                                                              const __bf16 *__restrict__ wbf16,
+                                                              float *__restrict__ z1, __bf16 *__restrict__ h1,
+                                                              float *__restrict__ z2, __bf16 *__restrict__ h2,
+                                                              float *__restrict__ y)
+{
+    __shared__ __attribute__((aligned(16))) __bf16 s_x[kTile * kXStride];
+    __shared__ __attribute__((aligned(16))) __bf16 s_h1[kTile * kHStride];
+    __shared__ __attribute__((aligned(16))) __bf16 s_h2[kTile * kHStride];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = 32 * wave + (lane & 31), kl = 8 * (lane >> 5);
+    constexpr int kPer = (kXChunks + kTileThreads - 1) / kTileThreads;
+    uint4 xv[kPer];
+    auto load_x = [&](int64_t t) {
+        const uint4 *src = reinterpret_cast<const uint4 *>(X + t * kTile * kIn);
+#pragma unroll
+        for (int i = 0; i < kPer; i++)
+            if (tid + i * kTileThreads < kXChunks) xv[i] = src[tid + i * kTileThreads];
+    };
+    int64_t t = blockIdx.x;
+    if (t >= tiles) return;
+    load_x(t);
+    const __bf16 *W1 = wbf16, *W2 = wbf16 + (int64_t)kHid * kIn;
+    bf16x8 w1[kK1], w2[kK2];
+#pragma unroll
+    for (int ks = 0; ks < kK1; ks++)
+        w1[ks] = *reinterpret_cast<const bf16x8 *>(W1 + (int64_t)col * kIn + 16 * ks + kl);
+#pragma unroll
+    for (int ks = 0; ks < kK2; ks++)
+        w2[ks] = *reinterpret_cast<const bf16x8 *>(W2 + (int64_t)col * kHid + 16 * ks + kl);
+    const float b1c = params[kOffB1 + col], b2c = params[kOffB2 + col], b3 = params[kOffB3];
+    float w3[kHid / 64];
+#pragma unroll
+    for (int i = 0; i < kHid / 64; i++) w3[i] = params[kOffW3 + lane + 64 * i];
+    for (; t < tiles; t += gridDim.x) {
+        const int64_t r0 = t * kTile;
+#pragma unroll
+        for (int i = 0; i < kPer; i++) {
+            const int c = tid + i * kTileThreads;
+            if (c < kXChunks) *reinterpret_cast<uint4 *>(s_x + (c / (kIn / 8)) * kXStride + 8 * (c % (kIn / 8))) = xv[i];
         }
+        if (t + gridDim.x < tiles) load_x(t + gridDim.x);
+        __syncthreads();
+        f32x16 acc = tile_product(s_x, kXStride, w1, lane);
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+            const int row = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+            const float z = acc[e] + b1c;
+            z1[(r0 + row) * kHid + col] = z;
+            s_h1[row * kHStride + col] = to_bf16(gelu(z));
+        }
+        __syncthreads();
+        store_tile(s_h1, h1, r0);
+        acc = tile_product(s_h1, kHStride, w2, lane);
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+            const int row = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+            const float z = acc[e] + b2c;
+            z2[(r0 + row) * kHid + col] = z;
+            s_h2[row * kHStride + col] = to_bf16(gelu(z));
+        }
+        __syncthreads();
+        store_tile(s_h2, h2, r0);
+#pragma unroll
+        for (int u = 0; u < kTile / kTileWaves; u++) {
+            const int row = wave + kTileWaves * u;
+            const float s = row_dot(s_h2 + row * kHStride, w3, lane);
+            if (lane == 0) y[r0 + row] = 1.0f / (1.0f + expf(-(s + b3)));
+        }
+        // s_x is written next by threads past the first product; s_h2's
+        // readers are past before its next writes, two barriers on
     }
 }
 
-// dH2[r, j] = dz3[r] * w3[j] as bf16 (operand of the next product is the
-// GELU' scaling, fused into the elementwise pass below).
-__global__ __launch_bounds__(256) void k_head_back(const float *__restrict__ dz3, const float *__restrict__ w3,
-                                                   const float *__restrict__ z2, int64_t B,
-                                                   float *__restrict__ dz2f, __bf16 *__restrict__ dz2b)
+// W2^T in BF16, the operand of the backward product.
+__global__ __launch_bounds__(256) void k_transpose_w2(const __bf16 *__restrict__ w2, __bf16 *__restrict__ w2t)
 {
-    const int64_t total = B * kHid;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = i / kHid;
-        const int j = (int)(i - r * kHid);
-        const float d = dz3[r] * w3[j] * gelu_grad(z2[i]);
-        dz2f[i] = d;
-        dz2b[i] = to_bf16(d);
-    }
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kHid * kHid; i += gridDim.x * blockDim.x)
+        w2t[i] = w2[(i % kHid) * kHid + i / kHid];
 }
 
-// Column sums over the batch: out[j] = sum_r M[r, j] (bias gradients) and,
-// for the output layer, dw3[j] = sum_r dz3[r] h2[r, j].
-__global__ __launch_bounds__(256) void k_colsum(const float *__restrict__ m, int64_t B, int ncol,
-                                                float *__restrict__ out)
+// Partial sums of a workgroup of k_mlp_back over its rows: columns' db1, db2
+// and dw3, then db3 and the loss.
+constexpr int kBackItems = 3 * kHid + 2;
+
+// From the loss back to the first layer's pre-activations, 32 rows at a time:
+// y and dz3 = 2 (y - label) / B y (1 - y) from h2, dz2 = dz3 w3 gelu'(z2),
+// dz1 = (dz2 W2) gelu'(z1); dz2 and dz1 in BF16 for the weight gradients, the
+// column sums of the FP32 values and the loss as a workgroup's partials.
+__global__ __launch_bounds__(kTileThreads) void k_mlp_back(int64_t tiles, int64_t B, const float *__restrict__ params,
+                                                           const __bf16 *__restrict__ w2t,
+                                                           const float *__restrict__ z1, const float *__restrict__ z2,
+                                                           const __bf16 *__restrict__ h2,
+                                                           const float *__restrict__ label, float *__restrict__ y,
+                                                           __bf16 *__restrict__ dz1, __bf16 *__restrict__ dz2,
+                                                           float *__restrict__ part)
 {
-    const int j = blockIdx.x;
-    float s = 0.f;
-    for (int64_t r = threadIdx.x; r < B; r += blockDim.x) s += m[r * ncol + j];
-    __shared__ float sh[256];
-    sh[threadIdx.x] = s;
+    __shared__ __attribute__((aligned(16))) __bf16 s_d2[kTile * kHStride];
+    __shared__ __attribute__((aligned(16))) __bf16 s_d1[kTile * kHStride];
+    __shared__ float s_dz3[kTile], s_loss[kTile];
+    __shared__ float s_sum[3][2][kHid];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = 32 * wave + (lane & 31), kl = 8 * (lane >> 5);
+    bf16x8 w[kK2];
+#pragma unroll
+    for (int ks = 0; ks < kK2; ks++)
+        w[ks] = *reinterpret_cast<const bf16x8 *>(w2t + (int64_t)col * kHid + 16 * ks + kl);
+    float w3[kHid / 64];
+#pragma unroll
+    for (int i = 0; i < kHid / 64; i++) w3[i] = params[kOffW3 + lane + 64 * i];
+    const float b3 = params[kOffB3];
+    const int vc = tid & (kHid - 1), half = tid / kHid;   // column phase: a column, 16 of the 32 rows
+    const float w3c = params[kOffW3 + vc];
+    float db1 = 0.f, db2 = 0.f, dw3 = 0.f, db3 = 0.f, loss = 0.f;
+    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const int64_t r0 = t * kTile;
+        float zz1[16];
+#pragma unroll
+        for (int e = 0; e < 16; e++)
+            zz1[e] = z1[(r0 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)) * kHid + col];
+#pragma unroll
+        for (int u = 0; u < kTile / kTileWaves; u++) {
+            const int row = wave + kTileWaves * u;
+            const float s = row_dot(h2 + (r0 + row) * kHid, w3, lane);
+            if (lane == 0) {
+                const float yy = 1.0f / (1.0f + expf(-(s + b3)));
+                const float e = yy - label[r0 + row];
+                y[r0 + row] = yy;
+                s_dz3[row] = 2.0f * e / (float)B * yy * (1.0f - yy);
+                s_loss[row] = e * e / (float)B;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kTile / 2; u++) {
+            const int row = kTile / 2 * half + u;
+            const int64_t i = (r0 + row) * kHid + vc;
+            const float d = s_dz3[row] * w3c * gelu_grad(z2[i]);
+            db2 += d;
+            dw3 += s_dz3[row] * (float)h2[i];
+            s_d2[row * kHStride + vc] = to_bf16(d);
+        }
+        if (tid == 0)
+            for (int r = 0; r < kTile; r++) {
+                db3 += s_dz3[r];
+                loss += s_loss[r];
+            }
+        __syncthreads();
+        store_tile(s_d2, dz2, r0);
+        const f32x16 acc = tile_product(s_d2, kHStride, w, lane);
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+            const int row = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+            const float d = acc[e] * gelu_grad(zz1[e]);
+            db1 += d;
+            s_d1[row * kHStride + col] = to_bf16(d);
+        }
+        __syncthreads();
+        store_tile(s_d1, dz1, r0);
+    }
+    s_sum[0][lane >> 5][col] = db1;
+    s_sum[1][half][vc] = db2;
+    s_sum[2][half][vc] = dw3;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
+    float *out = part + (int64_t)blockIdx.x * kBackItems;
+    for (int i = tid; i < 3 * kHid; i += kTileThreads) out[i] = s_sum[i / kHid][0][i % kHid] + s_sum[i / kHid][1][i % kHid];
+    if (tid == 0) {
+        out[3 * kHid] = db3;
+        out[3 * kHid + 1] = loss;
+    }
+}
+
+// Weight gradients dW2 = dz2^T h1 and dW1 = dz1^T X, reductions over the
+// whole batch with outputs of a few dozen tiles: split over the rows
+// (blockIdx.x, kc rows each, partials added in order by k_grad_sum, so the
+// gradient is deterministic), over 64 output rows (blockIdx.y) and over the
+// two products (blockIdx.z), so that 8,192 rows occupy 256 workgroups.  Both
+// operands have the batch as the reduction index, which is their slow one:
+// 64 rows at a time are transposed into LDS (a thread takes two columns of
+// eight rows), where a lane's eight k values are one 16-byte read.  Four
+// wavefronts: 32 output rows by half the output columns each.
+constexpr int kGradRows = 64;                       // batch rows a step
+constexpr int kGradStride = kGradRows + 8;
+constexpr int kMaxSplit = 32;
+constexpr int64_t kW2Size = (int64_t)kHid * kHid, kW1Size = (int64_t)kHid * kIn;
+
+template <int N>
+__device__ __forceinline__ void wgrad(const __bf16 *__restrict__ dz, const __bf16 *__restrict__ in, int64_t B,
+                                      int64_t kc, float *__restrict__ out, __bf16 *s_a, __bf16 *s_b)
+{
+    constexpr int kGroups = kGradRows / 8;
+    constexpr int kItems = N / 2 * kGroups, kPer = (kItems + 255) / 256;
+    constexpr int kMost = (N / 32 + 1) / 2;         // output tiles of a wavefront
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wo = wave & 1, t0 = (wave >> 1) * kMost, nt = min(kMost, N / 32 - t0);
+    const int o0 = 64 * blockIdx.y;
+    const int64_t lo = (int64_t)blockIdx.x * kc, hi = min(B, lo + kc);
+    uint32_t av[8], bv[kPer][8];
+    auto load = [&](int64_t k0) {
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            const int64_t r = k0 + 8 * (tid >> 5) + u;
+            av[u] = r < hi ? *reinterpret_cast<const uint32_t *>(dz + r * kHid + o0 + 2 * (tid & 31)) : 0u;
+        }
+#pragma unroll
+        for (int i = 0; i < kPer; i++) {
+            const int w = tid + 256 * i, c = w % (N / 2), g = w / (N / 2);
+#pragma unroll
+            for (int u = 0; u < 8; u++) {
+                const int64_t r = k0 + 8 * g + u;
+                bv[i][u] = w < kItems && r < hi ? *reinterpret_cast<const uint32_t *>(in + r * N + 2 * c) : 0u;
+            }
+        }
+    };
+    // two columns of eight rows as two 16-byte rows of the transposed tile
+    auto put = [](__bf16 *s, int c, int g, const uint32_t (&v)[8]) {
+        uint4 e, o;
+        e.x = (v[0] & 0xffffu) | v[1] << 16; o.x = v[0] >> 16 | (v[1] & 0xffff0000u);
+        e.y = (v[2] & 0xffffu) | v[3] << 16; o.y = v[2] >> 16 | (v[3] & 0xffff0000u);
+        e.z = (v[4] & 0xffffu) | v[5] << 16; o.z = v[4] >> 16 | (v[5] & 0xffff0000u);
+        e.w = (v[6] & 0xffffu) | v[7] << 16; o.w = v[6] >> 16 | (v[7] & 0xffff0000u);
+        *reinterpret_cast<uint4 *>(s + 2 * c * kGradStride + 8 * g) = e;
+        *reinterpret_cast<uint4 *>(s + (2 * c + 1) * kGradStride + 8 * g) = o;
+    };
+    f32x16 acc[kMost] = {};
+    load(lo);
+    for (int64_t k0 = lo; k0 < hi; k0 += kGradRows) {
+        put(s_a, tid & 31, tid >> 5, av);
+#pragma unroll
+        for (int i = 0; i < kPer; i++) {
+            const int w = tid + 256 * i;
+            if (w < kItems) put(s_b, w % (N / 2), w / (N / 2), bv[i]);
+        }
+        __syncthreads();
+        if (k0 + kGradRows < hi) load(k0 + kGradRows);
+        const __bf16 *a = s_a + (32 * wo + (lane & 31)) * kGradStride + 8 * (lane >> 5);
+        const __bf16 *b = s_b + (32 * t0 + (lane & 31)) * kGradStride + 8 * (lane >> 5);
+#pragma unroll
+        for (int ks = 0; ks < kGradRows / 16; ks++) {
+            const bf16x8 fa = *reinterpret_cast<const bf16x8 *>(a + 16 * ks);
+#pragma unroll
+            for (int j = 0; j < kMost; j++)
+                if (j < nt)
+                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        fa, *reinterpret_cast<const bf16x8 *>(b + 32 * j * kGradStride + 16 * ks), acc[j], 0, 0, 0);
+        }
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[j] = sh[0];
+#pragma unroll
+    for (int j = 0; j < kMost; j++)
+        if (j < nt)
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                const int row = o0 + 32 * wo + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+                out[(int64_t)row * N + 32 * (t0 + j) + (lane & 31)] = acc[j][e];
+            }
 }
 
-__global__ __launch_bounds__(256) void k_head_grads(const float *__restrict__ dz3, const __bf16 *__restrict__ h2,
-                                                    int64_t B, float *__restrict__ dw3, float *__restrict__ db3)
+__global__ __launch_bounds__(256, 2) void k_wgrad(const __bf16 *__restrict__ dz1, const __bf16 *__restrict__ dz2,
+                                               const __bf16 *__restrict__ X, const __bf16 *__restrict__ h1, int64_t B,
+                                               int64_t kc, float *__restrict__ part)
 {
-    const int j = blockIdx.x;  // 0..kHid (kHid = the bias)
-    float s = 0.f;
-    for (int64_t r = threadIdx.x; r < B; r += blockDim.x) s += dz3[r] * (j < kHid ? (float)h2[r * kHid + j] : 1.0f);
-    __shared__ float sh[256];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        if (j < kHid) dw3[j] = sh[0];
-        else db3[0] = sh[0];
-    }
+    __shared__ __attribute__((aligned(16))) __bf16 s_a[64 * kGradStride];
+    __shared__ __attribute__((aligned(16))) __bf16 s_b[kIn * kGradStride];
+    float *out = part + (int64_t)blockIdx.x * (kW1Size + kW2Size);
+    if (blockIdx.z == 0) wgrad<kIn>(dz1, X, B, kc, out, s_a, s_b);
+    else wgrad<kHid>(dz2, h1, B, kc, out + kW1Size, s_a, s_b);
 }
 
+// The partials' sums, each in the order of the splits: the weight gradients
+// (one thread an entry), then the biases', w3's gradients and the loss (eight
+// threads an item, each a run of the partials).
+__global__ __launch_bounds__(256) void k_grad_sum(const float *__restrict__ wpart, int nsplit,
+                                                  const float *__restrict__ bpart, int nback, int wblocks,
+                                                  float *__restrict__ grad, float *__restrict__ loss)
+{
+    constexpr int64_t kSize = kW1Size + kW2Size;
+    if ((int)blockIdx.x < wblocks) {
+        const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+        if (e >= kSize) return;
+        float v = 0.f;
+#pragma unroll 8
+        for (int s = 0; s < nsplit; s++) v += wpart[s * kSize + e];
+        grad[e < kW1Size ? kOffW1 + e : kOffW2 + e - kW1Size] = v;
+        return;
+    }
+    __shared__ float s_v[8][32];
+    const int item = 32 * ((int)blockIdx.x - wblocks) + (threadIdx.x & 31), g = threadIdx.x >> 5;
+    const int run = (nback + 7) / 8;
+    float v = 0.f;
+    if (item < kBackItems) {
+#pragma unroll 8
+        for (int s = g * run; s < min(nback, (g + 1) * run); s++) v += bpart[(int64_t)s * kBackItems + item];
+    }
+    s_v[g][threadIdx.x & 31] = v;
+    __syncthreads();
+    if (g != 0 || item >= kBackItems) return;
+    for (int i = 1; i < 8; i++) v += s_v[i][threadIdx.x & 31];
+    if (item < kHid) grad[kOffB1 + item] = v;
+    else if (item < 2 * kHid) grad[kOffB2 + item - kHid] = v;
+    else if (item < 3 * kHid) grad[kOffW3 + item - 2 * kHid] = v;
+    else if (item == 3 * kHid) grad[kOffB3] = v;
+    else *loss = v;
+}
+
+// One Adam step, and the BF16 copy of the weights it moved.
 __global__ __launch_bounds__(256) void k_adam(float *__restrict__ p, const float *__restrict__ g,
                                               float *__restrict__ m, float *__restrict__ v, int64_t n,
-                                              float lr, float b1, float b2, float eps, float c1, float c2)
+                                              float lr, float b1, float b2, float eps, float c1, float c2,
+                                              __bf16 *__restrict__ wbf16)
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
@@ -226,7 +450,10 @@ __global__ __launch_bounds__(256) void k_adam(float *__restrict__ p, const float
         const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
         m[i] = mi;
         v[i] = vi;
-        p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+        const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+        p[i] = pi;
+        if (i < kOffB1) wbf16[i] = to_bf16(pi);
+        else if (i >= kOffW2 && i < kOffB2) wbf16[i - kOffW2 + kW1Size] = to_bf16(pi);
     }
 }
 
@@ -235,13 +462,6 @@ __global__ __launch_bounds__(256) void k_to_bf16(const float *__restrict__ x, __
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
         y[i] = to_bf16(x[i]);
-}
-
-__global__ void k_zero_f32(float *p, int64_t n)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0.f;
 }
 
 int grid_of(int64_t items, int per)
@@ -266,39 +486,7 @@ polymh_status gemm(const GemmArgs &g, hipStream_t s)
     return check_launch("mlp gemm");
 }
 
-// At most kMaxSplit splits of at least kMinSplitK reduction steps each.
-constexpr int kMaxSplit = 64, kMinSplitK = 256;
-
-// The product as split-K with plain FP32 stores (the weight gradients);
-// part holds kMaxSplit x M x N floats.
-polymh_status gemm_split(const GemmArgs &g, float *part, hipStream_t s)
-{
-    const int64_t tiles = (g.M / 32) * (g.N / 32);
-    if (tiles == 0) return POLYMH_OK;
-    int64_t kc = (g.K + kMaxSplit - 1) / kMaxSplit;
-    kc = std::max<int64_t>(kMinSplitK, (kc + 15) / 16 * 16);
-    const int nsplit = (int)std::max<int64_t>(1, (g.K + kc - 1) / kc);
-    const dim3 grid((unsigned)((tiles + 3) / 4), (unsigned)nsplit), block(256);
-    const bool akc = g.A.sk == 1, bkc = g.B.sk == 1;
-    if (akc && bkc) hipLaunchKernelGGL((k_gemm_part<true, true>), grid, block, 0, s, g, kc, part);
-    else if (akc) hipLaunchKernelGGL((k_gemm_part<true, false>), grid, block, 0, s, g, kc, part);
-    else if (bkc) hipLaunchKernelGGL((k_gemm_part<false, true>), grid, block, 0, s, g, kc, part);
-    else hipLaunchKernelGGL((k_gemm_part<false, false>), grid, block, 0, s, g, kc, part);
-    polymh_status st = check_launch("mlp gemm (split)");
-    if (st) return st;
-    hipLaunchKernelGGL(k_split_sum, dim3(grid_of(g.M * g.N, 256)), dim3(256), 0, s, part, nsplit, g.M, g.N,
-                       g.outf, g.ldo);
-    return check_launch("mlp gemm (split sum)");
-}
-
 }  // namespace
-
-// Parameter block (FP32 master): W1[256][288], b1[256], W2[256][256], b2[256], w3[256], b3.
-constexpr int64_t kOffW1 = 0, kOffB1 = kOffW1 + (int64_t)kHid * kIn, kOffW2 = kOffB1 + kHid,
-                  kOffB2 = kOffW2 + (int64_t)kHid * kHid, kOffW3 = kOffB2 + kHid, kOffB3 = kOffW3 + kHid,
-                  kNParams = kOffB3 + 1;
-// BF16 copies: W1 then W2.
-constexpr int64_t kNBf16 = (int64_t)kHid * kIn + (int64_t)kHid * kHid;
 
 int64_t mlp_param_count() { return kNParams; }
 int64_t mlp_bf16_count() { return kNBf16; }
@@ -350,36 +538,24 @@ polymh_status launch_mlp_forward(const uint16_t *X, int64_t B, const float *para
 {
     if (B == 0) return POLYMH_OK;
     Acts a = carve_acts(acts, B);
-    const __bf16 *x = reinterpret_cast<const __bf16 *>(X);
-    const __bf16 *w1 = reinterpret_cast<const __bf16 *>(wbf16);
-    const __bf16 *w2 = w1 + (int64_t)kHid * kIn;
-    GemmArgs g{};
-    // z1 = X W1^T + b1, h1 = gelu(z1)
-    g.A = Operand{x, kIn, 1};
-    g.B = Operand{w1, kIn, 1};
-    g.M = B; g.N = kHid; g.K = kIn;
-    g.epi = kBiasGelu; g.outf = a.z1; g.outb = a.h1; g.bias = params + kOffB1; g.ldo = kHid;
-    polymh_status st = gemm(g, s);
-    if (st) return st;
-    // z2 = h1 W2^T + b2, h2 = gelu(z2)
-    g.A = Operand{a.h1, kHid, 1};
-    g.B = Operand{w2, kHid, 1};
-    g.K = kHid; g.outf = a.z2; g.outb = a.h2; g.bias = params + kOffB2;
-    if ((st = gemm(g, s))) return st;
-    hipLaunchKernelGGL(k_head, dim3(grid_of(B, 4)), dim3(256), 0, s, a.h2, params + kOffW3,
-                       params + kOffB3, B, y ? y : a.y, (const float *)nullptr, (float *)nullptr,
-                       (float *)nullptr);
-    return check_launch("mlp head");
+    const int64_t tiles = B / kTile;
+    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)std::min<int64_t>(tiles, cu_count())), dim3(kTileThreads), 0, s,
+                       reinterpret_cast<const __bf16 *>(X), tiles, params, reinterpret_cast<const __bf16 *>(wbf16),
+                       a.z1, a.h1, a.z2, a.h2, y ? y : a.y);
+    return check_launch("mlp forward");
 }
 
 // Loss and parameter gradient of one batch (the forward must have run on the
 // same X and acts).  grad [kNParams] is overwritten; loss (device float) is
-// overwritten with the batch MSE.  scratch: dz3 [B], dz2/dz1 fp32 and bf16,
-// the weight gradients' split-K partials.
+// overwritten with the batch MSE.  scratch: dz2 and dz1 in BF16, W2^T, and the
+// partial sums of k_mlp_back and k_wgrad.
+constexpr int kMaxBack = 512;                    // workgroups of k_mlp_back at most
+
 size_t mlp_backward_scratch_bytes(int64_t B)
 {
-    return align_up((size_t)B * 4, 256) + 2 * align_up((size_t)B * kHid * 4, 256) +
-           2 * align_up((size_t)B * kHid * 2, 256) + align_up((size_t)kMaxSplit * kHid * kIn * 4, 256) + 256;
+    return 2 * align_up((size_t)B * kHid * 2, 256) + align_up((size_t)kW2Size * 2, 256) +
+           align_up((size_t)kMaxBack * kBackItems * 4, 256) +
+           align_up((size_t)kMaxSplit * (kW1Size + kW2Size) * 4, 256) + 256;
 }
 
 polymh_status launch_mlp_backward(const uint16_t *X, int64_t B, const float *params,
@@ -389,43 +565,26 @@ polymh_status launch_mlp_backward(const uint16_t *X, int64_t B, const float *par
     if (B == 0) return POLYMH_OK;
     Acts a = carve_acts(acts, B);
     char *c = static_cast<char *>(scratch);
-    float *dz3 = reinterpret_cast<float *>(c); c += align_up((size_t)B * 4, 256);
-    float *dz2f = reinterpret_cast<float *>(c); c += align_up((size_t)B * kHid * 4, 256);
-    float *dz1f = reinterpret_cast<float *>(c); c += align_up((size_t)B * kHid * 4, 256);
-    __bf16 *dz2b = reinterpret_cast<__bf16 *>(c); c += align_up((size_t)B * kHid * 2, 256);
-    __bf16 *dz1b = reinterpret_cast<__bf16 *>(c); c += align_up((size_t)B * kHid * 2, 256);
-    float *part = reinterpret_cast<float *>(c);
-    const __bf16 *x = reinterpret_cast<const __bf16 *>(X);
-    const __bf16 *w2 = reinterpret_cast<const __bf16 *>(wbf16) + (int64_t)kHid * kIn;
-
-    hipLaunchKernelGGL(k_zero_f32, dim3(1), dim3(64), 0, s, loss, (int64_t)1);
-    hipLaunchKernelGGL(k_head, dim3(grid_of(B, 4)), dim3(256), 0, s, a.h2, params + kOffW3,
-                       params + kOffB3, B, a.y, label, dz3, loss);
-    hipLaunchKernelGGL(k_head_grads, dim3(kHid + 1), dim3(256), 0, s, dz3, a.h2, B,
-                       grad + kOffW3, grad + kOffB3);
-    hipLaunchKernelGGL(k_head_back, dim3(grid_of(B * kHid, 256)), dim3(256), 0, s, dz3,
-                       params + kOffW3, a.z2, B, dz2f, dz2b);
-    polymh_status st = check_launch("mlp head backward");
-    if (st) return st;
-    GemmArgs g{};
-    // dW2 = dz2^T h1 : (out i, in j), reduction over rows r
-    g.A = Operand{dz2b, 1, kHid};
-    g.B = Operand{a.h1, 1, kHid};
-    g.M = kHid; g.N = kHid; g.K = B; g.epi = kStoreF32; g.outf = grad + kOffW2; g.ldo = kHid;
-    if ((st = gemm_split(g, part, s))) return st;
-    hipLaunchKernelGGL(k_colsum, dim3(kHid), dim3(256), 0, s, dz2f, B, kHid, grad + kOffB2);
-    // dz1 = (dz2 W2) * gelu'(z1)
-    g.A = Operand{dz2b, kHid, 1};
-    g.B = Operand{w2, 1, kHid};
-    g.M = B; g.N = kHid; g.K = kHid; g.epi = kGeluGrad; g.outf = dz1f; g.outb = dz1b;
-    g.zin = a.z1; g.ldo = kHid;
-    if ((st = gemm(g, s))) return st;
-    // dW1 = dz1^T X : (out i, in j) over rows r
-    g.A = Operand{dz1b, 1, kHid};
-    g.B = Operand{x, 1, kIn};
-    g.M = kHid; g.N = kIn; g.K = B; g.epi = kStoreF32; g.outf = grad + kOffW1; g.ldo = kIn;
-    if ((st = gemm_split(g, part, s))) return st;
-    hipLaunchKernelGGL(k_colsum, dim3(kHid), dim3(256), 0, s, dz1f, B, kHid, grad + kOffB1);
+    __bf16 *dz2 = reinterpret_cast<__bf16 *>(c); c += align_up((size_t)B * kHid * 2, 256);
+    __bf16 *dz1 = reinterpret_cast<__bf16 *>(c); c += align_up((size_t)B * kHid * 2, 256);
+    __bf16 *w2t = reinterpret_cast<__bf16 *>(c); c += align_up((size_t)kW2Size * 2, 256);
+    float *bpart = reinterpret_cast<float *>(c); c += align_up((size_t)kMaxBack * kBackItems * 4, 256);
+    float *wpart = reinterpret_cast<float *>(c);
+    const __bf16 *w2 = reinterpret_cast<const __bf16 *>(wbf16) + kW1Size;
+    const int64_t tiles = B / kTile;
+    const int nback = (int)std::min<int64_t>(tiles, std::min(cu_count(), kMaxBack));
+    hipLaunchKernelGGL(k_transpose_w2, dim3(64), dim3(256), 0, s, w2, w2t);
+    hipLaunchKernelGGL(k_mlp_back, dim3(nback), dim3(kTileThreads), 0, s, tiles, B, params, w2t, a.z1, a.z2, a.h2,
+                       label, a.y, dz1, dz2, bpart);
+    // at most kMaxSplit splits of a whole number of steps, at least two
+    const int64_t steps = (B + kGradRows - 1) / kGradRows;
+    const int64_t kc = std::max<int64_t>(2, (steps + kMaxSplit - 1) / kMaxSplit) * kGradRows;
+    const int nsplit = (int)((B + kc - 1) / kc);
+    hipLaunchKernelGGL(k_wgrad, dim3(nsplit, kHid / 64, 2), dim3(256), 0, s, dz1, dz2,
+                       reinterpret_cast<const __bf16 *>(X), a.h1, B, kc, wpart);
+    const int wblocks = (int)((kW1Size + kW2Size + 255) / 256), bblocks = (kBackItems + 31) / 32;
+    hipLaunchKernelGGL(k_grad_sum, dim3(wblocks + bblocks), dim3(256), 0, s, wpart, nsplit, bpart, nback, wblocks, grad,
+                       loss);
     return check_launch("mlp backward");
 }
 
@@ -434,10 +593,8 @@ polymh_status launch_mlp_adam(float *params, const float *grad, float *m, float 
 {
     const float c1 = 1.0f - powf(b1, (float)step), c2 = 1.0f - powf(b2, (float)step);
     hipLaunchKernelGGL(k_adam, dim3(grid_of(kNParams, 256)), dim3(256), 0, s, params, grad, m, v,
-                       kNParams, lr, b1, b2, eps, c1, c2);
-    polymh_status st = check_launch("mlp adam");
-    if (st) return st;
-    return launch_mlp_sync_bf16(params, wbf16, s);
+                       kNParams, lr, b1, b2, eps, c1, c2, reinterpret_cast<__bf16 *>(wbf16));
+    return check_launch("mlp adam");
 }
 
 polymh_status launch_gemm_bf16(const uint16_t *A, int64_t sai, int64_t sak, const uint16_t *B,
@@ -447,7 +604,7 @@ polymh_status launch_gemm_bf16(const uint16_t *A, int64_t sai, int64_t sak, cons
     GemmArgs g{};
     g.A = Operand{reinterpret_cast<const __bf16 *>(A), sai, sak};
     g.B = Operand{reinterpret_cast<const __bf16 *>(B), sbj, sbk};
-    g.M = M; g.N = N; g.K = K; g.epi = kStoreF32; g.outf = C; g.ldo = N;
+    g.M = M; g.N = N; g.K = K; g.out = C;
     return gemm(g, s);
 }
 
