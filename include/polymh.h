@@ -284,10 +284,10 @@ polymh_status polymh_index_build(const uint64_t *keys, int64_t n, int32_t b, voi
  *   n_data is the number of indexed polygons (ids are < n_data).
  *   ws: polymh_query_workspace_size(n_data, nq) bytes (device, caller-owned,
  *   contents overwritten): a bitmap row of n_data bits per query plus two
- *   words per query.  When the rows add up to 1 GiB or more (rows of at
- *   least 16 KB), a query whose buckets hold at most 4096 entries gathers
- *   and sorts them on chip and leaves its row unused; the others (and every
- *   query of a smaller call) set bits in their row.  The lists are the same
+ *   words per query.  Where that row fits on chip it is built there and
+ *   written out; else a query's bucket entries are gathered into its row and
+ *   sorted on chip, up to 16384 of them, and a query with more sets bits in
+ *   its row (chosen by the sizes n_data and nq).  The lists are the same
  *   either way.  Stream-ordered except the
  *   capacity check above.
  */

@@ -1,90 +1,18 @@
 // Candidate generation (Sec. 3.2: a query's candidates are the polygons in
-// its buckets).  Each (query, band) key is looked up by binary search in the
-// sorted bucket table; a query's candidate list is the ids of the bucket
-// entries that belong to the same band, in ascending order without repeats.
-// For large data sets a query's same-band bucket entries are gathered into
-// its own bitmap row (work in proportion to its entries), then sorted and
-// kept without repeats on chip (one wavefront for up to kSparseCap entries,
-// a block for up to kBigCap); a query with more entries sets its polygons'
-// bits in the bitmap row and reads its set bits in order.  Every way gives
-// the same list.
+// its buckets).  Each (query, band) key is looked up in the sorted bucket
+// table; a query's candidate list is the ids of the bucket entries that
+// belong to the same band, in ascending order without repeats.  Where a
+// query's bitmap of the data set fits LDS and the queries run at once, its
+// entries mark it there (k_mark_row).  Else a query's same-band bucket
+// entries are gathered into its own bitmap row in memory (work in proportion
+// to its entries), then sorted and kept without repeats on chip (one wavefront
+// for up to kSparseCap entries, a block for up to kBigCap); a query with more
+// entries marks its polygons in that row.  Every way gives the same list.
 #include "internal.hpp"
 
 namespace polymh {
 
 namespace {
-
-__global__ __launch_bounds__(256) void k_zero_u32(uint32_t *p, int64_t count)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0u;
-}
-
-// First index in a[lo, hi) whose value is >= v, by a 64-way search: each
-// round the lanes sample 64 evenly spaced positions and the count of samples
-// below v (a ballot) narrows the range by a factor of 64.  All lanes of the
-// wavefront take part; the result is uniform.
-__device__ __forceinline__ int64_t lower_bound_wave(const uint64_t *a, int64_t lo, int64_t hi, uint64_t v,
-                                                    int lane)
-{
-    while (hi - lo > 64) {
-        const int64_t step = (hi - lo + 63) >> 6;
-        const int64_t p = lo + (int64_t)lane * step;
-        const bool valid = p < hi;
-        const bool less = valid && a[valid ? p : lo] < v;
-        const int c = __popcll(__ballot(less));
-        const int nvalid = __popcll(__ballot(valid));
-        const int64_t nlo = c > 0 ? lo + (int64_t)(c - 1) * step + 1 : lo;
-        const int64_t nhi = c < nvalid ? lo + (int64_t)c * step : hi;
-        lo = nlo;
-        hi = nhi;
-    }
-    const int64_t p = lo + lane;
-    const bool less = p < hi && a[p < hi ? p : lo] < v;
-    return lo + __popcll(__ballot(less));
-}
-
-// One wavefront per (query, band): find the bucket, lanes mark its entries.
-// The bucket's end is found by scanning forward 64 entries at a time (a
-// bucket holds the polygons sharing one 64-bit key: a handful).
-__global__ __launch_bounds__(256) void k_mark(const uint64_t *__restrict__ skeys,
-                                              const int32_t *__restrict__ sids, int64_t n_entries,
-                                              const uint64_t *__restrict__ qkeys, int64_t nq,
-                                              int32_t b, uint32_t *__restrict__ bitmap, int64_t words,
-                                              const int32_t *__restrict__ dense)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; w < nq * b; w += nw) {
-        if (!dense[w / b]) continue;
-        const uint64_t key = qkeys[w];
-        const int32_t t = (int32_t)(w % b);
-        uint32_t *row = bitmap + (w / b) * words;
-        int64_t e0 = lower_bound_wave(skeys, 0, n_entries, key, lane);
-        while (e0 < n_entries) {
-            const int64_t e = e0 + lane;
-            const bool in = e < n_entries && skeys[e < n_entries ? e : 0] == key;
-            const uint64_t mk = __ballot(in);
-            if (in) {
-                const int32_t ent = sids[e];          // entry p*b + t'
-                const int32_t id = ent / b;
-                if (ent - id * b == t) atomicOr(&row[id >> 5], 1u << (id & 31));
-            }
-            if (mk != ~0ull) break;                   // the bucket ended inside this window
-            e0 += 64;
-        }
-    }
-}
-
-// One block per query whose list is too long for LDS: clear its bitmap row.
-__global__ __launch_bounds__(256) void k_zero_rows(uint32_t *__restrict__ bitmap, int64_t words,
-                                                   const int32_t *__restrict__ dense)
-{
-    if (!dense[blockIdx.x]) return;
-    uint32_t *row = bitmap + (int64_t)blockIdx.x * words;
-    for (int64_t i = threadIdx.x; i < words; i += blockDim.x) row[i] = 0u;
-}
 
 constexpr int kSparseCap = 4096;
 
@@ -125,6 +53,121 @@ __device__ __forceinline__ int64_t lower_bound_interp(const uint64_t *__restrict
         }
     }
     return lo;
+}
+
+// One past the last entry of key's bucket, whose first one is at lo (lo if it
+// has none), by a galloping search: probes 1, 2, 4, ... entries on, then a
+// binary search between the last two.  (Eight probes at a time were slower:
+// 284 against 253 us for 10,000 queries of 100,000 polygons, and 34 against
+// 32 for ten.)
+__device__ __forceinline__ int64_t bucket_end(const uint64_t *__restrict__ skeys, int64_t n_entries, uint64_t key,
+                                              int64_t lo)
+{
+    if (lo >= n_entries || skeys[lo] != key) return lo;
+    int64_t last = lo, step = 1;
+    while (lo + step < n_entries && skeys[lo + step] == key) {
+        last = lo + step;
+        step <<= 1;
+    }
+    int64_t a = last + 1, c = lo + step < n_entries ? lo + step : n_entries;
+    while (a < c) {
+        const int64_t mid = (a + c) >> 1;
+        if (skeys[mid] == key) a = mid + 1;
+        else c = mid;
+    }
+    return a;
+}
+
+// The candidates of a query as a bitmap row, one workgroup per query: a thread
+// a band finds its bucket, the buckets' entries are spread over the threads
+// and mark their polygons, the bits are counted.  kLds: the row is built in
+// LDS and written out for k_emit; else it is built in place, and only for
+// the queries that the sparse passes left (dense).  Bound: the latency of the
+// searches' dependent reads.  100,000 polygons, 32 bands, 1,000 queries 53 us
+// for the whole lookup and 10,000 253, against 85 and 573 with a wavefront a
+// (query, band) and the rows cleared, marked and counted in memory.
+constexpr int kRowThreads = 256;
+template <bool kLds>
+__global__ __launch_bounds__(kRowThreads) void k_mark_row(const uint64_t *__restrict__ skeys,
+                                                          const int32_t *__restrict__ sids, int64_t n_entries,
+                                                          const uint64_t *__restrict__ qkeys, int32_t b,
+                                                          uint32_t *bitmap, int64_t words,
+                                                          int64_t *__restrict__ counts,
+                                                          const int32_t *__restrict__ dense)
+{
+    extern __shared__ uint32_t s_row[];
+    __shared__ int64_t s_base[kRowThreads + 1], s_lo[kRowThreads], s_w[kRowThreads / 64];
+    const int64_t q = blockIdx.x;
+    if (!kLds && !dense[q]) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t *row = bitmap + q * words;
+    uint32_t *bits = kLds ? s_row : row;
+    for (int64_t i = tid; i < words; i += kRowThreads) bits[i] = 0u;
+    for (int32_t t0 = 0; t0 < b; t0 += kRowThreads) {
+        const int32_t t = t0 + tid;
+        int64_t lo = 0, hi = 0;
+        if (t < b) {
+            const uint64_t key = qkeys[q * b + t];
+            lo = lower_bound_interp(skeys, n_entries, key);
+            hi = bucket_end(skeys, n_entries, key, lo);
+        }
+        const int64_t incl = wave_incl_scan64(hi - lo);
+        if (lane == 63) s_w[wave] = incl;
+        __syncthreads();
+        int64_t at = incl - (hi - lo);
+        for (int w = 0; w < wave; w++) at += s_w[w];
+        s_base[tid] = at;
+        s_lo[tid] = lo;
+        if (tid == kRowThreads - 1) s_base[kRowThreads] = at + (hi - lo);
+        __syncthreads();
+        const int64_t total = s_base[kRowThreads];
+        const int top = min(kRowThreads, b - t0) - 1;
+        constexpr int kU = 4;                   // entries in flight a thread
+        for (int64_t j0 = tid; j0 < total; j0 += kRowThreads * kU) {
+            int32_t ent[kU];
+            int band[kU];
+#pragma unroll
+            for (int u = 0; u < kU; u++) {
+                const int64_t j = j0 + kRowThreads * u;
+                ent[u] = -1;
+                band[u] = 0;
+                if (j < total) {
+                    int l = 0, h = top;         // the last band with s_base[l] <= j
+                    while (l < h) {
+                        const int mid = (l + h + 1) >> 1;
+                        if (s_base[mid] <= j) l = mid;
+                        else h = mid - 1;
+                    }
+                    ent[u] = sids[s_lo[l] + (j - s_base[l])];   // entry p*b + t'
+                    band[u] = t0 + l;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kU; u++) {
+                const int32_t id = ent[u] >= 0 ? ent[u] / b : 0;
+                if (ent[u] >= 0 && ent[u] - id * b == band[u]) atomicOr(&bits[id >> 5], 1u << (id & 31));
+            }
+        }
+        __syncthreads();
+    }
+    int64_t c = 0;
+    for (int64_t i = tid; i < words; i += kRowThreads) {
+        uint32_t v;
+        if constexpr (kLds) {
+            v = s_row[i];
+            row[i] = v;
+        } else {
+            v = __hip_atomic_load(&row[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        c += __popc(v);
+    }
+    c = wave_sum_i64(c);
+    if (lane == 0) s_w[wave] = c;
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < kRowThreads / 64; w++) c += s_w[w];
+        counts[q] = c;
+    }
 }
 
 // Sorts L[0, cnt) in place (bitonic, padded with INT32_MAX to a power of
@@ -213,8 +256,7 @@ constexpr int kBigCap = 16384;
 // than min(kBigCap, words) entries gets dense[q] = 1 (the bitmap takes it).
 //
 // Lane t takes band t's key: an interpolation search gives its bucket's
-// first entry, a galloping search (probes 1, 2, 4, ... entries on, then a
-// binary search between the last two) its end.  The bucket lengths' prefix
+// first entry, a galloping search its end.  The bucket lengths' prefix
 // sum then spreads every entry of the 64 buckets over the lanes, 64 entries
 // a step with independent loads, so the walk takes (entries / 64) steps
 // instead of as many as the longest bucket holds.
@@ -243,22 +285,7 @@ __global__ __launch_bounds__(256) void k_sparse(const uint64_t *__restrict__ ske
         int64_t lo = 0, hi = 0;
         if (live) {
             lo = lower_bound_interp(skeys, n_entries, key);
-            hi = lo;
-            if (lo < n_entries && skeys[lo] == key) {
-                // gallop: skeys[last] == key, probe = lo + step is the next test
-                int64_t last = lo, step = 1;
-                while (lo + step < n_entries && skeys[lo + step] == key) {
-                    last = lo + step;
-                    step <<= 1;
-                }
-                int64_t a = last + 1, c = lo + step < n_entries ? lo + step : n_entries;
-                while (a < c) {
-                    const int64_t mid = (a + c) >> 1;
-                    if (skeys[mid] == key) a = mid + 1;
-                    else c = mid;
-                }
-                hi = a;
-            }
+            hi = bucket_end(skeys, n_entries, key, lo);
         }
         // a bucket longer than the list sends the query to the bitmap (which
         // is exact in every case)
@@ -618,52 +645,13 @@ __global__ __launch_bounds__(1024) void k_sparse_sort_big(const int32_t *__restr
     if (tid == 0) counts[q] = total;
 }
 
-// One wavefront per query taken by k_sparse: its list copied from its row to
-// off[q] (nothing when the capacity flag is raised).
-__global__ __launch_bounds__(256) void k_sparse_emit(const uint32_t *__restrict__ bitmap, int64_t words,
-                                                     const int32_t *__restrict__ dense, int64_t nq,
-                                                     const int64_t *__restrict__ off, int32_t *__restrict__ ids,
-                                                     const int32_t *__restrict__ overflow)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t q = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (q >= nq || dense[q] || (overflow && overflow[0])) return;
-    const int32_t *row = reinterpret_cast<const int32_t *>(bitmap + q * words);
-    const int64_t base = off[q], n = off[q + 1] - base;
-    for (int64_t i = lane; i < n; i += 64) ids[base + i] = row[i];
-}
-
-// One block per dense query: popcount of its bitmap row.
-__global__ __launch_bounds__(256) void k_count(const uint32_t *__restrict__ bitmap, int64_t words,
-                                               int64_t *__restrict__ counts, const int32_t *__restrict__ dense)
-{
-    if (!dense[blockIdx.x]) return;
-    __shared__ int64_t s[256];
-    const uint32_t *row = bitmap + (int64_t)blockIdx.x * words;
-    int64_t c = 0;
-    // eight independent loads in flight a thread
-    int64_t i = threadIdx.x;
-    for (; i + 7 * 256 < words; i += 8 * 256) {
-        uint32_t v[8];
-#pragma unroll
-        for (int u = 0; u < 8; u++) v[u] = row[i + u * 256];
-#pragma unroll
-        for (int u = 0; u < 8; u++) c += __popc(v[u]);
-    }
-    for (; i < words; i += blockDim.x) c += __popc(row[i]);
-    s[threadIdx.x] = c;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) s[threadIdx.x] += s[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) counts[blockIdx.x] = s[0];
-}
-
 // Exclusive prefix of counts[0..nq) into off[0..nq], single block, in
 // tiles of 8192: each thread adds 8 consecutive counts, a wavefront scan of
 // those sums and a pass over the 16 wavefront totals place every thread.
-__global__ __launch_bounds__(1024) void k_offsets(int64_t *__restrict__ off, int64_t nq)
+// With `overflow` (graph-captured lookups): if the total passes cap, raise
+// the flag and empty every query's range so that later stages see none.
+__global__ __launch_bounds__(1024) void k_offsets(int64_t *__restrict__ off, int64_t nq, int64_t cap,
+                                                  int32_t *__restrict__ overflow)
 {
     constexpr int kPer = 8;
     __shared__ int64_t s_w[16];
@@ -696,42 +684,55 @@ __global__ __launch_bounds__(1024) void k_offsets(int64_t *__restrict__ off, int
         carry += tot;
         __syncthreads();
     }
-    if (threadIdx.x == 0) off[nq] = carry;
+    const bool over = overflow && carry > cap;
+    if (over)
+        for (int64_t q = threadIdx.x; q < nq; q += 1024) off[q] = 0;
+    if (threadIdx.x == 0) {
+        off[nq] = over ? 0 : carry;
+        if (overflow) overflow[0] = over ? 1 : 0;
+    }
 }
 
-// One block per dense query: write its set bits in ascending order (nothing
-// when the capacity flag is raised).  The row is read in tiles of 4096
-// words, 16 consecutive words a thread: one block-wide scan of the threads'
-// bit counts per tile places every thread's output.
+// One block per query: its list to off[q] (nothing when the capacity flag is
+// raised), copied from its row if the sparse passes took it, else (dense
+// null: every query) the row's set bits in ascending order.  The row is read in tiles of 4096 words, 16 consecutive words a thread: one
+// block-wide scan of the threads' bit counts per tile places every thread's
+// output.
 __global__ __launch_bounds__(256) void k_emit(const uint32_t *__restrict__ bitmap, int64_t words,
                                               const int64_t *__restrict__ off,
                                               int32_t *__restrict__ ids, const int32_t *__restrict__ dense,
                                               const int32_t *__restrict__ overflow)
 {
     constexpr int kPer = 16;
-    __shared__ uint32_t s[256];
+    __shared__ int32_t s_w[4];
     const int64_t q = blockIdx.x;
-    if (!dense[q] || (overflow && overflow[0])) return;
+    if (overflow && overflow[0]) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t *row = bitmap + q * words;
     int64_t base = off[q];
+    if (dense && !dense[q]) {
+        const int64_t n = off[q + 1] - base;
+        for (int64_t i = threadIdx.x; i < n; i += blockDim.x) ids[base + i] = (int32_t)row[i];
+        return;
+    }
     for (int64_t w0 = 0; w0 < words; w0 += 256 * kPer) {
         const int64_t w = w0 + (int64_t)threadIdx.x * kPer;
         uint32_t bits[kPer];
-        uint32_t c = 0;
+        int32_t c = 0;
 #pragma unroll
         for (int i = 0; i < kPer; i++) {
             bits[i] = w + i < words ? row[w + i] : 0u;
             c += __popc(bits[i]);
         }
-        s[threadIdx.x] = c;
+        const int32_t incl = wave_incl_scan32(c);
+        if (lane == 63) s_w[wave] = incl;
         __syncthreads();
-        for (int o = 1; o < 256; o <<= 1) {
-            const uint32_t t = threadIdx.x >= (unsigned)o ? s[threadIdx.x - o] : 0u;
-            __syncthreads();
-            s[threadIdx.x] += t;
-            __syncthreads();
+        int64_t pos = base + incl - c;
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+            pos += v < wave ? s_w[v] : 0;
+            base += s_w[v];
         }
-        int64_t pos = base + s[threadIdx.x] - c;
 #pragma unroll
         for (int i = 0; i < kPer; i++) {
             uint32_t v = bits[i];
@@ -741,35 +742,9 @@ __global__ __launch_bounds__(256) void k_emit(const uint32_t *__restrict__ bitma
                 v &= v - 1;
             }
         }
-        base += s[255];
         __syncthreads();
     }
 }
-
-// Capacity guard for graph-captured lookups: if the candidates do not fit,
-// raise the flag and empty every query's range so later stages see none.
-__global__ __launch_bounds__(256) void k_cap_guard(int64_t *__restrict__ off, int64_t nq, int64_t cap,
-                                                   int32_t *__restrict__ overflow)
-{
-    const int64_t total = off[nq];
-    if (total <= cap) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) overflow[0] = 0;
-        return;
-    }
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q <= nq;
-         q += (int64_t)gridDim.x * blockDim.x)
-        off[q] = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) overflow[0] = 1;
-}
-
-int blocks_for(int64_t items, int per_block)
-{
-    int64_t g = (items + per_block - 1) / per_block;
-    if (g < 1) g = 1;
-    if (g > 65536) g = 65536;
-    return (int)g;
-}
-
 
 // Workspace: dense flags [nq], counts [nq], bitmap rows [nq][words].
 struct QueryWs {
@@ -787,60 +762,52 @@ QueryWs carve_query(Carve &cv, int64_t nq, int64_t words)
     return w;
 }
 
-// Lengths of every query's list into counts (the sparse pass, then the
-// bitmap rows of the dense queries).
-// The bitmap is cleared, counted and read whole: once it passes 1 GiB (with
-// rows of 16 KB and more) that costs more than gathering and sorting the
-// queries' lists, and the lists are taken on chip where they fit.
-constexpr int64_t kSparseMinBytes = (int64_t)1 << 30;
-constexpr int64_t kSparseMinWords = 1 << 12;
-static_assert(kSparseMinWords >= kSparseCap, "a sparse list is kept in its query's bitmap row");
+// A query's bitmap fits LDS while the data set has up to 32 kRowMost polygons.
+// Building it there (one launch) is the faster way as long as the queries run
+// at once or the rows are short; else the queries' lists are gathered and
+// sorted (three launches, work in proportion to the lists).  Measured, rows
+// against lists: 140,000 polygons (4,375 words) and 10,000 queries 244 and 268
+// us; 300,000 (9,375 words) 1,000 queries 76 and 76, 2,500 147 and 118;
+// 1,000,000 (31,250 words) 200 queries 73 and 92, 1,000 225 and 114.
+constexpr int64_t kRowShort = 5120, kRowMost = 32768;
+static_assert(kRowShort >= kSparseCap, "a sparse list is kept in its query's bitmap row");
 static_assert(kBigCap <= 16384 && kSparseCap <= kBigCap, "list caps");
 
-__host__ __device__ inline bool use_sparse(int64_t nq, int64_t words)
+inline bool use_row(int64_t nq, int64_t words)
 {
-    return words >= kSparseMinWords && nq * words * 4 >= kSparseMinBytes;
+    if (words <= kRowShort) return true;
+    return words <= kRowMost && nq <= cu_count() * ((int64_t)(160 << 10) / (words * 4 + 6144));
 }
 
-__global__ __launch_bounds__(256) void k_fill_i32(int32_t *p, int64_t count, int32_t v)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
+// Lengths of every query's list into counts, and what k_emit and
+// k_sparse_emit read of them into the workspace.
 void lookup_counts(const uint64_t *skeys, const int32_t *sids, int64_t n_entries, int64_t words,
                    const uint64_t *qkeys, int64_t nq, int32_t b, const QueryWs &w, int64_t *counts, hipStream_t s)
 {
-    if (use_sparse(nq, words)) {
-        hipLaunchKernelGGL(k_sparse, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, skeys, sids, n_entries,
-                           qkeys, nq, b, w.dense, counts, w.bitmap, words);
-        hipLaunchKernelGGL(k_sparse_sort, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, w.dense, nq, counts,
-                           w.bitmap, words);
-        hipLaunchKernelGGL(k_sparse_sort_big, dim3((unsigned)nq), dim3(1024), 0, s, w.dense, counts, w.bitmap,
-                           words);
-    } else
-        hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for(nq, 256)), dim3(256), 0, s, w.dense, nq, 1);
-    if (words > 0) {
-        hipLaunchKernelGGL(k_zero_rows, dim3((unsigned)nq), dim3(256), 0, s, w.bitmap, words, w.dense);
-        if (n_entries > 0)
-            hipLaunchKernelGGL(k_mark, dim3(blocks_for(nq * b, 4)), dim3(256), 0, s, skeys, sids, n_entries,
-                               qkeys, nq, b, w.bitmap, words, w.dense);
+    if (use_row(nq, words)) {
+        if (words * 4 > 64 << 10)
+            (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mark_row<true>),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)words * 4);
+        hipLaunchKernelGGL(k_mark_row<true>, dim3((unsigned)nq), dim3(kRowThreads), (size_t)words * 4, s, skeys, sids,
+                           words > 0 ? n_entries : 0, qkeys, b, w.bitmap, words, counts, (const int32_t *)nullptr);
+        return;
     }
-    // also with no data (a zero count per query)
-    hipLaunchKernelGGL(k_count, dim3((unsigned)nq), dim3(256), 0, s, w.bitmap, words, counts, w.dense);
+    hipLaunchKernelGGL(k_sparse, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, skeys, sids, n_entries,
+                       qkeys, nq, b, w.dense, counts, w.bitmap, words);
+    hipLaunchKernelGGL(k_sparse_sort, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, w.dense, nq, counts,
+                       w.bitmap, words);
+    hipLaunchKernelGGL(k_sparse_sort_big, dim3((unsigned)nq), dim3(1024), 0, s, w.dense, counts, w.bitmap,
+                       words);
+    hipLaunchKernelGGL(k_mark_row<false>, dim3((unsigned)nq), dim3(kRowThreads), 0, s, skeys, sids, n_entries, qkeys, b,
+                       w.bitmap, words, counts, w.dense);
 }
 
-void lookup_emit(const uint64_t *skeys, const int32_t *sids, int64_t n_entries, int64_t words,
-                 const uint64_t *qkeys, int64_t nq, int32_t b, const QueryWs &w, int64_t *off, int32_t *ids,
-                 const int32_t *overflow, hipStream_t s)
+void lookup_emit(int64_t words, int64_t nq, const QueryWs &w, int64_t *off, int32_t *ids, const int32_t *overflow,
+                 hipStream_t s)
 {
-    if (use_sparse(nq, words))
-        hipLaunchKernelGGL(k_sparse_emit, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, w.bitmap, words, w.dense,
-                           nq, off, ids, overflow);
     if (words > 0)
-        hipLaunchKernelGGL(k_emit, dim3((unsigned)nq), dim3(256), 0, s, w.bitmap, words, off, ids, w.dense,
-                           overflow);
+        hipLaunchKernelGGL(k_emit, dim3((unsigned)nq), dim3(256), 0, s, w.bitmap, words, off, ids,
+                           use_row(nq, words) ? nullptr : w.dense, overflow);
 }
 
 }  // namespace
@@ -857,15 +824,14 @@ polymh_status launch_query_capped(const uint64_t *skeys, const int32_t *sids, in
         return set_error(POLYMH_ECAPACITY, "query_capped: workspace of %zu bytes, need %zu", ws_bytes, cv.used);
     if (nq > 0x7fffffffLL) return set_error(POLYMH_EINVAL, "query_capped: too many queries");
     if (nq > 0) lookup_counts(skeys, sids, n_entries, words, qkeys, nq, b, w, cand_off, s);
-    hipLaunchKernelGGL(k_offsets, dim3(1), dim3(1024), 0, s, cand_off, nq);
-    hipLaunchKernelGGL(k_cap_guard, dim3(blocks_for(nq + 1, 256)), dim3(256), 0, s, cand_off, nq, cand_cap, overflow);
-    if (nq > 0) lookup_emit(skeys, sids, n_entries, words, qkeys, nq, b, w, cand_off, cand_ids, overflow, s);
+    hipLaunchKernelGGL(k_offsets, dim3(1), dim3(1024), 0, s, cand_off, nq, cand_cap, overflow);
+    if (nq > 0) lookup_emit(words, nq, w, cand_off, cand_ids, overflow, s);
     return check_launch("query_capped");
 }
 
 polymh_status launch_offsets(int64_t *off, int64_t nq, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_offsets, dim3(1), dim3(1024), 0, s, off, nq);
+    hipLaunchKernelGGL(k_offsets, dim3(1), dim3(1024), 0, s, off, nq, (int64_t)0, (int32_t *)nullptr);
     return check_launch("offsets");
 }
 
@@ -887,18 +853,19 @@ polymh_status launch_query(const uint64_t *skeys, const int32_t *sids, int64_t n
     if (!cv.ok)
         return set_error(POLYMH_ECAPACITY, "query: workspace of %zu bytes, need %zu", ws_bytes, cv.used);
     if (nq == 0) {
-        hipLaunchKernelGGL(k_offsets, dim3(1), dim3(1024), 0, s, cand_off, (int64_t)0);
+        hipLaunchKernelGGL(k_offsets, dim3(1), dim3(1024), 0, s, cand_off, (int64_t)0, (int64_t)0,
+                           (int32_t *)nullptr);
         return check_launch("query");
     }
     if (nq > 0x7fffffffLL) return set_error(POLYMH_EINVAL, "query: too many queries");
     if (!cand_ids) {
         lookup_counts(skeys, sids, n_entries, words, qkeys, nq, b, w, cand_off, s);
-        hipLaunchKernelGGL(k_offsets, dim3(1), dim3(1024), 0, s, cand_off, nq);
+        hipLaunchKernelGGL(k_offsets, dim3(1), dim3(1024), 0, s, cand_off, nq, (int64_t)0, (int32_t *)nullptr);
     } else {
         // the offsets are the caller's from the first phase; the lengths go
         // to the workspace
         lookup_counts(skeys, sids, n_entries, words, qkeys, nq, b, w, w.counts, s);
-        lookup_emit(skeys, sids, n_entries, words, qkeys, nq, b, w, cand_off, cand_ids, nullptr, s);
+        lookup_emit(words, nq, w, cand_off, cand_ids, nullptr, s);
     }
     return check_launch("query");
 }
