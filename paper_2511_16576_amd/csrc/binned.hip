@@ -18,6 +18,7 @@
 // so the polygon's edges are staged once in LDS and every membership test
 // reads them as broadcasts; samples inside the MBR are queued per wavefront
 // and tested 64 at a time, one point per lane.
+#include <algorithm>
 #include <cmath>
 
 #include "internal.hpp"
@@ -31,6 +32,7 @@ constexpr int kBinThreads = 256;
 constexpr int kMaxSpt = 16;        // samples per thread of k_bin (chunk <= 4096)
 constexpr int kQueue = 128;        // per-wavefront queue of membership tests
 constexpr uint32_t kNone = 0xffffffffu;
+constexpr int kXcds = 8;           // workgroups are handed to the XCDs in turn
 
 struct BinArgs {
     uint64_t seed;
@@ -118,7 +120,8 @@ struct LookupArgs {
     const uint16_t *cell_off;
     uint32_t *sig;
     uint32_t *unresolved;          // [n] 1: a hash needs the walk, 2: the whole polygon is walked
-    const int32_t *order;          // [n] polygons, longest lookups first (null: index order)
+    const int32_t *order;          // [n] polygons in the order their workgroups start
+    int32_t by_place;              // the order is along the plane: a stretch of it an XCD
     int64_t n;
     int32_t k;
     uint32_t cap, horizon;
@@ -311,9 +314,14 @@ __global__ __launch_bounds__(256) void k_bin_lookup(LookupArgs A)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int per = blockDim.x;
     const int groups = (A.k + per - 1) / per;
-    // workgroups start in order of their index: the order (small launches)
-    // puts the longest first
-    const int64_t p = A.order ? (int64_t)A.order[blockIdx.x / groups] : (int64_t)(blockIdx.x / groups);
+    // workgroups start in order of their index, index b on XCD b % kXcds
+    int64_t at = blockIdx.x / groups;
+    if (A.by_place) {
+        const int64_t per_xcd = (A.n + kXcds - 1) / kXcds;
+        at = at % kXcds * per_xcd + at / kXcds;
+        if (at >= A.n) return;
+    }
+    const int64_t p = A.order[at];
     const int i = (int)(blockIdx.x % groups) * per + tid;
     const bool active = i < A.k;
     if (A.unresolved[p] & 2u) return;    // walked (uniform per workgroup, before any barrier)
@@ -409,6 +417,63 @@ __global__ __launch_bounds__(256) void k_order_count(const int64_t *__restrict__
         if (!last) atomicAdd(&counts[k], 1);
         else if ((int)(threadIdx.x & 63) == __builtin_ctzll(m)) atomicAdd(&counts[k], __popcll(m));
     }
+}
+
+// Dispatch order of a large launch: along the Z-order curve of the polygons'
+// MBR centres (64 x 64 cells), walked polygons last.  A (polygon, hash) unit
+// reads a few lines of that hash's bins; polygons of one place read the same
+// lines, and started together they find them in their XCD's L2.
+// A counting sort: a block counts its stretch of the polygons in LDS and adds
+// one number a cell to the totals (k_place_count), then reserves its range of
+// every cell and fills it (k_place_scatter); the order inside a cell affects
+// only timing.
+__device__ __forceinline__ uint32_t spread_bits8(uint32_t v)
+{
+    v = (v | v << 4) & 0x0f0fu;
+    v = (v | v << 2) & 0x3333u;
+    return (v | v << 1) & 0x5555u;
+}
+
+constexpr int kPlaceThreads = 1024;
+
+__global__ __launch_bounds__(kPlaceThreads) void k_place_count(const int32_t *__restrict__ mbr, int64_t n, int64_t per,
+                                                               int32_t bx0, int32_t by0, int32_t bx1, int32_t by1,
+                                                               int32_t sx, int32_t sy, uint16_t *__restrict__ key,
+                                                               int32_t *__restrict__ counts)
+{
+    __shared__ int32_t s_cnt[kOrderCells];
+    for (int c = threadIdx.x; c < kOrderCells; c += kPlaceThreads) s_cnt[c] = 0;
+    __syncthreads();
+    const int64_t end = min(n, (blockIdx.x + 1) * per);
+    for (int64_t p = blockIdx.x * per + threadIdx.x; p < end; p += kPlaceThreads) {
+        const int32_t *m = mbr + 4 * p;
+        // the MBR's centre, brought into B, as an offset from its corner
+        const int64_t x = min(max(((int64_t)m[0] + m[2]) >> 1, (int64_t)bx0), (int64_t)bx1) - bx0;
+        const int64_t y = min(max(((int64_t)m[1] + m[3]) >> 1, (int64_t)by0), (int64_t)by1) - by0;
+        const uint32_t c = spread_bits8((uint32_t)(x >> sx)) | spread_bits8((uint32_t)(y >> sy)) << 1;
+        key[p] = (uint16_t)c;
+        atomicAdd(&s_cnt[c], 1);
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < kOrderCells; c += kPlaceThreads)
+        if (s_cnt[c]) atomicAdd(&counts[c], s_cnt[c]);
+}
+
+__global__ __launch_bounds__(kPlaceThreads) void k_place_scatter(const uint16_t *__restrict__ key, int64_t n, int64_t per,
+                                                                 int32_t *__restrict__ cursor,
+                                                                 int32_t *__restrict__ order)
+{
+    __shared__ int32_t s_cnt[kOrderCells];
+    for (int c = threadIdx.x; c < kOrderCells; c += kPlaceThreads) s_cnt[c] = 0;
+    __syncthreads();
+    const int64_t begin = blockIdx.x * per, end = min(n, begin + per);
+    for (int64_t p = begin + threadIdx.x; p < end; p += kPlaceThreads) atomicAdd(&s_cnt[key[p]], 1);
+    __syncthreads();
+    for (int c = threadIdx.x; c < kOrderCells; c += kPlaceThreads)
+        if (s_cnt[c]) s_cnt[c] = atomicAdd(&cursor[c], s_cnt[c]);
+    __syncthreads();
+    for (int64_t p = begin + threadIdx.x; p < end; p += kPlaceThreads)
+        order[atomicAdd(&s_cnt[key[p]], 1)] = (int32_t)p;
 }
 
 // Exclusive prefix of the kOrderCells counts in place (one block of 1024).
@@ -627,14 +692,22 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
     hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t *>(w.count), (int64_t)1);
     // the lookup's dispatch order (after the classification: walked polygons
     // last), in small launches only
+    hipLaunchKernelGGL(k_zero_words, dim3(kOrderCells / 256), dim3(256), 0, s,
+                       reinterpret_cast<uint32_t *>(w.cell_counts), (int64_t)kOrderCells);
     if (ordered) {
-        hipLaunchKernelGGL(k_zero_words, dim3(kOrderCells / 256), dim3(256), 0, s,
-                           reinterpret_cast<uint32_t *>(w.cell_counts), (int64_t)kOrderCells);
         hipLaunchKernelGGL(k_order_count, dim3(grid_for(L.n)), dim3(256), 0, s, area2, L.off, L.mbr, w.unresolved, L.n,
                            (double)wx * (double)wy, (double)((int64_t)1 << lchunk), (double)nchunks, w.key,
                            w.cell_counts);
         hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(1024), 0, s, w.cell_counts);
         hipLaunchKernelGGL(k_order_scatter, dim3(grid_for(L.n)), dim3(256), 0, s, w.key, L.n, w.cell_counts, w.order);
+    } else {
+        const int64_t blocks = std::min<int64_t>(cu_count(), (L.n + 4095) / 4096), each = (L.n + blocks - 1) / blocks;
+        hipLaunchKernelGGL(k_place_count, dim3((unsigned)blocks), dim3(kPlaceThreads), 0, s, L.mbr, L.n, each,
+                           L.box.xmin, L.box.ymin, L.box.xmax, L.box.ymax, lx > 6 ? lx - 6 : 0, ly > 6 ? ly - 6 : 0,
+                           w.key, w.cell_counts);
+        hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(1024), 0, s, w.cell_counts);
+        hipLaunchKernelGGL(k_place_scatter, dim3((unsigned)blocks), dim3(kPlaceThreads), 0, s, w.key, L.n, each,
+                           w.cell_counts, w.order);
     }
     polymh_status st0 = check_launch("sign_binned: order");
     if (st0) return st0;
@@ -648,7 +721,8 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
     A.cell_off = w.cell_off;
     A.sig = L.sig;
     A.unresolved = w.unresolved;
-    A.order = ordered ? w.order : nullptr;
+    A.order = w.order;
+    A.by_place = ordered ? 0 : 1;
     A.n = L.n;
     A.k = L.k;
     A.cap = L.cap;
@@ -660,7 +734,9 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
     A.sby = B.sby;
     A.bx0 = L.box.xmin; A.by0 = L.box.ymin; A.bx1 = L.box.xmax; A.by1 = L.box.ymax;
     A.lds_edges = L.cfg.lds_edges;
-    const int64_t grid = units;
+    // by place, every XCD's stretch is rounded up (the workgroups past the
+    // end return)
+    const int64_t grid = ordered ? units : (L.n + kXcds - 1) / kXcds * kXcds * groups;
     if (grid > 0x7fffffff) return set_error(POLYMH_EINVAL, "sign_binned: too many work items");
     const size_t lds = (size_t)L.cfg.lds_edges * sizeof(int4);
     hipLaunchKernelGGL(k_bin_lookup, dim3((unsigned)grid), dim3((unsigned)per), lds, s, A);
