@@ -200,11 +200,10 @@ polymh_status polymh_join_rings(const int32_t *xy, int64_t n_vertices, const int
 /* polymh_sign_binned -- the same signatures as polymh_sign, bit for bit,
  * computed from shared samples: every polygon reads the same point stream
  * per hash (Sec. 3.2's fixed-seed generators; Def. 2), so for every hash the
- * samples j < horizon are drawn once, in chunks of C = 2^clamp(2 bin_bits,
- * 8, 12), and each chunk's samples are grouped by cell of a 2^bin_bits x
- * 2^bin_bits grid over B.  A (polygon, hash) takes the smallest j of the
- * first chunk whose samples in the cells under its MBR include one inside
- * the polygon; units with no such sample below the horizon (and polygons
+ * samples j < horizon are drawn once, in chunks of a few hundred, and each
+ * chunk's samples of up to 256 hashes are grouped by cell of a 2^bin_bits x
+ * 2^bin_bits grid over B.  A (polygon, hash) takes the smallest j whose
+ * sample, in the cells under its MBR, is inside the polygon; units with no such sample below the horizon (and polygons
  * needing them) are walked as in polymh_sign.  Work per unit is then about
  * the samples that fall in its cells instead of the N_B / N_P draws of a
  * walk (Thm. 2).
@@ -222,7 +221,7 @@ polymh_status polymh_join_rings(const int32_t *xy, int64_t n_vertices, const int
  *            also the lookup's edge cache (polygons beyond it are walked
  *            when walk_ratio > 0).
  *   ws       polymh_sign_binned_workspace_size(...) bytes: about
- *            10 * k * horizon bytes of binned samples.
+ *            13 * k * horizon bytes of binned samples.
  * POLYMH_EINVAL for k > 65535, bin_bits outside 0..6, horizon < 1 or a
  * negative walk_ratio.
  * Stream-ordered. */

@@ -2,24 +2,30 @@
 // bit, without walking every (polygon, hash) stream.  All polygons read the
 // same point stream per hash (Sec. 3.2's fixed-seed generators), so the
 // samples j < horizon of every hash are drawn once, in chunks of C, and each
-// chunk's samples are grouped by cell of a 2^b x 2^b grid over B.  A
-// (polygon, hash) unit visits the chunks in order and, in each, the samples
-// of the cells its MBR meets: those inside the MBR are tested for membership
-// and the smallest inside index of the first chunk that has one is the first
-// hit (every sample inside the polygon lies in its MBR, hence in those
-// cells).  Units with no hit below the horizon are walked from the start by
-// the per-unit kernel, so every value equals Alg. 1's.
+// chunk's samples of a group of up to 256 hashes are grouped by cell of a
+// 2^b x 2^b grid over B.  A polygon visits the chunks in order and, in each,
+// the samples of the cells its MBR meets, which are one stretch of memory a
+// grid row: those inside the MBR whose hash has no hit yet are tested for
+// membership, and the smallest inside index of a hash is its first hit (every
+// sample inside the polygon lies in its MBR, hence in those cells).  Units
+// with no hit below the horizon are walked from the start by the per-unit
+// kernel, so every value equals Alg. 1's.
 //
 // Polygons whose expected walk is short (|B| / area below a threshold) are
 // left to the walk altogether: a first-hit index near N_B / N_P is cheaper
 // to draw than to look up.
 //
-// Lookup layout: one workgroup per (polygon, block of hashes), lane = hash,
-// so the polygon's edges are staged once in LDS and every membership test
-// reads them as broadcasts; samples inside the MBR are queued per wavefront
-// and tested 64 at a time, one point per lane.
+// Lookup layout: one workgroup per (polygon, group of hashes), lane = sample,
+// so all lanes read one stretch whatever hashes it holds, the polygon's edges
+// are staged once in LDS and every membership test reads them as broadcasts;
+// samples inside the MBR are queued per wavefront and tested 64 at a time,
+// one point per lane.  Bound: VALU issue (about 70% busy).  2 M polygons of
+// 22 vertices at k = 256: 40 ms; 76 with bins a hash, lane = hash (64 places
+// of memory a read, and a wavefront as slow as the hash with most samples),
+// and 100 before the polygons were ordered along the plane.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "internal.hpp"
 #include "sign_common.hpp"
@@ -28,10 +34,11 @@ namespace polymh {
 
 namespace {
 
-constexpr int kBinThreads = 256;
-constexpr int kMaxSpt = 16;        // samples per thread of k_bin (chunk <= 4096)
 constexpr int kQueue = 128;        // per-wavefront queue of membership tests
+constexpr int kGroup = 256;        // hashes a lookup workgroup at most
+constexpr int kBinLog = 13;        // log2 of the samples a workgroup of k_bin takes
 constexpr uint32_t kNone = 0xffffffffu;
+constexpr int kRound0 = 8;         // chunks of a lookup's first rounds
 constexpr int kXcds = 8;           // workgroups are handed to the XCDs in turn
 
 struct BinArgs {
@@ -44,70 +51,190 @@ struct BinArgs {
     int32_t sbx, sby;              // cell of offset o: o >> sb
     uint32_t wx, wy;
     int32_t shx, shy;
-    uint2 *sxy;                    // [k][nchunks][C] lattice offsets, grouped by cell
-    uint16_t *sj;                  // index inside the chunk
-    uint16_t *cell_off;            // [k][nchunks][cells + 1]
+    uint32_t per;                  // samples of a (group, chunk): hashes of a group << lchunk
+    int32_t parts;                 // k_bin files by this many parts of the plane: grid rows, or cells
+    int32_t by_row;                // ... rows, which k_bin_row then files by cell
+    uint2 *xy;                     // [groups][nchunks][per] lattice offsets, grouped by cell
+    uint32_t *meta;                // hash in the group << 24 | index in the chunk
+    int32_t cbits, csx;            // columns of a row: 2^cbits, that of offset o: o >> csx
+    uint2 *range;                  // [groups][nchunks][rows][columns] first and past-the-end place
+    uint32_t *cursor;              // [groups][nchunks][parts] counts, then next free place
 };
 
-// One workgroup per (chunk, hash): draw, cell, counting sort in LDS (samples
-// past the horizon go to an extra last cell that no lookup reads).  Dynamic
-// LDS: counts and starts, (cells + 1) ints each.
-template <bool POW2>
-__global__ __launch_bounds__(kBinThreads) void k_bin(BinArgs A)
+constexpr int kBinSamples = 1 << kBinLog;
+
+// k_bin counts (PLACE false) or files (PLACE true) some hashes' samples of a
+// chunk by part: counted in LDS, one global atomic a part, and where they are
+// filed first ordered in LDS, so that a part's samples are written together.
+// 117 M samples take 0.2 ms to count, 0.5 to file by row and 0.65 by column
+// (k_bin_row), against 3.2 written one by one to the 4,096 cells.  The order
+// inside a part does not matter.
+template <bool POW2, bool PLACE>
+__global__ __launch_bounds__(1024) void k_bin(BinArgs A)
 {
-    extern __shared__ int s_dyn[];
-    __shared__ int s_wsum[kBinThreads / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c = blockIdx.x, i = blockIdx.y;
-    const int cells = 1 << (2 * A.bits);
-    const int C = 1 << A.lchunk, spt = C / kBinThreads;
-    int *s_cnt = s_dyn, *s_start = s_dyn + cells + 1;
-    for (int t = tid; t <= cells; t += kBinThreads) s_cnt[t] = 0;
+    constexpr int kPer = kBinSamples / 1024;
+    __shared__ uint32_t s_cnt[256], s_start[256];
+    __shared__ uint32_t s_w[16];
+    __shared__ uint2 s_xy[PLACE ? kBinSamples : 1];
+    __shared__ uint32_t s_meta[PLACE ? kBinSamples : 1];
+    __shared__ uint8_t s_part[PLACE ? kBinSamples : 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = blockIdx.x;
+    // kBinSamples >> lchunk hashes of the chunk, or a stretch of one hash's
+    const int lh = kBinLog - A.lchunk;
+    const int h0 = lh >= 0 ? (int)blockIdx.y << lh : (int)(blockIdx.y >> -lh);
+    const uint32_t i0 = lh >= 0 ? 0u : (blockIdx.y & ((1u << -lh) - 1)) << kBinLog;
+    const int g = h0 / kGroup;
+    const size_t gc = (size_t)g * A.nchunks + c;
+    if (tid < 256) s_cnt[tid] = 0;
     __syncthreads();
-    const uint64_t key = mix64(A.seed + (uint64_t)(i + 1) * kGamma);
-    uint32_t ox[kMaxSpt], oy[kMaxSpt];
-    int cell[kMaxSpt], rank[kMaxSpt];
+    uint32_t ox[kPer], oy[kPer], meta[kPer], rank[kPer];
+    int part[kPer];
 #pragma unroll
-    for (int q = 0; q < kMaxSpt; q++) {
-        if (q < spt) {
-            const uint64_t j = ((uint64_t)c << A.lchunk) + (uint64_t)(q * kBinThreads + tid);
-            const uint64_t r = mix64(key + (j + 1) * kGamma);
-            ox[q] = lattice<POW2>((uint32_t)(r >> 32), A.wx, A.shx);
-            oy[q] = lattice<POW2>((uint32_t)r, A.wy, A.shy);
+    for (int u = 0; u < kPer; u++) {
+        const uint32_t e = (uint32_t)(u * 1024 + tid);
+        const int h = h0 + (lh >= 0 ? (int)(e >> A.lchunk) : 0);
+        const uint32_t i = i0 + (lh >= 0 ? e & ((1u << A.lchunk) - 1) : e);
+        const uint64_t j = ((uint64_t)c << A.lchunk) + i;
+        part[u] = -1;
+        if (h < A.k && j < A.horizon) {
+            const uint64_t r = mix64(mix64(A.seed + (uint64_t)(h + 1) * kGamma) + (j + 1) * kGamma);
+            ox[u] = lattice<POW2>((uint32_t)(r >> 32), A.wx, A.shx);
+            oy[u] = lattice<POW2>((uint32_t)r, A.wy, A.shy);
             // 64-bit shifts: a 2^32-wide side with one cell shifts by 32
-            const int cx = (int)((uint64_t)ox[q] >> A.sbx), cy = (int)((uint64_t)oy[q] >> A.sby);
-            cell[q] = j < A.horizon ? ((cy << A.bits) | cx) : cells;
-            rank[q] = atomicAdd(&s_cnt[cell[q]], 1);
+            const int cy = (int)((uint64_t)oy[u] >> A.sby);
+            part[u] = A.by_row ? cy : cy << A.bits | (int)((uint64_t)ox[u] >> A.sbx);
+            meta[u] = (uint32_t)(h % kGroup) << 24 | i;
+            rank[u] = atomicAdd(&s_cnt[part[u]], 1u);
         }
     }
     __syncthreads();
-    // exclusive scan of the cells + 1 counts: strips of consecutive counts per
-    // thread, a wavefront scan of the strip sums, then the wavefront totals
-    const int per = (cells + 1 + kBinThreads - 1) / kBinThreads;
-    const int t0 = tid * per, t1 = min(t0 + per, cells + 1);
-    int sum = 0;
-    for (int t = t0; t < t1; t++) sum += s_cnt[t];
-    const int incl = wave_incl_scan32(sum);
-    if (lane == 63) s_wsum[wave] = incl;
-    __syncthreads();
-    int acc = incl - sum;
-    for (int w = 0; w < wave; w++) acc += s_wsum[w];
-    for (int t = t0; t < t1; t++) {
-        s_start[t] = acc;
-        acc += s_cnt[t];
-    }
-    __syncthreads();
-    const size_t chunk = (size_t)i * A.nchunks + c;
-    const size_t base = chunk << A.lchunk;
+    uint32_t *cursor = A.cursor + gc * A.parts;
+    if constexpr (!PLACE) {
+        if (tid < A.parts && s_cnt[tid]) atomicAdd(&cursor[tid], s_cnt[tid]);
+    } else {
+        const uint32_t cnt = tid < A.parts ? s_cnt[tid] : 0u;
+        const uint32_t incl = (uint32_t)wave_incl_scan32((int)cnt);
+        if (lane == 63) s_w[wave] = incl;
+        __syncthreads();
+        uint32_t at = incl - cnt;
+        for (int w = 0; w < min(wave, 4); w++) at += s_w[w];
+        if (tid < 256) {
+            s_start[tid] = at;
+            // where a part's stretch goes, less where it starts here
+            s_cnt[tid] = (cnt ? atomicAdd(&cursor[tid], cnt) : 0u) - at;
+        }
+        uint32_t total = 0;
+        for (int w = 0; w < 4; w++) total += s_w[w];
+        __syncthreads();
 #pragma unroll
-    for (int q = 0; q < kMaxSpt; q++) {
-        if (q < spt) {
-            const size_t pos = base + s_start[cell[q]] + rank[q];
-            A.sxy[pos] = make_uint2(ox[q], oy[q]);
-            A.sj[pos] = (uint16_t)(q * kBinThreads + tid);
+        for (int u = 0; u < kPer; u++) {
+            if (part[u] >= 0) {
+                const uint32_t p = s_start[part[u]] + rank[u];
+                s_xy[p] = make_uint2(ox[u], oy[u]);
+                s_meta[p] = meta[u];
+                s_part[p] = (uint8_t)part[u];
+            }
+        }
+        __syncthreads();
+        const size_t base = gc * A.per;
+        for (uint32_t e = tid; e < total; e += 1024) {
+            const size_t p = base + s_cnt[s_part[e]] + e;
+            A.xy[p] = s_xy[e];
+            A.meta[p] = s_meta[e];
         }
     }
-    for (int t = tid; t <= cells; t += kBinThreads) A.cell_off[chunk * (cells + 1) + t] = (uint16_t)s_start[t];
+}
+
+// Counts to starts, a wavefront a (group, chunk); where the parts are cells,
+// their ranges too.
+__global__ __launch_bounds__(256) void k_bin_scan(BinArgs A, int64_t lists)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t l = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (l >= lists) return;
+    uint32_t *cursor = A.cursor + l * A.parts;
+    uint32_t carry = 0;
+    for (int t0 = 0; t0 < A.parts; t0 += 64) {
+        const int t = t0 + lane;
+        const uint32_t c = t < A.parts ? cursor[t] : 0u;
+        const uint32_t incl = (uint32_t)wave_incl_scan32((int)c);
+        if (t < A.parts) {
+            cursor[t] = carry + incl - c;
+            if (!A.by_row) A.range[l * A.parts + t] = make_uint2(carry + incl - c, carry + incl);
+        }
+        carry += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    }
+}
+
+// One workgroup a (group, chunk, grid row): its samples by column, in place,
+// kPer a thread in registers and ordered in LDS before they are written.
+// Columns are a quarter of a cell wide, so that a stretch ends near the MBR's
+// sides.  cursor holds the rows' ends by now.  A row of more samples than
+// the threads hold (the hashes spread them evenly: none) stays as it is, and
+// each of its columns is the whole row.
+template <int kPer>
+__global__ __launch_bounds__(1024) void k_bin_row(BinArgs A)
+{
+    constexpr uint32_t kMost = kPer * 1024;
+    __shared__ uint2 s_xy[kMost];
+    __shared__ uint32_t s_meta[kMost];
+    __shared__ uint32_t s_cnt[256], s_w[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, row = blockIdx.x, side = 1 << A.cbits;
+    const size_t gc = blockIdx.y;
+    const uint32_t *ends = A.cursor + gc * A.parts;
+    const uint32_t e0 = row ? ends[row - 1] : 0u, e1 = ends[row], n = e1 - e0;
+    uint2 *xy = A.xy + gc * A.per + e0;
+    uint32_t *meta = A.meta + gc * A.per + e0;
+    uint2 *range = A.range + (gc << (A.bits + A.cbits)) + (row << A.cbits);
+    if (n > kMost) {
+        if (tid < side) range[tid] = make_uint2(e0, e1);
+        return;
+    }
+    uint2 o[kPer];
+    uint32_t m[kPer], rank[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; u++) {
+        const uint32_t e = (uint32_t)(u * 1024 + tid);
+        o[u] = make_uint2(0u, 0u);
+        m[u] = 0;
+        if (e < n) {
+            o[u] = xy[e];
+            m[u] = meta[e];
+        }
+    }
+    if (tid < 256) s_cnt[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; u++)
+        rank[u] = (uint32_t)(u * 1024 + tid) < n ? atomicAdd(&s_cnt[o[u].x >> A.csx], 1u) : 0u;
+    __syncthreads();
+    const uint32_t c = tid < 256 ? s_cnt[tid] : 0u, incl = (uint32_t)wave_incl_scan32((int)c);
+    if (lane == 63) s_w[wave] = incl;
+    __syncthreads();
+    if (tid < 256) {
+        uint32_t at = incl - c;
+        for (int w = 0; w < wave; w++) at += s_w[w];
+        s_cnt[tid] = at;
+        if (tid < side) range[tid] = make_uint2(e0 + at, e0 + at + c);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; u++) {
+        if ((uint32_t)(u * 1024 + tid) < n) {
+            const uint32_t p = s_cnt[o[u].x >> A.csx] + rank[u];
+            s_xy[p] = o[u];
+            s_meta[p] = m[u];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; u++) {
+        const uint32_t e = (uint32_t)(u * 1024 + tid);
+        if (e < n) {
+            xy[e] = s_xy[e];
+            meta[e] = s_meta[e];
+        }
+    }
 }
 
 struct LookupArgs {
@@ -115,9 +242,10 @@ struct LookupArgs {
     const int64_t *off;
     const int32_t *mbr;
     const uint32_t *flags;
-    const uint2 *sxy;
-    const uint16_t *sj;
-    const uint16_t *cell_off;
+    const uint2 *bxy;              // the bins, see BinArgs
+    const uint32_t *bmeta;
+    const uint2 *brange;
+    uint32_t per;
     uint32_t *sig;
     uint32_t *unresolved;          // [n] 1: a hash needs the walk, 2: the whole polygon is walked
     const int32_t *order;          // [n] polygons in the order their workgroups start
@@ -125,20 +253,28 @@ struct LookupArgs {
     int64_t n;
     int32_t k;
     uint32_t cap, horizon;
-    int32_t nchunks, lchunk, bits, sbx, sby;
+    int32_t nchunks, lchunk, bits, cbits, csx, sby;
     int32_t bx0, by0, bx1, by1;
     int32_t lds_edges;
 };
 
-enum TestMode { kTestLds = 0, kTestStream = 1, kTestWide = 2 };
+enum TestMode { kTestRec = 0, kTestLds = 1, kTestStream = 2, kTestWide = 3 };
 
 // Lane-serial crossing-number test of the lane's own point; every lane walks
 // the same edge sequence, so the edge reads are broadcasts.
 template <int MODE>
 __device__ __forceinline__ bool inside_lane(const int4 *s_edges, const int32_t *pxy, int32_t n,
-                                            int32_t px, int32_t py)
+                                            int32_t px, int32_t py, int32_t x0, int32_t y0)
 {
     bool odd = false;
+    if constexpr (MODE == kTestRec) {
+        const EdgeRec *rec = reinterpret_cast<const EdgeRec *>(s_edges);
+        const int32_t ry = py - y0;
+        const double dx = (double)(px - x0), dy = (double)ry;
+#pragma unroll 2
+        for (int e = 0; e < n; e++) odd ^= crosses_rec(rec[e], ry, dx, dy);
+        return odd;
+    }
     for (int e = 0; e < n; e++) {
         if constexpr (MODE == kTestLds) {
             odd ^= crosses_fp64(s_edges[e], px, py);
@@ -180,29 +316,14 @@ __device__ __forceinline__ bool inside_stream_block(const int32_t *pxy, int32_t 
     return odd;
 }
 
-// Test up to 64 queued points (lane = entry) and lower the owners' best index.
-template <int MODE>
-__device__ __forceinline__ void drain(const LookupArgs &A, const int4 *s_edges, const int32_t *pxy,
-                                      int32_t n, const uint32_t *qm, const uint32_t *qx, const uint32_t *qy,
-                                      int head, int count, uint32_t chunk_base, uint32_t *s_best, int lane)
-{
-    if constexpr (MODE == kTestStream) {
-        // all lanes load the edge blocks; lanes past count test entry head
-        const int q = (head + (lane < count ? lane : 0)) & (kQueue - 1);
-        const uint32_t meta = qm[q];
-        const int32_t px = (int32_t)((uint32_t)A.bx0 + qx[q]), py = (int32_t)((uint32_t)A.by0 + qy[q]);
-        const bool in = inside_stream_block(pxy, n, px, py, lane);
-        if (lane < count && in) atomicMin(&s_best[meta >> 12], chunk_base + (meta & 0xfffu));
-        return;
-    }
-    if (lane < count) {
-        const int q = (head + lane) & (kQueue - 1);
-        const uint32_t meta = qm[q];
-        const int32_t px = (int32_t)((uint32_t)A.bx0 + qx[q]), py = (int32_t)((uint32_t)A.by0 + qy[q]);
-        if (inside_lane<MODE>(s_edges, pxy, n, px, py))
-            atomicMin(&s_best[meta >> 12], chunk_base + (meta & 0xfffu));
-    }
-}
+// Per-wavefront state of one polygon's lookup.
+struct Scan {
+    uint32_t mx0, my0, mwx, mwy;   // MBR inside B: corner as a lattice offset, width - 1, height - 1
+    int32_t x0, y0;                // the MBR's corner
+    uint4 *queue;                  // samples inside the MBR: lattice offset, hash, index
+    uint32_t *s_best;              // smallest inside index a hash of the workgroup
+    int head, tail;
+};
 
 __device__ __forceinline__ void wave_sync_lds()
 {
@@ -210,96 +331,117 @@ __device__ __forceinline__ void wave_sync_lds()
     __builtin_amdgcn_wave_barrier();
 }
 
-// Per-wavefront state of one polygon's lookup.
-struct Scan {
-    uint32_t mx0, my0, mx1, my1;   // MBR as lattice offsets inside B
-    uint32_t *qm, *qx, *qy, *s_best;
-    int head, tail;
-};
-
-// Stream the lane's samples [lo, hi) of one grid row (cells contiguous in the
-// chunk's order), queue those inside the MBR, drain whenever 64 are waiting.
+// Test up to 64 queued points (lane = entry) and lower their hashes' best
+// index.
 template <int MODE>
-__device__ __forceinline__ void scan_row(const LookupArgs &A, const int4 *s_edges, const int32_t *pxy, int32_t n,
-                                         Scan &S, size_t base, int lo, int hi, uint32_t chunk_base, int lane)
+__device__ __forceinline__ void drain(const LookupArgs &A, const int4 *s_edges, const int32_t *pxy, int32_t n,
+                                      const Scan &S, int count, int lane)
 {
-    const int cnt = hi - lo;
-    const int steps = wave_max32(cnt);
-    for (int s = 0; s < steps; s++) {
-        bool pass = false;
-        uint2 o = make_uint2(0u, 0u);
-        if (s < cnt) {
-            o = A.sxy[base + lo + s];
-            pass = (o.x >= S.mx0) & (o.x <= S.mx1) & (o.y >= S.my0) & (o.y <= S.my1);
-        }
-        const uint64_t mk = __ballot(pass);
-        if (pass) {
-            const uint32_t jl = A.sj[base + lo + s];
-            const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0u));
-            const int q = (S.tail + rank) & (kQueue - 1);
-            S.qm[q] = ((uint32_t)lane << 12) | jl;
-            S.qx[q] = o.x;
-            S.qy[q] = o.y;
-        }
-        S.tail += __popcll(mk);
-        if (S.tail - S.head >= 64) {
-            wave_sync_lds();
-            drain<MODE>(A, s_edges, pxy, n, S.qm, S.qx, S.qy, S.head, 64, chunk_base, S.s_best, lane);
-            S.head += 64;
-            wave_sync_lds();
-        }
+    // lanes past count test the first entry where every lane takes part
+    if (MODE != kTestStream && lane >= count) return;
+    const int q = (S.head + (lane < count ? lane : 0)) & (kQueue - 1);
+    const uint4 o = S.queue[q];
+    const int32_t px = (int32_t)((uint32_t)A.bx0 + o.x), py = (int32_t)((uint32_t)A.by0 + o.y);
+    bool in;
+    if constexpr (MODE == kTestStream) in = inside_stream_block(pxy, n, px, py, lane) && lane < count;
+    else in = inside_lane<MODE>(s_edges, pxy, n, px, py, S.x0, S.y0);
+    if (in) atomicMin(&S.s_best[o.z], o.w);
+}
+
+// One sample a lane: those inside the MBR whose hash has no smaller index yet
+// are queued, 64 waiting are tested.
+template <int MODE>
+__device__ __forceinline__ void take(const LookupArgs &A, const int4 *s_edges, const int32_t *pxy, int32_t n, Scan &S,
+                                     uint2 o, uint32_t meta, uint32_t chunk_base, int lane)
+{
+    const uint32_t hash = meta >> 24, j = chunk_base + (meta & 0xffffffu);
+    const bool pass = (o.x - S.mx0 <= S.mwx) & (o.y - S.my0 <= S.mwy) & (S.s_best[hash] > j);
+    const uint64_t mk = __ballot(pass);
+    if (mk == 0) return;
+    if (pass) {
+        const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0u));
+        S.queue[(S.tail + rank) & (kQueue - 1)] = make_uint4(o.x, o.y, hash, j);
+    }
+    S.tail += __popcll(mk);
+    if (S.tail - S.head >= 64) {
+        wave_sync_lds();
+        drain<MODE>(A, s_edges, pxy, n, S, 64, lane);
+        S.head += 64;
+        wave_sync_lds();
     }
 }
 
-// Lane = hash i.  Chunks in order; a lane stops after the first chunk with a
-// hit, the wavefront when all its lanes have.
+// The chunks in rounds of some at a time: lane l of a wavefront knows the
+// stretch of (chunk l / rows of the round, grid row l % rows), the
+// wavefronts take 64 samples at a time in turn.  After a round, a hash with a
+// hit is settled (all smaller indices have been seen); the workgroup is done
+// when all are.  Rounds grow, as what is left open shrinks: the barriers and
+// the ranges' latency are paid once a round, the samples of settled hashes
+// read on the way cost one compare.  Every wavefront takes part; all
+// arguments but `active`, tid and lane are wavefront-uniform.
 template <int MODE>
-__device__ void lookup_polygon(const LookupArgs &A, const int4 *s_edges, const int32_t *pxy, int32_t n,
-                               Scan &S, int cx0, int cx1, int cy0, int cy1, int i, bool active, int lane,
-                               uint32_t &best)
+__device__ void lookup_polygon(const LookupArgs &A, const int4 *s_edges, const int32_t *pxy, int32_t n, Scan &S, int cx0,
+                               int cx1, int cy0, int cy1, bool active, int tid, int lane, int wave, int waves, int group)
 {
-    const int cells = 1 << (2 * A.bits);
-    const int C = 1 << A.lchunk;
-    const int rows = cy1 - cy0 + 1;
-    best = active ? kNone : 0u;
-    for (int c = 0; c < A.nchunks; c++) {
-        const bool open = active && best == kNone;
-        if (__ballot(open) == 0) break;
-        S.s_best[lane] = kNone;
-        S.head = S.tail = 0;
-        const size_t chunk = (size_t)i * A.nchunks + c;
-        const uint16_t *co = A.cell_off + chunk * (cells + 1);
-        const size_t base = chunk << A.lchunk;
-        const uint32_t chunk_base = (uint32_t)c << A.lchunk;
-        // the first four rows' ranges are loaded together
-        int lo[4], hi[4];
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            lo[r] = hi[r] = 0;
-            if (open && r < rows) {
-                const int row = (cy0 + r) << A.bits;
-                lo[r] = min((int)co[row | cx0], C);
-                hi[r] = min((int)co[(row | cx1) + 1], C);
-            }
+    const int rows = cy1 - cy0 + 1;              // at most 64
+    const int most = 64 / rows;                  // chunks a round at most
+    const int sub = lane / rows, row = (cy0 + lane % rows) << A.cbits;
+    int m = min(most, kRound0);
+    for (int c0 = 0; c0 < A.nchunks; c0 += m, m = min(most, max(kRound0, c0))) {
+        const size_t gc = (size_t)group * A.nchunks + c0;
+        uint32_t e0 = 0, e1 = 0;
+        if (sub < m && c0 + sub < A.nchunks) {
+            const uint2 *range = A.brange + ((gc + sub) << (A.bits + A.cbits));
+            // bounded also where the bins are not there
+            e0 = min(range[row | cx0].x, A.per);
+            e1 = min(range[row | cx1].y, A.per);
         }
-#pragma unroll
-        for (int r = 0; r < 4; r++)
-            if (r < rows) scan_row<MODE>(A, s_edges, pxy, n, S, base, lo[r], hi[r], chunk_base, lane);
-        for (int r = 4; r < rows; r++) {
-            const int row = (cy0 + r) << A.bits;
-            const int l = open ? min((int)co[row | cx0], C) : 0, h = open ? min((int)co[(row | cx1) + 1], C) : 0;
-            scan_row<MODE>(A, s_edges, pxy, n, S, base, l, h, chunk_base, lane);
+        const int steps = e1 > e0 ? (int)((e1 - e0 + 63) / 64) : 0;
+        const int incl = wave_incl_scan32(steps);
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        const int from = (int)e0 - 64 * (incl - steps), last = (int)e1 - 1;
+        S.head = S.tail = 0;
+        // step t: its stretch is the first that ends after it; lanes past the
+        // stretch's end take its last sample again, which changes nothing
+        struct Step {
+            uint2 o;
+            uint32_t meta, base;
+        } a{}, b{};
+        auto load = [&](int t, Step &s) {
+            const int l = __builtin_ctzll(__ballot(incl > t));
+            const int at = min(__builtin_amdgcn_readlane(from, l) + 64 * t + lane, __builtin_amdgcn_readlane(last, l));
+            const int c = __builtin_amdgcn_readlane(sub, l);
+            const size_t first = (gc + (size_t)c) * A.per;
+            const uint2 *xy = A.bxy + first;
+            const uint32_t *meta = A.bmeta + first;
+            s.base = (uint32_t)(c0 + c) << A.lchunk;
+            __builtin_assume(at >= 0 && at < 1 << 28);
+            s.o = xy[at];
+            s.meta = meta[at];
+        };
+        // two steps in flight
+        int t = wave;
+        if (t < total) load(t, a);
+        if (t + waves < total) load(t + waves, b);
+        while (t < total) {
+            take<MODE>(A, s_edges, pxy, n, S, a.o, a.meta, a.base, lane);
+            t += waves;
+            if (t + waves < total) load(t + waves, a);
+            if (t >= total) break;
+            take<MODE>(A, s_edges, pxy, n, S, b.o, b.meta, b.base, lane);
+            t += waves;
+            if (t + waves < total) load(t + waves, b);
         }
         while (S.tail > S.head) {
             wave_sync_lds();
-            const int cnt = min(64, S.tail - S.head);
-            drain<MODE>(A, s_edges, pxy, n, S.qm, S.qx, S.qy, S.head, cnt, chunk_base, S.s_best, lane);
-            S.head += cnt;
+            const int left = min(64, S.tail - S.head);
+            drain<MODE>(A, s_edges, pxy, n, S, left, lane);
+            S.head += left;
             wave_sync_lds();
         }
-        wave_sync_lds();
-        if (open) best = S.s_best[lane];
+        __syncthreads();
+        if (!__syncthreads_or(active && S.s_best[tid] == kNone)) break;
     }
 }
 
@@ -308,8 +450,8 @@ __device__ void lookup_polygon(const LookupArgs &A, const int4 *s_edges, const i
 __global__ __launch_bounds__(256) void k_bin_lookup(LookupArgs A)
 {
     extern __shared__ int4 s_edges[];
-    __shared__ uint32_t s_qm[4][kQueue], s_qx[4][kQueue], s_qy[4][kQueue];
-    __shared__ uint32_t s_best[4][64];
+    __shared__ uint4 s_queue[4][kQueue];
+    __shared__ uint32_t s_best[kGroup];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int per = blockDim.x;
@@ -321,14 +463,19 @@ __global__ __launch_bounds__(256) void k_bin_lookup(LookupArgs A)
         at = at % kXcds * per_xcd + at / kXcds;
         if (at >= A.n) return;
     }
-    const int64_t p = A.order[at];
+    // read through a vector load, made uniform so that what follows is scalar
+    const int64_t p = __builtin_amdgcn_readfirstlane(A.order[at]);
     const int i = (int)(blockIdx.x % groups) * per + tid;
     const bool active = i < A.k;
     if (A.unresolved[p] & 2u) return;    // walked (uniform per workgroup, before any barrier)
-    const int64_t a = A.off[p];
-    const int32_t n = (int32_t)(A.off[p + 1] - a);
-    const uint32_t fl = A.flags[p];
-    const int4 mb = *reinterpret_cast<const int4 *>(A.mbr + 4 * p);
+    const int64_t a = (int64_t)dpp::readlane64((uint64_t)A.off[p], 0);
+    const int32_t n = __builtin_amdgcn_readfirstlane((int32_t)(A.off[p + 1] - a));
+    const uint32_t fl = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.flags[p]);
+    int4 mb = *reinterpret_cast<const int4 *>(A.mbr + 4 * p);
+    mb.x = __builtin_amdgcn_readfirstlane(mb.x);
+    mb.y = __builtin_amdgcn_readfirstlane(mb.y);
+    mb.z = __builtin_amdgcn_readfirstlane(mb.z);
+    mb.w = __builtin_amdgcn_readfirstlane(mb.w);
     uint32_t *out = A.sig + (size_t)p * (size_t)A.k;
     const bool empty = (fl & (kFlagFew | kFlagCollinear)) || mb.z < A.bx0 || mb.x > A.bx1 ||
                        mb.w < A.by0 || mb.y > A.by1;
@@ -337,39 +484,45 @@ __global__ __launch_bounds__(256) void k_bin_lookup(LookupArgs A)
         return;
     }
     const int32_t *pxy = A.xy + 2 * a;
-    const int mode = (fl & kFlagWide) ? kTestWide : (n <= A.lds_edges ? kTestLds : kTestStream);
-    if (mode == kTestLds) {
+    // the cache holds lds_edges edges, or half as many with their products
+    const int mode = (fl & kFlagWide) ? kTestWide
+                                      : 2 * n <= A.lds_edges ? kTestRec : n <= A.lds_edges ? kTestLds : kTestStream;
+    if (mode <= kTestLds) {
         for (int e = tid; e < n; e += per) {
             const int f = (e + 1 == n) ? 0 : e + 1;
             const int2 u = *reinterpret_cast<const int2 *>(pxy + 2 * e);
             const int2 v = *reinterpret_cast<const int2 *>(pxy + 2 * f);
-            s_edges[e] = make_edge(u.x, u.y, v.x, v.y);
+            const int4 ed = make_edge(u.x, u.y, v.x, v.y);
+            if (mode == kTestRec) reinterpret_cast<EdgeRec *>(s_edges)[e] = make_edge_rec(ed, mb.x, mb.y);
+            else s_edges[e] = ed;
         }
     }
     __syncthreads();
     Scan S;
     S.mx0 = (uint32_t)max(mb.x, A.bx0) - (uint32_t)A.bx0;
     S.my0 = (uint32_t)max(mb.y, A.by0) - (uint32_t)A.by0;
-    S.mx1 = (uint32_t)min(mb.z, A.bx1) - (uint32_t)A.bx0;
-    S.my1 = (uint32_t)min(mb.w, A.by1) - (uint32_t)A.by0;
-    S.qm = s_qm[wave];
-    S.qx = s_qx[wave];
-    S.qy = s_qy[wave];
-    S.s_best = s_best[wave];
+    const uint32_t mx1 = (uint32_t)min(mb.z, A.bx1) - (uint32_t)A.bx0, my1 = (uint32_t)min(mb.w, A.by1) - (uint32_t)A.by0;
+    S.mwx = mx1 - S.mx0;
+    S.mwy = my1 - S.my0;
+    S.x0 = mb.x;
+    S.y0 = mb.y;
+    S.queue = s_queue[wave];
+    S.s_best = s_best;
     // 64-bit shifts: a 2^32-wide side with one cell shifts by 32
-    const int cx0 = (int)((uint64_t)S.mx0 >> A.sbx), cx1 = (int)((uint64_t)S.mx1 >> A.sbx);
-    const int cy0 = (int)((uint64_t)S.my0 >> A.sby), cy1 = (int)((uint64_t)S.my1 >> A.sby);
-    // a wavefront with no hash of its own skips the lookup (uniform per wave)
-    uint32_t best = 0u;
-    const int ic = active ? i : 0;
-    if (__ballot(active) != 0) {
-        if (mode == kTestLds)
-            lookup_polygon<kTestLds>(A, s_edges, pxy, n, S, cx0, cx1, cy0, cy1, ic, active, lane, best);
-        else if (mode == kTestStream)
-            lookup_polygon<kTestStream>(A, s_edges, pxy, n, S, cx0, cx1, cy0, cy1, ic, active, lane, best);
-        else
-            lookup_polygon<kTestWide>(A, s_edges, pxy, n, S, cx0, cx1, cy0, cy1, ic, active, lane, best);
-    }
+    const int cx0 = (int)((uint64_t)S.mx0 >> A.csx), cx1 = (int)((uint64_t)mx1 >> A.csx);
+    const int cy0 = (int)((uint64_t)S.my0 >> A.sby), cy1 = (int)((uint64_t)my1 >> A.sby);
+    for (int t = tid; t < kGroup; t += per) s_best[t] = kNone;
+    __syncthreads();                 // the edges and the bests
+    const int group = (int)(blockIdx.x % groups);
+    if (mode == kTestRec)
+        lookup_polygon<kTestRec>(A, s_edges, pxy, n, S, cx0, cx1, cy0, cy1, active, tid, lane, wave, per >> 6, group);
+    else if (mode == kTestLds)
+        lookup_polygon<kTestLds>(A, s_edges, pxy, n, S, cx0, cx1, cy0, cy1, active, tid, lane, wave, per >> 6, group);
+    else if (mode == kTestStream)
+        lookup_polygon<kTestStream>(A, s_edges, pxy, n, S, cx0, cx1, cy0, cy1, active, tid, lane, wave, per >> 6, group);
+    else
+        lookup_polygon<kTestWide>(A, s_edges, pxy, n, S, cx0, cx1, cy0, cy1, active, tid, lane, wave, per >> 6, group);
+    const uint32_t best = active ? s_best[tid] : 0u;
     if (active) {
         if (best != kNone) out[i] = best + 1;
         else if (A.horizon >= A.cap) out[i] = 0u;
@@ -377,25 +530,26 @@ __global__ __launch_bounds__(256) void k_bin_lookup(LookupArgs A)
     }
 }
 
-// Dispatch order of the polygons for the lookup, longest first.  With
-// h = C x area / |B| expected hits per chunk, a chunk has a hit with
-// probability P = 1 - exp(-h); a workgroup runs until the last of its 256
-// hashes has one, about ln(256) / P chunks (capped at the horizon), each a
-// few round trips to memory, and tests about max(1, m) / P samples a hash
-// (m = C x A_MBR / |B| samples in the MBR per chunk) against its n edges.
-// Started last, the few polygons with the largest such cost set the
-// launch's duration; started first, they overlap the rest.  A counting sort
-// on a quantised estimate (descending; the order within a key is the
-// arrival order, which affects only timing).  Walked and degenerate
-// polygons, whose workgroups return at once, go last.
+// Dispatch order of the polygons for the lookup, longest first.  A workgroup
+// runs until the last of its 256 hashes has a hit, about ln(256) |B| / area
+// samples a hash (capped at the horizon), read in rounds of a few round trips
+// to memory, and tests about kTestSlack A_MBR / area samples a hash against
+// its n edges.  Started last, the few polygons with the largest such cost set
+// the launch's duration; started first, they overlap the rest.  A counting
+// sort on a quantised estimate (descending; the order within a key is the
+// arrival order, which affects only timing).  Walked and degenerate polygons,
+// whose workgroups return at once, go last.
 constexpr int kOrderCells = 4096;
 constexpr int64_t kOrderMaxPolys = 65536;
+// Samples of a hash tested, over the A_MBR / area up to its first hit: those
+// queued before that hit was known.
+constexpr double kTestSlack = 1.5;
 
 __global__ __launch_bounds__(256) void k_order_count(const int64_t *__restrict__ area2,
                                                      const int64_t *__restrict__ off,
                                                      const int32_t *__restrict__ mbr,
                                                      const uint32_t *__restrict__ unresolved, int64_t n,
-                                                     double box_area, double chunk, double nchunks,
+                                                     double box_area, double horizon,
                                                      uint16_t *__restrict__ key, int32_t *__restrict__ counts)
 {
     for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) {
@@ -404,10 +558,9 @@ __global__ __launch_bounds__(256) void k_order_count(const int64_t *__restrict__
         if (!(unresolved[p] & 2u) && area > 0.0) {
             const int4 b = *reinterpret_cast<const int4 *>(mbr + 4 * p);
             const double a_mbr = ((double)b.z - (double)b.x + 1.0) * ((double)b.w - (double)b.y + 1.0);
-            const double P = -expm1(-chunk * area / box_area);
-            const double chunks = fmin(nchunks, 5.545 / P);             // ln(256) / P
-            const double tests = fmax(1.0, chunk * a_mbr / box_area) / P;
-            const double est = 16.0 * chunks + tests * (double)(off[p + 1] - off[p]) / 8.0;
+            const double samples = fmin(horizon, 5.545 * box_area / area);   // ln(256) |B| / area
+            const double tests = kTestSlack * a_mbr / area;
+            const double est = samples / 256.0 + tests * (double)(off[p + 1] - off[p]) / 8.0;
             k = kOrderCells - 1 - (int)fmin(est, (double)(kOrderCells - 1));
         }
         key[p] = (uint16_t)k;
@@ -527,17 +680,14 @@ __global__ __launch_bounds__(256) void k_order_scatter(const uint16_t *__restric
 // area, or when its walk is expected to cost less than its lookup, in edge
 // tests per hash: the walk draws about |B| / area points (kDrawTests edge
 // tests each) and tests the about A_mbr / area of them inside the MBR against
-// its n edges; the lookup visits chunks until one has a hit (each does with
-// probability P = 1 - exp(-C area / |B|)) and tests every sample of them
-// that lies in the MBR, about max(1, C A_mbr / |B|) a chunk, against its n
-// edges.  Either way the signature is the same.  A polygon beyond the
-// lookup's LDS edge cache (walk_edges) is walked too, and in a small launch
-// so is one whose lookup would test more than test_cap edges a hash: one
-// lookup workgroup tests its 256 hashes' points with four wavefronts, a
-// long serial run that sets a small launch's duration, where the walk
-// spreads a polygon's hashes over many work items and each test over the
-// lanes.  Degenerate polygons stay with the lookup, which signs them 0 at
-// once.
+// its n edges; the lookup tests about kTestSlack as many.  Either way the
+// signature is the same.  A polygon beyond the lookup's LDS edge cache
+// (walk_edges) is walked too, and in a small launch so is one whose lookup
+// would test more than test_cap edges a hash: one lookup workgroup tests its
+// 256 hashes' points with four wavefronts, a long serial run that sets a
+// small launch's duration, where the walk spreads a polygon's hashes over
+// many work items and each test over the lanes.  Degenerate polygons stay
+// with the lookup, which signs them 0 at once.
 constexpr double kDrawTests = 5.0;
 constexpr double kLookupTestCap = 2048.0;
 
@@ -545,7 +695,7 @@ __global__ __launch_bounds__(256) void k_classify(const int64_t *__restrict__ ar
                                                   const uint32_t *__restrict__ flags,
                                                   const int64_t *__restrict__ off,
                                                   const int32_t *__restrict__ mbr, int64_t n,
-                                                  double box_area, double walk_ratio, double chunk,
+                                                  double box_area, double walk_ratio,
                                                   double walk_edges, double test_cap,
                                                   uint32_t *__restrict__ unresolved)
 {
@@ -558,8 +708,7 @@ __global__ __launch_bounds__(256) void k_classify(const int64_t *__restrict__ ar
             const double a_mbr = ((double)m.z - (double)m.x + 1.0) * ((double)m.w - (double)m.y + 1.0);
             const double edges = (double)(off[p + 1] - off[p]);
             const double walk_cost = kDrawTests * box_area / area + edges * a_mbr / area;
-            const double hit = -expm1(-chunk * area / box_area);         // P(a chunk has a hit)
-            const double bin_cost = edges * fmax(1.0, chunk * a_mbr / box_area) / hit;
+            const double bin_cost = kTestSlack * edges * a_mbr / area;
             walk = box_area < walk_ratio * area || walk_cost < bin_cost || edges > walk_edges ||
                    bin_cost > test_cap;
         }
@@ -595,30 +744,59 @@ int grid_for(int64_t items)
     return (int)(g < 1 ? 1 : (g > 65536 ? 65536 : g));
 }
 
-// Chunk of about one sample per cell, 256..4096 samples.
-int chunk_log2(int32_t bits)
+// Chunks of 256 to 1,024 samples a hash, a quarter of a sample per cell at
+// the finest grid, so that a settled hash is found so early; more where a
+// group has fewer than kGroup hashes, so that a chunk's cells hold enough of
+// them together to fill a wavefront's reads, or for a horizon of many chunks.
+// A grid row of a chunk then holds 4,096 samples where k_bin_row files it, or
+// half as many rows twice that.
+constexpr int64_t kMostChunks = 65535;
+
+int64_t chunks_of(uint32_t horizon, int lchunk) { return ((int64_t)horizon + ((int64_t)1 << lchunk) - 1) >> lchunk; }
+
+bool horizon_fits(uint32_t horizon, int32_t bits)
 {
-    const int l = 2 * bits;
-    return l < 8 ? 8 : (l > 12 ? 12 : l);
+    return chunks_of(horizon, std::min(12, std::max(8, 2 * bits))) <= kMostChunks;
 }
 
+int chunk_log2(int32_t bits, int32_t k, uint32_t horizon)
+{
+    int l = std::max(8, bits + 4);
+    for (int h = k; 2 * h <= kGroup; h *= 2) l++;
+    while (chunks_of(horizon, l) > kMostChunks) l++;
+    return l;
+}
+
+// k_bin files straight by cell while its 8,192 samples leave 32 a cell.
+bool bins_by_row(int32_t bits) { return bits > 4; }
+// ... and k_bin_row by quarters of a cell where a cell has them.
+int col_bits(int32_t bits, int lx) { return bits + (bins_by_row(bits) && lx >= bits + 2 ? 2 : 0); }
+int64_t bin_parts(int32_t bits) { return (int64_t)1 << (bins_by_row(bits) ? bits : 2 * bits); }
+
+// Samples of a (group, chunk).
+int64_t group_samples(int32_t k, int lchunk) { return (int64_t)std::min(k, kGroup) << lchunk; }
+
 struct BinnedWs {
-    uint2 *sxy;
-    uint16_t *sj, *cell_off;
+    uint2 *xy;
+    uint32_t *meta, *cursor;
+    uint2 *range;
     uint32_t *unresolved;
     int32_t *list, *count;
     int32_t *order, *cell_counts;
     uint16_t *key;
 };
 
-BinnedWs carve_binned(Carve &c, int32_t k, int64_t nchunks, int32_t bits, int64_t n)
+BinnedWs carve_binned(Carve &c, int32_t k, uint32_t horizon, int32_t bits, int64_t n)
 {
-    const int64_t samples = ((int64_t)k * nchunks) << chunk_log2(bits);
-    const int64_t cells = ((int64_t)1 << (2 * bits)) + 1;
+    const int lchunk = chunk_log2(bits, k, horizon);
+    const int64_t nchunks = chunks_of(horizon, lchunk);
+    const int64_t lists = (int64_t)((k + kGroup - 1) / kGroup) * nchunks, samples = lists * group_samples(k, lchunk);
+    const int64_t cells = (int64_t)1 << (2 * bits + (bins_by_row(bits) ? 2 : 0));
     BinnedWs w{};
-    w.sxy = c.take<uint2>((size_t)samples);
-    w.sj = c.take<uint16_t>((size_t)samples);
-    w.cell_off = c.take<uint16_t>((size_t)((int64_t)k * nchunks * cells));
+    w.xy = c.take<uint2>((size_t)samples);
+    w.meta = c.take<uint32_t>((size_t)samples);
+    w.range = c.take<uint2>((size_t)(lists * cells));
+    w.cursor = c.take<uint32_t>((size_t)(lists * bin_parts(bits)));
     w.unresolved = c.take<uint32_t>((size_t)n);
     w.list = c.take<int32_t>((size_t)n);
     w.count = c.take<int32_t>(1);
@@ -632,9 +810,8 @@ BinnedWs carve_binned(Carve &c, int32_t k, int64_t nchunks, int32_t bits, int64_
 
 size_t binned_workspace_bytes(int32_t k, uint32_t horizon, int32_t bits, int64_t n)
 {
-    const int64_t C = (int64_t)1 << chunk_log2(bits);
     Carve c{nullptr, 0};
-    carve_binned(c, k, ((int64_t)horizon + C - 1) / C, bits, n);
+    carve_binned(c, k, horizon, bits, n);
     return align_up(c.used, 256);
 }
 
@@ -645,11 +822,11 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
     const uint64_t wy = (uint64_t)((int64_t)L.box.ymax - L.box.ymin + 1);
     const int lx = ceil_log2(wx), ly = ceil_log2(wy);
     const bool pow2 = (1ull << lx) == wx && (1ull << ly) == wy && lx >= 1 && ly >= 1;
-    const int lchunk = chunk_log2(bits);
-    const int64_t nchunks = ((int64_t)horizon + ((int64_t)1 << lchunk) - 1) >> lchunk;
-    if (nchunks > 65535) return set_error(POLYMH_EINVAL, "sign_binned: horizon too large");
+    if (!horizon_fits(horizon, bits)) return set_error(POLYMH_EINVAL, "sign_binned: horizon too large");
+    const int lchunk = chunk_log2(bits, L.k, horizon);
+    const int64_t nchunks = chunks_of(horizon, lchunk);
     Carve cv{static_cast<char *>(ws), ws_bytes};
-    BinnedWs w = carve_binned(cv, L.k, nchunks, bits, L.n);
+    BinnedWs w = carve_binned(cv, L.k, horizon, bits, L.n);
     if (!cv.ok)
         return set_error(POLYMH_ECAPACITY, "sign_binned: workspace of %zu bytes, need %zu", ws_bytes, cv.used);
     BinArgs B{};
@@ -665,16 +842,42 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
     B.wy = (uint32_t)wy;
     B.shx = pow2 ? 32 - lx : 0;
     B.shy = pow2 ? 32 - ly : 0;
-    B.sxy = w.sxy;
-    B.sj = w.sj;
-    B.cell_off = w.cell_off;
-    const size_t bin_lds = 2 * (((size_t)1 << (2 * bits)) + 1) * sizeof(int);
+    B.per = (uint32_t)group_samples(L.k, lchunk);
+    B.xy = w.xy;
+    B.meta = w.meta;
+    B.range = w.range;
+    B.cursor = w.cursor;
+    B.parts = (int32_t)bin_parts(bits);
+    B.by_row = bins_by_row(bits) ? 1 : 0;
+    B.cbits = col_bits(bits, lx);
+    B.csx = lx > B.cbits ? lx - B.cbits : 0;
     // without rebin the workspace already holds these bins (an earlier call
-    // with the same arguments); the lookup clamps every cell range to its
-    // chunk, so bins that are not there give wrong values, never a stray read
+    // with the same arguments); the lookup clamps every stretch to its chunk,
+    // so bins that are not there give wrong values, never a stray read
     if (rebin) {
-        if (pow2) hipLaunchKernelGGL(k_bin<true>, dim3((unsigned)nchunks, (unsigned)L.k), dim3(kBinThreads), bin_lds, s, B);
-        else hipLaunchKernelGGL(k_bin<false>, dim3((unsigned)nchunks, (unsigned)L.k), dim3(kBinThreads), bin_lds, s, B);
+        const int64_t lists = (int64_t)((L.k + kGroup - 1) / kGroup) * nchunks;
+        const int64_t ys = lchunk <= kBinLog ? (L.k + (1 << (kBinLog - lchunk)) - 1) >> (kBinLog - lchunk)
+                                             : (int64_t)L.k << (lchunk - kBinLog);
+        const dim3 bgrid((unsigned)nchunks, (unsigned)ys);
+        hipLaunchKernelGGL(k_zero_words, dim3(grid_for(lists * B.parts)), dim3(256), 0, s, w.cursor, lists * B.parts);
+        if (pow2) hipLaunchKernelGGL((k_bin<true, false>), bgrid, dim3(1024), 0, s, B);
+        else hipLaunchKernelGGL((k_bin<false, false>), bgrid, dim3(1024), 0, s, B);
+        hipLaunchKernelGGL(k_bin_scan, dim3((unsigned)((lists + 3) / 4)), dim3(256), 0, s, B, lists);
+        if (pow2) hipLaunchKernelGGL((k_bin<true, true>), bgrid, dim3(1024), 0, s, B);
+        else hipLaunchKernelGGL((k_bin<false, true>), bgrid, dim3(1024), 0, s, B);
+        // a row's samples, with room for what chance adds to them
+        const double even = (double)B.per * std::ldexp(1.0, B.sby) / (double)wy;
+        const bool narrow = even + 8.0 * std::sqrt(even) <= 5 * 1024;
+        for (int64_t l0 = 0; B.by_row && l0 < lists; l0 += 65535) {
+            BinArgs R = B;
+            R.xy += l0 * B.per;
+            R.meta += l0 * B.per;
+            R.range += l0 << (bits + B.cbits);
+            R.cursor += l0 * B.parts;
+            const dim3 rgrid(1u << bits, (unsigned)std::min<int64_t>(65535, lists - l0));
+            if (narrow) hipLaunchKernelGGL(k_bin_row<5>, rgrid, dim3(1024), 0, s, R);
+            else hipLaunchKernelGGL(k_bin_row<12>, rgrid, dim3(1024), 0, s, R);
+        }
     }
     polymh_status st = check_launch("sign_binned: bin");
     if (st) return st;
@@ -687,7 +890,7 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
     // few costly polygons set the duration; a large launch hides them
     const bool ordered = L.n <= kOrderMaxPolys;
     hipLaunchKernelGGL(k_classify, dim3(grid_for(L.n)), dim3(256), 0, s, area2, L.flags, L.off, L.mbr, L.n,
-                       (double)wx * (double)wy, walk_ratio, (double)((int64_t)1 << lchunk), walk_edges,
+                       (double)wx * (double)wy, walk_ratio, walk_edges,
                        ordered ? kLookupTestCap : INFINITY, w.unresolved);
     hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t *>(w.count), (int64_t)1);
     // the lookup's dispatch order (after the classification: walked polygons
@@ -696,7 +899,7 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
                        reinterpret_cast<uint32_t *>(w.cell_counts), (int64_t)kOrderCells);
     if (ordered) {
         hipLaunchKernelGGL(k_order_count, dim3(grid_for(L.n)), dim3(256), 0, s, area2, L.off, L.mbr, w.unresolved, L.n,
-                           (double)wx * (double)wy, (double)((int64_t)1 << lchunk), (double)nchunks, w.key,
+                           (double)wx * (double)wy, (double)horizon, w.key,
                            w.cell_counts);
         hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(1024), 0, s, w.cell_counts);
         hipLaunchKernelGGL(k_order_scatter, dim3(grid_for(L.n)), dim3(256), 0, s, w.key, L.n, w.cell_counts, w.order);
@@ -716,9 +919,10 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
     A.off = L.off;
     A.mbr = L.mbr;
     A.flags = L.flags;
-    A.sxy = w.sxy;
-    A.sj = w.sj;
-    A.cell_off = w.cell_off;
+    A.bxy = w.xy;
+    A.bmeta = w.meta;
+    A.brange = w.range;
+    A.per = B.per;
     A.sig = L.sig;
     A.unresolved = w.unresolved;
     A.order = w.order;
@@ -730,7 +934,8 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
     A.nchunks = (int32_t)nchunks;
     A.lchunk = lchunk;
     A.bits = bits;
-    A.sbx = B.sbx;
+    A.cbits = B.cbits;
+    A.csx = B.csx;
     A.sby = B.sby;
     A.bx0 = L.box.xmin; A.by0 = L.box.ymin; A.bx1 = L.box.xmax; A.by1 = L.box.ymax;
     A.lds_edges = L.cfg.lds_edges;
