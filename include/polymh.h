@@ -133,15 +133,19 @@ polymh_status polymh_box_of(const polymh_polys *polys, void *ws, size_t ws_bytes
  *   gives the same bits.  Stream-ordered.
  */
 typedef struct {
-    int32_t persistent;       /* 1: one persistent launch popping (polygon, hash
-                                 block) items longest-expected-first from a
-                                 device queue; 0: one workgroup per item.   */
+    int32_t persistent;       /* 1: (polygon, hash block) items start longest-
+                                 expected-first (popped from a device queue
+                                 by a persistent launch where a grid could
+                                 not hold them, or where their count is on
+                                 the device); 0: in the order given.        */
     int32_t block_threads;    /* 64..1024, multiple of 64                     */
-    int32_t hash_block;       /* hashes per work item (1..k; 0 = all k)       */
+    int32_t hash_block;       /* hashes per work item (1..k; 0 = the library's
+                                 choice: all k in large sets, fewer in small
+                                 ones, to fill the device)                  */
     int32_t lds_edges;        /* polygons with more edges stream them from
                                  global memory instead of LDS (64..8192)     */
     int32_t samples_per_lane; /* 1 or 2 draws per lane per tile step          */
-    int32_t blocks_per_cu;    /* persistent grid = blocks_per_cu * CU count   */
+    int32_t blocks_per_cu;    /* grid of a persistent launch / CU count       */
 } polymh_sign_config;
 
 void polymh_sign_default_config(polymh_sign_config *cfg_host);

@@ -229,7 +229,8 @@ polymh_status polymh_sign(const polymh_polys *polys, polymh_box box, uint64_t se
         return set_error(POLYMH_ECAPACITY, "sign: workspace of %zu bytes, need %zu", ws_bytes, cv.used);
     hipStream_t s = as_stream(stream);
     if ((st = launch_prepare(polys->xy, polys->offsets, polys->n, w.mbr, w.area2, w.flags, s))) return st;
-    if (c.persistent) {
+    const bool ordered = c.persistent && sign_needs_order(c, polys->n, k);
+    if (ordered) {
         if ((st = launch_sign_order(polys->offsets, w.mbr, w.area2, w.flags, polys->n, box, k, cap,
                                     w.counts, w.order, s)))
             return st;
@@ -239,7 +240,7 @@ polymh_status polymh_sign(const polymh_polys *polys, polymh_box box, uint64_t se
     L.off = polys->offsets;
     L.mbr = w.mbr;
     L.flags = w.flags;
-    L.order = c.persistent ? w.order : nullptr;
+    L.order = ordered ? w.order : nullptr;
     L.queue = c.persistent ? w.queue : nullptr;
     L.sig = sig;
     L.n = polys->n;

@@ -200,6 +200,8 @@ struct SignLaunch {
     uint32_t cap;
     polymh_sign_config cfg;
 };
+int32_t sign_hash_block(const polymh_sign_config &c, int64_t n, int32_t k);
+bool sign_needs_order(const polymh_sign_config &c, int64_t n, int32_t k);
 polymh_status launch_sign(const SignLaunch &L, hipStream_t s);
 
 // rings.hip
