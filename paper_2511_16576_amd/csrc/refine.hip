@@ -18,8 +18,8 @@
 // gives exactly area(P n Q).  Orientations are exact: coordinate differences
 // below 2^26 make each FP64 product exact (128-bit integers beyond that).
 //
-// One wavefront per candidate pair; lanes take the edges of one polygon while
-// the other polygon's vertices are read at a uniform index (scalar loads).
+// General form (below): one wavefront per candidate pair, lanes take the edges
+// of one polygon while the other's vertices are read 64 at a time.
 #include <algorithm>
 
 #include "internal.hpp"
@@ -291,8 +291,8 @@ __device__ __forceinline__ void poly_mbr(const int32_t *v, int32_t n, int lane, 
 // the ring, so with S_e the net sign of edge e's crossings,
 //   sum_e cr_e * I(e) = sum_e cr_e * (w_0 + s * sum_{e' < e} S_e')
 //                       + s * sum_{crossings} cr_e * sign * (1 - t).
-// Q (the query) is staged once per workgroup; each wavefront stages its data
-// polygon.  Pairs with a polygon beyond kTileCap edges, or coordinate spans of
+// Q (the query) is staged once per workgroup; each wavefront stages groups of
+// data polygons (k_refine) or windows (k_refine_wide).  Pairs with a polygon beyond kTileCap edges, or coordinate spans of
 // 2^26 and more, take the general per-edge form above.
 //
 // Work layout: overlapping tiles are compacted into a per-wavefront list and
@@ -363,6 +363,11 @@ __device__ __forceinline__ double orient_d(int2 a, int2 b, int2 c)
 
 __device__ __forceinline__ int sgn_tb(double o, int tb) { return o > 0 ? 1 : (o < 0 ? -1 : tb); }
 
+__device__ __forceinline__ int lanes_below(uint64_t mask)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
 __device__ __forceinline__ void wave_lds_sync()
 {
     __builtin_amdgcn_s_waitcnt(0xc07f);
@@ -378,58 +383,6 @@ __device__ void stage_ring(const int32_t *src, int n, int pad_to, int64_t ox, in
         const int k = i < n ? i : 0;
         R.v[i] = make_int2((int)((int64_t)src[2 * k] - ox), (int)((int64_t)src[2 * k + 1] - oy));
     }
-}
-
-// Wavefront staging of a data polygon (as stage_ring) that also returns the
-// MBR of its absolute coordinates (uniform), the ring's doubled area about
-// the origin (exact, 64-bit; meaningful when the pair is not wide) and the
-// first vertex strictly outside the box qb (-1 if none): that vertex is
-// outside Q, and so is the vertex minus delta.
-// Vertices i and i + 1 of the first two 64-vertex windows, fetched one
-// candidate ahead (indices as the staging loop clamps them).
-struct RingPrefetch {
-    int2 p[2], q[2];
-};
-
-__device__ __forceinline__ void prefetch_ring(const int32_t *src, int n, int lane, RingPrefetch &pf)
-{
-    const int2 *v = reinterpret_cast<const int2 *>(src);
-#pragma unroll
-    for (int h = 0; h < 2; h++) {
-        const int i = 64 * h + lane;
-        pf.p[h] = v[i < n ? i : 0];
-        pf.q[h] = v[i + 1 < n ? i + 1 : 0];
-    }
-}
-
-__device__ void stage_ring_mbr(const int32_t *src, int n, int pad_to, int64_t ox, int64_t oy,
-                               RingLds R, int lane, const int32_t *qb, const RingPrefetch &pf, int32_t *mbr,
-                               int64_t &area2, int &anchor)
-{
-    int x0 = INT32_MAX, y0 = INT32_MAX, x1 = INT32_MIN, y1 = INT32_MIN;
-    const int2 *v = reinterpret_cast<const int2 *>(src);
-    int k = -1;
-    int64_t a2 = 0;
-    for (int base = 0; base < pad_to; base += 64) {
-        const int i = base + lane;
-        const bool live = i < pad_to, edge = i < n;
-        const int2 p = base == 0 ? pf.p[0] : base == 64 ? pf.p[1] : v[edge ? i : 0];
-        const int2 q = base == 0 ? pf.q[0] : base == 64 ? pf.q[1] : v[i + 1 < n ? i + 1 : 0];
-        // relative coordinates in 32 bits (wrapping): exact unless the pair
-        // spans 2^26 or more, whose area the caller takes from elsewhere
-        const int px = (int)((uint32_t)p.x - (uint32_t)ox), py = (int)((uint32_t)p.y - (uint32_t)oy);
-        const int qx = (int)((uint32_t)q.x - (uint32_t)ox), qy = (int)((uint32_t)q.y - (uint32_t)oy);
-        if (live) R.v[i] = make_int2(px, py);
-        a2 += edge ? (int64_t)px * qy - (int64_t)qx * py : 0;
-        x0 = min(x0, p.x); y0 = min(y0, p.y); x1 = max(x1, p.x); y1 = max(y1, p.y);
-        const bool out = edge & ((p.x < qb[0]) | (p.x > qb[2]) | (p.y < qb[1]) | (p.y > qb[3]));
-        const uint64_t mk = __ballot(out);
-        if (k < 0 && mk != 0) k = base + __builtin_ctzll(mk);
-    }
-    mbr[0] = wave_min32(x0); mbr[1] = wave_min32(y0);
-    mbr[2] = wave_max32(x1); mbr[3] = wave_max32(y1);
-    area2 = wave_sum_i64(a2);
-    anchor = k;
 }
 
 __device__ void chunk_boxes(RingLds R, int n, int t0, int nt)
@@ -495,23 +448,6 @@ __device__ __forceinline__ bool member_edge(const int2 *v, int e, int2 a, int sh
     return flips_parity(v[e], v[e + 1], a, sh);
 }
 
-// Ring-start memberships of both rings in one pass: w0p for P's vertex 0
-// against Q + delta, w0q for Q's vertex 0 + delta against P.
-__device__ void member_starts(RingLds P, int n, RingLds Q, int m, int lane, bool need_p, bool need_q,
-                              int &w0p, int &w0q)
-{
-    const int2 p0 = P.v[0], q0 = Q.v[0];
-    bool oddp = false, oddq = false;
-    const int top = max(need_p ? m : 0, need_q ? n : 0);
-    for (int e = lane; e < top; e += 64) {
-        const bool lq = need_p & (e < m), lp = need_q & (e < n);
-        oddp ^= lq & member_edge(Q.v, lq ? e : 0, p0, -1);
-        oddq ^= lp & member_edge(P.v, lp ? e : 0, q0, +1);
-    }
-    w0p = __popcll(__ballot(oddp)) & 1;
-    w0q = __popcll(__ballot(oddq)) & 1;
-}
-
 // P's membership sum: sum_e cr_e * w_e with w_e = w0 + s * (exclusive prefix
 // of S along the ring), s = Q's orientation; a per-lane partial.  Branch-free,
 // so the scan runs with every lane active.
@@ -549,14 +485,6 @@ __device__ double membership_term_window(RingLds P, int n, int anchor, int lane,
     return acc;
 }
 
-__device__ double membership_term_p(RingLds P, int n, int anchor, int lane, int &K)
-{
-    int carry = 0;
-    double crs = 0.0;
-    K = 0;
-    return membership_term_window(P, n, anchor, lane, carry, K, crs);
-}
-
 // Indices of a leftmost, a rightmost, a lowest and a highest vertex of Q
 // (rb: Q's MBR relative to the origin), by one wavefront.  A pair whose P
 // MBR leaves one of those sides of Q's MBR open anchors Q's memberships at
@@ -580,7 +508,8 @@ __device__ void q_extremes(RingLds Q, int m, int4 rb, int lane, int *ext)
 
 // Q's suffix sums Suf(f) = A2Q - sum_{f' <= f} cr_f' (exact in 64-bit
 // integers), by one wavefront.
-__device__ int64_t q_suffix_sums(RingLds Q, int m, int64_t a2q, int lane, int64_t carry = 0)
+template <typename T>
+__device__ int64_t q_suffix_sums(RingLds Q, int m, int64_t a2q, int lane, T *suf, int64_t carry = 0)
 {
     for (int base = 0; base < m; base += 64) {
         const int e = base + lane;
@@ -589,7 +518,7 @@ __device__ int64_t q_suffix_sums(RingLds Q, int m, int64_t a2q, int lane, int64_
         const int2 a = Q.v[ee], b = Q.v[ee + 1];
         const int64_t cr = live ? (int64_t)a.x * b.y - (int64_t)b.x * a.y : 0;
         const int64_t incl = carry + wave_incl_scan64(cr);
-        if (live) Q.suf[e] = (double)(a2q - incl);
+        if (live) suf[e] = (T)(a2q - incl);
         carry = (int64_t)dpp::readlane64((uint64_t)incl, 63);
     }
     return carry;
@@ -626,72 +555,80 @@ __device__ void flush_crossings(RingLds P, RingLds Q, const uint32_t *buf, int c
     }
 }
 
+// A vertex as a whole number that falls along an edge that points down, or is
+// horizontal and points right: the edges whose tie-break threshold
+// (p_edge_threshold) is negative.
+__device__ __forceinline__ int64_t down_right_key(int2 v)
+{
+    return (int64_t)(((uint64_t)(uint32_t)v.y << 32) | (uint32_t)(INT32_MAX - v.x));
+}
+
+// Masks of several comparisons are combined as scalars: combined as lane
+// values they cost the vector unit two to twelve instructions more.
+__device__ __forceinline__ bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
+// The lanes whose value is of the class set (a ballot of the builtin's result
+// turns the mask into numbers and compares those again).
+__device__ __forceinline__ uint64_t class_mask(double v, int mask)
+{
+    uint64_t lanes;
+    asm("v_cmp_class_f64 %0, %1, %2" : "=s"(lanes) : "v"(v), "v"(mask));
+    return lanes;
+}
+
 // One sweep unit per lane: Q edge f held in registers against the 8 edges of
-// P chunk cp (entry = cp << USHIFT | f).  Crossing lanes only append
-// (e << 16 | f) to the wavefront's crossing buffer, which is flushed before
-// it can overflow.
-template <int USHIFT>
-__device__ __forceinline__ void sweep_units(RingLds P, RingLds Q, int entry, int lane, uint32_t *xbuf,
-                                            int &xcount, int kq, double &accP, double &accQ, double &accM,
-                                            double &accK)
+// P chunk cp (entry = cp << USHIFT | f).  Returns the lane's crossings, edge
+// i of the chunk as bit 7 - i: the steps have no branches, and the few
+// crossings are appended to the buffer after them.
+template <int USHIFT, int CSTEP>
+__device__ __forceinline__ uint32_t sweep_units(RingLds P, RingLds Q, int entry)
 {
     const int cp = entry >> USHIFT, f = entry & ((1 << USHIFT) - 1);
     const int2 c = Q.v[f], d = Q.v[f + 1];
-    const double cx = (double)c.x, cy = (double)c.y;
     const double fx = (double)(d.x - c.x), fy = (double)(d.y - c.y);
     const int mf = q_edge_class(d.x - c.x, d.y - c.y);
-    const int e0 = 8 * cp;
-    // the chunk's 9 vertices up front: the crossing-buffer stores in the
-    // sweep would otherwise keep these loads from being issued early
     int2 pv[9];
 #pragma unroll
-    for (int i = 0; i < 9; i++) pv[i] = P.v[e0 + i];
-    double ax = (double)pv[0].x, ay = (double)pv[0].y;
-    double rx = cx - ax, ry = cy - ay;
-    // orient(c, d, a) of the chunk's first vertex; each edge's end value
-    // orient(c, d, b) = that - X is the next edge's start value (all exact
-    // integers below 2^53, so carrying it equals recomputing it)
+    for (int i = 0; i < 9; i++) pv[i] = P.v[CSTEP * cp + i];
+    double rx = (double)(c.x - pv[0].x), ry = (double)(c.y - pv[0].y);
+    // orient(c, d, a) of the chunk's first vertex; each edge's end value is
+    // the next edge's start value
     double oa = __fma_rn(fy, rx, -(fx * ry));
+    uint64_t p3 = class_mask(oa, mf);
+    int64_t ka = down_right_key(pv[0]);
+    uint32_t hits = 0;
 #pragma unroll
     for (int i = 0; i < 8; i++) {
+        // with r = c - a and r' = c - b: e = r - r', so orient(a, b, c) =
+        // cross(r, r'), orient(c, d, b) = cross(r', f) and X = their change
+        // from a to b (all exact integers below 2^53)
         const int2 b = pv[i + 1];
-        const double bx = (double)b.x, by = (double)b.y;
-        const double ex = bx - ax, ey = by - ay;
-        const double thr = p_edge_threshold(ex, ey);
-        const double oc = __fma_rn(ex, ry, -(ey * rx));
-        const double X = __fma_rn(ex, fy, -(ey * fx));
-        const double od = oc + X, ob = oa - X;
-        const bool p1 = oc > thr, p2 = od > thr;
-        const bool p3 = __builtin_amdgcn_class(oa, mf), p4 = __builtin_amdgcn_class(ob, mf);
-        const bool cross = (p1 != p2) & (p3 != p4);
-        const uint64_t cm = __ballot(cross);
-        if (cross) {
-            const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(cm >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)cm, 0u));
-            xbuf[xcount + rank] = ((uint32_t)(e0 + i) << 16) | (uint32_t)f;
-        }
-        xcount += __popcll(cm);
-        if (xcount > kCrossCap - 64) {
-            wave_lds_sync();
-            flush_crossings(P, Q, xbuf, xcount, lane, kq, accP, accQ, accM, accK);
-            wave_lds_sync();
-            xcount = 0;
-        }
-        ax = bx; ay = by;
-        rx = cx - bx; ry = cy - by;
+        const double sx = (double)(c.x - b.x), sy = (double)(c.y - b.y);
+        const int64_t kb = down_right_key(b);
+        const double thr = kb < ka ? -0.5 : 0.5;
+        const double oc = __fma_rn(rx, sy, -(ry * sx));
+        const double ob = __fma_rn(fy, sx, -(fx * sy));
+        const double od = oc + (oa - ob);
+        const uint64_t p1 = __ballot(oc > thr), p2 = __ballot(od > thr), p4 = class_mask(ob, mf);
+        const uint64_t cross = (p1 ^ p2) & (p3 ^ p4);
+        // hits = 2 hits + cross
+        asm("v_addc_co_u32 %0, vcc, %0, %0, %1" : "+v"(hits) : "s"(cross) : "vcc");
+        rx = sx; ry = sy; ka = kb;
         oa = ob;
+        p3 = p4;
     }
+    return hits;
 }
 
 // Expand up to 16 listed tiles (lane = tile slot x Q edge j, two slots per
 // lane) into sweep units, keeping the (P chunk, Q edge) pairs whose boxes
 // touch: a crossing needs the Q edge's box to meet the box of the P edge it
 // crosses, inside the chunk's.
-template <typename UnitT, int USHIFT>
-__device__ __forceinline__ void expand_tiles(RingLds P, RingLds Q, int m, const uint16_t *tiles, int head,
-                                             int count, int lane, UnitT *units, int &utail)
+template <typename UnitT, int USHIFT, bool CID>
+__device__ __forceinline__ void expand_tiles(RingLds P, RingLds Q, int m, const uint8_t *cid, const uint16_t *tiles,
+                                             int head, int count, int lane, UnitT *units, int &utail)
 {
-    bool keep[2];
+    uint64_t keep[2];
     int entry[2];
 #pragma unroll
     for (int h = 0; h < 2; h++) {
@@ -703,124 +640,104 @@ __device__ __forceinline__ void expand_tiles(RingLds P, RingLds Q, int m, const 
         const int f = 8 * cq + (lane & 7);
         const int2 c = Q.v[f], d = Q.v[f + 1];
         const int4 bp = P.box[cp];
-        const bool apart = (max(c.x, d.x) < bp.x) | (bp.z < min(c.x, d.x)) | (max(c.y, d.y) < bp.y) |
-                           (bp.w < min(c.y, d.y));
-        keep[h] = live & (f < m) & !apart;
-        entry[h] = (cp << USHIFT) | f;
+        keep[h] = __ballot(live) & __ballot(f < m) & __ballot(max(c.x, d.x) >= bp.x) & __ballot(bp.z >= min(c.x, d.x)) &
+                  __ballot(max(c.y, d.y) >= bp.y) & __ballot(bp.w >= min(c.y, d.y));
+        if constexpr (CID) entry[h] = ((int)cid[cp] << USHIFT) | f;
+        else entry[h] = (cp << USHIFT) | f;
     }
-    const uint64_t mk0 = __ballot(keep[0]), mk1 = __ballot(keep[1]);
-    const int r0 = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mk0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk0, 0u));
-    const int r1 = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mk1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk1, 0u));
-    const int c0 = __popcll(mk0);
-    if (keep[0]) units[(utail + r0) & (kUnitCap - 1)] = (UnitT)entry[0];
-    if (keep[1]) units[(utail + c0 + r1) & (kUnitCap - 1)] = (UnitT)entry[1];
-    utail += c0 + __popcll(mk1);
+    const int c0 = __popcll(keep[0]);
+    const int r0 = lanes_below(keep[0]), r1 = lanes_below(keep[1]);
+    if (lane_in(keep[0])) units[(utail + r0) & (kUnitCap - 1)] = (UnitT)entry[0];
+    if (lane_in(keep[1])) units[(utail + c0 + r1) & (kUnitCap - 1)] = (UnitT)entry[1];
+    utail = __builtin_amdgcn_readfirstlane(utail + c0 + __popcll(keep[1]));
 }
 
-// The crossings of P's edges with the m edges of Q staged in LDS (a whole
-// ring, or a window of a longer one) added to the four sums; kq is the
-// anchor's index relative to the staged edges.  Sweep units are (P chunk,
-// Q edge) entries packed as cp << USHIFT | f in UnitT (16 bits up to 512
-// edges a side, 32 beyond).
-template <typename UnitT, int USHIFT>
-__device__ void tiled_accumulate(RingLds P, int n, RingLds Q, int m, int kq, int lane, uint16_t *list,
-                                 UnitT *units, uint32_t *xbuf, unsigned long long *swept, double &accP,
-                                 double &accQ, double &accM, double &accK)
+// The crossings of the edges of ncp chunks of P with the m edges of Q staged
+// in LDS (a whole ring, or a window of a longer one), handed to `flush` 64
+// and more at a time.  Sweep units are (P chunk, Q edge) entries packed as
+// cp << USHIFT | f in UnitT (16 bits up to 512 edges a side, 32 beyond).  P's
+// chunks hold CSTEP vertices each; with CID, box c is that of chunk cid[c].
+template <typename UnitT, int USHIFT, int CSTEP, bool CID, int XCAP, typename Flush>
+__device__ __forceinline__ void tiled_accumulate(RingLds P, int ncp, RingLds Q, int m, int lane, const uint8_t *cid,
+                                                 uint16_t *list, UnitT *units, uint32_t *xbuf,
+                                                 unsigned long long *swept, Flush flush)
 {
-    const int ncp = (n + 7) >> 3, ncq = (m + 7) >> 3;
+    const int ncq = (m + 7) >> 3;
     const int total = ncp * ncq;
-    // idx -> (idx / ncq, idx % ncq) without an integer division: the float
-    // quotient of idx + 1/2 is at least 1/(2 ncq) >= 1/256 away from an
-    // integer (ncq <= 128) while its rounding error is below 2^-15 (the
-    // quotient is below ncp <= 128 and carries two roundings of 2^-24).
+    // chunk pair idx = (idx / ncq, idx % ncq), a lane's next one 128 on: the
+    // float quotient of idx + 1/2 is at least 1/(2 ncq) >= 1/256 away from an
+    // integer (ncq <= 128) while its rounding error is below 2^-15
     const float rq = 1.0f / (float)ncq;
+    const int dp = (int)(128.5f * rq), dq = 128 - dp * ncq;
+    int cp[2], cq[2];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        cp[h] = (int)(((float)(64 * h + lane) + 0.5f) * rq);
+        cq[h] = 64 * h + lane - cp[h] * ncq;
+    }
     int head = 0, tail = 0, uhead = 0, utail = 0, xcount = 0;
     // two batches of 64 chunk pairs per round trip through the tile list
     for (int base = 0; base < total; base += 128) {
+        uint64_t ov[2];
         int en[2];
-        bool ov[2];
-        // branch-free: whole boxes loaded at once, bitwise tests (no
-        // short-circuit chains of dependent LDS reads)
+        // branch-free: whole boxes loaded at once (no short-circuit chains of
+        // dependent LDS reads); pairs past the end read pair 0's
 #pragma unroll
         for (int h = 0; h < 2; h++) {
-            const int i0 = base + 64 * h + lane;
-            const bool live = i0 < total;
-            const int idx = live ? i0 : 0;
-            const int cp = (int)(((float)idx + 0.5f) * rq);
-            const int cq = idx - cp * ncq;
-            const int4 bp = P.box[cp], bq = Q.box[cq];
-            const bool apart = (bp.z < bq.x) | (bq.z < bp.x) | (bp.w < bq.y) | (bq.w < bp.y);
-            ov[h] = live & !apart;
-            en[h] = (cp << 8) | cq;
+            const bool live = cp[h] < ncp;
+            const int4 bp = P.box[live ? cp[h] : 0], bq = Q.box[cq[h]];
+            ov[h] = __ballot(live) & __ballot(bp.z >= bq.x) & __ballot(bq.z >= bp.x) & __ballot(bp.w >= bq.y) &
+                    __ballot(bq.w >= bp.y);
+            en[h] = (cp[h] << 8) | cq[h];
+            cp[h] += dp;
+            cq[h] += dq;
+            if (cq[h] >= ncq) { cq[h] -= ncq; cp[h]++; }
         }
-        const uint64_t mk0 = __ballot(ov[0]), mk1 = __ballot(ov[1]);
-        const int r0 = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mk0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk0, 0u));
-        const int r1 = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mk1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk1, 0u));
-        const int c0 = __popcll(mk0);
-        if (ov[0]) list[(tail + r0) & (kListCap - 1)] = (uint16_t)en[0];
-        if (ov[1]) list[(tail + c0 + r1) & (kListCap - 1)] = (uint16_t)en[1];
-        tail += c0 + __popcll(mk1);
+        const int c0 = __popcll(ov[0]);
+        const int r0 = lanes_below(ov[0]), r1 = lanes_below(ov[1]);
+        if (lane_in(ov[0])) list[(tail + r0) & (kListCap - 1)] = (uint16_t)en[0];
+        if (lane_in(ov[1])) list[(tail + c0 + r1) & (kListCap - 1)] = (uint16_t)en[1];
+        tail = __builtin_amdgcn_readfirstlane(tail + c0 + __popcll(ov[1]));
         const bool last = base + 128 >= total;
-        while (tail - head >= 16 || (last && tail > head)) {
+        while (tail - head >= 16 || (last && (tail > head || utail > uhead))) {
             wave_lds_sync();
-            const int cnt = min(16, tail - head);
-            expand_tiles<UnitT, USHIFT>(P, Q, m, list, head, cnt, lane, units, utail);
-            head += cnt;
+            if (tail > head) {
+                const int cnt = min(16, tail - head);
+                expand_tiles<UnitT, USHIFT, CID>(P, Q, m, cid, list, head, cnt, lane, units, utail);
+                head += cnt;
+            }
             wave_lds_sync();
-            while (utail - uhead >= 64) {
-                sweep_units<USHIFT>(P, Q, (int)units[(uhead + lane) & (kUnitCap - 1)], lane, xbuf, xcount, kq, accP,
-                                    accQ, accM, accK);
-                uhead += 64;
+            const bool rest = last && tail == head;
+            while (utail - uhead >= 64 || (rest && utail > uhead)) {
+                // in a partial sweep idle lanes take a padding edge of Q (zero length)
+                const int k = min(64, utail - uhead);
+                const int entry = lane < k ? (int)units[(uhead + lane) & (kUnitCap - 1)] : 8 * ncq;
+                uint32_t hits = sweep_units<USHIFT, CSTEP>(P, Q, entry);
+                uhead += k;
+                // (e << 16 | f) of the lanes' crossings, one a lane and turn
+                for (uint64_t cm = __ballot(hits != 0); cm != 0; cm = __ballot(hits != 0)) {
+                    if (xcount + __popcll(cm) > XCAP) {
+                        wave_lds_sync();
+                        flush(xcount);
+                        wave_lds_sync();
+                        xcount = 0;
+                    }
+                    if (hits != 0) {
+                        const int lead = __builtin_clz(hits);    // 24 + i
+                        xbuf[xcount + lanes_below(cm)] =
+                            ((uint32_t)(8 * (entry >> USHIFT) + lead - 24) << 16) | (uint32_t)(entry & ((1 << USHIFT) - 1));
+                        hits &= ~(0x80000000u >> lead);
+                    }
+                    xcount = __builtin_amdgcn_readfirstlane(xcount + __popcll(cm));
+                }
             }
         }
     }
-    if (utail > uhead) {
-        // partial sweep: idle lanes take a padding edge of Q (zero length)
-        const int k = utail - uhead;
-        const int entry = lane < k ? (int)units[(uhead + lane) & (kUnitCap - 1)] : 8 * ncq;
-        sweep_units<USHIFT>(P, Q, entry, lane, xbuf, xcount, kq, accP, accQ, accM, accK);
-    }
     if (xcount > 0) {
         wave_lds_sync();
-        flush_crossings(P, Q, xbuf, xcount, lane, kq, accP, accQ, accM, accK);
+        flush(xcount);
     }
     *swept += 8ull * (unsigned long long)utail;   // edge pairs tested (idle lanes excluded)
-}
-
-// 2 A(P n Q) from the crossing sums and the anchors' memberships (wkp at
-// P's vertex kp, wkq at Q's vertex kq).
-__device__ double tiled_finish(RingLds P, int n, int sp, int sq, int64_t a2p, int64_t a2q, int kp, int wkp,
-                               int wkq, int lane, double accP, double accQ, double accM, double accK)
-{
-    // make the crossing sums visible to the whole wavefront
-    wave_lds_sync();
-    // 2 A = sp * (mp + sq * accP) + sq * (mq + sp * accQ) with
-    //   mp = w0p * A2P + sq * T,  w0p = w(kp) - sq * pre_P(kp),
-    //   mq = w0q * A2Q + sp * accM,  w0q = w(kq) - sp * pre_Q(kq), pre_Q(kq) = sum of accK
-    int K;
-    const double T = membership_term_p(P, n, kp, lane, K);
-    const double tot = (double)(sp * sq) * (T + accP + accQ + accM - (double)a2q * accK);
-    return wave_sum(tot) + (double)(sp * (wkp - sq * K)) * (double)a2p + (double)(sq * wkq) * (double)a2q;
-}
-
-// kp / kq: a vertex of P outside Q (and of Q outside P), or -1; the ring's
-// memberships are anchored there (membership 0), else at vertex 0 by a
-// crossing-number pass.
-template <typename UnitT, int USHIFT>
-__device__ double tiled_pair(RingLds P, int n, RingLds Q, int m, int sp, int sq, int64_t a2p, int64_t a2q,
-                             int kp, int kq, int lane, uint16_t *list, UnitT *units, uint32_t *xbuf,
-                             unsigned long long *swept)
-{
-    int wkp = 0, wkq = 0;
-    if (kp < 0 || kq < 0) {
-        int w0p, w0q;
-        member_starts(P, n, Q, m, lane, kp < 0, kq < 0, w0p, w0q);
-        if (kp < 0) { kp = 0; wkp = w0p; }
-        if (kq < 0) { kq = 0; wkq = w0q; }
-    }
-    double accP = 0.0, accQ = 0.0, accM = 0.0, accK = 0.0;
-    tiled_accumulate<UnitT, USHIFT>(P, n, Q, m, kq, lane, list, units, xbuf, swept, accP, accQ, accM, accK);
-    return tiled_finish(P, n, sp, sq, a2p, a2q, kp, wkp, wkq, lane, accP, accQ, accM, accK);
 }
 
 // A vertex of Q strictly outside P's MBR among Q's extreme vertices, or -1.
@@ -970,6 +887,111 @@ __device__ __forceinline__ double jaccard_of(double inter2, int64_t a2p, int64_t
     return u > 0 ? inter / u : 0.0;
 }
 
+// Groups of pairs.  A wavefront takes its candidates 64 at a time, a lane
+// each, and packs consecutive tiled ones into groups of up to kGroup data
+// polygons and 64 chunks: the pass over the vertices (a chunk a lane), the
+// tile list, the sweep and the crossing buffer then serve the group together,
+// where a pair of average size (78 by 76 edges, 58 sweep units) fills a third
+// of each.  A chunk is staged with its 9 vertices (the shared ones twice), so
+// polygons follow each other without padding and the sweep's strided reads
+// fall on different banks.
+//
+// With T exchanged like Q's sum, sum_e cr_e * sum_{e' < e} S_e' =
+// sum_{e'} S_e' Suf_P(e'), every term of 2 A(P n Q) but the anchors' is a sum
+// over crossings, and the anchors' K are too: for a crossing of edges e and f
+// with signs s4 (along P) and s2 (along Q), parameters t and t',
+//   s4 (cr_e (1 - t) + Suf_P(e) - [e < kp] A2P) + s2 (cr_f (1 - t') + Suf_Q(f) - [f < kq] A2Q).
+// Suf_P comes from the chunks' exclusive prefix of cross products and the
+// cross products inside the crossing's chunk.  All but the parameters' terms
+// are whole numbers; those are rounded to a fixed point of the query (sums
+// wrap, the result does not: 2 A(P n Q) is at most twice the query's MBR, and
+// 6 bits are spare), so a pair's sum is taken by 64-bit integer additions in
+// any order and does not depend on the pairs beside it.
+//
+// Bound by the vector units: 477 instructions a pair at 6.5 million pairs of
+// 78 by 76 edges on average (a third of them the sweep's, 463 edge pairs and
+// 24 crossings a pair), 7.2 ms with the units issuing 71% of the time, 12.4 ms
+// a pair at a time (949 instructions).  Four wavefronts a SIMD by registers
+// and LDS.  Not better: 16 pairs a group (LDS for three workgroups), a test
+// of a chunk's box against the line of Q's edge (few units fall out).
+constexpr int kGroup = 8;
+constexpr int kGroupCross = 64;    // a crossing a lane
+
+struct GroupLds {
+    int2 *v;               // 9 vertices a chunk
+    int64_t *pre;          // cross products before chunk c of the group
+    uint8_t *pair_of;      // pair of chunk c
+    int4 *con;             // per pair: first chunk, end chunk, P's anchor (edge of the group), Q's anchor
+    unsigned long long *acc;   // per pair: its sum, in fixed point
+};
+
+// A value below 2^62 as a whole number of 2^-s, modulo 2^64 (s <= 52).
+__device__ __forceinline__ int64_t fixed_point(double v, int s, double scale)
+{
+    const double w = floor(v);
+    return (int64_t)((uint64_t)(int64_t)w << s) + (int64_t)rint((v - w) * scale);
+}
+
+__device__ void flush_group(const GroupLds &G, RingLds Q, const int64_t *suf, int64_t a2q, int s, double scale,
+                            const uint32_t *buf, int count, int lane)
+{
+    if (lane < count) {
+        const uint32_t ef = buf[lane];
+        const int e = (int)(ef >> 16), f = (int)(ef & 0xffffu);
+        const int cc = e >> 3, i = e & 7;
+        const int g = G.pair_of[cc];
+        const int4 con = G.con[g];
+        const int2 c = Q.v[f], d = Q.v[f + 1];
+        const int2 *v = G.v + 9 * cc;
+        const int2 a = v[i], b = v[i + 1];
+        int2 u = v[0];
+        int64_t before = 0;    // cross products of the chunk's edges up to e
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            const int2 w = v[j + 1];
+            const int keep = j <= i ? -1 : 0;
+            before += (int64_t)(u.x & keep) * w.y - (int64_t)(w.x & keep) * u.y;
+            u = w;
+        }
+        const int64_t sp = G.pre[e < con.z ? con.x : con.y] - G.pre[cc] - before;
+        const int64_t sq = suf[f] - (f < con.w ? a2q : 0);
+        const double ax = (double)a.x, ay = (double)a.y, bx = (double)b.x, by = (double)b.y;
+        const double cx = (double)c.x, cy = (double)c.y;
+        const double ex = bx - ax, ey = by - ay;
+        const double fx = (double)(d.x - c.x), fy = (double)(d.y - c.y);
+        const double rx = cx - ax, ry = cy - ay;
+        const double oc = __fma_rn(ex, ry, -(ey * rx));
+        const double oa = __fma_rn(fy, rx, -(fx * ry));
+        const double X = __fma_rn(ex, fy, -(ey * fx));
+        const double od = oc + X, ob = oa - X;
+        const bool p2 = od > p_edge_threshold(ex, ey);
+        const bool p4 = __builtin_amdgcn_class(ob, q_edge_class(d.x - c.x, d.y - c.y));
+        const double cre = __fma_rn(ax, by, -(bx * ay));
+        const double crf = __fma_rn(cx, fy, -(fx * cy));
+        const double t = cre * (p4 ? 1.0 : -1.0) * (-ob) * rcp_refined(oa - ob) +
+                         crf * (p2 ? 1.0 : -1.0) * (-od) * rcp_refined(oc - od);
+        const int64_t whole = (p4 ? sp : -sp) + (p2 ? sq : -sq);
+        atomicAdd(&G.acc[g], (unsigned long long)(((uint64_t)whole << s) + (uint64_t)fixed_point(t, s, scale)));
+    }
+}
+
+// Ring-start memberships of a pair in one pass: w0p for P's vertex 0 against
+// Q + delta, w0q for Q's vertex 0 + delta against P (chunks of 9 vertices).
+__device__ void member_starts(const int2 *P, int n, const int2 *Q, int m, int lane, bool need_p, bool need_q, int &w0p,
+                              int &w0q)
+{
+    const int2 p0 = P[0], q0 = Q[0];
+    bool oddp = false, oddq = false;
+    const int top = max(need_p ? m : 0, need_q ? n : 0);
+    for (int e = lane; e < top; e += 64) {
+        const bool lq = need_p & (e < m), lp = need_q & (e < n);
+        oddp ^= lq & member_edge(Q, lq ? e : 0, p0, -1);
+        oddq ^= lp & member_edge(P, lp ? e + (e >> 3) : 0, q0, +1);
+    }
+    w0p = __popcll(__ballot(oddp)) & 1;
+    w0q = __popcll(__ballot(oddq)) & 1;
+}
+
 __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ dxy,
                                                 const int64_t *__restrict__ doff,
                                                 const int32_t *__restrict__ qxy,
@@ -982,19 +1004,25 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
 {
     __shared__ int2 sQv[kRingLds];
     __shared__ int4 sQbox[kTileCap / 8];
-    __shared__ int2 sPv[kWavesPerBlock][kRingLds];
-    __shared__ int4 sPbox[kWavesPerBlock][kTileCap / 8];
-    __shared__ uint32_t sPS[kWavesPerBlock][kTileCap / 2];
-    __shared__ double sQsuf[kTileCap];
+    __shared__ int64_t sQsuf[kTileCap];
+    __shared__ int2 sPv[kWavesPerBlock][64 * 9];
+    __shared__ int4 sPbox[kWavesPerBlock][64];
+    __shared__ int64_t sPre[kWavesPerBlock][64 + 1];
+    __shared__ int4 sCon[kWavesPerBlock][kGroup];
+    __shared__ unsigned long long sAcc[kWavesPerBlock][kGroup];
+    __shared__ uint8_t sPairOf[kWavesPerBlock][64];
+    __shared__ uint8_t sCid[kWavesPerBlock][64];
     __shared__ uint16_t sList[kWavesPerBlock][kListCap];
     __shared__ uint16_t sUnits[kWavesPerBlock][kUnitCap];
-    __shared__ uint32_t sCross[kWavesPerBlock][kCrossCap];
+    // the crossing buffer; before the sweep, the pairs' MBRs and P's anchors
+    __shared__ __align__(16) uint32_t sCross[kWavesPerBlock][kGroupCross];
+    static_assert(kGroupCross >= 5 * kGroup, "MBRs and anchors fit the crossing buffer");
     __shared__ int32_t sQmbr[4];
     __shared__ long long sQa2;
     __shared__ int sQext[4];
 
-    // `slices` workgroups share a query (small batches): slice s's wavefronts
-    // take candidates s * waves + wave, stepping by slices * waves
+    // `slices` workgroups share a query, and their wavefronts its candidates
+    // in equal runs
     const int64_t q = blockIdx.x / slices;
     const int slice = (int)(blockIdx.x % slices);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1009,6 +1037,16 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
             cand_j[c] = 0.0;
         return;
     }
+    const int nwaves = (int)(blockDim.x >> 6) * slices;   // wavefronts on this query
+    const int64_t w = (int64_t)slice * (blockDim.x >> 6) + wave;
+    const int64_t cs = c0 + (c1 - c0) * w / nwaves, ce = c0 + (c1 - c0) * (w + 1) / nwaves;
+    // the first candidates' vertex ranges are fetched behind Q's staging
+    int64_t pa_next = 0, pe_next = 0;
+    if (cs < ce) {
+        const int32_t id = cand_ids[cs + lane < ce ? cs + lane : cs];
+        pa_next = doff[id];
+        pe_next = doff[id + 1];
+    }
     const int64_t ox = Qg[0], oy = Qg[1];
     const bool q_tiled = m <= kTileCap;
     if (wave == 0) {
@@ -1020,17 +1058,17 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
             sQa2 = a2;
         }
     }
+    const RingLds Qs{sQv, sQbox, nullptr, nullptr};
     if (q_tiled) {
         // Q padded by one extra chunk: the all-padding chunk ncq fills empty
         // slots of a partial tile group
         const int qpad = 8 * ((m + 7) >> 3) + 8;
-        RingLds Qs{sQv, sQbox, nullptr, sQsuf};
         stage_ring(Qg, m, qpad + 1, ox, oy, Qs, tid, blockDim.x);
         __syncthreads();
         chunk_boxes(Qs, m, tid, blockDim.x);
         __syncthreads();
         if (wave == 0) {
-            q_suffix_sums(Qs, m, sQa2, lane);
+            q_suffix_sums(Qs, m, sQa2, lane, sQsuf);
             const int4 rb = make_int4((int)((int64_t)sQmbr[0] - ox), (int)((int64_t)sQmbr[1] - oy),
                                       (int)((int64_t)sQmbr[2] - ox), (int)((int64_t)sQmbr[3] - oy));
             q_extremes(Qs, m, rb, lane, sQext);
@@ -1040,44 +1078,153 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
     const int32_t qmbr[4] = {sQmbr[0], sQmbr[1], sQmbr[2], sQmbr[3]};
     const int qext[4] = {sQext[0], sQext[1], sQext[2], sQext[3]};
     const int64_t a2q = sQa2;
-    const int nwaves = (int)(blockDim.x >> 6) * slices;   // wavefronts on this query
+    // 2^qs: the fixed point of this query's sums
+    const int qs = [&] {
+        const double box2 = 2.0 * ((double)qmbr[2] - qmbr[0] + 1) * ((double)qmbr[3] - qmbr[1] + 1);
+        const int bits = (int)((__double_as_longlong(box2) >> 52) & 0x7ff) - 1022;   // box2 < 2^bits
+        return __builtin_amdgcn_readfirstlane(max(0, min(52, 56 - bits)));
+    }();
+    const double qscale = (double)(1ll << qs), qunscale = 1.0 / qscale;
+    const GroupLds G{sPv[wave], sPre[wave], sPairOf[wave], sCon[wave], sAcc[wave]};
+    const RingLds Ps{sPv[wave], sPbox[wave], nullptr, nullptr};
+    int32_t *const box_of = reinterpret_cast<int32_t *>(sCross[wave]), *const anchor_of = box_of + 4 * kGroup;
     unsigned long long st_tiled = 0, st_swept = 0, st_general = 0, st_disjoint = 0;
-    // Candidate metadata is fetched ahead: the id two candidates on and the
-    // vertex range of the next one, so their latency hides behind this pair.
-    int64_t c = c0 + (int64_t)slice * (blockDim.x >> 6) + wave;
-    int32_t p_ahead = c < c1 ? cand_ids[c] : 0;
-    int64_t pa_next = 0, pe_next = 0;
-    if (c < c1) { pa_next = doff[p_ahead]; pe_next = doff[p_ahead + 1]; }
-    p_ahead = (c + nwaves < c1) ? cand_ids[c + nwaves] : 0;
-    // the data polygon's first 128 vertices are fetched one candidate ahead
-    RingPrefetch pf_next;
-    if (c < c1 && pe_next - pa_next >= 3) prefetch_ring(dxy + 2 * pa_next, (int)(pe_next - pa_next), lane, pf_next);
-    for (; c < c1; c += nwaves) {
+    for (int64_t cb = cs; cb < ce; cb += 64) {
+        const int64_t c = cb + lane;
+        const bool live = c < ce;
         const int64_t pa = pa_next;
         const int n = (int)(pe_next - pa_next);
-        const RingPrefetch pf = pf_next;
-        if (c + nwaves < c1) { pa_next = doff[p_ahead]; pe_next = doff[p_ahead + 1]; }
-        p_ahead = (c + 2 * nwaves < c1) ? cand_ids[c + 2 * nwaves] : 0;
-        const int32_t *Pg = dxy + 2 * pa;
-        double J = 0.0;
-        bool deferred = false;
-        int slot = 0;
-        const bool valid = n >= 3 && a2q != 0;
-        const bool tiled_size = valid && q_tiled && n <= kTileCap;
-        RingLds Ps{sPv[wave], sPbox[wave], sPS[wave], nullptr};
-        RingLds Qs{sQv, sQbox, nullptr, sQsuf};
-        const int ppad = 8 * ((n + 7) >> 3);
-        int32_t pm[4] = {0, 0, 0, 0};
-        // staging records the MBR of the absolute coordinates, so a wide
-        // pair (whose relative coordinates do not fit) is still detected
-        int kp = -1;
-        int64_t a2p_staged = 0;
-        if (tiled_size) stage_ring_mbr(Pg, n, ppad + 1, ox, oy, Ps, lane, qmbr, pf, pm, a2p_staged, kp);
-        else if (valid) poly_mbr(Pg, n, lane, pm);
-        // the next candidate's vertices, whatever this pair turns out to need
-        if (c + nwaves < c1 && pe_next - pa_next >= 3)
-            prefetch_ring(dxy + 2 * pa_next, (int)(pe_next - pa_next), lane, pf_next);
-        if (valid) {
+        if (cb + 64 < ce) {
+            const int32_t id = cand_ids[c + 64 < ce ? c + 64 : cb + 64];
+            pa_next = doff[id];
+            pe_next = doff[id + 1];
+        }
+        const bool valid = live & (n >= 3) & (a2q != 0);
+        const bool small = valid & q_tiled & (n <= kTileCap);
+        if (live & !valid) cand_j[c] = 0.0;
+        uint64_t big = __ballot(valid & !small), todo = __ballot(small);
+        const int nch = small ? (n + 7) >> 3 : 0;
+        const int before = wave_incl_scan32(nch) - nch, rank = lanes_below(todo);
+        while (todo) {
+            // the group: lanes `gm`, pair g's chunks from first_chunk
+            const int first = __builtin_ctzll(todo);
+            const int first_chunk = before - __builtin_amdgcn_readlane(before, first);
+            const int g = rank - __builtin_amdgcn_readlane(rank, first);
+            const bool mem = small & (lane >= first) & (first_chunk + nch <= 64) & (g < kGroup);
+            const uint64_t gm = __ballot(mem);
+            todo &= ~gm;
+            const int total = __builtin_amdgcn_readlane(first_chunk + nch, 63 - __builtin_clzll(gm));
+            // lane = chunk from here on: its pair's lane, polygon and place
+            int src = first;
+            for (uint64_t mm = gm & (gm - 1); mm; mm &= mm - 1) {
+                const int sl = __builtin_ctzll(mm);
+                src = lane >= __builtin_amdgcn_readlane(first_chunk, sl) ? sl : src;
+            }
+            const int pn = __shfl(n, src), pg = __shfl(g, src), v0 = 8 * (lane - __shfl(first_chunk, src));
+            const int2 *V = reinterpret_cast<const int2 *>(dxy) + __shfl(pa, src);
+            int2 p[9];
+#pragma unroll
+            for (int j = 0; j < 9; j++) p[j] = V[v0 + j < pn ? v0 + j : 0];
+            // the wavefront is done with the group before
+            wave_lds_sync();
+            if (lane < 4 * kGroup) box_of[lane] = (lane & 3) < 2 ? INT32_MAX : INT32_MIN;
+            if (lane < kGroup) { anchor_of[lane] = -1; G.acc[lane] = 0; }
+            wave_lds_sync();
+            int4 box = make_int4(p[0].x, p[0].y, p[0].x, p[0].y);
+            int out = -1;
+            int64_t cross = 0;
+            int2 r0 = make_int2((int)((uint32_t)p[0].x - (uint32_t)ox), (int)((uint32_t)p[0].y - (uint32_t)oy));
+            G.v[9 * lane] = r0;
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                // relative coordinates in 32 bits (wrapping): exact unless the
+                // pair spans 2^26 or more, which is found from the MBRs
+                const int2 r1 = make_int2((int)((uint32_t)p[j + 1].x - (uint32_t)ox),
+                                          (int)((uint32_t)p[j + 1].y - (uint32_t)oy));
+                G.v[9 * lane + j + 1] = r1;
+                cross += (int64_t)r0.x * r1.y - (int64_t)r1.x * r0.y;
+                r0 = r1;
+                box.x = min(box.x, p[j + 1].x); box.z = max(box.z, p[j + 1].x);
+                box.y = min(box.y, p[j + 1].y); box.w = max(box.w, p[j + 1].y);
+                const bool o = ((uint32_t)p[j].x - (uint32_t)qmbr[0] > (uint32_t)qmbr[2] - (uint32_t)qmbr[0]) |
+                               ((uint32_t)p[j].y - (uint32_t)qmbr[1] > (uint32_t)qmbr[3] - (uint32_t)qmbr[1]);
+                out = o ? (v0 + j < pn ? v0 + j : 0) : out;
+            }
+            const int64_t upto = wave_incl_scan64(cross);
+            G.pre[lane + 1] = upto;
+            if (lane == 0) G.pre[0] = 0;
+            G.pair_of[lane] = (uint8_t)pg;
+            if (lane < total) {
+                atomicMin(&box_of[4 * pg], box.x); atomicMin(&box_of[4 * pg + 1], box.y);
+                atomicMax(&box_of[4 * pg + 2], box.z); atomicMax(&box_of[4 * pg + 3], box.w);
+                // any vertex outside Q's MBR will do
+                if (out >= 0) atomicMax(&anchor_of[pg], out);
+            }
+            wave_lds_sync();
+            // lane = pair: what it is, and its anchors
+            const int gi = mem ? g : 0, ca = mem ? first_chunk : 0, cz = mem ? first_chunk + nch : 0;
+            const int4 pb = *reinterpret_cast<const int4 *>(box_of + 4 * gi);
+            int kp = anchor_of[gi];
+            const int64_t a2p = G.pre[cz] - G.pre[ca];
+            const bool apart = (pb.z <= qmbr[0]) | (qmbr[2] <= pb.x) | (pb.w <= qmbr[1]) | (qmbr[3] <= pb.y);
+            const bool wide = ((uint32_t)max(pb.z, qmbr[2]) - (uint32_t)min(pb.x, qmbr[0]) >= 1u << 26) |
+                              ((uint32_t)max(pb.w, qmbr[3]) - (uint32_t)min(pb.y, qmbr[1]) >= 1u << 26);
+            const uint64_t wm = __ballot(mem & !apart & wide);
+            st_disjoint += (unsigned long long)__popcll(__ballot(mem & apart));
+            st_tiled += (unsigned long long)__popcll(__ballot(mem & !apart & !wide));
+            big |= wm;
+            const bool act = mem & !apart & !wide & (a2p != 0);
+            const uint64_t am = __ballot(act);
+            int kq = qmbr[0] < pb.x ? qext[0] : qmbr[2] > pb.z ? qext[1] : qmbr[1] < pb.y ? qext[2]
+                   : qmbr[3] > pb.w ? qext[3] : -1;
+            int wkp = 0, wkq = 0;
+            for (uint64_t mm = __ballot(act & ((kp < 0) | (kq < 0))); mm; mm &= mm - 1) {
+                const int sl = __builtin_ctzll(mm);
+                int w0p, w0q;
+                member_starts(G.v + 9 * __builtin_amdgcn_readlane(first_chunk, sl), __builtin_amdgcn_readlane(n, sl), sQv,
+                              m, lane, __builtin_amdgcn_readlane(kp, sl) < 0, __builtin_amdgcn_readlane(kq, sl) < 0,
+                              w0p, w0q);
+                wkp = lane == sl ? w0p : wkp;
+                wkq = lane == sl ? w0q : wkq;
+            }
+            kp = max(kp, 0);
+            kq = max(kq, 0);
+            if (mem) G.con[g] = make_int4(first_chunk, first_chunk + nch, 8 * first_chunk + kp, kq);
+            // lane = chunk: those that meet Q's MBR are listed
+            const bool keep = (lane < total) & (((am >> src) & 1) != 0) & !((box.z < qmbr[0]) | (qmbr[2] < box.x) |
+                              (box.w < qmbr[1]) | (qmbr[3] < box.y));
+            const uint64_t km = __ballot(keep);
+            const int at = lanes_below(km);
+            if (keep) {
+                sPbox[wave][at] = make_int4((int)((uint32_t)box.x - (uint32_t)ox), (int)((uint32_t)box.y - (uint32_t)oy),
+                                            (int)((uint32_t)box.z - (uint32_t)ox), (int)((uint32_t)box.w - (uint32_t)oy));
+                sCid[wave][at] = (uint8_t)lane;
+            }
+            wave_lds_sync();
+            tiled_accumulate<uint16_t, 10, 9, true, kGroupCross>(
+                Ps, __popcll(km), Qs, m, lane, sCid[wave], sList[wave], sUnits[wave], sCross[wave], &st_swept,
+                [&](int count) { flush_group(G, Qs, sQsuf, a2q, qs, qscale, sCross[wave], count, lane); });
+            wave_lds_sync();
+            // lane = pair: 2 A = sp sq sum + sp w(kp) A2P + sq w(kq) A2Q
+            const int64_t sum = (int64_t)G.acc[gi];
+            const int64_t ends = (wkp ? (a2p < 0 ? -a2p : a2p) : 0) + (wkq ? (a2q < 0 ? -a2q : a2q) : 0);
+            const int64_t fixed = (int64_t)((uint64_t)((a2p ^ a2q) < 0 ? -sum : sum) + ((uint64_t)ends << qs));
+            const double J = act ? jaccard_of((double)fixed * qunscale, a2p, a2q) : 0.0;
+            if (mem & !(!apart & wide)) cand_j[c] = J;
+        }
+        // pairs beyond the tiled form, one at a time
+        for (; big; big &= big - 1) {
+            const int sl = __builtin_ctzll(big);
+            const int64_t cl = cb + sl;
+            const int64_t pal = (int64_t)dpp::readlane64((uint64_t)pa, sl);
+            const int nl = __builtin_amdgcn_readlane(n, sl);
+            const int32_t *Pg = dxy + 2 * pal;
+            double J = 0.0;
+            bool deferred = false;
+            int slot = 0;
+            int32_t pm[4];
+            poly_mbr(Pg, nl, lane, pm);
+            const bool small_pair = q_tiled & (nl <= kTileCap);   // only wide ones come here, counted above
             const bool disjoint = pm[2] <= qmbr[0] || qmbr[2] <= pm[0] || pm[3] <= qmbr[1] || qmbr[3] <= pm[1];
             st_disjoint += disjoint;
             if (!disjoint) {
@@ -1086,37 +1233,26 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
                 const bool wide = span >= (1ll << 26);
                 double inter2 = 0.0;
                 int64_t a2p = 0;
-                if (!wide && tiled_size) {
-                    for (int i = lane; i < (n + 1) >> 1; i += 64) Ps.S[i] = kSBias;
-                    wave_lds_sync();
-                    chunk_boxes_p<kTileCap / 8>(Ps, n, lane);
-                    a2p = a2p_staged;
-                    wave_lds_sync();
-                    if (a2p != 0)
-                        inter2 = tiled_pair<uint16_t, 10>(Ps, n, Qs, m, a2p > 0 ? 1 : -1, a2q > 0 ? 1 : -1, a2p,
-                                                          a2q, kp, anchor_q(qmbr, pm, qext), lane,
-                                                          sList[wave], sUnits[wave], sCross[wave], &st_swept);
-                    st_tiled++;
-                } else if (hw.count && !wide && defer_wide(hw, c, pa, n, (int32_t)q, lane)) {
+                if (hw.count && !wide && !small_pair && defer_wide(hw, cl, pal, nl, (int32_t)q, lane)) {
                     // tiled form on wavefronts of the next launch
                     deferred = true;
-                } else if (hw.count && (int64_t)n * m >= kHeavyMin &&
-                           (a2p = poly_area2(Pg, n, ox, oy, lane)) != 0 &&
+                } else if (hw.count && (int64_t)nl * m >= kHeavyMin &&
+                           (a2p = poly_area2(Pg, nl, ox, oy, lane)) != 0 &&
                            (slot = __builtin_amdgcn_readfirstlane(lane == 0 ? atomicAdd(hw.count, 1) : 0)) <
                                kHeavyCap) {
                     // split over many wavefronts by the next launches
-                    st_general += 2ull * (unsigned long long)n * (unsigned long long)m;
+                    st_general += 2ull * (unsigned long long)nl * (unsigned long long)m;
                     if (lane == 0) {
                         HeavyPair &h = hw.pairs[slot];
-                        h.c = c; h.pa = pa; h.qa = qa; h.ox = ox; h.oy = oy; h.a2p = a2p; h.a2q = a2q;
-                        h.n = n; h.m = m; h.wide = wide; h.pad = 0;
+                        h.c = cl; h.pa = pal; h.qa = qa; h.ox = ox; h.oy = oy; h.a2p = a2p; h.a2q = a2q;
+                        h.n = nl; h.m = m; h.wide = wide; h.pad = 0;
                         for (int i = 0; i < 4; i++) { h.qmbr[i] = qmbr[i]; h.pm[i] = pm[i]; }
                     }
                     deferred = true;
                 } else {
-                    st_general += 2ull * (unsigned long long)n * (unsigned long long)m;
+                    st_general += 2ull * (unsigned long long)nl * (unsigned long long)m;
                     PairIn in;
-                    in.P = Pg; in.n = n; in.Q = Qg; in.m = m; in.ox = ox; in.oy = oy;
+                    in.P = Pg; in.n = nl; in.Q = Qg; in.m = m; in.ox = ox; in.oy = oy;
                     in.qmbr[0] = qmbr[0]; in.qmbr[1] = qmbr[1]; in.qmbr[2] = qmbr[2]; in.qmbr[3] = qmbr[3];
                     in.sq = a2q > 0 ? 1 : -1;
                     double sa, sb;
@@ -1133,22 +1269,22 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
                 }
                 if (a2p != 0) J = jaccard_of(inter2, a2p, a2q);
             }
+            if (lane == 0 && !deferred) cand_j[cl] = J;
         }
-        if (lane == 0 && !deferred) cand_j[c] = J;
     }
     if (stats) {
         // one sum per workgroup, added to one of kStatSlots slots when the
         // workspace has them (atomics of every wavefront on four words
         // serialise at the cache), nonzero counts only
-        __shared__ unsigned long long sStat[kWavesPerBlock][4];
+        unsigned long long *const sStat = sAcc[wave];
         if (lane == 0) {
-            sStat[wave][0] = st_tiled; sStat[wave][1] = st_swept;
-            sStat[wave][2] = st_general; sStat[wave][3] = st_disjoint;
+            sStat[0] = st_tiled; sStat[1] = st_swept;
+            sStat[2] = st_general; sStat[3] = st_disjoint;
         }
         __syncthreads();
         if (tid < 4) {
             unsigned long long v = 0;
-            for (int w = 0; w < (int)(blockDim.x >> 6); w++) v += sStat[w][tid];
+            for (int w = 0; w < (int)(blockDim.x >> 6); w++) v += sAcc[w][tid];
             if (v) {
                 if (hw.stat_slots) atomicAdd(hw.stat_slots + (blockIdx.x % kStatSlots) * 4 + tid, v);
                 else atomicAdd(stats + tid, v);
@@ -1605,10 +1741,12 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
                     stage_window(Qg, m, w0, len, 8 * ((len + 7) >> 3) + 9, ox, oy, Qs, lane);
                     wave_lds_sync();
                     chunk_boxes(Qs, len, lane, 64);
-                    qcarry = q_suffix_sums(Qs, len, a2q, lane, qcarry);
+                    qcarry = q_suffix_sums(Qs, len, a2q, lane, sQsuf, qcarry);
                     wave_lds_sync();
-                    tiled_accumulate<uint32_t, 16>(Ps, plen, Qs, len, kq - w0, lane, sList, sUnits, sCross,
-                                                   &st_swept, accP, accQ, accM, accK);
+                    tiled_accumulate<uint32_t, 16, 8, false, kCrossCap>(
+                        Ps, (plen + 7) >> 3, Qs, len, lane, nullptr, sList, sUnits, sCross, &st_swept, [&](int count) {
+                            flush_crossings(Ps, Qs, sCross, count, lane, kq - w0, accP, accQ, accM, accK);
+                        });
                     // every lane is done with the window before the next one
                     wave_lds_sync();
                 }
@@ -1813,12 +1951,13 @@ polymh_status launch_refine(const polymh_polys *data, const polymh_polys *querie
     if (nq > 0x7fffffffLL) return set_error(POLYMH_EINVAL, "refine: too many queries");
     // a query's candidates are spread over several workgroups (each stages
     // the query once) when the batch is small or its lists are long: at
-    // least 2048 workgroups, at most about 64 candidates per workgroup on
-    // average (16 per wavefront: the query's staging is cheap beside them
-    // and the long lists no longer set the launch's tail), at most 64
+    // least 2048 workgroups, at most about 128 candidates per workgroup on
+    // average (32 per wavefront, a few groups: at 650 candidates a query
+    // 7.99 ms, with 64 8.20, with 256 8.09), at least 4 (one per wavefront: 35
+    // queries of 121 candidates 45 us, with 2 a workgroup 51), at most 64
     // workgroups per query
-    const int64_t by_batch = (2048 + nq - 1) / nq;
-    const int64_t by_length = (n_cand + nq * 64 - 1) / (nq * 64);
+    const int64_t by_batch = std::min((2048 + nq - 1) / nq, (n_cand + nq * 4 - 1) / (nq * 4));
+    const int64_t by_length = (n_cand + nq * 128 - 1) / (nq * 128);
     int64_t sl = std::max<int64_t>(1, std::min<int64_t>(64, std::max(by_batch, by_length)));
     if (nq * sl > 0x7fffffffLL) sl = 1;
     const int slices = (int)sl;
