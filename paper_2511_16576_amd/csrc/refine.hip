@@ -755,8 +755,10 @@ __device__ __forceinline__ int anchor_q(const int32_t *qb, const int32_t *pb, co
 // would keep one wavefront busy for a long serial run (milliseconds for a few
 // thousand edges a side), so it is deferred: the wavefront records it, and a
 // second launch splits each side's edges into kHeavySlices strided slices,
-// one wavefront each, whose partial sums a third launch adds in a fixed
-// order.  Up to kHeavyCap pairs per call are deferred; the rest run in place.
+// one wavefront each; the one that finishes a pair's last slice adds the
+// partial sums in a fixed order (a launch of its own for that, and for the
+// split pairs' sums, cost a small call 5 us each even with nothing deferred:
+// 120 pairs 24 us, with eight launches 35).  Up to kHeavyCap pairs per call are deferred; the rest run in place.
 constexpr int kHeavySlices = 64;
 constexpr int kHeavyCap = 8192;
 constexpr int64_t kHeavyMin = 1 << 17;
@@ -769,7 +771,7 @@ struct HeavyPair {
     int32_t n, m;
     int32_t qmbr[4], pm[4];
     int32_t wide;
-    int32_t pad;
+    int32_t done;         // slices finished
 };
 
 constexpr int kStatSlots = 64;   // work counters spread over slots, folded at the end
@@ -788,9 +790,9 @@ constexpr int kWideListCap = 1 << 20;
 // staged polygon of kSplitFineP edges or more, else the shortest of 256, 512
 // and kWideCap that keeps the units within kMultiUnits), each walking Q's
 // windows, or, when Q has more than two windows, each (P window, Q window)
-// alone.  k_wide_meta finds the pair's own quantities once (areas, anchors,
+// alone.  wide_meta finds the pair's own quantities once (areas, anchors,
 // Q's window carries), every unit writes its partial sums, all linear in the
-// crossing signs, and k_refine_multi_finish adds them in window order.  Up
+// crossing signs, and finish_split adds them in window order.  Up
 // to kMultiCap such pairs per call (the rest take all their windows on one
 // wavefront).
 constexpr int kMultiCap = 4096;
@@ -837,12 +839,13 @@ struct WidePair {
 struct MultiPair {
     int64_t c;            // candidate slot (-1: the pair was not deferred)
     int64_t pa;
-    int32_t n, q, units;
-    int32_t first;        // list position of its first unit (k_wide_meta writes the units there)
-    // the pair's own quantities, written by k_wide_meta for its units and
+    int32_t n, q;
+    int32_t units;        // counted down as they are done
+    int32_t first;        // its first unit's place from the list's back
+    // the pair's own quantities, written by wide_meta for its units and
     // the finish (P and Q in k_refine_wide's roles)
     int64_t a2p, a2q;     // exact doubled areas
-    int32_t kp, kq;       // anchors (0 where a membership pass stands in)
+    int32_t kp, kq;       // anchors (0 where a membership pass stands in; kp first holds the list entry)
     int32_t wkp, wkq;     // memberships of P's vertex 0 in Q, of Q's vertex 0 in P (0 when anchored)
 };
 
@@ -851,13 +854,13 @@ struct MultiUnit {
     double cr;            // sum of the P window's cross products (first Q window's unit only)
     int32_t stot;         // sum of the window's crossing signs
     int32_t kloc;         // exclusive prefix of crossing signs at the anchor, if in this window
-    int64_t qpre;         // in: Q's cross-product sum before the unit's Q window (k_wide_meta)
+    int64_t qpre;         // in: Q's cross-product sum before the unit's Q window (wide_meta)
 };
 
 struct HeavyWs {
-    int32_t *count;       // [0] heavy pairs, [1] wide list entries recorded, [2] split pairs, [4] split
-                          // units appended after the recorded entries (each may exceed its cap: the
-                          // excess runs in place or whole), [3] wide entries taken
+    int32_t *count;       // [0] heavy pairs, [1] wide list entries recorded, [2] split pairs, [4] their
+                          // units, from the list's back (each may exceed its cap: the excess runs
+                          // in place or whole), [3] wide entries taken
     HeavyPair *pairs;     // [kHeavyCap]
     double *partial;      // [kHeavyCap][2][kHeavySlices]
     unsigned long long *stat_slots;   // [kStatSlots][4]
@@ -866,15 +869,29 @@ struct HeavyWs {
     MultiUnit *units;     // [kMultiCap][kMultiUnits]
 };
 
-// Records a pair for k_refine_wide as one list entry (k_expand splits the
-// ones split_shape splits).  False when the list is full.
-__device__ bool defer_wide(const HeavyWs &hw, int64_t c, int64_t pa, int n, int32_t q, int lane)
+// Records a pair for k_refine_wide as one list entry, from the list's front;
+// a pair that split_shape splits also gets a split slot and places for its
+// units, counted from the list's back (wide_meta writes the units there and
+// takes the entry back, or leaves the pair whole where they do not fit).  False
+// when the list is full.
+__device__ bool defer_wide(const HeavyWs &hw, int64_t c, int64_t pa, int n, int m, int32_t q, int lane)
 {
     const int slot = __builtin_amdgcn_readfirstlane(lane == 0 ? atomicAdd(hw.count + 1, 1) : 0);
     if (slot >= kWideListCap) return false;
     if (lane == 0) {
         WidePair &w = hw.wide[slot];
         w.c = c; w.pa = pa; w.n = n; w.q = q; w.pw = -1; w.qw = -1; w.slot = -1;
+        const bool swap = n > kWideCap && n > m;
+        const SplitShape sh = split_shape(swap ? m : n, swap ? n : m);
+        if (sh.units > 1) {
+            const int ms = atomicAdd(hw.count + 2, 1);
+            if (ms < kMultiCap) {
+                MultiPair &mp = hw.multi[ms];
+                mp.c = c; mp.pa = pa; mp.n = n; mp.q = q; mp.units = sh.units;
+                mp.first = atomicAdd(hw.count + 4, sh.units);
+                mp.kp = slot;
+            }
+        }
     }
     return true;
 }
@@ -1233,7 +1250,7 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
                 const bool wide = span >= (1ll << 26);
                 double inter2 = 0.0;
                 int64_t a2p = 0;
-                if (hw.count && !wide && !small_pair && defer_wide(hw, cl, pal, nl, (int32_t)q, lane)) {
+                if (hw.count && !wide && !small_pair && defer_wide(hw, cl, pal, nl, m, (int32_t)q, lane)) {
                     // tiled form on wavefronts of the next launch
                     deferred = true;
                 } else if (hw.count && (int64_t)nl * m >= kHeavyMin &&
@@ -1245,7 +1262,7 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
                     if (lane == 0) {
                         HeavyPair &h = hw.pairs[slot];
                         h.c = cl; h.pa = pal; h.qa = qa; h.ox = ox; h.oy = oy; h.a2p = a2p; h.a2q = a2q;
-                        h.n = nl; h.m = m; h.wide = wide; h.pad = 0;
+                        h.n = nl; h.m = m; h.wide = wide; h.done = 0;
                         for (int i = 0; i < 4; i++) { h.qmbr[i] = qmbr[i]; h.pm[i] = pm[i]; }
                     }
                     deferred = true;
@@ -1430,15 +1447,12 @@ __device__ int first_outside_global(const int32_t *V, int n, const int32_t *b, i
 // window, written into the units' slots as their suffix-sum carry.  All are
 // exact integers, the same as the per-unit passes gave.  Rings of up to
 // kMetaThreads x kMetaU vertices take one round trip to memory a pass.  The
-// workgroup also writes the pair's unit entries at the list positions
-// k_expand reserved (one thread each, where a thread of k_expand wrote them
-// all in turn).
+// workgroup also writes the pair's unit entries at their places in the list.
 constexpr int kMetaThreads = 1024;
 constexpr int kMetaU = 8;
 
-__global__ __launch_bounds__(kMetaThreads) void k_wide_meta(const int32_t *__restrict__ dxy,
-                                                          const int32_t *__restrict__ qxy,
-                                                          const int64_t *__restrict__ qoff, HeavyWs hw)
+__device__ void wide_meta(const int32_t *__restrict__ dxy, const int32_t *__restrict__ qxy,
+                          const int64_t *__restrict__ qoff, const HeavyWs &hw, int block, int blocks)
 {
     __shared__ unsigned long long sWin[kMultiUnits];   // Q's cross products per window of kWideCap edges
     __shared__ unsigned long long sA[2];               // doubled areas of Q and P
@@ -1447,9 +1461,16 @@ __global__ __launch_bounds__(kMetaThreads) void k_wide_meta(const int32_t *__res
     __shared__ int32_t sOdd[2];                        // crossings of the two membership passes
     const int tid = threadIdx.x, lane = tid & 63;
     const int64_t count = min((int64_t)hw.count[2], (int64_t)kMultiCap);
-    for (int64_t s = blockIdx.x; s < count; s += gridDim.x) {
+    const int64_t room = kWideListCap - min((int64_t)hw.count[1], (int64_t)kWideListCap);
+    for (int64_t s = block; s < count; s += blocks) {
         const MultiPair mp = hw.multi[s];
-        if (mp.c < 0) continue;
+        if (mp.first + mp.units > room) {
+            // its units do not fit the list: the pair stays whole, the places
+            // that it claimed are unused
+            for (int64_t j = mp.first + tid; j < room && j < mp.first + mp.units; j += kMetaThreads)
+                hw.wide[kWideListCap - 1 - j].c = -1;
+            continue;
+        }
         // the roles of k_refine_wide
         const int64_t qa = qoff[mp.q];
         const int mq = (int)(qoff[mp.q + 1] - qa);
@@ -1587,6 +1608,7 @@ __global__ __launch_bounds__(kMetaThreads) void k_wide_meta(const int32_t *__res
         if (tid == 0) {
             MultiPair &out = hw.multi[s];
             out.a2p = a2p; out.a2q = a2q; out.kp = kp; out.kq = kq; out.wkp = wkp; out.wkq = wkq;
+            hw.wide[mp.kp].c = -1;
         }
         for (int u = tid; u < mp.units; u += kMetaThreads) {
             const int qw = sh.qs > 1 ? u % sh.qs : 0;
@@ -1598,41 +1620,62 @@ __global__ __launch_bounds__(kMetaThreads) void k_wide_meta(const int32_t *__res
             e.pw = (int16_t)(u / sh.qs);
             e.qw = (int16_t)(sh.qs == 1 ? -1 : qw);
             e.slot = (int32_t)s;
-            hw.wide[mp.first + u] = e;
+            hw.wide[kWideListCap - 1 - (mp.first + u)] = e;
         }
         // every thread is done with the LDS before the next pair clears it
         __syncthreads();
     }
 }
 
-// Splits the recorded wide entries that split_shape splits, one thread per
-// entry: a split slot and the list positions of its units, appended after the
-// recorded entries (k_wide_meta writes the units there; the recorded entry is
-// then marked unused).  A pair stays whole when the
-// split slots run out; when its units do not fit the list, the positions it
-// claimed are marked unused and its slot is dropped.
-__global__ __launch_bounds__(256) void k_expand(const int64_t *__restrict__ qoff, HeavyWs hw)
+// A split pair's value, by the wavefront that finished its last unit: the P
+// windows' sums (each the sum of its Q windows' units, one window a lane) with
+// the crossing signs of the earlier windows carried into each, added in a
+// fixed order (deterministic), then J.
+__device__ double finish_split(const int64_t *qoff, const HeavyWs &hw, int32_t s, int lane)
 {
-    const int64_t norig = min((int64_t)hw.count[1], (int64_t)kWideListCap);
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < norig;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const WidePair w = hw.wide[i];
-        const int mq = (int)(qoff[w.q + 1] - qoff[w.q]);
-        const bool swap = w.n > kWideCap && w.n > mq;
-        const SplitShape sh = split_shape(swap ? mq : w.n, swap ? w.n : mq);
-        if (sh.units <= 1) continue;
-        const int ms = atomicAdd(hw.count + 2, 1);
-        if (ms >= kMultiCap) continue;
-        MultiPair &mp = hw.multi[ms];
-        const int64_t base = norig + atomicAdd(hw.count + 4, sh.units);
-        if (base + sh.units > kWideListCap) {
-            for (int64_t j = base; j < kWideListCap; j++) hw.wide[j].c = -1;
-            mp.c = -1;
-            continue;
+    const MultiPair mp = hw.multi[s];
+    // the roles of k_refine_wide; the pair's own quantities from wide_meta
+    const int mq = (int)(qoff[mp.q + 1] - qoff[mp.q]);
+    const bool swap = mp.n > kWideCap && mp.n > mq;
+    const int n = swap ? mq : mp.n, m = swap ? mp.n : mq;
+    const int64_t a2q = mp.a2q, a2p = mp.a2p;
+    double J = 0.0;
+    if (a2p != 0 && a2q != 0) {
+        const int kp = mp.kp, wkp = mp.wkp, wkq = mp.wkq;
+        const int sp = a2p > 0 ? 1 : -1, sq = a2q > 0 ? 1 : -1;
+        const SplitShape sh = split_shape(n, m);
+        const int pk = kp / sh.plen;
+        // lanes take the P windows, 64 at a time; the carry of crossing
+        // signs into each is a scan in window order
+        const int qs = sh.qs, npw = sh.units / qs;
+        const MultiUnit *U = hw.units + (int64_t)s * kMultiUnits;
+        double acc = 0.0;
+        int carry = 0, K = 0;
+        for (int base = 0; base < npw; base += 64) {
+            const int wdw = base + lane;
+            const bool live = wdw < npw;
+            double part = 0.0, cr = 0.0;
+            int stot = 0, kloc = 0;
+            if (live) {
+                cr = U[wdw * qs].cr;
+                for (int v = 0; v < qs; v++) {
+                    const MultiUnit x = U[wdw * qs + v];
+                    part += x.part;
+                    stot += x.stot;
+                    kloc += x.kloc;
+                }
+            }
+            const int incl = wave_incl_scan32(stot);
+            const int excl = carry + incl - stot;
+            acc += live ? part + (double)(sp * sq) * cr * (double)excl : 0.0;
+            if (pk >= base && pk < base + 64) K = __builtin_amdgcn_readlane(excl + kloc, pk - base);
+            carry += __builtin_amdgcn_readlane(incl, 63);
         }
-        mp.c = w.c; mp.pa = w.pa; mp.n = w.n; mp.q = w.q; mp.units = sh.units; mp.first = (int32_t)base;
-        hw.wide[i].c = -1;
+        const double total = wave_sum(acc);
+        const double inter2 = total + (double)(sp * (wkp - sq * K)) * (double)a2p + (double)(sq * wkq) * (double)a2q;
+        J = jaccard_of(inter2, a2p, a2q);
     }
+    return J;
 }
 
 // One wavefront per deferred pair (workgroups of one wavefront, so four fit a
@@ -1671,7 +1714,7 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
     for (;;) {
         const int64_t t = __builtin_amdgcn_readfirstlane(lane == 0 ? atomicAdd(hw.count + 3, 1) : 0);
         if (t >= norig + nunits) break;
-        const WidePair w = hw.wide[t < nunits ? norig + t : t - nunits];
+        const WidePair w = hw.wide[t < nunits ? kWideListCap - 1 - t : t - nunits];
         if (w.c < 0) continue;
         const int64_t qa = qoff[w.q];
         const int mq = (int)(qoff[w.q + 1] - qa);
@@ -1691,7 +1734,7 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
         int64_t a2q, a2p, qpre;
         int kp = 0, kq = 0, wkp = 0, wkq = 0;
         if (w.pw >= 0) {
-            // a split pair's unit: the pair's own quantities from k_wide_meta
+            // a split pair's unit: the pair's own quantities from wide_meta
             // (its ring starts' memberships are the finish's)
             const MultiPair &mp = hw.multi[w.slot];
             a2p = mp.a2p; a2q = mp.a2q; kp = mp.kp; kq = mp.kq;
@@ -1771,9 +1814,22 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
             }
         }
         st_pairs += (w.pw <= 0) & (w.qw <= 0);
-        if (lane == 0) {
-            if (w.pw < 0) cand_j[w.c] = J;
-            else hw.units[(int64_t)w.slot * kMultiUnits + u] = unit;
+        if (w.pw < 0) {
+            if (lane == 0) cand_j[w.c] = J;
+        } else {
+            // the wavefront whose unit is the pair's last adds them up (all
+            // have been made visible by then)
+            int left = 0;
+            if (lane == 0) {
+                hw.units[(int64_t)w.slot * kMultiUnits + u] = unit;
+                __threadfence();
+                left = atomicSub(&hw.multi[w.slot].units, 1);
+            }
+            if (__builtin_amdgcn_readfirstlane(left) == 1) {
+                __threadfence();
+                const double Js = finish_split(qoff, hw, w.slot, lane);
+                if (lane == 0) cand_j[w.c] = Js;
+            }
         }
         // every lane is done with both rings before the next pair restages them
         wave_lds_sync();
@@ -1785,74 +1841,14 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
     }
 }
 
-// One wavefront per split pair: the P windows' sums (each the sum of its Q
-// windows' units, one window a lane)
-// with the crossing signs of the earlier windows carried into each, added in
-// a fixed order (deterministic), then J.
-__global__ __launch_bounds__(256) void k_refine_multi_finish(const int64_t *__restrict__ qoff,
-                                                            double *__restrict__ cand_j, HeavyWs hw)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    const int64_t count = min((int64_t)hw.count[2], (int64_t)kMultiCap);
-    for (int64_t s = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; s < count; s += nw) {
-        const MultiPair mp = hw.multi[s];
-        if (mp.c < 0) continue;
-        // the roles of k_refine_wide; the pair's own quantities from k_wide_meta
-        const int mq = (int)(qoff[mp.q + 1] - qoff[mp.q]);
-        const bool swap = mp.n > kWideCap && mp.n > mq;
-        const int n = swap ? mq : mp.n, m = swap ? mp.n : mq;
-        const int64_t a2q = mp.a2q, a2p = mp.a2p;
-        double J = 0.0;
-        if (a2p != 0 && a2q != 0) {
-            const int kp = mp.kp, wkp = mp.wkp, wkq = mp.wkq;
-            const int sp = a2p > 0 ? 1 : -1, sq = a2q > 0 ? 1 : -1;
-            const SplitShape sh = split_shape(n, m);
-            const int pk = kp / sh.plen;
-            // lanes take the P windows, 64 at a time; the carry of crossing
-            // signs into each is a scan in window order
-            const int qs = sh.qs, npw = mp.units / qs;
-            const MultiUnit *U = hw.units + s * kMultiUnits;
-            double acc = 0.0;
-            int carry = 0, K = 0;
-            for (int base = 0; base < npw; base += 64) {
-                const int wdw = base + lane;
-                const bool live = wdw < npw;
-                double part = 0.0, cr = 0.0;
-                int stot = 0, kloc = 0;
-                if (live) {
-                    cr = U[wdw * qs].cr;
-                    for (int v = 0; v < qs; v++) {
-                        const MultiUnit x = U[wdw * qs + v];
-                        part += x.part;
-                        stot += x.stot;
-                        kloc += x.kloc;
-                    }
-                }
-                const int incl = wave_incl_scan32(stot);
-                const int excl = carry + incl - stot;
-                acc += live ? part + (double)(sp * sq) * cr * (double)excl : 0.0;
-                if (pk >= base && pk < base + 64) K = __builtin_amdgcn_readlane(excl + kloc, pk - base);
-                carry += __builtin_amdgcn_readlane(incl, 63);
-            }
-            const double total = wave_sum(acc);
-            const double inter2 = total + (double)(sp * (wkp - sq * K)) * (double)a2p + (double)(sq * wkq) * (double)a2q;
-            J = jaccard_of(inter2, a2p, a2q);
-        }
-        if (lane == 0) cand_j[mp.c] = J;
-    }
-}
-
 // One wavefront per (heavy pair, side, slice): the slice's share of that
-// side's edge sums; slices past the side's last block add nothing.
-__global__ __launch_bounds__(256) void k_heavy(const int32_t *__restrict__ dxy, const int32_t *__restrict__ qxy,
-                                               HeavyWs hw)
+// side's edge sums; slices past the side's last block add nothing.  The one
+// that finishes a pair's last slice adds them in a fixed order, then J.
+__device__ void heavy_slices(const int32_t *__restrict__ dxy, const int32_t *__restrict__ qxy,
+                             double *__restrict__ cand_j, const HeavyWs &hw, int64_t wave, int64_t nw, int lane)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
     const int64_t count = min(hw.count[0], kHeavyCap);
-    for (int64_t t = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; t < count * 2 * kHeavySlices;
-         t += nw) {
+    for (int64_t t = wave; t < count * 2 * kHeavySlices; t += nw) {
         const int64_t h = t / (2 * kHeavySlices);
         const int side = (int)((t / kHeavySlices) & 1), slice = (int)(t % kHeavySlices);
         const HeavyPair &e = hw.pairs[h];
@@ -1872,26 +1868,39 @@ __global__ __launch_bounds__(256) void k_heavy(const int32_t *__restrict__ dxy, 
             else edges_in_other_Q<false>(in, pm, lane, s, unused, slice, kHeavySlices);
         }
         s = wave_sum(s);
-        if (lane == 0) hw.partial[(h * 2 + side) * kHeavySlices + slice] = s;
+        int done = 0;
+        if (lane == 0) {
+            hw.partial[(h * 2 + side) * kHeavySlices + slice] = s;
+            __threadfence();
+            done = atomicAdd(&hw.pairs[h].done, 1);
+        }
+        if (__builtin_amdgcn_readfirstlane(done) == 2 * kHeavySlices - 1) {
+            __threadfence();
+            static_assert(kHeavySlices == 64, "a slice a lane");
+            const double vp = hw.partial[(h * 2 + 0) * kHeavySlices + lane];
+            const double vq = hw.partial[(h * 2 + 1) * kHeavySlices + lane];
+            const double inter2 = wave_sum((double)in.sp * vp) + wave_sum((double)in.sq * vq);
+            if (lane == 0) cand_j[e.c] = jaccard_of(inter2, e.a2p, e.a2q);
+        }
     }
 }
 
-// One wavefront per heavy pair: the slices' sums in a fixed order, then J.
-__global__ __launch_bounds__(256) void k_heavy_finish(HeavyWs hw, double *__restrict__ cand_j)
+// What k_refine deferred, but for the wide tiled pairs: the first workgroups
+// prepare the split pairs, the others take the heavy pairs' slices.
+constexpr int kMetaBlocks = 256;
+__global__ __launch_bounds__(kMetaThreads) void k_deferred(const int32_t *__restrict__ dxy,
+                                                         const int32_t *__restrict__ qxy,
+                                                         const int64_t *__restrict__ qoff,
+                                                         double *__restrict__ cand_j, HeavyWs hw)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    const int64_t count = min(hw.count[0], kHeavyCap);
-    for (int64_t h = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; h < count; h += nw) {
-        const HeavyPair &e = hw.pairs[h];
-        const double sp = e.a2p > 0 ? 1.0 : -1.0, sq = e.a2q > 0 ? 1.0 : -1.0;
-        double vp = 0.0, vq = 0.0;
-        if (lane < kHeavySlices) {
-            vp = hw.partial[(h * 2 + 0) * kHeavySlices + lane];
-            vq = hw.partial[(h * 2 + 1) * kHeavySlices + lane];
-        }
-        const double inter2 = wave_sum(sp * vp) + wave_sum(sq * vq);
-        if (lane == 0) cand_j[e.c] = jaccard_of(inter2, e.a2p, e.a2q);
+    const int block = (int)blockIdx.x;
+    if (block < kMetaBlocks) {
+        wide_meta(dxy, qxy, qoff, hw, block, kMetaBlocks);
+    } else {
+        constexpr int kWaves = kMetaThreads / 64;
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        heavy_slices(dxy, qxy, cand_j, hw, (int64_t)(block - kMetaBlocks) * kWaves + wave,
+                     (int64_t)(gridDim.x - kMetaBlocks) * kWaves, threadIdx.x & 63);
     }
 }
 
@@ -1966,23 +1975,13 @@ polymh_status launch_refine(const polymh_polys *data, const polymh_polys *querie
                        slices, hw);
     polymh_status st = check_launch("refine");
     if (st || !ws) return st;
-    hipLaunchKernelGGL(k_expand, dim3(64), dim3(256), 0, s, queries->offsets, hw);
-    if ((st = check_launch("refine: split wide pairs"))) return st;
-    hipLaunchKernelGGL(k_wide_meta, dim3(256), dim3(kMetaThreads), 0, s, data->xy, queries->xy, queries->offsets,
-                       hw);
-    if ((st = check_launch("refine: split wide pairs"))) return st;
+    hipLaunchKernelGGL(k_deferred, dim3(2 * kMetaBlocks), dim3(kMetaThreads), 0, s, data->xy, queries->xy,
+                       queries->offsets, cand_j, hw);
+    if ((st = check_launch("refine: heavy pairs, split pairs"))) return st;
     // deferred wide tiled pairs: four one-wavefront workgroups per CU
     hipLaunchKernelGGL(k_refine_wide, dim3(1024), dim3(64), 0, s, data->xy, queries->xy, queries->offsets, cand_j,
                        hw, stats ? 1 : 0);
     if ((st = check_launch("refine: wide pairs"))) return st;
-    hipLaunchKernelGGL(k_refine_multi_finish, dim3(64), dim3(256), 0, s, queries->offsets, cand_j, hw);
-    if ((st = check_launch("refine: split wide pairs"))) return st;
-    // deferred heavy pairs: a grid that covers every (pair, side, slice) of a
-    // full list in a few rounds, then the per-pair sums
-    hipLaunchKernelGGL(k_heavy, dim3(2048), dim3(256), 0, s, data->xy, queries->xy, hw);
-    if ((st = check_launch("refine: heavy pairs"))) return st;
-    hipLaunchKernelGGL(k_heavy_finish, dim3(256), dim3(256), 0, s, hw, cand_j);
-    if ((st = check_launch("refine: heavy pairs"))) return st;
     if (!stats) return POLYMH_OK;
     hipLaunchKernelGGL(k_fold_stats, dim3(1), dim3(64), 0, s, hw.stat_slots, stats);
     return check_launch("refine: counters");
