@@ -19,6 +19,9 @@
 // in a register costs no LDS read: 100,000 polygons of 32 vertices on
 // average, 128 hashes, went from 4,446 to 3,840 us, 30,000 of 8 vertices, 64
 // hashes, from 476 to 345 us (of these 100 us by the hardware's dispatch).
+// A tile of draws is 24 vector instructions (33 with the cap tested in every
+// lane and the masks combined as lane values: 3,690 us now for the former,
+// and 10.3 to 8.8 ms for 10,000 polygons of a millionth of the box).
 //
 // The orientation test o = dx*(py - y_lo) - (px - x_lo)*dy only runs for
 // samples inside the polygon's MBR on edges straddling py, so each product is
@@ -80,10 +83,10 @@ __device__ __forceinline__ bool inside_wave(const PolyCtx &C, const EdgeRec *reg
         if constexpr (MODE == kRec) {
             const EdgeRec *rec = reinterpret_cast<const EdgeRec *>(C.s_edges);
             for (int e = lane; e < C.n + lane; e += 64)
-                odd ^= __ballot((e < C.n) & crosses_rec(rec[e < C.n ? e : 0], ry, dx, dy));
+                odd ^= __ballot(e < C.n) & crosses_mask(rec[e < C.n ? e : 0], ry, dx, dy);
         } else {
 #pragma unroll
-            for (int u = 0; u < reg_edges<MODE>(); u++) odd ^= __ballot(crosses_rec(reg[u], ry, dx, dy));
+            for (int u = 0; u < reg_edges<MODE>(); u++) odd ^= crosses_mask(reg[u], ry, dx, dy);
         }
         return __popcll(odd) & 1;
     }
@@ -125,8 +128,11 @@ template <bool POW2, int MODE, int SPL>
 __device__ uint32_t walk(const SignArgs &A, const PolyCtx &C, const EdgeRec *reg, uint64_t key, int lane)
 {
     constexpr uint32_t kTile = 64u * SPL;
+    // whole tiles, then one of the samples left (conditions that are the same
+    // for all lanes stay scalar; a mask per comparison, combined as scalars)
+    const uint32_t whole = A.cap / kTile, left = A.cap % kTile;
     uint64_t z = key + (uint64_t)(lane + 1) * kGamma;
-    for (uint64_t base = 0; base < A.cap; base += kTile) {
+    for (uint32_t t = 0; t <= whole; t++) {
         uint32_t ox[SPL], oy[SPL];
         uint64_t m[SPL];
 #pragma unroll
@@ -135,9 +141,14 @@ __device__ uint32_t walk(const SignArgs &A, const PolyCtx &C, const EdgeRec *reg
             // relative to the MBR's origin
             ox[s] = lattice<POW2>((uint32_t)(r >> 32), A.wx, A.shx) + C.cx;
             oy[s] = lattice<POW2>((uint32_t)r, A.wy, A.shy) + C.cy;
-            const uint64_t j = base + 64u * s + lane;
-            const bool in = (ox[s] <= C.wmx) & (oy[s] <= C.wmy) & (j < A.cap);
-            m[s] = __ballot(in);
+            m[s] = __ballot(ox[s] <= C.wmx) & __ballot(oy[s] <= C.wmy);
+        }
+        if (t == whole) {
+#pragma unroll
+            for (int s = 0; s < SPL; s++) {
+                const uint32_t n = left > 64u * s ? left - 64u * s : 0u;
+                if (n < 64u) m[s] &= (1ull << n) - 1;
+            }
         }
         z += (uint64_t)kTile * kGamma;
 #pragma unroll
@@ -148,7 +159,7 @@ __device__ uint32_t walk(const SignArgs &A, const PolyCtx &C, const EdgeRec *reg
                 const int32_t rx = (int32_t)__builtin_amdgcn_readlane(ox[s], c);
                 const int32_t ry = (int32_t)__builtin_amdgcn_readlane(oy[s], c);
                 if (inside_wave<MODE>(C, reg, rx, ry, lane))
-                    return (uint32_t)(base + 64u * s + c + 1);
+                    return t * kTile + 64u * s + c + 1;
                 mm &= mm - 1;
             }
         }
@@ -172,6 +183,8 @@ __device__ void hash_loop(const SignArgs &A, const PolyCtx &C, int i0, int i1, u
         const int2 a = v[ec], b = v[ec + 1 == C.n ? 0 : ec + 1];
         reg[u] = make_edge_rec(make_edge(a.x, a.y, b.x, b.y), C.x0, C.y0);
         if (e >= C.n) reg[u].yhi = INT32_MIN;    // never straddled
+        // or the compiler tests e < n with every sample instead
+        asm volatile("" : "+v"(reg[u].yhi));
     }
     for (int i = i0 + wave; i < i1; i += nwaves) {
         const uint64_t key = mix64(A.seed + (uint64_t)(i + 1) * kGamma);
@@ -180,7 +193,7 @@ __device__ void hash_loop(const SignArgs &A, const PolyCtx &C, int i0, int i1, u
     }
 }
 
-// Eight wavefronts a SIMD (64 registers): 3,840 us against 4,080 with the
+// Eight wavefronts a SIMD (64 registers): 3,690 us against 3,990 with the
 // compiler's own 72 (seven) at 100,000 polygons.
 template <bool POW2, int SPL>
 __global__ __launch_bounds__(512, 8) void k_sign(SignArgs A)

@@ -63,6 +63,14 @@ __device__ __forceinline__ bool crosses_rec(const EdgeRec &e, int32_t py, double
     return (e.ylo <= py) & (py < e.yhi) & (__fma_rn(e.a, dpy, __fma_rn(e.b, dpx, e.k)) > 0.0);
 }
 
+// The lanes whose edge the same point crosses: a mask a comparison, combined
+// as scalars (combined as lane values they are made numbers and compared
+// again).
+__device__ __forceinline__ uint64_t crosses_mask(const EdgeRec &e, int32_t py, double dpx, double dpy)
+{
+    return __ballot(e.ylo <= py) & __ballot(py < e.yhi) & __ballot(__fma_rn(e.a, dpy, __fma_rn(e.b, dpx, e.k)) > 0.0);
+}
+
 __device__ __forceinline__ bool crosses_i128(const int32_t *v0, const int32_t *v1, int32_t px,
                                              int32_t py)
 {
