@@ -34,7 +34,8 @@ namespace polymh {
 
 namespace {
 
-constexpr int kQueue = 128;        // per-wavefront queue of membership tests
+constexpr int kRecBatch = 128;      // points tested together against edges with their products
+constexpr int kQueue = 256;        // per-wavefront queue of membership tests
 constexpr int kGroup = 256;        // hashes a lookup workgroup at most
 constexpr int kBinLog = 13;        // log2 of the samples a workgroup of k_bin takes
 constexpr uint32_t kNone = 0xffffffffu;
@@ -264,17 +265,9 @@ enum TestMode { kTestRec = 0, kTestLds = 1, kTestStream = 2, kTestWide = 3 };
 // the same edge sequence, so the edge reads are broadcasts.
 template <int MODE>
 __device__ __forceinline__ bool inside_lane(const int4 *s_edges, const int32_t *pxy, int32_t n,
-                                            int32_t px, int32_t py, int32_t x0, int32_t y0)
+                                            int32_t px, int32_t py)
 {
     bool odd = false;
-    if constexpr (MODE == kTestRec) {
-        const EdgeRec *rec = reinterpret_cast<const EdgeRec *>(s_edges);
-        const int32_t ry = py - y0;
-        const double dx = (double)(px - x0), dy = (double)ry;
-#pragma unroll 2
-        for (int e = 0; e < n; e++) odd ^= crosses_rec(rec[e], ry, dx, dy);
-        return odd;
-    }
     for (int e = 0; e < n; e++) {
         if constexpr (MODE == kTestLds) {
             odd ^= crosses_fp64(s_edges[e], px, py);
@@ -320,10 +313,27 @@ __device__ __forceinline__ bool inside_stream_block(const int32_t *pxy, int32_t 
 struct Scan {
     uint32_t mx0, my0, mwx, mwy;   // MBR inside B: corner as a lattice offset, width - 1, height - 1
     int32_t x0, y0;                // the MBR's corner
-    uint4 *queue;                  // samples inside the MBR: lattice offset, hash, index
+    uint32_t *queue;               // samples inside the MBR: chunk of the round << sub_shift | place in it
     uint32_t *s_best;              // smallest inside index a hash of the workgroup
     int head, tail;
+    // this round's bins
+    const uint2 *xy;
+    const uint32_t *meta;
+    int c0, sub_shift;
 };
+
+// A queued sample again: its lattice offset, hash and index.  (Queued by its
+// place alone, four bytes, the queues of a workgroup that tests two points a
+// lane leave room for seven workgroups a CU; with the sample's 16 bytes for
+// four: 2 million polygons of 256 hashes 46.3 ms instead of 56.5.)
+__device__ __forceinline__ uint4 queued(const LookupArgs &A, const Scan &S, int q)
+{
+    const uint32_t en = S.queue[(S.head + q) & (kQueue - 1)];
+    const uint32_t at = en & ((1u << S.sub_shift) - 1);
+    const uint2 o = S.xy[at];
+    const uint32_t m = S.meta[at];
+    return make_uint4(o.x, o.y, m >> 24, ((uint32_t)(S.c0 + (int)(en >> S.sub_shift)) << A.lchunk) + (m & 0xffffffu));
+}
 
 __device__ __forceinline__ void wave_sync_lds()
 {
@@ -331,43 +341,84 @@ __device__ __forceinline__ void wave_sync_lds()
     __builtin_amdgcn_wave_barrier();
 }
 
-// Test up to 64 queued points (lane = entry) and lower their hashes' best
+// Test POINTS * 64 queued points, POINTS a lane, against edges with their
+// products taken out, and lower their hashes' best index (entries past count
+// are tested again as the first one and dropped).  The edge reads are
+// broadcasts, 16 cycles of the LDS an edge, three times what four SIMDs need
+// for one point a lane: two points share them (46.3 ms, one point 49.5).
+template <int POINTS>
+__device__ __forceinline__ void drain_rec(const LookupArgs &A, const EdgeRec *rec, int32_t n, const Scan &S, int count,
+                                          int lane)
+{
+    uint4 o[POINTS];
+    int32_t ry[POINTS];
+    double dx[POINTS], dy[POINTS];
+    uint64_t odd[POINTS];
+#pragma unroll
+    for (int u = 0; u < POINTS; u++) {
+        const int at = 64 * u + lane;
+        o[u] = queued(A, S, at < count ? at : 0);
+        ry[u] = (int32_t)((uint32_t)A.by0 + o[u].y) - S.y0;
+        dx[u] = (double)((int32_t)((uint32_t)A.bx0 + o[u].x) - S.x0);
+        dy[u] = (double)ry[u];
+        odd[u] = 0;
+    }
+    EdgeRec next = rec[0];
+    for (int e = 1; e <= n; e++) {
+        const EdgeRec r = next;
+        next = rec[e < n ? e : 0];
+#pragma unroll
+        for (int u = 0; u < POINTS; u++) odd[u] ^= crosses_mask(r, ry[u], dx[u], dy[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < POINTS; u++) {
+        const uint64_t in = odd[u] & __ballot(64 * u + lane < count);
+        if (__builtin_amdgcn_inverse_ballot_w64(in)) atomicMin(&S.s_best[o[u].z], o[u].w);
+    }
+}
+
+// Test up to 64 (kTestRec: 128) queued points and lower their hashes' best
 // index.
 template <int MODE>
 __device__ __forceinline__ void drain(const LookupArgs &A, const int4 *s_edges, const int32_t *pxy, int32_t n,
                                       const Scan &S, int count, int lane)
 {
+    if constexpr (MODE == kTestRec) {
+        const EdgeRec *rec = reinterpret_cast<const EdgeRec *>(s_edges);
+        if (count > 64) drain_rec<2>(A, rec, n, S, count, lane);
+        else drain_rec<1>(A, rec, n, S, count, lane);
+        return;
+    }
     // lanes past count test the first entry where every lane takes part
     if (MODE != kTestStream && lane >= count) return;
-    const int q = (S.head + (lane < count ? lane : 0)) & (kQueue - 1);
-    const uint4 o = S.queue[q];
+    const uint4 o = queued(A, S, lane < count ? lane : 0);
     const int32_t px = (int32_t)((uint32_t)A.bx0 + o.x), py = (int32_t)((uint32_t)A.by0 + o.y);
     bool in;
     if constexpr (MODE == kTestStream) in = inside_stream_block(pxy, n, px, py, lane) && lane < count;
-    else in = inside_lane<MODE>(s_edges, pxy, n, px, py, S.x0, S.y0);
+    else in = inside_lane<MODE>(s_edges, pxy, n, px, py);
     if (in) atomicMin(&S.s_best[o.z], o.w);
 }
 
 // One sample a lane: those inside the MBR whose hash has no smaller index yet
-// are queued, 64 waiting are tested.
+// are queued, 64 (kTestRec: 128) waiting are tested.
 template <int MODE>
 __device__ __forceinline__ void take(const LookupArgs &A, const int4 *s_edges, const int32_t *pxy, int32_t n, Scan &S,
-                                     uint2 o, uint32_t meta, uint32_t chunk_base, int lane)
+                                     uint2 o, uint32_t meta, uint32_t chunk_base, uint32_t place, int lane)
 {
     const uint32_t hash = meta >> 24, j = chunk_base + (meta & 0xffffffu);
-    const bool pass = (o.x - S.mx0 <= S.mwx) & (o.y - S.my0 <= S.mwy) & (S.s_best[hash] > j);
-    const uint64_t mk = __ballot(pass);
+    const uint64_t mk = __ballot(o.x - S.mx0 <= S.mwx) & __ballot(o.y - S.my0 <= S.mwy) & __ballot(S.s_best[hash] > j);
     if (mk == 0) return;
-    if (pass) {
+    if (__builtin_amdgcn_inverse_ballot_w64(mk)) {
         const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32),
                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0u));
-        S.queue[(S.tail + rank) & (kQueue - 1)] = make_uint4(o.x, o.y, hash, j);
+        S.queue[(S.tail + rank) & (kQueue - 1)] = place;
     }
     S.tail += __popcll(mk);
-    if (S.tail - S.head >= 64) {
+    constexpr int kBatch = MODE == kTestRec ? kRecBatch : 64;
+    if (S.tail - S.head >= kBatch) {
         wave_sync_lds();
-        drain<MODE>(A, s_edges, pxy, n, S, 64, lane);
-        S.head += 64;
+        drain<MODE>(A, s_edges, pxy, n, S, kBatch, lane);
+        S.head += kBatch;
         wave_sync_lds();
     }
 }
@@ -385,7 +436,10 @@ __device__ void lookup_polygon(const LookupArgs &A, const int4 *s_edges, const i
                                int cx1, int cy0, int cy1, bool active, int tid, int lane, int wave, int waves, int group)
 {
     const int rows = cy1 - cy0 + 1;              // at most 64
-    const int most = 64 / rows;                  // chunks a round at most
+    // chunks a round at most: a round's samples are counted in 26 bits, or,
+    // alone, a chunk's in 28
+    const int most = max(1, min(64 / rows, (int)((1u << 26) / A.per)));
+    S.sub_shift = most > 1 ? 26 : 31;
     const int sub = lane / rows, row = (cy0 + lane % rows) << A.cbits;
     int m = min(most, kRound0);
     for (int c0 = 0; c0 < A.nchunks; c0 += m, m = min(most, max(kRound0, c0))) {
@@ -400,42 +454,45 @@ __device__ void lookup_polygon(const LookupArgs &A, const int4 *s_edges, const i
         const int steps = e1 > e0 ? (int)((e1 - e0 + 63) / 64) : 0;
         const int incl = wave_incl_scan32(steps);
         const int total = __builtin_amdgcn_readlane(incl, 63);
-        const int from = (int)e0 - 64 * (incl - steps), last = (int)e1 - 1;
+        // places count from the round's first sample
+        const int skip = sub * (int)A.per;
+        const int from = skip + (int)e0 - 64 * (incl - steps), last = skip + (int)e1 - 1;
+        const uint32_t base = (uint32_t)(c0 + sub) << A.lchunk;
+        S.xy = A.bxy + gc * A.per;
+        S.meta = A.bmeta + gc * A.per;
+        S.c0 = c0;
         S.head = S.tail = 0;
         // step t: its stretch is the first that ends after it; lanes past the
         // stretch's end take its last sample again, which changes nothing
         struct Step {
             uint2 o;
-            uint32_t meta, base;
+            uint32_t meta, base, place;
         } a{}, b{};
         auto load = [&](int t, Step &s) {
             const int l = __builtin_ctzll(__ballot(incl > t));
             const int at = min(__builtin_amdgcn_readlane(from, l) + 64 * t + lane, __builtin_amdgcn_readlane(last, l));
-            const int c = __builtin_amdgcn_readlane(sub, l);
-            const size_t first = (gc + (size_t)c) * A.per;
-            const uint2 *xy = A.bxy + first;
-            const uint32_t *meta = A.bmeta + first;
-            s.base = (uint32_t)(c0 + c) << A.lchunk;
+            s.base = (uint32_t)__builtin_amdgcn_readlane((int)base, l);
             __builtin_assume(at >= 0 && at < 1 << 28);
-            s.o = xy[at];
-            s.meta = meta[at];
+            s.o = S.xy[at];
+            s.meta = S.meta[at];
+            s.place = (uint32_t)at | (uint32_t)__builtin_amdgcn_readlane(sub, l) << S.sub_shift;
         };
         // two steps in flight
         int t = wave;
         if (t < total) load(t, a);
         if (t + waves < total) load(t + waves, b);
         while (t < total) {
-            take<MODE>(A, s_edges, pxy, n, S, a.o, a.meta, a.base, lane);
+            take<MODE>(A, s_edges, pxy, n, S, a.o, a.meta, a.base, a.place, lane);
             t += waves;
             if (t + waves < total) load(t + waves, a);
             if (t >= total) break;
-            take<MODE>(A, s_edges, pxy, n, S, b.o, b.meta, b.base, lane);
+            take<MODE>(A, s_edges, pxy, n, S, b.o, b.meta, b.base, b.place, lane);
             t += waves;
             if (t + waves < total) load(t + waves, b);
         }
         while (S.tail > S.head) {
             wave_sync_lds();
-            const int left = min(64, S.tail - S.head);
+            const int left = min(MODE == kTestRec ? kRecBatch : 64, S.tail - S.head);
             drain<MODE>(A, s_edges, pxy, n, S, left, lane);
             S.head += left;
             wave_sync_lds();
@@ -450,7 +507,7 @@ __device__ void lookup_polygon(const LookupArgs &A, const int4 *s_edges, const i
 __global__ __launch_bounds__(256) void k_bin_lookup(LookupArgs A)
 {
     extern __shared__ int4 s_edges[];
-    __shared__ uint4 s_queue[4][kQueue];
+    __shared__ uint32_t s_queue[4][kQueue];
     __shared__ uint32_t s_best[kGroup];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -182,9 +182,9 @@ __device__ void hash_loop(const SignArgs &A, const PolyCtx &C, int i0, int i1, u
         const int2 *v = reinterpret_cast<const int2 *>(C.pxy);
         const int2 a = v[ec], b = v[ec + 1 == C.n ? 0 : ec + 1];
         reg[u] = make_edge_rec(make_edge(a.x, a.y, b.x, b.y), C.x0, C.y0);
-        if (e >= C.n) reg[u].yhi = INT32_MIN;    // never straddled
+        if (e >= C.n) reg[u].h = 0;    // never straddled
         // or the compiler tests e < n with every sample instead
-        asm volatile("" : "+v"(reg[u].yhi));
+        asm volatile("" : "+v"(reg[u].h));
     }
     for (int i = i0 + wave; i < i1; i += nwaves) {
         const uint64_t key = mix64(A.seed + (uint64_t)(i + 1) * kGamma);

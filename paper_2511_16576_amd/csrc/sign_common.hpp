@@ -38,10 +38,11 @@ __device__ __forceinline__ bool crosses_fp64(int4 e, int32_t px, int32_t py)
 // dx py - dy px + k, k = dy x_lo - dx y_lo.  With MBR sides below 2^26 every
 // product and partial sum is an integer of at most 2^53 (dy px and dy x_lo
 // differ by less than 2^52, as k's other product), so both forms are exact;
-// this one is two fused multiply-adds and three compares.
+// this one is two fused multiply-adds and two compares.
 struct __attribute__((aligned(16))) EdgeRec {
     double a, b, k;          // dx, -dy, dy x_lo - dx y_lo
-    int32_t ylo, yhi;
+    int32_t ylo;
+    uint32_t h;              // y_hi - y_lo: straddled if y - y_lo, unsigned, is below
 };
 
 // `e` from make_edge; (x0, y0) the MBR's corner.
@@ -53,22 +54,16 @@ __device__ __forceinline__ EdgeRec make_edge_rec(int4 e, int32_t x0, int32_t y0)
     r.b = -dy;
     r.k = __fma_rn(dy, (double)(e.x - x0), -(dx * (double)(e.y - y0)));
     r.ylo = e.y - y0;
-    r.yhi = e.z - y0;
+    r.h = (uint32_t)(e.z - e.y);
     return r;
 }
 
-// (px, py) relative to the corner too, also as doubles.
-__device__ __forceinline__ bool crosses_rec(const EdgeRec &e, int32_t py, double dpx, double dpy)
-{
-    return (e.ylo <= py) & (py < e.yhi) & (__fma_rn(e.a, dpy, __fma_rn(e.b, dpx, e.k)) > 0.0);
-}
-
-// The lanes whose edge the same point crosses: a mask a comparison, combined
-// as scalars (combined as lane values they are made numbers and compared
-// again).
+// The lanes whose point, relative to the corner too (also as doubles), crosses
+// their edge: a mask a comparison, combined as scalars (combined as lane
+// values they are made numbers and compared again).
 __device__ __forceinline__ uint64_t crosses_mask(const EdgeRec &e, int32_t py, double dpx, double dpy)
 {
-    return __ballot(e.ylo <= py) & __ballot(py < e.yhi) & __ballot(__fma_rn(e.a, dpy, __fma_rn(e.b, dpx, e.k)) > 0.0);
+    return __ballot((uint32_t)(py - e.ylo) < e.h) & __ballot(__fma_rn(e.a, dpy, __fma_rn(e.b, dpx, e.k)) > 0.0);
 }
 
 __device__ __forceinline__ bool crosses_i128(const int32_t *v0, const int32_t *v1, int32_t px,
