@@ -860,7 +860,8 @@ struct MultiUnit {
 struct HeavyWs {
     int32_t *count;       // [0] heavy pairs, [1] wide list entries recorded, [2] split pairs, [4] their
                           // units, from the list's back (each may exceed its cap: the excess runs
-                          // in place or whole), [3] wide entries taken
+                          // in place or whole), [3] wide entries taken, [5] entries of up to
+                          // kWideCap edges a side, [6] entries looked at for those
     HeavyPair *pairs;     // [kHeavyCap]
     double *partial;      // [kHeavyCap][2][kHeavySlices]
     unsigned long long *stat_slots;   // [kStatSlots][4]
@@ -883,6 +884,7 @@ __device__ bool defer_wide(const HeavyWs &hw, int64_t c, int64_t pa, int n, int 
         w.c = c; w.pa = pa; w.n = n; w.q = q; w.pw = -1; w.qw = -1; w.slot = -1;
         const bool swap = n > kWideCap && n > m;
         const SplitShape sh = split_shape(swap ? m : n, swap ? n : m);
+        if (max(n, m) <= kWideCap) atomicAdd(hw.count + 5, 1);
         if (sh.units > 1) {
             const int ms = atomicAdd(hw.count + 2, 1);
             if (ms < kMultiCap) {
@@ -941,6 +943,22 @@ struct GroupLds {
     int4 *con;             // per pair: first chunk, end chunk, P's anchor (edge of the group), Q's anchor
     unsigned long long *acc;   // per pair: its sum, in fixed point
 };
+
+// The fixed point of a query's sums, 2^-s: from its MBR.
+__device__ __forceinline__ int fixed_point_bits(const int32_t *qmbr)
+{
+    const double box2 = 2.0 * ((double)qmbr[2] - qmbr[0] + 1) * ((double)qmbr[3] - qmbr[1] + 1);
+    const int bits = (int)((__double_as_longlong(box2) >> 52) & 0x7ff) - 1022;   // box2 < 2^bits
+    return __builtin_amdgcn_readfirstlane(max(0, min(52, 56 - bits)));
+}
+
+// 2 A = sp sq sum + sp w(kp) A2P + sq w(kq) A2Q, then J.
+__device__ __forceinline__ double group_jaccard(int64_t sum, int wkp, int wkq, int64_t a2p, int64_t a2q, int s)
+{
+    const int64_t ends = (wkp ? (a2p < 0 ? -a2p : a2p) : 0) + (wkq ? (a2q < 0 ? -a2q : a2q) : 0);
+    const int64_t fixed = (int64_t)((uint64_t)((a2p ^ a2q) < 0 ? -sum : sum) + ((uint64_t)ends << s));
+    return jaccard_of((double)fixed * (1.0 / (double)(1ll << s)), a2p, a2q);
+}
 
 // A value below 2^62 as a whole number of 2^-s, modulo 2^64 (s <= 52).
 __device__ __forceinline__ int64_t fixed_point(double v, int s, double scale)
@@ -1017,7 +1035,7 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
                                                 const int32_t *__restrict__ cand_ids,
                                                 double *__restrict__ cand_j,
                                                 unsigned long long *__restrict__ stats,
-                                                int slices, HeavyWs hw)
+                                                int slices, int mid_min, HeavyWs hw)
 {
     __shared__ int2 sQv[kRingLds];
     __shared__ int4 sQbox[kTileCap / 8];
@@ -1095,13 +1113,8 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
     const int32_t qmbr[4] = {sQmbr[0], sQmbr[1], sQmbr[2], sQmbr[3]};
     const int qext[4] = {sQext[0], sQext[1], sQext[2], sQext[3]};
     const int64_t a2q = sQa2;
-    // 2^qs: the fixed point of this query's sums
-    const int qs = [&] {
-        const double box2 = 2.0 * ((double)qmbr[2] - qmbr[0] + 1) * ((double)qmbr[3] - qmbr[1] + 1);
-        const int bits = (int)((__double_as_longlong(box2) >> 52) & 0x7ff) - 1022;   // box2 < 2^bits
-        return __builtin_amdgcn_readfirstlane(max(0, min(52, 56 - bits)));
-    }();
-    const double qscale = (double)(1ll << qs), qunscale = 1.0 / qscale;
+    const int qs = fixed_point_bits(qmbr);
+    const double qscale = (double)(1ll << qs);
     const GroupLds G{sPv[wave], sPre[wave], sPairOf[wave], sCon[wave], sAcc[wave]};
     const RingLds Ps{sPv[wave], sPbox[wave], nullptr, nullptr};
     int32_t *const box_of = reinterpret_cast<int32_t *>(sCross[wave]), *const anchor_of = box_of + 4 * kGroup;
@@ -1117,7 +1130,7 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
             pe_next = doff[id + 1];
         }
         const bool valid = live & (n >= 3) & (a2q != 0);
-        const bool small = valid & q_tiled & (n <= kTileCap);
+        const bool small = valid & q_tiled & (n <= kTileCap) & (n * m < mid_min);
         if (live & !valid) cand_j[c] = 0.0;
         uint64_t big = __ballot(valid & !small), todo = __ballot(small);
         const int nch = small ? (n + 7) >> 3 : 0;
@@ -1222,11 +1235,8 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
                 Ps, __popcll(km), Qs, m, lane, sCid[wave], sList[wave], sUnits[wave], sCross[wave], &st_swept,
                 [&](int count) { flush_group(G, Qs, sQsuf, a2q, qs, qscale, sCross[wave], count, lane); });
             wave_lds_sync();
-            // lane = pair: 2 A = sp sq sum + sp w(kp) A2P + sq w(kq) A2Q
-            const int64_t sum = (int64_t)G.acc[gi];
-            const int64_t ends = (wkp ? (a2p < 0 ? -a2p : a2p) : 0) + (wkq ? (a2q < 0 ? -a2q : a2q) : 0);
-            const int64_t fixed = (int64_t)((uint64_t)((a2p ^ a2q) < 0 ? -sum : sum) + ((uint64_t)ends << qs));
-            const double J = act ? jaccard_of((double)fixed * qunscale, a2p, a2q) : 0.0;
+            // lane = pair
+            const double J = act ? group_jaccard((int64_t)G.acc[gi], wkp, wkq, a2p, a2q, qs) : 0.0;
             if (mem & !(!apart & wide)) cand_j[c] = J;
         }
         // pairs beyond the tiled form, one at a time
@@ -1241,7 +1251,8 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
             int slot = 0;
             int32_t pm[4];
             poly_mbr(Pg, nl, lane, pm);
-            const bool small_pair = q_tiled & (nl <= kTileCap);   // only wide ones come here, counted above
+            // of those that fit a group only wide ones come here
+            const bool small_pair = q_tiled & (nl <= kTileCap) & (nl * m < mid_min);
             const bool disjoint = pm[2] <= qmbr[0] || qmbr[2] <= pm[0] || pm[3] <= qmbr[1] || qmbr[3] <= pm[1];
             st_disjoint += disjoint;
             if (!disjoint) {
@@ -1707,7 +1718,9 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
     const int lane = threadIdx.x;
     const int64_t norig = min((int64_t)hw.count[1], (int64_t)kWideListCap);
     const int64_t nunits = max((int64_t)0, min((int64_t)hw.count[4], (int64_t)kWideListCap - norig));
-    if (norig + nunits == 0) return;   // nothing deferred (the usual case): no atomics on the counter
+    // nothing deferred, or nothing of more than kWideCap edges (the usual
+    // cases): no atomics on the counter
+    if (norig + nunits <= hw.count[5]) return;
     unsigned long long st_pairs = 0, st_swept = 0;
     // entries are taken from a counter as wavefronts come free, the split
     // pairs' units first: costs range from one window to many
@@ -1722,6 +1735,7 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
         const int32_t *Pg = swap ? qxy + 2 * qa : dxy + 2 * w.pa;
         const int32_t *Qg = swap ? dxy + 2 * w.pa : qxy + 2 * qa;
         const int n = swap ? mq : w.n, m = swap ? w.n : mq;
+        if (max(n, m) <= kWideCap) continue;     // mid_pairs'
         const int64_t ox = Qg[0], oy = Qg[1];
         // windows of this entry: all, or one P window (and one Q window) of
         // a split pair
@@ -1885,22 +1899,199 @@ __device__ void heavy_slices(const int32_t *__restrict__ dxy, const int32_t *__r
     }
 }
 
-// What k_refine deferred, but for the wide tiled pairs: the first workgroups
-// prepare the split pairs, the others take the heavy pairs' slices.
+// Pairs of up to kWideCap edges a side, a workgroup each: its first lanes take
+// a chunk of P or of Q each (vertices, box, prefix of cross products), its 16
+// wavefronts share P's chunks, and the crossings' terms are added as in
+// k_refine's groups.  A wavefront a pair, 33 KB of LDS each, left a SIMD with
+// one wavefront and the launch with the time of its longest pair (20,000
+// pairs of which 595 of 513 to 1,024 edges: 258 us, so 137).
+constexpr int kMidWaves = kMetaThreads / 64;
+// In a small call the same goes for the largest pairs of a group, of kMidMin
+// edge pairs and more: one wavefront each set the time of k_refine (those
+// 20,000 pairs 120 us, 1,000 queries of 121 pairs 232 us, 272 without; from
+// half the edge pairs on small calls lose up to 3 us, from a quarter on all
+// lose).  A large call has others to run beside them, and loses: 6.5 million
+// pairs 7.2 ms, with 2^16 edge pairs and more moved 8.3.
+constexpr int kMidMin = 1 << 17;
+constexpr int64_t kMidCand = 1 << 18;
+
+struct MidLds {
+    int2 qv[kWideRing];
+    int4 qbox[kWideCap / 8];
+    int64_t suf[kWideCap];
+    int2 pv[kWideCap / 8 * 9];
+    int4 pbox[kWideCap / 8];
+    int64_t pre[kWideCap / 8 + 1];
+    uint8_t pair_of[kWideCap / 8], cid[kWideCap / 8];
+    uint16_t list[kMidWaves][kListCap];
+    uint32_t units[kMidWaves][kUnitCap];
+    uint32_t cross[kMidWaves][kGroupCross];
+    int64_t sum[4];              // cross products of P's chunks 0-63, 64-127, Q's
+    int4 con;
+    unsigned long long acc;
+    int32_t mbr[8];              // P's, Q's
+    int32_t anchor[2], odd[2], kept[2];
+    int32_t taken;
+};
+
+__device__ void mid_pairs(MidLds &L, const int32_t *__restrict__ dxy, const int32_t *__restrict__ qxy,
+                          const int64_t *__restrict__ qoff, double *__restrict__ cand_j, const HeavyWs &hw, int slot)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t count = min((int64_t)hw.count[1], (int64_t)kWideListCap);
+    if (hw.count[5] == 0) return;
+    unsigned long long st_swept = 0, st_pairs = 0;
+    if (tid < kWideCap / 8) L.pair_of[tid] = 0;
+    for (;;) {
+        __syncthreads();
+        if (tid == 0) L.taken = atomicAdd(hw.count + 6, 1);
+        __syncthreads();
+        const int64_t t = __builtin_amdgcn_readfirstlane(L.taken);
+        if (t >= count) break;
+        const WidePair w = hw.wide[t];
+        const int64_t qa = qoff[w.q];
+        const int n = __builtin_amdgcn_readfirstlane(w.n), m = __builtin_amdgcn_readfirstlane((int)(qoff[w.q + 1] - qa));
+        if (max(n, m) > kWideCap) continue;      // k_refine_wide's
+        const int ncp = (n + 7) >> 3, ncq = (m + 7) >> 3;
+        // this lane's chunk: of P, of Q (and one of padding), or none
+        const bool isq = tid >= kWideCap / 8;
+        const int c = isq ? tid - kWideCap / 8 : tid, nv = isq ? m : n;
+        const bool mine = isq ? c <= ncq : c < ncp, real = isq ? c < ncq : c < ncp;
+        const int2 *V = reinterpret_cast<const int2 *>(isq ? qxy + 2 * qa : dxy + 2 * w.pa);
+        const int2 org = *reinterpret_cast<const int2 *>(qxy + 2 * qa);
+        int2 v[9];
+        int4 box{};
+        int64_t cross[8];
+        if (tid < 8) L.mbr[tid] = (tid & 3) < 2 ? INT32_MAX : INT32_MIN;
+        if (tid < 2) { L.anchor[tid] = -1; L.odd[tid] = 0; }
+        if (tid == 0) L.acc = 0;
+        __syncthreads();
+        int64_t upto = 0, own = 0;
+        if (wave <= 4) {
+            int2 p[9];
+#pragma unroll
+            for (int j = 0; j < 9; j++) {
+                const int i = mine && 8 * c + j < nv ? 8 * c + j : 0;
+                p[j] = V[i];
+                v[j] = make_int2(p[j].x - org.x, p[j].y - org.y);
+            }
+            box = make_int4(p[0].x, p[0].y, p[0].x, p[0].y);
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                cross[j] = mine ? (int64_t)v[j].x * v[j + 1].y - (int64_t)v[j + 1].x * v[j].y : 0;
+                own += cross[j];
+                box.x = min(box.x, p[j + 1].x); box.z = max(box.z, p[j + 1].x);
+                box.y = min(box.y, p[j + 1].y); box.w = max(box.w, p[j + 1].y);
+            }
+            if (mine) {
+#pragma unroll
+                for (int j = 0; j < 9; j++) {
+                    if (!isq) L.pv[9 * c + j] = v[j];
+                    else if (j < 8 || c == ncq) L.qv[8 * c + j] = v[j];
+                }
+            }
+            if (real) {
+                int32_t *b = L.mbr + (isq ? 4 : 0);
+                atomicMin(b, box.x); atomicMin(b + 1, box.y);
+                atomicMax(b + 2, box.z); atomicMax(b + 3, box.w);
+            }
+            upto = wave_incl_scan64(own);
+            if (lane == 63 && wave < 4) L.sum[wave] = upto;
+        }
+        __syncthreads();
+        const int64_t a2p = L.sum[0] + L.sum[1], a2q = L.sum[2] + L.sum[3];
+        const int32_t *pm = L.mbr, *qm = L.mbr + 4;
+        const int qs = fixed_point_bits(qm);
+        const double qscale = (double)(1ll << qs);
+        bool keep = false;
+        uint64_t km = 0;
+        if (wave <= 4) {
+            upto += (wave == 1 || wave == 3) ? L.sum[wave - 1] : 0;
+            const int32_t *o = isq ? pm : qm;
+            int out = -1;
+            int64_t run = upto - own;
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                const int x = v[j].x + org.x, y = v[j].y + org.y, i = 8 * c + j;
+                if (real && i < nv && ((x < o[0]) | (x > o[2]) | (y < o[1]) | (y > o[3]))) out = i;
+                run += cross[j];
+                if (isq && real) L.suf[i] = a2q - run;
+            }
+            if (out >= 0) atomicMax(&L.anchor[isq ? 1 : 0], out);
+            const int4 rel = make_int4(box.x - org.x, box.y - org.y, box.z - org.x, box.w - org.y);
+            if (isq) {
+                if (real) L.qbox[c] = rel;
+            } else {
+                if (real) L.pre[c] = upto - own;
+                if (c == ncp - 1) L.pre[ncp] = upto;
+                keep = real & !((box.z < o[0]) | (o[2] < box.x) | (box.w < o[1]) | (o[3] < box.y));
+            }
+            km = __ballot(keep);
+            if (lane == 0 && wave < 2) L.kept[wave] = __popcll(km);
+            box = rel;
+        }
+        __syncthreads();
+        if (keep) {
+            const int at = lanes_below(km) + (wave == 1 ? L.kept[0] : 0);
+            L.pbox[at] = box;
+            L.cid[at] = (uint8_t)c;
+        }
+        int kp = L.anchor[0], kq = L.anchor[1];
+        if (kp < 0 || kq < 0) {
+            // no anchor: the ring starts' memberships, an edge a thread
+            const int e = tid;
+            const bool op = kp < 0 && e < m && member_edge(L.qv, e < m ? e : 0, L.pv[0], -1);
+            const bool oq = kq < 0 && e < n && member_edge(L.pv, e < n ? e + (e >> 3) : 0, L.qv[0], +1);
+            const int cp = __popcll(__ballot(op)), cq = __popcll(__ballot(oq));
+            if (lane == 0) { atomicAdd(&L.odd[0], cp); atomicAdd(&L.odd[1], cq); }
+        }
+        if (tid == 0) L.con = make_int4(0, ncp, max(kp, 0), max(kq, 0));
+        __syncthreads();
+        if (a2p != 0 && a2q != 0) {
+            const int kept = L.kept[0] + L.kept[1];
+            const int b0 = kept * wave / kMidWaves, b1 = kept * (wave + 1) / kMidWaves;
+            const RingLds Q{L.qv, L.qbox, nullptr, nullptr}, P{L.pv, L.pbox + b0, nullptr, nullptr};
+            const GroupLds G{L.pv, L.pre, L.pair_of, &L.con, &L.acc};
+            tiled_accumulate<uint32_t, 16, 9, true, kGroupCross>(
+                P, b1 - b0, Q, m, lane, L.cid + b0, L.list[wave], L.units[wave], L.cross[wave], &st_swept,
+                [&](int got) { flush_group(G, Q, L.suf, a2q, qs, qscale, L.cross[wave], got, lane); });
+        }
+        __syncthreads();
+        if (tid == 0) {
+            double J = 0.0;
+            if (a2p != 0 && a2q != 0) J = group_jaccard((int64_t)L.acc, L.odd[0] & 1, L.odd[1] & 1, a2p, a2q, qs);
+            cand_j[w.c] = J;
+            st_pairs++;
+        }
+    }
+    if (hw.stat_slots && lane == 0) {
+        unsigned long long *out = hw.stat_slots + (slot % kStatSlots) * 4;
+        if (st_pairs) atomicAdd(out + 0, st_pairs);
+        if (st_swept) atomicAdd(out + 1, st_swept);
+    }
+}
+
+// What k_refine deferred, but for the pairs of more than kWideCap edges: the
+// first workgroups prepare those that are split, the next take the heavy
+// pairs' slices, the last the pairs of up to kWideCap edges.
 constexpr int kMetaBlocks = 256;
 __global__ __launch_bounds__(kMetaThreads) void k_deferred(const int32_t *__restrict__ dxy,
                                                          const int32_t *__restrict__ qxy,
                                                          const int64_t *__restrict__ qoff,
                                                          double *__restrict__ cand_j, HeavyWs hw)
 {
+    __shared__ MidLds mid;
     const int block = (int)blockIdx.x;
     if (block < kMetaBlocks) {
         wide_meta(dxy, qxy, qoff, hw, block, kMetaBlocks);
-    } else {
+    } else if (block < 2 * kMetaBlocks) {
         constexpr int kWaves = kMetaThreads / 64;
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
         heavy_slices(dxy, qxy, cand_j, hw, (int64_t)(block - kMetaBlocks) * kWaves + wave,
-                     (int64_t)(gridDim.x - kMetaBlocks) * kWaves, threadIdx.x & 63);
+                     (int64_t)kMetaBlocks * kWaves, threadIdx.x & 63);
+    } else {
+        mid_pairs(mid, dxy, qxy, qoff, cand_j, hw, block);
     }
 }
 
@@ -1920,7 +2111,7 @@ HeavyWs carve_heavy(Carve &cv)
 // Clears the pair counts, the work counter and the counter slots (256 threads).
 __global__ void k_zero_count(int32_t *p, unsigned long long *slots)
 {
-    if (threadIdx.x < 5) p[threadIdx.x] = 0;
+    if (threadIdx.x < 7) p[threadIdx.x] = 0;
     if (threadIdx.x < kStatSlots * 4) slots[threadIdx.x] = 0;
 }
 
@@ -1970,14 +2161,15 @@ polymh_status launch_refine(const polymh_polys *data, const polymh_polys *querie
     int64_t sl = std::max<int64_t>(1, std::min<int64_t>(64, std::max(by_batch, by_length)));
     if (nq * sl > 0x7fffffffLL) sl = 1;
     const int slices = (int)sl;
+    const int mid_min = ws && n_cand < kMidCand ? kMidMin : INT32_MAX;
     hipLaunchKernelGGL(k_refine, dim3((unsigned)(nq * slices)), dim3(64 * kWavesPerBlock), 0, s, data->xy,
                        data->offsets, queries->xy, queries->offsets, cand_off, cand_ids, cand_j, stats,
-                       slices, hw);
+                       slices, mid_min, hw);
     polymh_status st = check_launch("refine");
     if (st || !ws) return st;
-    hipLaunchKernelGGL(k_deferred, dim3(2 * kMetaBlocks), dim3(kMetaThreads), 0, s, data->xy, queries->xy,
+    hipLaunchKernelGGL(k_deferred, dim3(3 * kMetaBlocks), dim3(kMetaThreads), 0, s, data->xy, queries->xy,
                        queries->offsets, cand_j, hw);
-    if ((st = check_launch("refine: heavy pairs, split pairs"))) return st;
+    if ((st = check_launch("refine: deferred pairs"))) return st;
     // deferred wide tiled pairs: four one-wavefront workgroups per CU
     hipLaunchKernelGGL(k_refine_wide, dim3(1024), dim3(64), 0, s, data->xy, queries->xy, queries->offsets, cand_j,
                        hw, stats ? 1 : 0);

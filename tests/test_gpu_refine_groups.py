@@ -84,3 +84,29 @@ def test_short_lists(pm, orc):
     want = orc.jaccard_candidates(ds, qs, off, ids)
     got = _refine(pm, pm.to_device(ds), pm.to_device(qs), off, ids)
     assert np.all(np.abs(got - want) <= 1e-9 * want + 1e-12)
+
+
+@pytest.mark.parametrize("m", [3, 513, 700, 1017, 1023, 1024, 1025])
+@pytest.mark.parametrize("side", [1 << 18, 1 << 25])
+def test_pairs_beyond_a_group(pm, orc, m, side):
+    """513 to 1,024 edges a side (a workgroup a pair) beside smaller and larger
+    ones: about the chunk edges, contained, containing, apart, without area."""
+    data = _stars([3, 9, 512, 513, 520, 767, 768, 1016, 1017, 1023, 1024, 1025, 1600], side, 0.15, 0.3, 3)
+    data += _stars([600, 900], side, 0.01, 0.02, 4) + _stars([600, 1000], side, 0.4, 0.45, 6)
+    q = side // 4
+    flat = np.stack([np.linspace(q, 3 * q, 600).astype(np.int64)] * 2, axis=1)
+    data += [flat, dg.rectangle(0, 0, side - 1, side - 1), data[5][::-1]]
+    ds, qs = dg.from_list(data), dg.from_list(_stars([m, max(3, m - 1)], side, 0.15, 0.3, 20 + m))
+    n = ds.n
+    want = orc.jaccard_candidates(ds, qs, np.array([0, n, 2 * n]), np.tile(np.arange(n, dtype=np.int32), 2))
+    D, Q = pm.to_device(ds), pm.to_device(qs)
+    rng, first = np.random.default_rng(m), None
+    for rep in range(3):
+        order = np.concatenate([rng.permutation(n) if rep else np.arange(n) for _ in range(2)])
+        got = _refine(pm, D, Q, np.array([0, n, 2 * n]), order)
+        ref = np.concatenate([want[:n][order[:n]], want[n:][order[n:]]])
+        assert np.all(np.abs(got - ref) <= 1e-9 * ref + 1e-12), rep
+        first = got if first is None else first
+        whole = (np.diff(ds.offsets)[order] <= 1024) & (m <= 1024)
+        same = np.concatenate([first[:n][order[:n]], first[n:][order[n:]]])
+        assert np.array_equal(got[whole], same[whole]), rep
