@@ -35,20 +35,19 @@ PEAK_VALU = 256 * 4 * 16 * 2.4e9      # lane-cycles/s: 256 CUs x 4 SIMD16 x 2.4 
 # VALU instructions per lane, counted in the built gfx950 code of the signing
 # kernel's walk: one draw of the tile loop (SplitMix64 with its two 64 x 64-bit
 # products as 4 v_mul_lo_u32 + 2 v_mad_u64_u32, the lattice map, the MBR
-# check and the loop latch: 28 + 3 instructions) and one edge test of the
-# point-in-polygon loop (3 subtractions, 4 conversions, an FP64 product and
-# FMA, 3 compares, 3 index updates: 15).  Each is taken as one lane-cycle:
-# the walk of workload 5 (4.8e12 draws in 3.85 s) would exceed the VALU peak
-# at more than about 32 lane-cycles a draw, so the multiplies issue at full
-# rate on gfx950.
-C_DRAW = 31
-C_EDGE = 15
+# check's two compares and the stream's advance: 24 instructions; the loop
+# runs on the scalar unit) and one edge test with the edge in a register (a
+# subtraction, 2 FP64 FMAs, 2 compares: 5; the point's two conversions serve
+# all edges).  Each is taken as one lane-cycle: the multiplies issue at full
+# rate on gfx950 (measured, as do the FP64 FMAs).
+C_DRAW = 24
+C_EDGE = 5
 # Algorithmic VALU operations of one exact edge-pair test in the refinement:
-# the four orientations from one shared difference r = c - a and X = cross(e, f)
-# (2 subtractions, 3 products with their fused subtractions = 6, 2 additions)
-# plus the 4 sign decisions; the general per-edge form adds the half-open
-# membership update (2 compares, and, xor).
-C_PAIR = 14
+# the four orientations from r = c - a, r' = c - b and orient(c, d, a) carried
+# over (2 subtractions, 2 products with their fused subtractions = 4, 2
+# additions) plus the 4 sign decisions; the general per-edge form takes 18 with
+# the half-open membership update.
+C_PAIR = 12
 C_GENERAL = 18
 
 
@@ -391,18 +390,23 @@ def bin_lookup_bytes(Q, qsig, box, horizon, bits, walk_ratio, lds_edges):
     """Algorithmic bytes of one binned-lookup launch over the query batch:
     for every (polygon, hash) the lookup settles, each chunk of C samples it
     visits (up to the chunk of the first hit, the signature value) costs the
-    two 16-bit cell offsets of every grid row under the MBR, the 8-byte
-    records of the samples of those rows' cells (C x cells / 4^bits of them
-    on average) and the 2-byte indices of those inside the MBR; per unit the
-    4-byte signature; per polygon its vertices (8 n) and staging (24 B).
-    Polygons left to the walk (the same rule as the kernel's classification)
-    are not counted."""
+    12-byte records of the samples of the grid rows under the MBR between its
+    quarter-cell columns (C x columns / (rows of the grid x columns of the
+    grid) of them on average), those inside the MBR again when they are
+    tested, and the hash's share of the rows' 8-byte ranges (shared by up to
+    256 hashes); per unit the 4-byte signature; per polygon its vertices (8 n)
+    and staging (24 B).  Polygons left to the walk (the same rule as the
+    kernel's classification) are not counted."""
     from paper_2511_16576_amd import polymh as pm
     mbr, area2, flags = (x.cpu().numpy() for x in pm.prepare(Q))
     mbr = mbr.astype(np.float64)
     wx, wy = float(box[2]) - box[0] + 1, float(box[3]) - box[1] + 1
     lx, ly = int(round(np.log2(wx))), int(round(np.log2(wy)))
-    C = float(1 << int(np.clip(2 * bits, 8, 12)))
+    k = qsig.shape[1]
+    C = 2.0 ** max(8, bits + 4)
+    group = min(k, 256)
+    while 2 * group <= 256:                       # chunks of few hashes hold more samples
+        group, C = 2 * group, 2 * C
     nchunks = np.ceil(horizon / C)
     area = np.abs(area2.astype(np.float64)) / 2
     n = (Q.offsets[1:] - Q.offsets[:-1]).cpu().numpy().astype(np.float64)
@@ -410,16 +414,18 @@ def bin_lookup_bytes(Q, qsig, box, horizon, bits, walk_ratio, lds_edges):
     deg = (flags & 3) != 0
     with np.errstate(divide="ignore", invalid="ignore"):
         walk_cost = 5.0 * wx * wy / area + n * a_mbr / area
-        bin_cost = n * np.maximum(1.0, C * a_mbr / (wx * wy))
+        bin_cost = 1.5 * n * a_mbr / area
         walk = (~deg) & (area > 0) & ((wx * wy < walk_ratio * area) | (walk_cost < bin_cost) | (n > lds_edges))
+        if Q.n <= 65536:
+            walk |= (~deg) & (area > 0) & (bin_cost > 2048.0)
     binned = ~walk & ~deg
-    sx, sy = max(lx - bits, 0), max(ly - bits, 0)
+    cbits = bits + (2 if bits > 4 and lx >= bits + 2 else 0)
+    sx, sy = max(lx - cbits, 0), max(ly - bits, 0)
     cols = (np.floor((mbr[:, 2] - box[0]) / 2 ** sx) - np.floor((mbr[:, 0] - box[0]) / 2 ** sx)) + 1
     rows = (np.floor((mbr[:, 3] - box[1]) / 2 ** sy) - np.floor((mbr[:, 1] - box[1]) / 2 ** sy)) + 1
-    per_chunk = rows * 4 + C * rows * cols / 4.0 ** bits * 8 + C * a_mbr / (wx * wy) * 2
+    per_chunk = rows * 8 / min(k, 256) + 12 * C * (rows * cols / 2.0 ** (bits + cbits) + a_mbr / (wx * wy))
     sg = qsig.cpu().numpy().view(np.uint32).astype(np.float64)
     chunks = np.where(sg > 0, np.minimum(np.ceil(sg / C), nchunks), nchunks).sum(axis=1)
-    k = sg.shape[1]
     return float(((chunks * per_chunk + 4.0 * k + 8.0 * n + 24.0) * binned).sum())
 
 
