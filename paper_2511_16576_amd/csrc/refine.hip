@@ -898,6 +898,18 @@ __device__ bool defer_wide(const HeavyWs &hw, int64_t c, int64_t pa, int n, int 
     return true;
 }
 
+// Are the pairs of up to kWideCap edges a side taken by workgroups (mid_pairs,
+// before k_refine_wide), or by k_refine_wide with the larger ones?  Many of
+// them beside larger pairs fill the time of those pairs' long units (4.5
+// million pairs of workload 5's polygons 2.03 ms, first by workgroups 2.29;
+// 900,000 pairs 0.75 and 0.80); a few are faster by workgroups, and so are any
+// number without larger ones (20,000 pairs 99 us, one wavefront each 195;
+// 400,000 pairs 882 and 922).
+__device__ __forceinline__ bool mids_by_workgroup(const HeavyWs &hw)
+{
+    return hw.count[5] <= 512 || hw.count[5] == hw.count[1];
+}
+
 __device__ __forceinline__ double jaccard_of(double inter2, int64_t a2p, int64_t a2q)
 {
     const double inter = 0.5 * inter2;
@@ -1720,7 +1732,8 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
     const int64_t nunits = max((int64_t)0, min((int64_t)hw.count[4], (int64_t)kWideListCap - norig));
     // nothing deferred, or nothing of more than kWideCap edges (the usual
     // cases): no atomics on the counter
-    if (norig + nunits <= hw.count[5]) return;
+    const bool mids = mids_by_workgroup(hw);     // taken by mid_pairs
+    if (norig + nunits <= (mids ? hw.count[5] : 0)) return;
     unsigned long long st_pairs = 0, st_swept = 0;
     // entries are taken from a counter as wavefronts come free, the split
     // pairs' units first: costs range from one window to many
@@ -1735,7 +1748,7 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
         const int32_t *Pg = swap ? qxy + 2 * qa : dxy + 2 * w.pa;
         const int32_t *Qg = swap ? dxy + 2 * w.pa : qxy + 2 * qa;
         const int n = swap ? mq : w.n, m = swap ? w.n : mq;
-        if (max(n, m) <= kWideCap) continue;     // mid_pairs'
+        if (mids && max(n, m) <= kWideCap) continue;
         const int64_t ox = Qg[0], oy = Qg[1];
         // windows of this entry: all, or one P window (and one Q window) of
         // a split pair
@@ -1940,7 +1953,7 @@ __device__ void mid_pairs(MidLds &L, const int32_t *__restrict__ dxy, const int3
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t count = min((int64_t)hw.count[1], (int64_t)kWideListCap);
-    if (hw.count[5] == 0) return;
+    if (hw.count[5] == 0 || !mids_by_workgroup(hw)) return;
     unsigned long long st_swept = 0, st_pairs = 0;
     if (tid < kWideCap / 8) L.pair_of[tid] = 0;
     for (;;) {

@@ -110,3 +110,17 @@ def test_pairs_beyond_a_group(pm, orc, m, side):
         whole = (np.diff(ds.offsets)[order] <= 1024) & (m <= 1024)
         same = np.concatenate([first[:n][order[:n]], first[n:][order[n:]]])
         assert np.array_equal(got[whole], same[whole]), rep
+
+
+@pytest.mark.parametrize("larger", [0, 1])
+@pytest.mark.parametrize("n", [500, 513, 700])
+def test_many_pairs_beyond_a_group(pm, orc, n, larger):
+    """As many pairs of 513 to 1,024 edges as workgroups take beside a larger
+    pair, more, and more without one."""
+    side = 1 << 20
+    data = _stars([600, 1024, 1100], side, 0.2, 0.3, 8)
+    ds, qs = dg.from_list(data), dg.from_list(_stars([520], side, 0.2, 0.3, 9))
+    ids = np.concatenate([np.arange(n) % 2, np.full(larger, 2)]).astype(np.int32)
+    want = orc.jaccard_candidates(ds, qs, np.array([0, 3]), np.arange(3, dtype=np.int32))[ids]
+    got = _refine(pm, pm.to_device(ds), pm.to_device(qs), np.array([0, ids.size]), ids)
+    assert np.all(np.abs(got - want) <= 1e-9 * want + 1e-12)
