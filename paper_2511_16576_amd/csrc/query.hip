@@ -86,9 +86,56 @@ __device__ __forceinline__ int64_t bucket_end(const uint64_t *__restrict__ skeys
 // searches' dependent reads.  100,000 polygons, 32 bands, 1,000 queries 53 us
 // for the whole lookup and 10,000 253, against 85 and 573 with a wavefront a
 // (query, band) and the rows cleared, marked and counted in memory.
-constexpr int kRowThreads = 256;
-template <bool kLds>
-__global__ __launch_bounds__(kRowThreads) void k_mark_row(const uint64_t *__restrict__ skeys,
+// The same searches by 16 lanes (a DPP row) with the same key.  A round reads
+// 16 keys about the interpolated place, the square root of the bracket's
+// length apart up to a quarter (a uniform key lies within half of it, about),
+// so that some 3 rounds of memory latency find the place instead of the 8
+// probes the last of a wavefront's lanes needs; from the fifth round on the
+// bracket is cut into 17 equal parts, which bounds them.  Lanes of other rows
+// may be done.
+struct Bucket {
+    int64_t lo, hi;
+};
+__device__ __forceinline__ Bucket bucket_by_row(const uint64_t *__restrict__ a, int64_t n, uint64_t key, int l16,
+                                                int row_shift)
+{
+    int64_t lo = 0, hi = n;                 // answer in [lo, hi]
+    uint64_t klo = 0, khi = ~0ull;
+    for (int round = 0; lo < hi; round++) {
+        const int64_t len = hi - lo;
+        const double f = khi > klo ? (double)(key - klo) / (double)(khi - klo) : 0.5;
+        const int64_t d = max((int64_t)1, (int64_t)(0.25f * sqrtf((float)len)));
+        const int64_t about = lo + (int64_t)(f * (double)len) + (l16 - 8) * d, part = lo + (l16 + 1) * len / 17;
+        int64_t p = len <= 16 ? lo + l16 : round < 4 ? about : part;
+        // lanes past the bracket count as at its last key
+        p = p < lo ? lo : (p >= hi ? hi - 1 : p);
+        const uint64_t v = a[p];
+        const uint32_t below = (uint32_t)(__ballot(v < key) >> row_shift) & 0xffffu;
+        const int c = __popc(below);        // the first c lanes' keys are below
+        const int from = row_shift + (c > 0 ? c - 1 : 0), to = row_shift + (c < 16 ? c : 15);
+        const int64_t pf = __shfl(p, from), pt = __shfl(p, to);
+        const uint64_t vf = __shfl(v, from), vt = __shfl(v, to);
+        if (c > 0) { lo = pf + 1; klo = vf; }
+        if (c < 16) { hi = pt; khi = vt; }
+    }
+    Bucket r{lo, lo};
+    for (;;) {
+        const bool in = r.hi + l16 < n && a[r.hi + l16] == key;
+        const uint32_t run = (uint32_t)(__ballot(in) >> row_shift) & 0xffffu;
+        const int c = __builtin_ctz(~run);  // 16 if all are
+        r.hi += c;
+        if (c < 16) break;
+        if (r.hi - r.lo >= 64) {            // a long bucket: gallop on from here
+            r.hi = bucket_end(a, n, key, r.hi);
+            break;
+        }
+    }
+    return r;
+}
+
+constexpr int kRowThreads = 256, kRowTeam = 1024;
+template <bool kLds, int kThreads>
+__global__ __launch_bounds__(kThreads) void k_mark_row(const uint64_t *__restrict__ skeys,
                                                           const int32_t *__restrict__ sids, int64_t n_entries,
                                                           const uint64_t *__restrict__ qkeys, int32_t b,
                                                           uint32_t *bitmap, int64_t words,
@@ -96,17 +143,32 @@ __global__ __launch_bounds__(kRowThreads) void k_mark_row(const uint64_t *__rest
                                                           const int32_t *__restrict__ dense)
 {
     extern __shared__ uint32_t s_row[];
-    __shared__ int64_t s_base[kRowThreads + 1], s_lo[kRowThreads], s_w[kRowThreads / 64];
+    __shared__ int64_t s_base[kThreads + 1], s_lo[kThreads], s_w[kThreads / 64];
     const int64_t q = blockIdx.x;
     if (!kLds && !dense[q]) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t *row = bitmap + q * words;
     uint32_t *bits = kLds ? s_row : row;
-    for (int64_t i = tid; i < words; i += kRowThreads) bits[i] = 0u;
-    for (int32_t t0 = 0; t0 < b; t0 += kRowThreads) {
+    for (int64_t i = tid; i < words; i += kThreads) bits[i] = 0u;
+    for (int32_t t0 = 0; t0 < b; t0 += kThreads) {
         const int32_t t = t0 + tid;
         int64_t lo = 0, hi = 0;
-        if (t < b) {
+        if constexpr (kThreads == kRowTeam) {
+            // few queries: the searches' latency is the launch's
+            const int l16 = tid & 15, row_shift = lane & 48, count = min(kThreads, b - t0);
+            for (int r = tid >> 4; r < count; r += kThreads / 16) {
+                const Bucket k = bucket_by_row(skeys, n_entries, qkeys[q * b + t0 + r], l16, row_shift);
+                if (l16 == 0) {
+                    s_lo[r] = k.lo;
+                    s_base[r] = k.hi - k.lo;
+                }
+            }
+            __syncthreads();
+            if (t < b) {
+                lo = s_lo[tid];
+                hi = lo + s_base[tid];
+            }
+        } else if (t < b) {
             const uint64_t key = qkeys[q * b + t];
             lo = lower_bound_interp(skeys, n_entries, key);
             hi = bucket_end(skeys, n_entries, key, lo);
@@ -118,17 +180,17 @@ __global__ __launch_bounds__(kRowThreads) void k_mark_row(const uint64_t *__rest
         for (int w = 0; w < wave; w++) at += s_w[w];
         s_base[tid] = at;
         s_lo[tid] = lo;
-        if (tid == kRowThreads - 1) s_base[kRowThreads] = at + (hi - lo);
+        if (tid == kThreads - 1) s_base[kThreads] = at + (hi - lo);
         __syncthreads();
-        const int64_t total = s_base[kRowThreads];
-        const int top = min(kRowThreads, b - t0) - 1;
+        const int64_t total = s_base[kThreads];
+        const int top = min(kThreads, b - t0) - 1;
         constexpr int kU = 4;                   // entries in flight a thread
-        for (int64_t j0 = tid; j0 < total; j0 += kRowThreads * kU) {
+        for (int64_t j0 = tid; j0 < total; j0 += kThreads * kU) {
             int32_t ent[kU];
             int band[kU];
 #pragma unroll
             for (int u = 0; u < kU; u++) {
-                const int64_t j = j0 + kRowThreads * u;
+                const int64_t j = j0 + kThreads * u;
                 ent[u] = -1;
                 band[u] = 0;
                 if (j < total) {
@@ -151,7 +213,7 @@ __global__ __launch_bounds__(kRowThreads) void k_mark_row(const uint64_t *__rest
         __syncthreads();
     }
     int64_t c = 0;
-    for (int64_t i = tid; i < words; i += kRowThreads) {
+    for (int64_t i = tid; i < words; i += kThreads) {
         uint32_t v;
         if constexpr (kLds) {
             v = s_row[i];
@@ -165,7 +227,7 @@ __global__ __launch_bounds__(kRowThreads) void k_mark_row(const uint64_t *__rest
     if (lane == 0) s_w[wave] = c;
     __syncthreads();
     if (tid == 0) {
-        for (int w = 1; w < kRowThreads / 64; w++) c += s_w[w];
+        for (int w = 1; w < kThreads / 64; w++) c += s_w[w];
         counts[q] = c;
     }
 }
@@ -785,11 +847,19 @@ void lookup_counts(const uint64_t *skeys, const int32_t *sids, int64_t n_entries
                    const uint64_t *qkeys, int64_t nq, int32_t b, const QueryWs &w, int64_t *counts, hipStream_t s)
 {
     if (use_row(nq, words)) {
-        if (words * 4 > 64 << 10)
-            (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mark_row<true>),
+        const bool team = nq <= cu_count();
+        if (words * 4 > 40 << 10)
+            (void)hipFuncSetAttribute(team ? reinterpret_cast<const void *>(&k_mark_row<true, kRowTeam>)
+                                           : reinterpret_cast<const void *>(&k_mark_row<true, kRowThreads>),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)words * 4);
-        hipLaunchKernelGGL(k_mark_row<true>, dim3((unsigned)nq), dim3(kRowThreads), (size_t)words * 4, s, skeys, sids,
-                           words > 0 ? n_entries : 0, qkeys, b, w.bitmap, words, counts, (const int32_t *)nullptr);
+        if (team)
+            hipLaunchKernelGGL((k_mark_row<true, kRowTeam>), dim3((unsigned)nq), dim3(kRowTeam), (size_t)words * 4, s,
+                               skeys, sids, words > 0 ? n_entries : 0, qkeys, b, w.bitmap, words, counts,
+                               (const int32_t *)nullptr);
+        else
+            hipLaunchKernelGGL((k_mark_row<true, kRowThreads>), dim3((unsigned)nq), dim3(kRowThreads),
+                               (size_t)words * 4, s, skeys, sids, words > 0 ? n_entries : 0, qkeys, b, w.bitmap, words,
+                               counts, (const int32_t *)nullptr);
         return;
     }
     hipLaunchKernelGGL(k_sparse, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, skeys, sids, n_entries,
@@ -798,7 +868,7 @@ void lookup_counts(const uint64_t *skeys, const int32_t *sids, int64_t n_entries
                        w.bitmap, words);
     hipLaunchKernelGGL(k_sparse_sort_big, dim3((unsigned)nq), dim3(1024), 0, s, w.dense, counts, w.bitmap,
                        words);
-    hipLaunchKernelGGL(k_mark_row<false>, dim3((unsigned)nq), dim3(kRowThreads), 0, s, skeys, sids, n_entries, qkeys, b,
+    hipLaunchKernelGGL((k_mark_row<false, kRowThreads>), dim3((unsigned)nq), dim3(kRowThreads), 0, s, skeys, sids, n_entries, qkeys, b,
                        w.bitmap, words, counts, w.dense);
 }
 

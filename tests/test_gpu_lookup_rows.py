@@ -49,3 +49,31 @@ def test_lookup_at_its_limits(pm, orc, nd, nq, b, vals):
     short = cids[:ids.numel() - 1].fill_(-7)
     pm.query_capped(sk, si, nd, t(qk), coff, short, flag, ws)
     assert int(flag.item()) == 1 and not coff.any() and bool((short == -7).all())
+
+
+@pytest.mark.parametrize("nq", [1, 7, 256, 257])
+@pytest.mark.parametrize("nd, b", [(1, 1), (2, 3), (5, 3), (17, 1), (33, 2), (4000, 16), (4000, 65)])
+def test_searches(pm, orc, nd, b, nq):
+    """Searches by one thread a band and by 16 (up to 256 queries on 256 CUs):
+    tables shorter and longer than a round's 16 keys, uniform keys, crowded
+    ones at either end of the range, keys below and above all others."""
+    rng = np.random.default_rng([nd, b, nq])
+    top = np.uint64(2 ** 64 - 1)
+    for spread in ("uniform", "low", "high", "few"):
+        dk = rng.integers(0, 2 ** 64 - 1, (nd, b), dtype=np.uint64, endpoint=True)
+        if spread == "low":
+            dk >>= np.uint64(40)
+        elif spread == "high":
+            dk |= top << np.uint64(30)
+        elif spread == "few":
+            dk = dk % np.uint64(3) * (top // np.uint64(2))
+        qk = dk[rng.integers(0, nd, nq)].copy()
+        qk[rng.random(qk.shape) < 0.2] = 0
+        qk[rng.random(qk.shape) < 0.2] = top
+        qk[rng.random(qk.shape) < 0.2] += np.uint64(1)
+        t = lambda a: torch.from_numpy(a.view(np.int64)).cuda()
+        import torch
+        sk, si = pm.index_build(t(dk))
+        off, ids = pm.query(sk, si, nd, t(qk))
+        ooff, oids = orc.candidates(dk, qk)
+        assert np.array_equal(off.cpu().numpy(), ooff) and np.array_equal(ids.cpu().numpy(), oids), spread
