@@ -602,6 +602,15 @@ polymh_status polymh_mlp_score_pairs(const uint32_t *lsig, const float *lfeat, c
                                      const int64_t *out_idx, int64_t R, const float *params,
                                      const uint16_t *wbf16, float *out, void *stream);
 
+/* polymh_mlp_predict_pairs -- polymh_mlp_score_pairs with every prediction at
+ * out[r]; a row with li[r] < 0 or ri[r] < 0 gets the network's value of a zero
+ * input row, as polymh_pair_features + polymh_mlp_forward give it.
+ * Stream-ordered. */
+polymh_status polymh_mlp_predict_pairs(const uint32_t *lsig, const float *lfeat, const uint32_t *rsig,
+                                       const float *rfeat, int32_t k, const int32_t *li, const int32_t *ri,
+                                       int64_t R, const float *params, const uint16_t *wbf16, float *out,
+                                       void *stream);
+
 /* polymh_rank_refine_ordered -- polymh_rank_refine without host reads, so
  * that a whole query batch (signing, lookup, scoring, ordered refinement)
  * can be captured in one graph.  The order comes from the caller

@@ -883,19 +883,36 @@ polymh_status polymh_rank_reorder_head(const int64_t *cand_off, int64_t nq, cons
     return launch_reorder_head(cand_off, nq, score, order_in, M, sorted_ok, order_out, as_stream(stream));
 }
 
+static polymh_status score_pairs(const char *what, const uint32_t *lsig, const float *lfeat, const uint32_t *rsig,
+                                 const float *rfeat, int32_t k, const int32_t *li, const int32_t *ri,
+                                 const int64_t *out_idx, int64_t R, const float *params, const uint16_t *wbf16,
+                                 float *out, int write_empty, void *stream)
+{
+    if (k != 256) return set_error(POLYMH_EINVAL, "%s: the scorer takes k = 256 signatures", what);
+    if (R < 0) return set_error(POLYMH_EINVAL, "%s: negative row count", what);
+    if (R == 0) return POLYMH_OK;
+    if (!lsig || !lfeat || !rsig || !rfeat || !li || !ri || !params || !wbf16 || !out)
+        return set_error(POLYMH_EINVAL, "%s: NULL array", what);
+    if ((reinterpret_cast<uintptr_t>(lsig) | reinterpret_cast<uintptr_t>(rsig) | reinterpret_cast<uintptr_t>(wbf16)) & 15)
+        return set_error(POLYMH_EINVAL, "%s: signatures and weights must be 16-byte aligned", what);
+    return launch_score_pairs(lsig, lfeat, rsig, rfeat, li, ri, out_idx, R, params, wbf16, out, write_empty,
+                              as_stream(stream));
+}
+
 polymh_status polymh_mlp_score_pairs(const uint32_t *lsig, const float *lfeat, const uint32_t *rsig,
                                      const float *rfeat, int32_t k, const int32_t *li, const int32_t *ri,
                                      const int64_t *out_idx, int64_t R, const float *params, const uint16_t *wbf16,
                                      float *out, void *stream)
 {
-    if (k != 256) return set_error(POLYMH_EINVAL, "mlp_score_pairs: the scorer takes k = 256 signatures");
-    if (R < 0) return set_error(POLYMH_EINVAL, "mlp_score_pairs: negative row count");
-    if (R == 0) return POLYMH_OK;
-    if (!lsig || !lfeat || !rsig || !rfeat || !li || !ri || !params || !wbf16 || !out)
-        return set_error(POLYMH_EINVAL, "mlp_score_pairs: NULL array");
-    if ((reinterpret_cast<uintptr_t>(lsig) | reinterpret_cast<uintptr_t>(rsig) | reinterpret_cast<uintptr_t>(wbf16)) & 15)
-        return set_error(POLYMH_EINVAL, "mlp_score_pairs: signatures and weights must be 16-byte aligned");
-    return launch_score_pairs(lsig, lfeat, rsig, rfeat, li, ri, out_idx, R, params, wbf16, out, as_stream(stream));
+    return score_pairs("mlp_score_pairs", lsig, lfeat, rsig, rfeat, k, li, ri, out_idx, R, params, wbf16, out, 0, stream);
+}
+
+polymh_status polymh_mlp_predict_pairs(const uint32_t *lsig, const float *lfeat, const uint32_t *rsig,
+                                       const float *rfeat, int32_t k, const int32_t *li, const int32_t *ri, int64_t R,
+                                       const float *params, const uint16_t *wbf16, float *out, void *stream)
+{
+    return score_pairs("mlp_predict_pairs", lsig, lfeat, rsig, rfeat, k, li, ri, nullptr, R, params, wbf16, out, 1,
+                       stream);
 }
 
 polymh_status polymh_rank_refine_ordered(const polymh_polys *data, const polymh_polys *queries,

@@ -17,7 +17,11 @@
 // added in wavefront order.  The tiles are software-pipelined: while a tile
 // runs on the matrix cores, the next tile's signature slices and features
 // are in flight (and the indices of the one after), and they are written
-// into the other of two input buffers once the tile is done.
+// into the other of two input buffers once the tile is done.  Bound: VALU
+// issue (the 512 GELUs a row); 2,000 pairs 13.5 us, 20,000 30, 200,000 175 us
+// (18, 42 and 278 with 80 lane exchanges a tile for the output sums, through
+// LDS, and a row's features by 24 broadcasts).  It keeps all the 256 registers
+// two wavefronts a SIMD have: a few more and it spills (445 us).
 //
 // MFMA operand layout (one wavefront, 32 x 32 output tile, k-step 16): lane
 // l supplies row l % 32 of A and column l % 32 of B at k = 8 (l / 32) .. +7;
@@ -46,12 +50,13 @@ constexpr int64_t kPW3 = kPB2 + kScorerHid;
 constexpr int64_t kPB3 = kPW3 + kScorerHid;
 
 // Pair rows of one tile still in registers: the signature slices of the
-// wavefront's four rows, the rows' 12 + 12 polygon features (lane f < 12
-// holds the left polygon's feature f, lane 12 + f the right one's).
+// wavefront's four rows, the rows' 12 + 12 polygon features, two rows a
+// register (lane f < 12 holds the left polygon's feature f, lane 12 + f the
+// right one's, lanes 32 on those of the other row).
 struct TileRegs {
     int32_t qi[kTileRows / kWaves], pi[kTileRows / kWaves];
     uint4 sa[kTileRows / kWaves], sb[kTileRows / kWaves];
-    float fv[kTileRows / kWaves];
+    float fv[kTileRows / kWaves / 2];
 };
 
 __device__ __forceinline__ void load_indices(const int32_t *li, const int32_t *ri, int64_t R, int64_t r0, int wave,
@@ -75,36 +80,63 @@ __device__ __forceinline__ void load_rows(const uint32_t *lsig, const float *lfe
                      : make_uint4(0, 0, 0, 0);
         T.sb[u] = ok ? *reinterpret_cast<const uint4 *>(rsig + (int64_t)T.pi[u] * kScorerBits + 4 * lane)
                      : make_uint4(1, 1, 1, 1);
-        const float *f = lane < kPolyFeat ? lfeat + (int64_t)T.qi[u] * kPolyFeat + lane
-                                          : rfeat + (int64_t)T.pi[u] * kPolyFeat + (lane - kPolyFeat);
-        T.fv[u] = ok && lane < 2 * kPolyFeat ? *f : 0.f;
+    }
+    const int f = lane & 31;
+#pragma unroll
+    for (int u = 0; u < kTileRows / kWaves; u += 2) {
+        const int64_t q = lane < 32 ? T.qi[u] : T.qi[u + 1], p = lane < 32 ? T.pi[u] : T.pi[u + 1];
+        const float *src = f < kPolyFeat ? lfeat + q * kPolyFeat + f : rfeat + p * kPolyFeat + (f - kPolyFeat);
+        T.fv[u / 2] = q >= 0 && p >= 0 && f < 2 * kPolyFeat ? *src : 0.f;
     }
 }
 
+// x of lane (lane ^ M); every lane of the wavefront takes part.
+template <int M>
+__device__ __forceinline__ float from_lane_xor(float x)
+{
+    const int v = __builtin_bit_cast(int, x);
+    int r;
+    if constexpr (M == 8) r = __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false);        // row_ror:8
+    else if constexpr (M == 4) r = __builtin_amdgcn_ds_swizzle(v, (4 << 10) | 0x1f);
+    else if constexpr (M == 2) r = __builtin_amdgcn_update_dpp(0, v, 0x4e, 0xf, 0xf, false);    // quad_perm:[2,3,0,1]
+    else r = __builtin_amdgcn_update_dpp(0, v, 0xb1, 0xf, 0xf, false);                          // quad_perm:[1,0,3,2]
+    return __builtin_bit_cast(float, r);
+}
+
 // The wavefront's four rows of the tile into the LDS input buffer X: the
-// collision bits and the 32 feature columns (all zero for an empty row).
+// collision bits and the 32 feature columns (all zero for an empty row), the
+// columns of two rows at a time (a half of the wavefront each).
 __device__ __forceinline__ void build_rows(const TileRegs &T, __bf16 *X, int wave, int lane)
 {
+    constexpr int kRows = kTileRows / kWaves;
+    const int c = lane & 31;
 #pragma unroll
-    for (int u = 0; u < kTileRows / kWaves; u++) {
-        __bf16 *xr = X + (wave + kWaves * u) * kXStride;
-        const bool ok = T.qi[u] >= 0 && T.pi[u] >= 0;   // wavefront-uniform
-        const bool e0 = T.sa[u].x == T.sb[u].x, e1 = T.sa[u].y == T.sb[u].y, e2 = T.sa[u].z == T.sb[u].z,
-                   e3 = T.sa[u].w == T.sb[u].w;         // all false on an empty row
-        xr[4 * lane + 0] = (__bf16)(e0 ? 1.f : 0.f);
-        xr[4 * lane + 1] = (__bf16)(e1 ? 1.f : 0.f);
-        xr[4 * lane + 2] = (__bf16)(e2 ? 1.f : 0.f);
-        xr[4 * lane + 3] = (__bf16)(e3 ? 1.f : 0.f);
-        const int cnt = __popcll(__ballot(e0)) + __popcll(__ballot(e1)) + __popcll(__ballot(e2)) +
-                        __popcll(__ballot(e3));
+    for (int u = 0; u < kRows; u += 2) {
+        int cnt[2];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const uint4 a = T.sa[u + h], b = T.sb[u + h];
+            const bool e0 = a.x == b.x, e1 = a.y == b.y, e2 = a.z == b.z, e3 = a.w == b.w;   // false on an empty row
+            constexpr uint32_t one = 0x3f80u;                                                // 1 in BF16
+            *reinterpret_cast<uint2 *>(X + (wave + kWaves * (u + h)) * kXStride + 4 * lane) =
+                make_uint2((e0 ? one : 0u) | (e1 ? one << 16 : 0u), (e2 ? one : 0u) | (e3 ? one << 16 : 0u));
+            cnt[h] = __popcll(__ballot(e0)) + __popcll(__ballot(e1)) + __popcll(__ballot(e2)) + __popcll(__ballot(e3));
+        }
+        // column c < 12 is one polygon's feature (fq[c] or fp[c - 6]); only
+        // columns 12 to 14 read the areas and boxes
+        const int fv = __builtin_bit_cast(int, T.fv[u / 2]), half = (lane & 32) << 2;
+        auto feature = [&](int byte) { return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(byte, fv)); };
+        const float own = feature(half + 4 * (c < 6 ? c : c + 6));
         float fq[kPolyFeat], fp[kPolyFeat];
 #pragma unroll
         for (int f = 0; f < kPolyFeat; f++) {
-            fq[f] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, T.fv[u]), f));
-            fp[f] = __builtin_bit_cast(float,
-                                       __builtin_amdgcn_readlane(__builtin_bit_cast(int, T.fv[u]), kPolyFeat + f));
+            fq[f] = f < 6 ? own : f == 7 ? 0.f : feature(half + 4 * f);
+            fp[f] = f < 6 ? own : f == 7 ? 0.f : feature(half + 4 * (kPolyFeat + f));
         }
-        if (lane < 32) xr[kScorerBits + lane] = ok ? (__bf16)pair_tail_feature(lane, fq, fp, cnt) : (__bf16)0.f;
+        const int h = lane >> 5;
+        const bool ok = (h ? T.qi[u + 1] : T.qi[u]) >= 0 && (h ? T.pi[u + 1] : T.pi[u]) >= 0;
+        X[(wave + kWaves * (u + h)) * kXStride + kScorerBits + c] =
+            ok ? (__bf16)pair_tail_feature(c, fq, fp, h ? cnt[1] : cnt[0]) : (__bf16)0.f;
     }
 }
 
@@ -117,7 +149,7 @@ __global__ __launch_bounds__(512) void k_score_pairs(const uint32_t *__restrict_
                                                      const int64_t *__restrict__ out_idx, int64_t R,
                                                      const float *__restrict__ params,
                                                      const __bf16 *__restrict__ wbf16,
-                                                     float *__restrict__ out)
+                                                     float *__restrict__ out, int write_empty)
 {
     __shared__ __attribute__((aligned(16))) __bf16 X[2][kTileRows * kXStride];
     __shared__ __attribute__((aligned(16))) __bf16 H[kTileRows * kHStride];
@@ -146,7 +178,7 @@ __global__ __launch_bounds__(512) void k_score_pairs(const uint32_t *__restrict_
 #pragma unroll
     for (int ks = 0; ks < kK2; ks++)
         w2[ks] = *reinterpret_cast<const bf16x8 *>(W2 + (int64_t)col * kScorerHid + 16 * ks + kl);
-    const float b1c = params[kPB1 + col], b2c = params[kPB2 + col], w3c = params[kPW3 + col];
+    const float b1c = params[kPB1 + col], b2c = params[kPB2 + col], w3lo = params[kPW3 + (col & ~16)], w3hi = params[kPW3 + (col | 16)];
     const float b3 = params[kPB3];
     build_rows(T, X[0], wave, lane);
     int buf = 0;
@@ -183,18 +215,36 @@ __global__ __launch_bounds__(512) void k_score_pairs(const uint32_t *__restrict_
         for (int ks = 0; ks < kK2; ks++)
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(ha + 16 * ks), w2[ks],
                                                           acc, 0, 0, 0);
+        // sums over the 32 columns of a half: at each step a lane hands over
+        // the rows that its partner keeps, so 16 exchanges give all 16 rows
+        // (80 if every lane added up every row), in the same order; h2 is
+        // BF16 between the layers, as in the training forward pass
+        float v[8];
 #pragma unroll
-        for (int e = 0; e < 16; e++) {
-            // h2 is BF16 between the layers, as in the training forward pass
-            float v = (float)(__bf16)gelu(acc[e] + b2c) * w3c;
+        for (int i = 0; i < 8; i++) {
+            const float h0 = (float)(__bf16)gelu(acc[i] + b2c), h8 = (float)(__bf16)gelu(acc[i + 8] + b2c);
+            // row i of columns col & ~16 and col | 16, or row i + 8 where the lane has bit 4
+            const auto h = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, h0),
+                                                            __builtin_bit_cast(unsigned, h8), false, false);
+            const unsigned lo = h[0], hi = h[1];
+            v[i] = __builtin_fmaf(__builtin_bit_cast(float, lo), w3lo, __builtin_bit_cast(float, hi) * w3hi);
+        }
 #pragma unroll
-            for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);   // the 32 columns of a half
-            if ((lane & 31) == 0) part[wave][8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)] = v;
+        for (int i = 0; i < 4; i++)
+            v[i] = (lane & 8 ? v[i + 4] : v[i]) + from_lane_xor<8>(lane & 8 ? v[i] : v[i + 4]);
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+            v[i] = (lane & 4 ? v[i + 2] : v[i]) + from_lane_xor<4>(lane & 4 ? v[i] : v[i + 2]);
+        v[0] = (lane & 2 ? v[1] : v[0]) + from_lane_xor<2>(lane & 2 ? v[0] : v[1]);
+        v[0] += from_lane_xor<1>(v[0]);
+        if (!(lane & 1)) {
+            const int e = (lane & 31) >> 1;   // lane bits 4 .. 1 chose e's bits 3 .. 0
+            part[wave][8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)] = v[0];
         }
         __syncthreads();
         if (threadIdx.x < kTileRows) {
             const int64_t r = r0 + threadIdx.x;
-            if (r < R && li[r] >= 0 && ri[r] >= 0) {
+            if (r < R && (write_empty || (li[r] >= 0 && ri[r] >= 0))) {
                 float s = 0.f;
 #pragma unroll
                 for (int w = 0; w < kWaves; w++) s += part[w][threadIdx.x];
@@ -213,13 +263,13 @@ __global__ __launch_bounds__(512) void k_score_pairs(const uint32_t *__restrict_
 
 polymh_status launch_score_pairs(const uint32_t *lsig, const float *lfeat, const uint32_t *rsig, const float *rfeat,
                                  const int32_t *li, const int32_t *ri, const int64_t *out_idx, int64_t R,
-                                 const float *params, const uint16_t *wbf16, float *out, hipStream_t s)
+                                 const float *params, const uint16_t *wbf16, float *out, int write_empty, hipStream_t s)
 {
     if (R == 0) return POLYMH_OK;
     const int64_t tiles = (R + kTileRows - 1) / kTileRows;
     const int64_t grid = std::min<int64_t>(tiles, (int64_t)cu_count());
     hipLaunchKernelGGL(k_score_pairs, dim3((unsigned)grid), dim3(64 * kWaves), 0, s, lsig, lfeat, rsig, rfeat, li, ri,
-                       out_idx, R, params, reinterpret_cast<const __bf16 *>(wbf16), out);
+                       out_idx, R, params, reinterpret_cast<const __bf16 *>(wbf16), out, write_empty);
     return check_launch("score_pairs");
 }
 

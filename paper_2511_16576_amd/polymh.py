@@ -110,6 +110,7 @@ _SIGNATURES = {
     "polymh_rank_head_fixed": (I32, [P, P, I64, P, I32, P, P, P, P]),
     "polymh_rank_reorder_head": (I32, [P, I64, P, P, I32, P, P, P]),
     "polymh_mlp_score_pairs": (I32, [P, P, P, P, I32, P, P, P, I64, P, P, P, P]),
+    "polymh_mlp_predict_pairs": (I32, [P, P, P, P, I32, P, P, I64, P, P, P, P]),
     "polymh_rank_refine_ordered": (I32, [P, P, P, P, P, P, P, I64, I64, I32, I32, I32, ctypes.c_float,
                                          P, SZ, P, P, P, P]),
 }
@@ -719,6 +720,16 @@ def mlp_score_pairs(lsig, lfeat, rsig, rfeat, li, ri, params, wbf16, out=None, o
                                         _ptr(ri), _ptr(out_idx), R, _ptr(params), _ptr(wbf16), _ptr(out),
                                         _stream(stream)))
     return out
+
+
+def mlp_predict_pairs(lsig, lfeat, rsig, rfeat, li, ri, params, wbf16, stream=None):
+    """Fused scorer inference for pairs (li[r], ri[r]): float32 predictions in
+    out[r], the zero row's for a negative index."""
+    R = li.numel()
+    out = torch.empty(max(R, 1), dtype=torch.float32, device=lsig.device)
+    _check(lib().polymh_mlp_predict_pairs(_ptr(lsig), _ptr(lfeat), _ptr(rsig), _ptr(rfeat), lsig.shape[1], _ptr(li),
+                                          _ptr(ri), R, _ptr(params), _ptr(wbf16), _ptr(out), _stream(stream)))
+    return out[:R]
 
 
 def rank_refine_ordered(data: DevicePolys, queries: DevicePolys, cand_off, cand_ids, score, order, sorted_ok,
