@@ -321,7 +321,7 @@ struct RingLds {
     int2 *v;            // vertices relative to the origin; v[n..] repeat v[0]
     int4 *box;          // per 8-edge chunk: xmin, ymin, xmax, ymax
     uint32_t *S;        // P only: net crossing sign per edge, two biased 16-bit halves a word
-    double *suf;        // Q only: suffix sums of the edges' cross products (see below)
+    int64_t *suf;       // Q only: suffix sums of the edges' cross products (see below)
 };
 
 // Crossing-sign sums are kept as 16-bit halves biased by 2^15 inside 32-bit
@@ -508,8 +508,7 @@ __device__ void q_extremes(RingLds Q, int m, int4 rb, int lane, int *ext)
 
 // Q's suffix sums Suf(f) = A2Q - sum_{f' <= f} cr_f' (exact in 64-bit
 // integers), by one wavefront.
-template <typename T>
-__device__ int64_t q_suffix_sums(RingLds Q, int m, int64_t a2q, int lane, T *suf, int64_t carry = 0)
+__device__ int64_t q_suffix_sums(RingLds Q, int m, int64_t a2q, int lane, int64_t *suf, int64_t carry = 0)
 {
     for (int base = 0; base < m; base += 64) {
         const int e = base + lane;
@@ -518,7 +517,7 @@ __device__ int64_t q_suffix_sums(RingLds Q, int m, int64_t a2q, int lane, T *suf
         const int2 a = Q.v[ee], b = Q.v[ee + 1];
         const int64_t cr = live ? (int64_t)a.x * b.y - (int64_t)b.x * a.y : 0;
         const int64_t incl = carry + wave_incl_scan64(cr);
-        if (live) suf[e] = (T)(a2q - incl);
+        if (live) suf[e] = a2q - incl;
         carry = (int64_t)dpp::readlane64((uint64_t)incl, 63);
     }
     return carry;
@@ -550,7 +549,7 @@ __device__ void flush_crossings(RingLds P, RingLds Q, const uint32_t *buf, int c
         accP += cre * (p4 ? 1.0 : -1.0) * (-ob) * rcp_refined(oa - ob);
         accQ += crf * (p2 ? 1.0 : -1.0) * (-od) * rcp_refined(oc - od);
         s_add(P.S, e, p4 ? 1 : -1);
-        accM += (p2 ? 1.0 : -1.0) * Q.suf[f];
+        accM += (p2 ? 1.0 : -1.0) * (double)Q.suf[f];
         accK += f < kq ? (p2 ? 1.0 : -1.0) : 0.0;
     }
 }
@@ -979,46 +978,55 @@ __device__ __forceinline__ int64_t fixed_point(double v, int s, double scale)
     return (int64_t)((uint64_t)(int64_t)w << s) + (int64_t)rint((v - w) * scale);
 }
 
+// A crossing's term in fixed point: of edge i of the chunk of P at v (9
+// vertices) and the edge (c, d) of Q.  past: P's cross products before the
+// chunk, taken from those of the whole ring, or from 0 before P's anchor;
+// sq: Q's suffix sum at the edge, less A2Q before Q's anchor.
+__device__ __forceinline__ uint64_t crossing_term(const int2 *v, int i, int64_t past, int2 c, int2 d, int64_t sq, int s,
+                                                  double scale)
+{
+    const int2 a = v[i], b = v[i + 1];
+    int2 u = v[0];
+    int64_t before = 0;    // cross products of the chunk's edges up to e
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+        const int2 w = v[j + 1];
+        const int keep = j <= i ? -1 : 0;
+        before += (int64_t)(u.x & keep) * w.y - (int64_t)(w.x & keep) * u.y;
+        u = w;
+    }
+    const int64_t sp = past - before;
+    const double ax = (double)a.x, ay = (double)a.y, bx = (double)b.x, by = (double)b.y;
+    const double cx = (double)c.x, cy = (double)c.y;
+    const double ex = bx - ax, ey = by - ay;
+    const double fx = (double)(d.x - c.x), fy = (double)(d.y - c.y);
+    const double rx = cx - ax, ry = cy - ay;
+    const double oc = __fma_rn(ex, ry, -(ey * rx));
+    const double oa = __fma_rn(fy, rx, -(fx * ry));
+    const double X = __fma_rn(ex, fy, -(ey * fx));
+    const double od = oc + X, ob = oa - X;
+    const bool p2 = od > p_edge_threshold(ex, ey);
+    const bool p4 = __builtin_amdgcn_class(ob, q_edge_class(d.x - c.x, d.y - c.y));
+    const double cre = __fma_rn(ax, by, -(bx * ay));
+    const double crf = __fma_rn(cx, fy, -(fx * cy));
+    const double t = cre * (p4 ? 1.0 : -1.0) * (-ob) * rcp_refined(oa - ob) +
+                     crf * (p2 ? 1.0 : -1.0) * (-od) * rcp_refined(oc - od);
+    const int64_t whole = (p4 ? sp : -sp) + (p2 ? sq : -sq);
+    return ((uint64_t)whole << s) + (uint64_t)fixed_point(t, s, scale);
+}
+
 __device__ void flush_group(const GroupLds &G, RingLds Q, const int64_t *suf, int64_t a2q, int s, double scale,
                             const uint32_t *buf, int count, int lane)
 {
     if (lane < count) {
         const uint32_t ef = buf[lane];
         const int e = (int)(ef >> 16), f = (int)(ef & 0xffffu);
-        const int cc = e >> 3, i = e & 7;
+        const int cc = e >> 3;
         const int g = G.pair_of[cc];
         const int4 con = G.con[g];
-        const int2 c = Q.v[f], d = Q.v[f + 1];
-        const int2 *v = G.v + 9 * cc;
-        const int2 a = v[i], b = v[i + 1];
-        int2 u = v[0];
-        int64_t before = 0;    // cross products of the chunk's edges up to e
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            const int2 w = v[j + 1];
-            const int keep = j <= i ? -1 : 0;
-            before += (int64_t)(u.x & keep) * w.y - (int64_t)(w.x & keep) * u.y;
-            u = w;
-        }
-        const int64_t sp = G.pre[e < con.z ? con.x : con.y] - G.pre[cc] - before;
-        const int64_t sq = suf[f] - (f < con.w ? a2q : 0);
-        const double ax = (double)a.x, ay = (double)a.y, bx = (double)b.x, by = (double)b.y;
-        const double cx = (double)c.x, cy = (double)c.y;
-        const double ex = bx - ax, ey = by - ay;
-        const double fx = (double)(d.x - c.x), fy = (double)(d.y - c.y);
-        const double rx = cx - ax, ry = cy - ay;
-        const double oc = __fma_rn(ex, ry, -(ey * rx));
-        const double oa = __fma_rn(fy, rx, -(fx * ry));
-        const double X = __fma_rn(ex, fy, -(ey * fx));
-        const double od = oc + X, ob = oa - X;
-        const bool p2 = od > p_edge_threshold(ex, ey);
-        const bool p4 = __builtin_amdgcn_class(ob, q_edge_class(d.x - c.x, d.y - c.y));
-        const double cre = __fma_rn(ax, by, -(bx * ay));
-        const double crf = __fma_rn(cx, fy, -(fx * cy));
-        const double t = cre * (p4 ? 1.0 : -1.0) * (-ob) * rcp_refined(oa - ob) +
-                         crf * (p2 ? 1.0 : -1.0) * (-od) * rcp_refined(oc - od);
-        const int64_t whole = (p4 ? sp : -sp) + (p2 ? sq : -sq);
-        atomicAdd(&G.acc[g], (unsigned long long)(((uint64_t)whole << s) + (uint64_t)fixed_point(t, s, scale)));
+        const uint64_t t = crossing_term(G.v + 9 * cc, e & 7, G.pre[e < con.z ? con.x : con.y] - G.pre[cc], Q.v[f],
+                                         Q.v[f + 1], suf[f] - (f < con.w ? a2q : 0), s, scale);
+        atomicAdd(&G.acc[g], (unsigned long long)t);
     }
 }
 
@@ -1701,6 +1709,52 @@ __device__ double finish_split(const int64_t *qoff, const HeavyWs &hw, int32_t s
     return J;
 }
 
+// A pair of up to kWideCap edges a side by one wavefront, with the terms and
+// the fixed point of k_refine's groups and of mid_pairs: whole numbers, so its
+// value is theirs bit for bit, whichever of them takes it.  pre: room for
+// P's cross products before each chunk.
+__device__ double fixed_pair(const int32_t *Pg, int n, const int32_t *Qg, int m, int64_t ox, int64_t oy,
+                             const int32_t *qm, int kp, int kq, int wkp, int wkq, int64_t a2p, int64_t a2q, RingLds P,
+                             RingLds Q, int64_t *pre, uint16_t *list, uint32_t *units, uint32_t *xbuf, int lane,
+                             unsigned long long *swept)
+{
+    const int ncp = (n + 7) >> 3;
+    stage_window(Pg, n, 0, n, 8 * ncp + 1, ox, oy, P, lane);
+    stage_window(Qg, m, 0, m, 8 * ((m + 7) >> 3) + 9, ox, oy, Q, lane);
+    wave_lds_sync();
+    chunk_boxes_p<kWideCap / 8>(P, n, lane);
+    chunk_boxes(Q, m, lane, 64);
+    q_suffix_sums(Q, m, a2q, lane, Q.suf);
+    int64_t carry = 0;
+    for (int c0 = 0; c0 < ncp; c0 += 64) {
+        const int c = c0 + lane;
+        int64_t own = 0;
+        for (int j = 0; j < 8; j++) {
+            const int e = c < ncp ? 8 * c + j : 0;
+            const int2 a = P.v[e], b = P.v[e + 1];
+            own += (int64_t)a.x * b.y - (int64_t)b.x * a.y;
+        }
+        own = c < ncp ? own : 0;
+        const int64_t upto = carry + wave_incl_scan64(own);
+        if (c < ncp) pre[c + 1] = upto;
+        carry = (int64_t)dpp::readlane64((uint64_t)upto, 63);
+    }
+    if (lane == 0) pre[0] = 0;
+    wave_lds_sync();
+    const int s = fixed_point_bits(qm);
+    const double scale = (double)(1ll << s);
+    uint64_t acc = 0;
+    tiled_accumulate<uint32_t, 16, 8, false, kCrossCap>(P, ncp, Q, m, lane, nullptr, list, units, xbuf, swept, [&](int count) {
+        for (int k = lane; k < count; k += 64) {
+            const uint32_t ef = xbuf[k];
+            const int e = (int)(ef >> 16), f = (int)(ef & 0xffffu);
+            acc += crossing_term(P.v + (e & ~7), e & 7, pre[e < kp ? 0 : ncp] - pre[e >> 3], Q.v[f], Q.v[f + 1],
+                                 Q.suf[f] - (f < kq ? a2q : 0), s, scale);
+        }
+    });
+    return group_jaccard(wave_sum_i64((int64_t)acc), wkp, wkq, a2p, a2q, s);
+}
+
 // One wavefront per deferred pair (workgroups of one wavefront, so four fit a
 // CU's LDS), any sizes: both rings pass through LDS in windows of up to
 // kWideCap edges, P's windows in the outer loop and Q's in the inner one.
@@ -1719,10 +1773,11 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
 {
     __shared__ int2 sQv[kWideRing];
     __shared__ int4 sQbox[kWideCap / 8];
-    __shared__ double sQsuf[kWideCap];
+    __shared__ int64_t sQsuf[kWideCap];
     __shared__ int2 sPv[kWideRing];
     __shared__ int4 sPbox[kWideCap / 8];
     __shared__ uint32_t sPS[kWideCap / 2];
+    __shared__ int64_t sPre[kWideCap / 8 + 1];
     __shared__ uint16_t sList[kListCap];
     __shared__ uint32_t sUnits[kUnitCap];
     __shared__ uint32_t sCross[kCrossCap];
@@ -1760,6 +1815,7 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
         const int u = w.qw < 0 ? w.pw : w.pw * sh.qs + w.qw;   // a split pair's unit slot
         int64_t a2q, a2p, qpre;
         int kp = 0, kq = 0, wkp = 0, wkq = 0;
+        int32_t qm[4] = {0, 0, 0, 0};
         if (w.pw >= 0) {
             // a split pair's unit: the pair's own quantities from wide_meta
             // (its ring starts' memberships are the finish's)
@@ -1767,7 +1823,7 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
             a2p = mp.a2p; a2q = mp.a2q; kp = mp.kp; kq = mp.kq;
             qpre = hw.units[(int64_t)w.slot * kMultiUnits + u].qpre;
         } else {
-            int32_t qm[4], pm[4];
+            int32_t pm[4];
             int64_t ppre;
             ring_sums_global(Qg, m, ox, oy, 0, lane, qm, a2q, qpre);
             ring_sums_global(Pg, n, ox, oy, 0, lane, pm, a2p, ppre);
@@ -1792,7 +1848,10 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
         }
         double J = 0.0;
         MultiUnit unit{0.0, 0.0, 0, 0, 0};
-        if (a2p != 0 && a2q != 0) {
+        if (a2p != 0 && a2q != 0 && max(n, m) <= kWideCap) {
+            J = fixed_pair(Pg, n, Qg, m, ox, oy, qm, kp, kq, wkp, wkq, a2p, a2q, RingLds{sPv, sPbox, nullptr, nullptr},
+                           RingLds{sQv, sQbox, nullptr, sQsuf}, sPre, sList, sUnits, sCross, lane, &st_swept);
+        } else if (a2p != 0 && a2q != 0) {
             RingLds Qs{sQv, sQbox, nullptr, sQsuf};
             RingLds Ps{sPv, sPbox, sPS, nullptr};
             double accP = 0.0, accQ = 0.0, accM = 0.0, accK = 0.0, T = 0.0, crs = 0.0;
@@ -1823,7 +1882,7 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
                 T += membership_term_window(Ps, plen, kp - p0, lane, pcarry, K, crs);
                 wave_lds_sync();
             }
-            // as tiled_finish, with T summed over P's windows
+            // T summed over P's windows, then the crossings' terms
             const int sp = a2p > 0 ? 1 : -1, sq = a2q > 0 ? 1 : -1;
             const double tot = wave_sum((double)(sp * sq) * (T + accP + accQ + accM - (double)a2q * accK));
             if (w.pw < 0) {
