@@ -23,6 +23,7 @@
 #include <algorithm>
 
 #include "internal.hpp"
+#include "refine_keys.hpp"
 
 namespace polymh {
 
@@ -554,14 +555,6 @@ __device__ void flush_crossings(RingLds P, RingLds Q, const uint32_t *buf, int c
     }
 }
 
-// A vertex as a whole number that falls along an edge that points down, or is
-// horizontal and points right: the edges whose tie-break threshold
-// (p_edge_threshold) is negative.
-__device__ __forceinline__ int64_t down_right_key(int2 v)
-{
-    return (int64_t)(((uint64_t)(uint32_t)v.y << 32) | (uint32_t)(INT32_MAX - v.x));
-}
-
 // Masks of several comparisons are combined as scalars: combined as lane
 // values they cost the vector unit two to twelve instructions more.
 __device__ __forceinline__ bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
@@ -594,7 +587,7 @@ __device__ __forceinline__ uint32_t sweep_units(RingLds P, RingLds Q, int entry)
     // the next edge's start value
     double oa = __fma_rn(fy, rx, -(fx * ry));
     uint64_t p3 = class_mask(oa, mf);
-    int64_t ka = down_right_key(pv[0]);
+    int64_t ka = down_right_key(pv[0].x, pv[0].y);
     uint32_t hits = 0;
 #pragma unroll
     for (int i = 0; i < 8; i++) {
@@ -603,7 +596,7 @@ __device__ __forceinline__ uint32_t sweep_units(RingLds P, RingLds Q, int entry)
         // from a to b (all exact integers below 2^53)
         const int2 b = pv[i + 1];
         const double sx = (double)(c.x - b.x), sy = (double)(c.y - b.y);
-        const int64_t kb = down_right_key(b);
+        const int64_t kb = down_right_key(b.x, b.y);
         const double thr = kb < ka ? -0.5 : 0.5;
         const double oc = __fma_rn(rx, sy, -(ry * sx));
         const double ob = __fma_rn(fy, sx, -(fx * sy));
