@@ -1143,7 +1143,7 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
             pe_next = doff[id + 1];
         }
         const bool valid = live & (n >= 3) & (a2q != 0);
-        const bool small = valid & q_tiled & (n <= kTileCap) & (n * m < mid_min);
+        const bool small = valid & q_tiled & (n <= kTileCap) & (edge_pairs(n, m) < mid_min);
         if (live & !valid) cand_j[c] = 0.0;
         uint64_t big = __ballot(valid & !small), todo = __ballot(small);
         const int nch = small ? (n + 7) >> 3 : 0;
@@ -1265,7 +1265,7 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
             int32_t pm[4];
             poly_mbr(Pg, nl, lane, pm);
             // of those that fit a group only wide ones come here
-            const bool small_pair = q_tiled & (nl <= kTileCap) & (nl * m < mid_min);
+            const bool small_pair = q_tiled & (nl <= kTileCap) & (edge_pairs(nl, m) < mid_min);
             const bool disjoint = pm[2] <= qmbr[0] || qmbr[2] <= pm[0] || pm[3] <= qmbr[1] || qmbr[3] <= pm[1];
             st_disjoint += disjoint;
             if (!disjoint) {
@@ -1277,7 +1277,7 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
                 if (hw.count && !wide && !small_pair && defer_wide(hw, cl, pal, nl, m, (int32_t)q, lane)) {
                     // tiled form on wavefronts of the next launch
                     deferred = true;
-                } else if (hw.count && (int64_t)nl * m >= kHeavyMin &&
+                } else if (hw.count && edge_pairs(nl, m) >= kHeavyMin &&
                            (a2p = poly_area2(Pg, nl, ox, oy, lane)) != 0 &&
                            (slot = __builtin_amdgcn_readfirstlane(lane == 0 ? atomicAdd(hw.count, 1) : 0)) <
                                kHeavyCap) {

@@ -15,4 +15,7 @@ constexpr int64_t down_right_key(int32_t x, int32_t y)
     return (int64_t)(((uint64_t)(uint32_t)y << 32) | (0x7fffffffu - (uint32_t)x));
 }
 
+// Edge pairs of two rings of any size.
+constexpr int64_t edge_pairs(int32_t n, int32_t m) { return (int64_t)n * m; }
+
 }  // namespace polymh

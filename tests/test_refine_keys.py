@@ -27,3 +27,8 @@ def test_vertex_key_orders_down_and_right(tmp_path, x):
                      for a, b in ends)
     got = run(tmp_path, body)
     assert got == [str(int(b < 0 or (b == 0 and a > x))) for a, b in ends]
+
+
+@pytest.mark.parametrize("n,m", [(3, 3), (512, 256), (46340, 46341), (46341, 46341), (2**31 - 1, 2**31 - 1)])
+def test_edge_pairs(tmp_path, n, m):
+    assert run(tmp_path, f'printf("%lld", (long long)edge_pairs({n}, {m}));') == [str(n * m)]
