@@ -926,10 +926,10 @@ __device__ __forceinline__ double jaccard_of(double inter2, int64_t a2p, int64_t
 //   s4 (cr_e (1 - t) + Suf_P(e) - [e < kp] A2P) + s2 (cr_f (1 - t') + Suf_Q(f) - [f < kq] A2Q).
 // Suf_P comes from the chunks' exclusive prefix of cross products and the
 // cross products inside the crossing's chunk.  All but the parameters' terms
-// are whole numbers; those are rounded to a fixed point of the query (sums
-// wrap, the result does not: 2 A(P n Q) is at most twice the query's MBR, and
-// 6 bits are spare), so a pair's sum is taken by 64-bit integer additions in
-// any order and does not depend on the pairs beside it.
+// are whole numbers, and those are rounded to 2^-kFrac.  A pair's sum is taken
+// by 64-bit integer additions in any order, its whole numbers (which wrap: the
+// result, twice an area below 2^52, does not) and its fractions apart, and
+// does not depend on the pairs beside it.
 //
 // Bound by the vector units: 477 instructions a pair at 6.5 million pairs of
 // 78 by 76 edges on average (a third of them the sweep's, 463 edge pairs and
@@ -939,44 +939,37 @@ __device__ __forceinline__ double jaccard_of(double inter2, int64_t a2p, int64_t
 // of a chunk's box against the line of Q's edge (few units fall out).
 constexpr int kGroup = 8;
 constexpr int kGroupCross = 64;    // a crossing a lane
+// Bits of a term's fraction: the up to 2^20 crossings of a pair (kWideCap
+// edges a side) add up below 2^64.
+constexpr int kFrac = 44;
+
+struct PairSum {
+    unsigned long long whole, frac;    // modulo 2^64; in units of 2^-kFrac
+};
 
 struct GroupLds {
     int2 *v;               // 9 vertices a chunk
     int64_t *pre;          // cross products before chunk c of the group
     uint8_t *pair_of;      // pair of chunk c
     int4 *con;             // per pair: first chunk, end chunk, P's anchor (edge of the group), Q's anchor
-    unsigned long long *acc;   // per pair: its sum, in fixed point
+    PairSum *acc;          // per pair
 };
 
-// The fixed point of a query's sums, 2^-s: from its MBR.
-__device__ __forceinline__ int fixed_point_bits(const int32_t *qmbr)
-{
-    const double box2 = 2.0 * ((double)qmbr[2] - qmbr[0] + 1) * ((double)qmbr[3] - qmbr[1] + 1);
-    const int bits = (int)((__double_as_longlong(box2) >> 52) & 0x7ff) - 1022;   // box2 < 2^bits
-    return __builtin_amdgcn_readfirstlane(max(0, min(52, 56 - bits)));
-}
-
 // 2 A = sp sq sum + sp w(kp) A2P + sq w(kq) A2Q, then J.
-__device__ __forceinline__ double group_jaccard(int64_t sum, int wkp, int wkq, int64_t a2p, int64_t a2q, int s)
+__device__ __forceinline__ double group_jaccard(PairSum sum, int wkp, int wkq, int64_t a2p, int64_t a2q)
 {
     const int64_t ends = (wkp ? (a2p < 0 ? -a2p : a2p) : 0) + (wkq ? (a2q < 0 ? -a2q : a2q) : 0);
-    const int64_t fixed = (int64_t)((uint64_t)((a2p ^ a2q) < 0 ? -sum : sum) + ((uint64_t)ends << s));
-    return jaccard_of((double)fixed * (1.0 / (double)(1ll << s)), a2p, a2q);
+    const bool flip = (a2p ^ a2q) < 0;
+    const int64_t whole = (int64_t)((flip ? 0 - sum.whole : sum.whole) + (uint64_t)ends);
+    const double frac = (double)sum.frac * (1.0 / (double)(1ll << kFrac));
+    return jaccard_of((double)whole + (flip ? -frac : frac), a2p, a2q);
 }
 
-// A value below 2^62 as a whole number of 2^-s, modulo 2^64 (s <= 52).
-__device__ __forceinline__ int64_t fixed_point(double v, int s, double scale)
-{
-    const double w = floor(v);
-    return (int64_t)((uint64_t)(int64_t)w << s) + (int64_t)rint((v - w) * scale);
-}
-
-// A crossing's term in fixed point: of edge i of the chunk of P at v (9
-// vertices) and the edge (c, d) of Q.  past: P's cross products before the
+// A crossing's term: of edge i of the chunk of P at v (9 vertices) and the edge
+// (c, d) of Q.  past: P's cross products before the
 // chunk, taken from those of the whole ring, or from 0 before P's anchor;
 // sq: Q's suffix sum at the edge, less A2Q before Q's anchor.
-__device__ __forceinline__ uint64_t crossing_term(const int2 *v, int i, int64_t past, int2 c, int2 d, int64_t sq, int s,
-                                                  double scale)
+__device__ __forceinline__ PairSum crossing_term(const int2 *v, int i, int64_t past, int2 c, int2 d, int64_t sq)
 {
     const int2 a = v[i], b = v[i + 1];
     int2 u = v[0];
@@ -1004,12 +997,14 @@ __device__ __forceinline__ uint64_t crossing_term(const int2 *v, int i, int64_t 
     const double crf = __fma_rn(cx, fy, -(fx * cy));
     const double t = cre * (p4 ? 1.0 : -1.0) * (-ob) * rcp_refined(oa - ob) +
                      crf * (p2 ? 1.0 : -1.0) * (-od) * rcp_refined(oc - od);
-    const int64_t whole = (p4 ? sp : -sp) + (p2 ? sq : -sq);
-    return ((uint64_t)whole << s) + (uint64_t)fixed_point(t, s, scale);
+    // |t| is below 2^54
+    const double down = floor(t);
+    const int64_t whole = (p4 ? sp : -sp) + (p2 ? sq : -sq) + (int64_t)down;
+    return {(unsigned long long)whole, (unsigned long long)rint((t - down) * (double)(1ll << kFrac))};
 }
 
-__device__ void flush_group(const GroupLds &G, RingLds Q, const int64_t *suf, int64_t a2q, int s, double scale,
-                            const uint32_t *buf, int count, int lane)
+__device__ void flush_group(const GroupLds &G, RingLds Q, const int64_t *suf, int64_t a2q, const uint32_t *buf,
+                            int count, int lane)
 {
     if (lane < count) {
         const uint32_t ef = buf[lane];
@@ -1017,9 +1012,10 @@ __device__ void flush_group(const GroupLds &G, RingLds Q, const int64_t *suf, in
         const int cc = e >> 3;
         const int g = G.pair_of[cc];
         const int4 con = G.con[g];
-        const uint64_t t = crossing_term(G.v + 9 * cc, e & 7, G.pre[e < con.z ? con.x : con.y] - G.pre[cc], Q.v[f],
-                                         Q.v[f + 1], suf[f] - (f < con.w ? a2q : 0), s, scale);
-        atomicAdd(&G.acc[g], (unsigned long long)t);
+        const PairSum t = crossing_term(G.v + 9 * cc, e & 7, G.pre[e < con.z ? con.x : con.y] - G.pre[cc], Q.v[f],
+                                        Q.v[f + 1], suf[f] - (f < con.w ? a2q : 0));
+        atomicAdd(&G.acc[g].whole, t.whole);
+        atomicAdd(&G.acc[g].frac, t.frac);
     }
 }
 
@@ -1057,7 +1053,7 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
     __shared__ int4 sPbox[kWavesPerBlock][64];
     __shared__ int64_t sPre[kWavesPerBlock][64 + 1];
     __shared__ int4 sCon[kWavesPerBlock][kGroup];
-    __shared__ unsigned long long sAcc[kWavesPerBlock][kGroup];
+    __shared__ PairSum sAcc[kWavesPerBlock][kGroup];
     __shared__ uint8_t sPairOf[kWavesPerBlock][64];
     __shared__ uint8_t sCid[kWavesPerBlock][64];
     __shared__ uint16_t sList[kWavesPerBlock][kListCap];
@@ -1126,8 +1122,6 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
     const int32_t qmbr[4] = {sQmbr[0], sQmbr[1], sQmbr[2], sQmbr[3]};
     const int qext[4] = {sQext[0], sQext[1], sQext[2], sQext[3]};
     const int64_t a2q = sQa2;
-    const int qs = fixed_point_bits(qmbr);
-    const double qscale = (double)(1ll << qs);
     const GroupLds G{sPv[wave], sPre[wave], sPairOf[wave], sCon[wave], sAcc[wave]};
     const RingLds Ps{sPv[wave], sPbox[wave], nullptr, nullptr};
     int32_t *const box_of = reinterpret_cast<int32_t *>(sCross[wave]), *const anchor_of = box_of + 4 * kGroup;
@@ -1171,7 +1165,7 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
             // the wavefront is done with the group before
             wave_lds_sync();
             if (lane < 4 * kGroup) box_of[lane] = (lane & 3) < 2 ? INT32_MAX : INT32_MIN;
-            if (lane < kGroup) { anchor_of[lane] = -1; G.acc[lane] = 0; }
+            if (lane < kGroup) { anchor_of[lane] = -1; G.acc[lane] = {0, 0}; }
             wave_lds_sync();
             int4 box = make_int4(p[0].x, p[0].y, p[0].x, p[0].y);
             int out = -1;
@@ -1246,10 +1240,10 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
             wave_lds_sync();
             tiled_accumulate<uint16_t, 10, 9, true, kGroupCross>(
                 Ps, __popcll(km), Qs, m, lane, sCid[wave], sList[wave], sUnits[wave], sCross[wave], &st_swept,
-                [&](int count) { flush_group(G, Qs, sQsuf, a2q, qs, qscale, sCross[wave], count, lane); });
+                [&](int count) { flush_group(G, Qs, sQsuf, a2q, sCross[wave], count, lane); });
             wave_lds_sync();
             // lane = pair
-            const double J = act ? group_jaccard((int64_t)G.acc[gi], wkp, wkq, a2p, a2q, qs) : 0.0;
+            const double J = act ? group_jaccard(G.acc[gi], wkp, wkq, a2p, a2q) : 0.0;
             if (mem & !(!apart & wide)) cand_j[c] = J;
         }
         // pairs beyond the tiled form, one at a time
@@ -1317,15 +1311,14 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
         // one sum per workgroup, added to one of kStatSlots slots when the
         // workspace has them (atomics of every wavefront on four words
         // serialise at the cache), nonzero counts only
-        unsigned long long *const sStat = sAcc[wave];
         if (lane == 0) {
-            sStat[0] = st_tiled; sStat[1] = st_swept;
-            sStat[2] = st_general; sStat[3] = st_disjoint;
+            sAcc[wave][0].whole = st_tiled; sAcc[wave][1].whole = st_swept;
+            sAcc[wave][2].whole = st_general; sAcc[wave][3].whole = st_disjoint;
         }
         __syncthreads();
         if (tid < 4) {
             unsigned long long v = 0;
-            for (int w = 0; w < (int)(blockDim.x >> 6); w++) v += sAcc[w][tid];
+            for (int w = 0; w < (int)(blockDim.x >> 6); w++) v += sAcc[w][tid].whole;
             if (v) {
                 if (hw.stat_slots) atomicAdd(hw.stat_slots + (blockIdx.x % kStatSlots) * 4 + tid, v);
                 else atomicAdd(stats + tid, v);
@@ -1703,11 +1696,11 @@ __device__ double finish_split(const int64_t *qoff, const HeavyWs &hw, int32_t s
 }
 
 // A pair of up to kWideCap edges a side by one wavefront, with the terms and
-// the fixed point of k_refine's groups and of mid_pairs: whole numbers, so its
+// sums of k_refine's groups and of mid_pairs: whole numbers, so its
 // value is theirs bit for bit, whichever of them takes it.  pre: room for
 // P's cross products before each chunk.
 __device__ double fixed_pair(const int32_t *Pg, int n, const int32_t *Qg, int m, int64_t ox, int64_t oy,
-                             const int32_t *qm, int kp, int kq, int wkp, int wkq, int64_t a2p, int64_t a2q, RingLds P,
+                             int kp, int kq, int wkp, int wkq, int64_t a2p, int64_t a2q, RingLds P,
                              RingLds Q, int64_t *pre, uint16_t *list, uint32_t *units, uint32_t *xbuf, int lane,
                              unsigned long long *swept)
 {
@@ -1734,18 +1727,20 @@ __device__ double fixed_pair(const int32_t *Pg, int n, const int32_t *Qg, int m,
     }
     if (lane == 0) pre[0] = 0;
     wave_lds_sync();
-    const int s = fixed_point_bits(qm);
-    const double scale = (double)(1ll << s);
-    uint64_t acc = 0;
+    PairSum acc{0, 0};
     tiled_accumulate<uint32_t, 16, 8, false, kCrossCap>(P, ncp, Q, m, lane, nullptr, list, units, xbuf, swept, [&](int count) {
         for (int k = lane; k < count; k += 64) {
             const uint32_t ef = xbuf[k];
             const int e = (int)(ef >> 16), f = (int)(ef & 0xffffu);
-            acc += crossing_term(P.v + (e & ~7), e & 7, pre[e < kp ? 0 : ncp] - pre[e >> 3], Q.v[f], Q.v[f + 1],
-                                 Q.suf[f] - (f < kq ? a2q : 0), s, scale);
+            const PairSum t = crossing_term(P.v + (e & ~7), e & 7, pre[e < kp ? 0 : ncp] - pre[e >> 3], Q.v[f],
+                                            Q.v[f + 1], Q.suf[f] - (f < kq ? a2q : 0));
+            acc.whole += t.whole;
+            acc.frac += t.frac;
         }
     });
-    return group_jaccard(wave_sum_i64((int64_t)acc), wkp, wkq, a2p, a2q, s);
+    acc.whole = (unsigned long long)wave_sum_i64((int64_t)acc.whole);
+    acc.frac = (unsigned long long)wave_sum_i64((int64_t)acc.frac);
+    return group_jaccard(acc, wkp, wkq, a2p, a2q);
 }
 
 // One wavefront per deferred pair (workgroups of one wavefront, so four fit a
@@ -1808,7 +1803,6 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
         const int u = w.qw < 0 ? w.pw : w.pw * sh.qs + w.qw;   // a split pair's unit slot
         int64_t a2q, a2p, qpre;
         int kp = 0, kq = 0, wkp = 0, wkq = 0;
-        int32_t qm[4] = {0, 0, 0, 0};
         if (w.pw >= 0) {
             // a split pair's unit: the pair's own quantities from wide_meta
             // (its ring starts' memberships are the finish's)
@@ -1816,7 +1810,7 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
             a2p = mp.a2p; a2q = mp.a2q; kp = mp.kp; kq = mp.kq;
             qpre = hw.units[(int64_t)w.slot * kMultiUnits + u].qpre;
         } else {
-            int32_t pm[4];
+            int32_t qm[4], pm[4];
             int64_t ppre;
             ring_sums_global(Qg, m, ox, oy, 0, lane, qm, a2q, qpre);
             ring_sums_global(Pg, n, ox, oy, 0, lane, pm, a2p, ppre);
@@ -1842,7 +1836,7 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
         double J = 0.0;
         MultiUnit unit{0.0, 0.0, 0, 0, 0};
         if (a2p != 0 && a2q != 0 && max(n, m) <= kWideCap) {
-            J = fixed_pair(Pg, n, Qg, m, ox, oy, qm, kp, kq, wkp, wkq, a2p, a2q, RingLds{sPv, sPbox, nullptr, nullptr},
+            J = fixed_pair(Pg, n, Qg, m, ox, oy, kp, kq, wkp, wkq, a2p, a2q, RingLds{sPv, sPbox, nullptr, nullptr},
                            RingLds{sQv, sQbox, nullptr, sQsuf}, sPre, sList, sUnits, sCross, lane, &st_swept);
         } else if (a2p != 0 && a2q != 0) {
             RingLds Qs{sQv, sQbox, nullptr, sQsuf};
@@ -1993,7 +1987,7 @@ struct MidLds {
     uint32_t cross[kMidWaves][kGroupCross];
     int64_t sum[4];              // cross products of P's chunks 0-63, 64-127, Q's
     int4 con;
-    unsigned long long acc;
+    PairSum acc;
     int32_t mbr[8];              // P's, Q's
     int32_t anchor[2], odd[2], kept[2];
     int32_t taken;
@@ -2030,7 +2024,7 @@ __device__ void mid_pairs(MidLds &L, const int32_t *__restrict__ dxy, const int3
         int64_t cross[8];
         if (tid < 8) L.mbr[tid] = (tid & 3) < 2 ? INT32_MAX : INT32_MIN;
         if (tid < 2) { L.anchor[tid] = -1; L.odd[tid] = 0; }
-        if (tid == 0) L.acc = 0;
+        if (tid == 0) L.acc = {0, 0};
         __syncthreads();
         int64_t upto = 0, own = 0;
         if (wave <= 4) {
@@ -2067,8 +2061,6 @@ __device__ void mid_pairs(MidLds &L, const int32_t *__restrict__ dxy, const int3
         __syncthreads();
         const int64_t a2p = L.sum[0] + L.sum[1], a2q = L.sum[2] + L.sum[3];
         const int32_t *pm = L.mbr, *qm = L.mbr + 4;
-        const int qs = fixed_point_bits(qm);
-        const double qscale = (double)(1ll << qs);
         bool keep = false;
         uint64_t km = 0;
         if (wave <= 4) {
@@ -2120,12 +2112,12 @@ __device__ void mid_pairs(MidLds &L, const int32_t *__restrict__ dxy, const int3
             const GroupLds G{L.pv, L.pre, L.pair_of, &L.con, &L.acc};
             tiled_accumulate<uint32_t, 16, 9, true, kGroupCross>(
                 P, b1 - b0, Q, m, lane, L.cid + b0, L.list[wave], L.units[wave], L.cross[wave], &st_swept,
-                [&](int got) { flush_group(G, Q, L.suf, a2q, qs, qscale, L.cross[wave], got, lane); });
+                [&](int got) { flush_group(G, Q, L.suf, a2q, L.cross[wave], got, lane); });
         }
         __syncthreads();
         if (tid == 0) {
             double J = 0.0;
-            if (a2p != 0 && a2q != 0) J = group_jaccard((int64_t)L.acc, L.odd[0] & 1, L.odd[1] & 1, a2p, a2q, qs);
+            if (a2p != 0 && a2q != 0) J = group_jaccard(L.acc, L.odd[0] & 1, L.odd[1] & 1, a2p, a2q);
             cand_j[w.c] = J;
             st_pairs++;
         }

@@ -1,6 +1,8 @@
 """A pair's J does not depend on the pairs beside it in the call, bit for bit:
 the paths that share a kind of pair (a wavefront's group, a workgroup, a
 wavefront of the launch for large pairs) are chosen by the call's counts."""
+from fractions import Fraction
+
 import numpy as np
 import pytest
 
@@ -54,3 +56,54 @@ def test_pairs_beyond_a_group_beside_larger_ones(pm, orc, m):
             ids = np.concatenate([np.arange(count) % n, np.full(larger, n)])
             got = _refine(pm, D, Q, ids)
             assert np.array_equal(got[:count], alone[ids[:count]]), (count, larger)
+
+
+def _clipped_area2(ring, convex):
+    """Twice the area of a ring inside a convex counter-clockwise one, exact
+    (Sutherland and Hodgman's clipping; the edges it adds cancel)."""
+    pts = [(Fraction(int(x)), Fraction(int(y))) for x, y in ring]
+    for (ax, ay), (bx, by) in zip(convex, np.roll(convex, -1, axis=0)):
+        ax, ay, bx, by = int(ax), int(ay), int(bx), int(by)
+        side = [(bx - ax) * (y - ay) - (by - ay) * (x - ax) for x, y in pts]
+        out = []
+        for i, p in enumerate(pts):
+            j = (i + 1) % len(pts)
+            q, s, t = pts[j], side[i], side[j]
+            if s >= 0:
+                out.append(p)
+            if (s > 0 > t) or (s < 0 < t):
+                u = s / (s - t)
+                out.append((p[0] + u * (q[0] - p[0]), p[1] + u * (q[1] - p[1])))
+        pts = out
+    return sum(a[0] * b[1] - b[0] * a[1] for a, b in zip(pts, pts[1:] + pts[:1]))
+
+
+@pytest.mark.parametrize("extra", [0, 300])
+@pytest.mark.parametrize("many", [False, True])
+def test_small_polygons_against_a_thin_query(pm, extra, many):
+    """Data polygons of some 100 lattice units against a thin query across a
+    box of 2^25: a crossing's term is rounded by the pair's size, not the
+    query's (all of a crossing's products here are below 2^18, whose terms the
+    refinement knows to 2^-48 relative)."""
+    w = 1 << 25
+    low = [(8 * i, 7 * i + i % 3) for i in range(24)] + [(w * (i + 1) // (extra + 2), w * (i + 1) // (extra + 2))
+                                                         for i in range(extra)] + [(w, w)]
+    up = [(x - 20, y + 24) for x, y in low]
+    q = np.array(low + up[::-1])
+    ring = np.array([(6, 1), (3, 6), (-2, 7), (-6, 2), (-5, -2), (-2, -6), (2, -5), (7, -2)])
+    data = [ring + (8 * i + dx, 7 * i + dy) for i in range(2, 20) for dx, dy in ((1, 0), (4, -3), (-18, 21), (-24, 20))]
+    aq = sum(int(a[0]) * int(b[1]) - int(b[0]) * int(a[1]) for a, b in zip(q, np.roll(q, -1, axis=0)))
+    want = []
+    for p in data:
+        ap = sum(int(a[0]) * int(b[1]) - int(b[0]) * int(a[1]) for a, b in zip(p, np.roll(p, -1, axis=0)))
+        inter = _clipped_area2(q, p)
+        assert 0 < inter < ap
+        want.append(float(inter / (ap + aq - inter)))
+    # `many` beside a larger pair: more than workgroups take
+    big = [np.stack([np.rint(2000 * np.cos(t)), np.rint(2000 * np.sin(t))], 1).astype(np.int64)
+           for t in [np.arange(1100) * (2 * np.pi / 1100)]]
+    ds, qs = dg.from_list(data + big), dg.from_list([q])
+    ids = np.concatenate([np.arange(600) % len(data), [len(data)]]) if many else np.arange(len(data))
+    got = _refine(pm, pm.to_device(ds), pm.to_device(qs), ids)[:600 if many else len(data)]
+    ref = np.array(want)[ids[:got.size]]
+    assert np.all(np.abs(got - ref) <= 1e-9 * ref)
