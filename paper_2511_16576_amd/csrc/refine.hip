@@ -926,10 +926,13 @@ __device__ __forceinline__ double jaccard_of(double inter2, int64_t a2p, int64_t
 //   s4 (cr_e (1 - t) + Suf_P(e) - [e < kp] A2P) + s2 (cr_f (1 - t') + Suf_Q(f) - [f < kq] A2Q).
 // Suf_P comes from the chunks' exclusive prefix of cross products and the
 // cross products inside the crossing's chunk.  All but the parameters' terms
-// are whole numbers, and those are rounded to 2^-kFrac.  A pair's sum is taken
-// by 64-bit integer additions in any order, its whole numbers (which wrap: the
-// result, twice an area below 2^52, does not) and its fractions apart, and
-// does not depend on the pairs beside it.
+// are whole numbers; those are rounded to a fixed point of the pair (sums
+// wrap, the result does not: 2 A(P n Q) is at most twice the box that the MBRs
+// share, and 6 bits are spare), so a pair's sum is taken by 64-bit integer
+// additions in any order and does not depend on the pairs beside it.  (By the
+// query's own box, small polygons against a large query lost the bits that
+// their areas need; whole numbers and fractions in sums of their own, two
+// additions a crossing, took 7.43 ms for 6.5 million pairs instead of 7.27.)
 //
 // Bound by the vector units: 477 instructions a pair at 6.5 million pairs of
 // 78 by 76 edges on average (a third of them the sweep's, 463 edge pairs and
@@ -939,37 +942,49 @@ __device__ __forceinline__ double jaccard_of(double inter2, int64_t a2p, int64_t
 // of a chunk's box against the line of Q's edge (few units fall out).
 constexpr int kGroup = 8;
 constexpr int kGroupCross = 64;    // a crossing a lane
-// Bits of a term's fraction: the up to 2^20 crossings of a pair (kWideCap
-// edges a side) add up below 2^64.
-constexpr int kFrac = 44;
-
-struct PairSum {
-    unsigned long long whole, frac;    // modulo 2^64; in units of 2^-kFrac
-};
 
 struct GroupLds {
     int2 *v;               // 9 vertices a chunk
     int64_t *pre;          // cross products before chunk c of the group
     uint8_t *pair_of;      // pair of chunk c
     int4 *con;             // per pair: first chunk, end chunk, P's anchor (edge of the group), Q's anchor
-    PairSum *acc;          // per pair
+                           // and, from bit 16, the bits of the fixed point
+    unsigned long long *acc;   // per pair: its sum, in fixed point
 };
 
-// 2 A = sp sq sum + sp w(kp) A2P + sq w(kq) A2Q, then J.
-__device__ __forceinline__ double group_jaccard(PairSum sum, int wkp, int wkq, int64_t a2p, int64_t a2q)
+// The fixed point of a pair's sums, 2^-s with 2 <= s <= 52 (MBRs within 2^26).
+__device__ __forceinline__ int fixed_point_bits(int4 pb, int4 qb)
 {
-    const int64_t ends = (wkp ? (a2p < 0 ? -a2p : a2p) : 0) + (wkq ? (a2q < 0 ? -a2q : a2q) : 0);
-    const bool flip = (a2p ^ a2q) < 0;
-    const int64_t whole = (int64_t)((flip ? 0 - sum.whole : sum.whole) + (uint64_t)ends);
-    const double frac = (double)sum.frac * (1.0 / (double)(1ll << kFrac));
-    return jaccard_of((double)whole + (flip ? -frac : frac), a2p, a2q);
+    const double box2 = 2.0 * ((double)min(pb.z, qb.z) - max(pb.x, qb.x) + 1) *
+                        ((double)min(pb.w, qb.w) - max(pb.y, qb.y) + 1);
+    const int bits = (int)((__double_as_longlong(box2) >> 52) & 0x7ff) - 1022;   // box2 < 2^bits
+    return max(1, min(52, 56 - bits));
 }
 
-// A crossing's term: of edge i of the chunk of P at v (9 vertices) and the edge
-// (c, d) of Q.  past: P's cross products before the
+// v << s, 0 < s < 64, in 32-bit shifts.  A 64-bit shift by an amount in the
+// kernel's last register gave wrong values (s differed from the one read).
+__device__ __forceinline__ uint64_t shift_left(uint64_t v, int s)
+{
+    const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32), l = lo << (s & 31);
+    const uint32_t h = s & 32 ? l : __builtin_amdgcn_alignbit(hi, lo, (uint32_t)(32 - s));
+    return ((uint64_t)h << 32) | (s & 32 ? 0u : l);
+}
+
+__device__ __forceinline__ double power_of_two(int s) { return __longlong_as_double((long long)(uint32_t)(1023 + s) << 52); }
+
+// 2 A = sp sq sum + sp w(kp) A2P + sq w(kq) A2Q, then J.
+__device__ __forceinline__ double group_jaccard(uint64_t sum, int wkp, int wkq, int64_t a2p, int64_t a2q, int s)
+{
+    const int64_t ends = (wkp ? (a2p < 0 ? -a2p : a2p) : 0) + (wkq ? (a2q < 0 ? -a2q : a2q) : 0);
+    const int64_t fixed = (int64_t)(((a2p ^ a2q) < 0 ? 0 - sum : sum) + shift_left((uint64_t)ends, s));
+    return jaccard_of((double)fixed * power_of_two(-s), a2p, a2q);
+}
+
+// A crossing's term in fixed point: of edge i of the chunk of P at v (9
+// vertices) and the edge (c, d) of Q.  past: P's cross products before the
 // chunk, taken from those of the whole ring, or from 0 before P's anchor;
 // sq: Q's suffix sum at the edge, less A2Q before Q's anchor.
-__device__ __forceinline__ PairSum crossing_term(const int2 *v, int i, int64_t past, int2 c, int2 d, int64_t sq)
+__device__ __forceinline__ uint64_t crossing_term(const int2 *v, int i, int64_t past, int2 c, int2 d, int64_t sq, int s)
 {
     const int2 a = v[i], b = v[i + 1];
     int2 u = v[0];
@@ -1000,7 +1015,9 @@ __device__ __forceinline__ PairSum crossing_term(const int2 *v, int i, int64_t p
     // |t| is below 2^54
     const double down = floor(t);
     const int64_t whole = (p4 ? sp : -sp) + (p2 ? sq : -sq) + (int64_t)down;
-    return {(unsigned long long)whole, (unsigned long long)rint((t - down) * (double)(1ll << kFrac))};
+    // the fraction rounded: added to 2^52, it is the low bits of the sum
+    const double frac = __fma_rn(t - down, power_of_two(s), 4503599627370496.0);
+    return shift_left((uint64_t)whole, s) + ((uint64_t)__double_as_longlong(frac) - 0x4330000000000000ull);
 }
 
 __device__ void flush_group(const GroupLds &G, RingLds Q, const int64_t *suf, int64_t a2q, const uint32_t *buf,
@@ -1012,10 +1029,9 @@ __device__ void flush_group(const GroupLds &G, RingLds Q, const int64_t *suf, in
         const int cc = e >> 3;
         const int g = G.pair_of[cc];
         const int4 con = G.con[g];
-        const PairSum t = crossing_term(G.v + 9 * cc, e & 7, G.pre[e < con.z ? con.x : con.y] - G.pre[cc], Q.v[f],
-                                        Q.v[f + 1], suf[f] - (f < con.w ? a2q : 0));
-        atomicAdd(&G.acc[g].whole, t.whole);
-        atomicAdd(&G.acc[g].frac, t.frac);
+        const uint64_t t = crossing_term(G.v + 9 * cc, e & 7, G.pre[e < con.z ? con.x : con.y] - G.pre[cc], Q.v[f],
+                                         Q.v[f + 1], suf[f] - (f < (con.w & 0xffff) ? a2q : 0), con.w >> 16);
+        atomicAdd(&G.acc[g], (unsigned long long)t);
     }
 }
 
@@ -1053,7 +1069,7 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
     __shared__ int4 sPbox[kWavesPerBlock][64];
     __shared__ int64_t sPre[kWavesPerBlock][64 + 1];
     __shared__ int4 sCon[kWavesPerBlock][kGroup];
-    __shared__ PairSum sAcc[kWavesPerBlock][kGroup];
+    __shared__ unsigned long long sAcc[kWavesPerBlock][kGroup];
     __shared__ uint8_t sPairOf[kWavesPerBlock][64];
     __shared__ uint8_t sCid[kWavesPerBlock][64];
     __shared__ uint16_t sList[kWavesPerBlock][kListCap];
@@ -1165,7 +1181,7 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
             // the wavefront is done with the group before
             wave_lds_sync();
             if (lane < 4 * kGroup) box_of[lane] = (lane & 3) < 2 ? INT32_MAX : INT32_MIN;
-            if (lane < kGroup) { anchor_of[lane] = -1; G.acc[lane] = {0, 0}; }
+            if (lane < kGroup) { anchor_of[lane] = -1; G.acc[lane] = 0; }
             wave_lds_sync();
             int4 box = make_int4(p[0].x, p[0].y, p[0].x, p[0].y);
             int out = -1;
@@ -1226,7 +1242,8 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
             }
             kp = max(kp, 0);
             kq = max(kq, 0);
-            if (mem) G.con[g] = make_int4(first_chunk, first_chunk + nch, 8 * first_chunk + kp, kq);
+            const int fs = fixed_point_bits(pb, make_int4(qmbr[0], qmbr[1], qmbr[2], qmbr[3]));
+            if (mem) G.con[g] = make_int4(first_chunk, first_chunk + nch, 8 * first_chunk + kp, kq | fs << 16);
             // lane = chunk: those that meet Q's MBR are listed
             const bool keep = (lane < total) & (((am >> src) & 1) != 0) & !((box.z < qmbr[0]) | (qmbr[2] < box.x) |
                               (box.w < qmbr[1]) | (qmbr[3] < box.y));
@@ -1243,7 +1260,7 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
                 [&](int count) { flush_group(G, Qs, sQsuf, a2q, sCross[wave], count, lane); });
             wave_lds_sync();
             // lane = pair
-            const double J = act ? group_jaccard(G.acc[gi], wkp, wkq, a2p, a2q) : 0.0;
+            const double J = act ? group_jaccard(G.acc[gi], wkp, wkq, a2p, a2q, G.con[gi].w >> 16) : 0.0;
             if (mem & !(!apart & wide)) cand_j[c] = J;
         }
         // pairs beyond the tiled form, one at a time
@@ -1312,13 +1329,13 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
         // workspace has them (atomics of every wavefront on four words
         // serialise at the cache), nonzero counts only
         if (lane == 0) {
-            sAcc[wave][0].whole = st_tiled; sAcc[wave][1].whole = st_swept;
-            sAcc[wave][2].whole = st_general; sAcc[wave][3].whole = st_disjoint;
+            sAcc[wave][0] = st_tiled; sAcc[wave][1] = st_swept;
+            sAcc[wave][2] = st_general; sAcc[wave][3] = st_disjoint;
         }
         __syncthreads();
         if (tid < 4) {
             unsigned long long v = 0;
-            for (int w = 0; w < (int)(blockDim.x >> 6); w++) v += sAcc[w][tid].whole;
+            for (int w = 0; w < (int)(blockDim.x >> 6); w++) v += sAcc[w][tid];
             if (v) {
                 if (hw.stat_slots) atomicAdd(hw.stat_slots + (blockIdx.x % kStatSlots) * 4 + tid, v);
                 else atomicAdd(stats + tid, v);
@@ -1700,7 +1717,7 @@ __device__ double finish_split(const int64_t *qoff, const HeavyWs &hw, int32_t s
 // value is theirs bit for bit, whichever of them takes it.  pre: room for
 // P's cross products before each chunk.
 __device__ double fixed_pair(const int32_t *Pg, int n, const int32_t *Qg, int m, int64_t ox, int64_t oy,
-                             int kp, int kq, int wkp, int wkq, int64_t a2p, int64_t a2q, RingLds P,
+                             int fs, int kp, int kq, int wkp, int wkq, int64_t a2p, int64_t a2q, RingLds P,
                              RingLds Q, int64_t *pre, uint16_t *list, uint32_t *units, uint32_t *xbuf, int lane,
                              unsigned long long *swept)
 {
@@ -1727,20 +1744,16 @@ __device__ double fixed_pair(const int32_t *Pg, int n, const int32_t *Qg, int m,
     }
     if (lane == 0) pre[0] = 0;
     wave_lds_sync();
-    PairSum acc{0, 0};
+    uint64_t acc = 0;
     tiled_accumulate<uint32_t, 16, 8, false, kCrossCap>(P, ncp, Q, m, lane, nullptr, list, units, xbuf, swept, [&](int count) {
         for (int k = lane; k < count; k += 64) {
             const uint32_t ef = xbuf[k];
             const int e = (int)(ef >> 16), f = (int)(ef & 0xffffu);
-            const PairSum t = crossing_term(P.v + (e & ~7), e & 7, pre[e < kp ? 0 : ncp] - pre[e >> 3], Q.v[f],
-                                            Q.v[f + 1], Q.suf[f] - (f < kq ? a2q : 0));
-            acc.whole += t.whole;
-            acc.frac += t.frac;
+            acc += crossing_term(P.v + (e & ~7), e & 7, pre[e < kp ? 0 : ncp] - pre[e >> 3], Q.v[f], Q.v[f + 1],
+                                 Q.suf[f] - (f < kq ? a2q : 0), fs);
         }
     });
-    acc.whole = (unsigned long long)wave_sum_i64((int64_t)acc.whole);
-    acc.frac = (unsigned long long)wave_sum_i64((int64_t)acc.frac);
-    return group_jaccard(acc, wkp, wkq, a2p, a2q);
+    return group_jaccard((uint64_t)wave_sum_i64((int64_t)acc), wkp, wkq, a2p, a2q, fs);
 }
 
 // One wavefront per deferred pair (workgroups of one wavefront, so four fit a
@@ -1802,7 +1815,7 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
         const int qend = w.qw < 0 ? m : min(m, qfirst + kWideCap);
         const int u = w.qw < 0 ? w.pw : w.pw * sh.qs + w.qw;   // a split pair's unit slot
         int64_t a2q, a2p, qpre;
-        int kp = 0, kq = 0, wkp = 0, wkq = 0;
+        int kp = 0, kq = 0, wkp = 0, wkq = 0, fs = 0;
         if (w.pw >= 0) {
             // a split pair's unit: the pair's own quantities from wide_meta
             // (its ring starts' memberships are the finish's)
@@ -1814,6 +1827,7 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
             int64_t ppre;
             ring_sums_global(Qg, m, ox, oy, 0, lane, qm, a2q, qpre);
             ring_sums_global(Pg, n, ox, oy, 0, lane, pm, a2p, ppre);
+            fs = fixed_point_bits(make_int4(pm[0], pm[1], pm[2], pm[3]), make_int4(qm[0], qm[1], qm[2], qm[3]));
             if (a2p != 0 && a2q != 0) {
                 // anchors: a vertex outside the other polygon's MBR has
                 // membership 0; without one, a crossing-number pass
@@ -1836,7 +1850,7 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
         double J = 0.0;
         MultiUnit unit{0.0, 0.0, 0, 0, 0};
         if (a2p != 0 && a2q != 0 && max(n, m) <= kWideCap) {
-            J = fixed_pair(Pg, n, Qg, m, ox, oy, kp, kq, wkp, wkq, a2p, a2q, RingLds{sPv, sPbox, nullptr, nullptr},
+            J = fixed_pair(Pg, n, Qg, m, ox, oy, fs, kp, kq, wkp, wkq, a2p, a2q, RingLds{sPv, sPbox, nullptr, nullptr},
                            RingLds{sQv, sQbox, nullptr, sQsuf}, sPre, sList, sUnits, sCross, lane, &st_swept);
         } else if (a2p != 0 && a2q != 0) {
             RingLds Qs{sQv, sQbox, nullptr, sQsuf};
@@ -1987,7 +2001,7 @@ struct MidLds {
     uint32_t cross[kMidWaves][kGroupCross];
     int64_t sum[4];              // cross products of P's chunks 0-63, 64-127, Q's
     int4 con;
-    PairSum acc;
+    unsigned long long acc;
     int32_t mbr[8];              // P's, Q's
     int32_t anchor[2], odd[2], kept[2];
     int32_t taken;
@@ -2024,7 +2038,7 @@ __device__ void mid_pairs(MidLds &L, const int32_t *__restrict__ dxy, const int3
         int64_t cross[8];
         if (tid < 8) L.mbr[tid] = (tid & 3) < 2 ? INT32_MAX : INT32_MIN;
         if (tid < 2) { L.anchor[tid] = -1; L.odd[tid] = 0; }
-        if (tid == 0) L.acc = {0, 0};
+        if (tid == 0) L.acc = 0;
         __syncthreads();
         int64_t upto = 0, own = 0;
         if (wave <= 4) {
@@ -2061,6 +2075,7 @@ __device__ void mid_pairs(MidLds &L, const int32_t *__restrict__ dxy, const int3
         __syncthreads();
         const int64_t a2p = L.sum[0] + L.sum[1], a2q = L.sum[2] + L.sum[3];
         const int32_t *pm = L.mbr, *qm = L.mbr + 4;
+        const int fs = fixed_point_bits(make_int4(pm[0], pm[1], pm[2], pm[3]), make_int4(qm[0], qm[1], qm[2], qm[3]));
         bool keep = false;
         uint64_t km = 0;
         if (wave <= 4) {
@@ -2103,7 +2118,7 @@ __device__ void mid_pairs(MidLds &L, const int32_t *__restrict__ dxy, const int3
             const int cp = __popcll(__ballot(op)), cq = __popcll(__ballot(oq));
             if (lane == 0) { atomicAdd(&L.odd[0], cp); atomicAdd(&L.odd[1], cq); }
         }
-        if (tid == 0) L.con = make_int4(0, ncp, max(kp, 0), max(kq, 0));
+        if (tid == 0) L.con = make_int4(0, ncp, max(kp, 0), max(kq, 0) | fs << 16);
         __syncthreads();
         if (a2p != 0 && a2q != 0) {
             const int kept = L.kept[0] + L.kept[1];
@@ -2117,7 +2132,7 @@ __device__ void mid_pairs(MidLds &L, const int32_t *__restrict__ dxy, const int3
         __syncthreads();
         if (tid == 0) {
             double J = 0.0;
-            if (a2p != 0 && a2q != 0) J = group_jaccard(L.acc, L.odd[0] & 1, L.odd[1] & 1, a2p, a2q);
+            if (a2p != 0 && a2q != 0) J = group_jaccard(L.acc, L.odd[0] & 1, L.odd[1] & 1, a2p, a2q, L.con.w >> 16);
             cand_j[w.c] = J;
             st_pairs++;
         }
