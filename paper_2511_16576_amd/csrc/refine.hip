@@ -862,29 +862,30 @@ struct HeavyWs {
     MultiUnit *units;     // [kMultiCap][kMultiUnits]
 };
 
-// Records a pair for k_refine_wide as one list entry, from the list's front;
-// a pair that split_shape splits also gets a split slot and places for its
-// units, counted from the list's back (wide_meta writes the units there and
-// takes the entry back, or leaves the pair whole where they do not fit).  False
-// when the list is full.
-__device__ bool defer_wide(const HeavyWs &hw, int64_t c, int64_t pa, int n, int m, int32_t q, int lane)
+// Records the lane's pair for the launches after k_refine as one list entry,
+// from the list's front; a pair that split_shape splits also gets a split slot
+// and places for its units, counted from the list's back (wide_meta writes the
+// units there and takes the entry back, or leaves the pair whole where they do
+// not fit).  False when the list is full.  The lanes of a wavefront come here
+// together, so that the counters, which all wavefronts share, take one addition
+// each for them (one a pair set the time of a call with many: 300,000 pairs of
+// 600 edges 6.6 ms, so 3.8).
+__device__ bool defer_wide(const HeavyWs &hw, int64_t c, int64_t pa, int n, int m, int32_t q)
 {
-    const int slot = __builtin_amdgcn_readfirstlane(lane == 0 ? atomicAdd(hw.count + 1, 1) : 0);
+    const int slot = atomicAdd(hw.count + 1, 1);
     if (slot >= kWideListCap) return false;
-    if (lane == 0) {
-        WidePair &w = hw.wide[slot];
-        w.c = c; w.pa = pa; w.n = n; w.q = q; w.pw = -1; w.qw = -1; w.slot = -1;
-        const bool swap = n > kWideCap && n > m;
-        const SplitShape sh = split_shape(swap ? m : n, swap ? n : m);
-        if (max(n, m) <= kWideCap) atomicAdd(hw.count + 5, 1);
-        if (sh.units > 1) {
-            const int ms = atomicAdd(hw.count + 2, 1);
-            if (ms < kMultiCap) {
-                MultiPair &mp = hw.multi[ms];
-                mp.c = c; mp.pa = pa; mp.n = n; mp.q = q; mp.units = sh.units;
-                mp.first = atomicAdd(hw.count + 4, sh.units);
-                mp.kp = slot;
-            }
+    WidePair &w = hw.wide[slot];
+    w.c = c; w.pa = pa; w.n = n; w.q = q; w.pw = -1; w.qw = -1; w.slot = -1;
+    const bool swap = n > kWideCap && n > m;
+    const SplitShape sh = split_shape(swap ? m : n, swap ? n : m);
+    if (max(n, m) <= kWideCap) atomicAdd(hw.count + 5, 1);
+    if (sh.units > 1) {
+        const int ms = atomicAdd(hw.count + 2, 1);
+        if (ms < kMultiCap) {
+            MultiPair &mp = hw.multi[ms];
+            mp.c = c; mp.pa = pa; mp.n = n; mp.q = q; mp.units = sh.units;
+            mp.first = atomicAdd(hw.count + 4, sh.units);
+            mp.kp = slot;
         }
     }
     return true;
@@ -1135,8 +1136,12 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
         }
     }
     __syncthreads();
-    const int32_t qmbr[4] = {sQmbr[0], sQmbr[1], sQmbr[2], sQmbr[3]};
-    const int qext[4] = {sQext[0], sQext[1], sQext[2], sQext[3]};
+    int32_t qmbr[4], qext[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        qmbr[i] = __builtin_amdgcn_readfirstlane(sQmbr[i]);
+        qext[i] = __builtin_amdgcn_readfirstlane(sQext[i]);
+    }
     const int64_t a2q = sQa2;
     const GroupLds G{sPv[wave], sPre[wave], sPairOf[wave], sCon[wave], sAcc[wave]};
     const RingLds Ps{sPv[wave], sPbox[wave], nullptr, nullptr};
@@ -1263,64 +1268,65 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
             const double J = act ? group_jaccard(G.acc[gi], wkp, wkq, a2p, a2q, G.con[gi].w >> 16) : 0.0;
             if (mem & !(!apart & wide)) cand_j[c] = J;
         }
-        // pairs beyond the tiled form, one at a time
-        for (; big; big &= big - 1) {
-            const int sl = __builtin_ctzll(big);
+        // pairs beyond the tiled form: their MBRs, one at a time
+        int4 box = make_int4(0, 0, 0, 0);
+        for (uint64_t mm = big; mm; mm &= mm - 1) {
+            const int sl = __builtin_ctzll(mm);
+            int32_t pm[4];
+            poly_mbr(dxy + 2 * (int64_t)dpp::readlane64((uint64_t)pa, sl), __builtin_amdgcn_readlane(n, sl), lane, pm);
+            box = lane == sl ? make_int4(pm[0], pm[1], pm[2], pm[3]) : box;
+        }
+        const bool apart = (box.z <= qmbr[0]) | (qmbr[2] <= box.x) | (box.w <= qmbr[1]) | (qmbr[3] <= box.y);
+        const bool wide = ((uint32_t)max(box.z, qmbr[2]) - (uint32_t)min(box.x, qmbr[0]) >= 1u << 26) |
+                          ((uint32_t)max(box.w, qmbr[3]) - (uint32_t)min(box.y, qmbr[1]) >= 1u << 26);
+        bool here = lane_in(big) & !apart;     // of those that fit a group only wide ones
+        st_disjoint += (unsigned long long)__popcll(__ballot(lane_in(big) & apart));
+        if (lane_in(big) & apart) cand_j[c] = 0.0;
+        // tiled form on the wavefronts of the next launches
+        if (hw.count && here && !wide && !small) here = !defer_wide(hw, c, pa, n, m, (int32_t)q);
+        for (uint64_t mm = __ballot(here); mm; mm &= mm - 1) {
+            const int sl = __builtin_ctzll(mm);
             const int64_t cl = cb + sl;
             const int64_t pal = (int64_t)dpp::readlane64((uint64_t)pa, sl);
             const int nl = __builtin_amdgcn_readlane(n, sl);
             const int32_t *Pg = dxy + 2 * pal;
+            const int32_t pm[4] = {__builtin_amdgcn_readlane(box.x, sl), __builtin_amdgcn_readlane(box.y, sl),
+                                   __builtin_amdgcn_readlane(box.z, sl), __builtin_amdgcn_readlane(box.w, sl)};
+            const bool wide_pair = __builtin_amdgcn_readlane((int)wide, sl) != 0;
             double J = 0.0;
             bool deferred = false;
             int slot = 0;
-            int32_t pm[4];
-            poly_mbr(Pg, nl, lane, pm);
-            // of those that fit a group only wide ones come here
-            const bool small_pair = q_tiled & (nl <= kTileCap) & (edge_pairs(nl, m) < mid_min);
-            const bool disjoint = pm[2] <= qmbr[0] || qmbr[2] <= pm[0] || pm[3] <= qmbr[1] || qmbr[3] <= pm[1];
-            st_disjoint += disjoint;
-            if (!disjoint) {
-                const int64_t span = max(max((int64_t)pm[2], (int64_t)qmbr[2]) - min((int64_t)pm[0], (int64_t)qmbr[0]),
-                                         max((int64_t)pm[3], (int64_t)qmbr[3]) - min((int64_t)pm[1], (int64_t)qmbr[1]));
-                const bool wide = span >= (1ll << 26);
-                double inter2 = 0.0;
-                int64_t a2p = 0;
-                if (hw.count && !wide && !small_pair && defer_wide(hw, cl, pal, nl, m, (int32_t)q, lane)) {
-                    // tiled form on wavefronts of the next launch
-                    deferred = true;
-                } else if (hw.count && edge_pairs(nl, m) >= kHeavyMin &&
-                           (a2p = poly_area2(Pg, nl, ox, oy, lane)) != 0 &&
-                           (slot = __builtin_amdgcn_readfirstlane(lane == 0 ? atomicAdd(hw.count, 1) : 0)) <
-                               kHeavyCap) {
-                    // split over many wavefronts by the next launches
-                    st_general += 2ull * (unsigned long long)nl * (unsigned long long)m;
-                    if (lane == 0) {
-                        HeavyPair &h = hw.pairs[slot];
-                        h.c = cl; h.pa = pal; h.qa = qa; h.ox = ox; h.oy = oy; h.a2p = a2p; h.a2q = a2q;
-                        h.n = nl; h.m = m; h.wide = wide; h.done = 0;
-                        for (int i = 0; i < 4; i++) { h.qmbr[i] = qmbr[i]; h.pm[i] = pm[i]; }
-                    }
-                    deferred = true;
-                } else {
-                    st_general += 2ull * (unsigned long long)nl * (unsigned long long)m;
-                    PairIn in;
-                    in.P = Pg; in.n = nl; in.Q = Qg; in.m = m; in.ox = ox; in.oy = oy;
-                    in.qmbr[0] = qmbr[0]; in.qmbr[1] = qmbr[1]; in.qmbr[2] = qmbr[2]; in.qmbr[3] = qmbr[3];
-                    in.sq = a2q > 0 ? 1 : -1;
-                    double sa, sb;
-                    if (!wide) edges_in_other_P<false>(in, lane, sa, a2p);
-                    else edges_in_other_P<true>(in, lane, sa, a2p);
-                    a2p = wave_sum_i64(a2p);
-                    in.sp = a2p > 0 ? 1 : -1;
-                    if (a2p != 0) {
-                        int64_t unused;
-                        if (!wide) edges_in_other_Q<false>(in, pm, lane, sb, unused);
-                        else edges_in_other_Q<true>(in, pm, lane, sb, unused);
-                        inter2 = wave_sum(in.sp * sa) + wave_sum(in.sq * sb);
-                    }
+            double inter2 = 0.0;
+            int64_t a2p = 0;
+            st_general += 2ull * (unsigned long long)nl * (unsigned long long)m;
+            if (hw.count && edge_pairs(nl, m) >= kHeavyMin && (a2p = poly_area2(Pg, nl, ox, oy, lane)) != 0 &&
+                (slot = __builtin_amdgcn_readfirstlane(lane == 0 ? atomicAdd(hw.count, 1) : 0)) < kHeavyCap) {
+                // split over many wavefronts by the next launches
+                if (lane == 0) {
+                    HeavyPair &h = hw.pairs[slot];
+                    h.c = cl; h.pa = pal; h.qa = qa; h.ox = ox; h.oy = oy; h.a2p = a2p; h.a2q = a2q;
+                    h.n = nl; h.m = m; h.wide = wide_pair; h.done = 0;
+                    for (int i = 0; i < 4; i++) { h.qmbr[i] = qmbr[i]; h.pm[i] = pm[i]; }
                 }
-                if (a2p != 0) J = jaccard_of(inter2, a2p, a2q);
+                deferred = true;
+            } else {
+                PairIn in;
+                in.P = Pg; in.n = nl; in.Q = Qg; in.m = m; in.ox = ox; in.oy = oy;
+                in.qmbr[0] = qmbr[0]; in.qmbr[1] = qmbr[1]; in.qmbr[2] = qmbr[2]; in.qmbr[3] = qmbr[3];
+                in.sq = a2q > 0 ? 1 : -1;
+                double sa, sb;
+                if (!wide_pair) edges_in_other_P<false>(in, lane, sa, a2p);
+                else edges_in_other_P<true>(in, lane, sa, a2p);
+                a2p = wave_sum_i64(a2p);
+                in.sp = a2p > 0 ? 1 : -1;
+                if (a2p != 0) {
+                    int64_t unused;
+                    if (!wide_pair) edges_in_other_Q<false>(in, pm, lane, sb, unused);
+                    else edges_in_other_Q<true>(in, pm, lane, sb, unused);
+                    inter2 = wave_sum(in.sp * sa) + wave_sum(in.sq * sb);
+                }
             }
+            if (a2p != 0) J = jaccard_of(inter2, a2p, a2q);
             if (lane == 0 && !deferred) cand_j[cl] = J;
         }
     }

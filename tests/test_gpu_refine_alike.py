@@ -107,3 +107,16 @@ def test_small_polygons_against_a_thin_query(pm, extra, many):
     got = _refine(pm, pm.to_device(ds), pm.to_device(qs), ids)[:600 if many else len(data)]
     ref = np.array(want)[ids[:got.size]]
     assert np.all(np.abs(got - ref) <= 1e-9 * ref)
+
+
+def test_more_large_pairs_than_the_list_holds(pm, orc):
+    """2^20 list entries, taken a wavefront's lanes at a time, and pairs past
+    them, which are computed in place."""
+    side = 1 << 20
+    data = _stars([600, 40, 530], side, 0.2, 0.3, 31) + [dg.rectangle(0, 0, 9, 9)]
+    ds, qs = dg.from_list(data), dg.from_list(_stars([520], side, 0.2, 0.3, 32))
+    want = orc.jaccard_candidates(ds, qs, np.array([0, 4]), np.arange(4, dtype=np.int32))
+    assert (want[:3] > 0).all()
+    ids = np.arange((1 << 20) * 4 // 3 + 3000) % 4    # three of four go to the list
+    got = _refine(pm, pm.to_device(ds), pm.to_device(qs), ids)
+    assert np.all(np.abs(got - want[ids]) <= 1e-9 * want[ids] + 1e-12)
