@@ -853,7 +853,8 @@ struct HeavyWs {
     int32_t *count;       // [0] heavy pairs, [1] wide list entries recorded, [2] split pairs, [4] their
                           // units, from the list's back (each may exceed its cap: the excess runs
                           // in place or whole), [3] wide entries taken, [5] entries of up to
-                          // kWideCap edges a side, [6] entries looked at for those
+                          // kWideCap edges a side, [6] entries looked at for those, [7] pairs of a
+                          // group moved there
     HeavyPair *pairs;     // [kHeavyCap]
     double *partial;      // [kHeavyCap][2][kHeavySlices]
     unsigned long long *stat_slots;   // [kStatSlots][4]
@@ -1053,6 +1054,19 @@ __device__ void member_starts(const int2 *P, int n, const int2 *Q, int m, int la
     w0q = __popcll(__ballot(oddq)) & 1;
 }
 
+// In a small call the few largest pairs of a group, of kMidMin edge pairs and
+// more, go to mid_pairs, a workgroup each: one wavefront each set the time of
+// k_refine (20,000 pairs of workload 3 139 us, so 120; 257,000 of workload 2
+// 840 and 735; from half the edge pairs on small calls lose up to 3 us, from a
+// quarter on all lose).  A large call has others to run beside them, and loses:
+// 6.5 million pairs 7.2 ms, with 2^16 edge pairs and more moved 8.3.  So does a
+// call that is made of them, where they are no tail: 30,000 pairs of 500 by 500
+// edges 141 us, with all of them moved 661.  So at most one candidate in
+// kMidShare is moved (such pairs are one in 500 to 1,000 of the workloads'), and
+// none of a wavefront whose candidates are all of them (139 us then).
+constexpr int kMidMin = 1 << 17;
+constexpr int64_t kMidCand = 1 << 18, kMidShare = 256;
+
 __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ dxy,
                                                 const int64_t *__restrict__ doff,
                                                 const int32_t *__restrict__ qxy,
@@ -1061,7 +1075,7 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
                                                 const int32_t *__restrict__ cand_ids,
                                                 double *__restrict__ cand_j,
                                                 unsigned long long *__restrict__ stats,
-                                                int slices, int mid_min, HeavyWs hw)
+                                                int slices, int mid_taken, HeavyWs hw)
 {
     __shared__ int2 sQv[kRingLds];
     __shared__ int4 sQbox[kTileCap / 8];
@@ -1158,7 +1172,15 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
             pe_next = doff[id + 1];
         }
         const bool valid = live & (n >= 3) & (a2q != 0);
-        const bool small = valid & q_tiled & (n <= kTileCap) & (edge_pairs(n, m) < mid_min);
+        bool small = valid & q_tiled & (n <= kTileCap);
+        // a small call's few largest go to the launch after this one
+        if (mid_taken > 0) {
+            const bool largest = small & (edge_pairs(n, m) >= kMidMin);
+            const uint64_t lm = __ballot(largest);
+            if ((__popcll(lm) < 3 || lm != __ballot(valid)) && largest &&
+                __hip_atomic_load(hw.count + 7, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < mid_taken)
+                small = atomicAdd(hw.count + 7, 1) >= mid_taken;
+        }
         if (live & !valid) cand_j[c] = 0.0;
         uint64_t big = __ballot(valid & !small), todo = __ballot(small);
         const int nch = small ? (n + 7) >> 3 : 0;
@@ -1985,14 +2007,6 @@ __device__ void heavy_slices(const int32_t *__restrict__ dxy, const int32_t *__r
 // one wavefront and the launch with the time of its longest pair (20,000
 // pairs of which 595 of 513 to 1,024 edges: 258 us, so 137).
 constexpr int kMidWaves = kMetaThreads / 64;
-// In a small call the same goes for the largest pairs of a group, of kMidMin
-// edge pairs and more: one wavefront each set the time of k_refine (those
-// 20,000 pairs 120 us, 1,000 queries of 121 pairs 232 us, 272 without; from
-// half the edge pairs on small calls lose up to 3 us, from a quarter on all
-// lose).  A large call has others to run beside them, and loses: 6.5 million
-// pairs 7.2 ms, with 2^16 edge pairs and more moved 8.3.
-constexpr int kMidMin = 1 << 17;
-constexpr int64_t kMidCand = 1 << 18;
 
 struct MidLds {
     int2 qv[kWideRing];
@@ -2189,7 +2203,7 @@ HeavyWs carve_heavy(Carve &cv)
 // Clears the pair counts, the work counter and the counter slots (256 threads).
 __global__ void k_zero_count(int32_t *p, unsigned long long *slots)
 {
-    if (threadIdx.x < 7) p[threadIdx.x] = 0;
+    if (threadIdx.x < 8) p[threadIdx.x] = 0;
     if (threadIdx.x < kStatSlots * 4) slots[threadIdx.x] = 0;
 }
 
@@ -2239,10 +2253,10 @@ polymh_status launch_refine(const polymh_polys *data, const polymh_polys *querie
     int64_t sl = std::max<int64_t>(1, std::min<int64_t>(64, std::max(by_batch, by_length)));
     if (nq * sl > 0x7fffffffLL) sl = 1;
     const int slices = (int)sl;
-    const int mid_min = ws && n_cand < kMidCand ? kMidMin : INT32_MAX;
+    const int mid_taken = ws && n_cand < kMidCand ? (int)(n_cand / kMidShare) : 0;
     hipLaunchKernelGGL(k_refine, dim3((unsigned)(nq * slices)), dim3(64 * kWavesPerBlock), 0, s, data->xy,
                        data->offsets, queries->xy, queries->offsets, cand_off, cand_ids, cand_j, stats,
-                       slices, mid_min, hw);
+                       slices, mid_taken, hw);
     polymh_status st = check_launch("refine");
     if (st || !ws) return st;
     hipLaunchKernelGGL(k_deferred, dim3(3 * kMetaBlocks), dim3(kMetaThreads), 0, s, data->xy, queries->xy,

@@ -1,0 +1,61 @@
+"""Calls whose path a rule on sizes chooses, against the same work on the other
+path: the rule may not cost a multiple (least of several runs each, and room
+for noise)."""
+import numpy as np
+import pytest
+
+from paper_2511_16576_amd import datagen as dg
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pm():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2511_16576_amd import polymh
+    polymh.check_device()
+    return polymh
+
+
+def _us(f, reps=7):
+    import torch
+    f()
+    best = float("inf")
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3)
+    return best
+
+
+def _rings(n, verts, side, lo, hi, seed):
+    """n rings of `verts` vertices near circles."""
+    rng = np.random.default_rng(seed)
+    r = rng.uniform(lo, hi, n) * side
+    c = rng.uniform(hi, 1 - hi, (n, 2)) * side
+    t = np.arange(verts) * (2 * np.pi / verts)
+    rad = r[:, None] * rng.uniform(0.9, 1.0, (n, verts))
+    xy = np.stack([c[:, :1] + rad * np.cos(t), c[:, 1:] + rad * np.sin(t)], 2)
+    return [np.rint(p).astype(np.int64) for p in xy]
+
+
+def test_refinement_of_many_pairs_of_500_edges(pm):
+    """30,000 of them: by the rule for small calls, and as part of a call with
+    room for 2^18."""
+    import torch
+    side, nq, per = 1 << 24, 300, 100
+    D = pm.to_device(dg.from_list(_rings(300, 500, side, 0.1, 0.2, 1)))
+    Q = pm.to_device(dg.from_list(_rings(nq, 500, side, 0.1, 0.2, 2)))
+    ids = torch.randint(0, 300, (nq * per,), generator=torch.Generator().manual_seed(3), dtype=torch.int32).cuda()
+    off = torch.arange(nq + 1, dtype=torch.int64).cuda() * per
+    ws = pm.refine_workspace()
+    small = _us(lambda: pm.refine(D, Q, off, ids, ws=ws, n_cand=nq * per))
+    large = _us(lambda: pm.refine(D, Q, off, ids, ws=ws, n_cand=1 << 18))
+    assert small <= 1.6 * large, (small, large)
+    a, b = (pm.refine(D, Q, off, ids, ws=ws, n_cand=n)[:nq * per] for n in (nq * per, 1 << 18))
+    assert torch.equal(a, b)
