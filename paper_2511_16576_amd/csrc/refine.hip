@@ -2245,11 +2245,14 @@ polymh_status launch_refine(const polymh_polys *data, const polymh_polys *querie
     // the query once) when the batch is small or its lists are long: at
     // least 2048 workgroups, at most about 128 candidates per workgroup on
     // average (32 per wavefront, a few groups: at 650 candidates a query
-    // 7.99 ms, with 64 8.20, with 256 8.09), at least 4 (one per wavefront: 35
+    // 7.99 ms, with 64 8.20, with 256 8.09; without a workspace 64, as a pair
+    // beyond the tiled form then runs in its wavefront: 300,000 pairs of
+    // workload 3 7.2 ms, with 128 8.7), at least 4 (one per wavefront: 35
     // queries of 121 candidates 45 us, with 2 a workgroup 51), at most 64
     // workgroups per query
+    const int64_t most = ws ? 128 : 64;
     const int64_t by_batch = std::min((2048 + nq - 1) / nq, (n_cand + nq * 4 - 1) / (nq * 4));
-    const int64_t by_length = (n_cand + nq * 128 - 1) / (nq * 128);
+    const int64_t by_length = (n_cand + nq * most - 1) / (nq * most);
     int64_t sl = std::max<int64_t>(1, std::min<int64_t>(64, std::max(by_batch, by_length)));
     if (nq * sl > 0x7fffffffLL) sl = 1;
     const int slices = (int)sl;
