@@ -339,7 +339,7 @@ polymh_status polymh_refine(const polymh_polys *data, const polymh_polys *querie
  *     one wavefront each (windows of 128 to 1024 edges of the staged
  *     polygon, each against the other's windows together or one at a
  *     time), whose shared quantities (areas, anchors, carries) are found
- *     once per pair, and the partial sums are added in window order (up to
+ *     once per pair, and the partial sums are added as whole numbers (up to
  *     2^20 list entries and 4096 split pairs per call);
  *   - with wider spans (128-bit signs), a pair with n m >= 2^17 edge pairs
  *     is split over 128 wavefronts of the general form (up to 8192 pairs),

@@ -313,7 +313,6 @@ constexpr int kTileCap = 512;
 constexpr int kRingLds = kTileCap + 16;   // ring vertices incl. padding
 constexpr int kWavesPerBlock = 4;
 constexpr int kListCap = 256;             // per-wavefront ring of tile entries (< 16 pending + 128 new)
-constexpr int kCrossCap = 128;            // per-wavefront crossing buffer
 constexpr int kUnitCap = 256;             // per-wavefront ring of sweep units (< 64 pending + 128 new)
 constexpr int kClassPos = (1 << 7) | (1 << 8) | (1 << 9);
 constexpr int kClassPosZ = kClassPos | (1 << 5) | (1 << 6);
@@ -321,22 +320,8 @@ constexpr int kClassPosZ = kClassPos | (1 << 5) | (1 << 6);
 struct RingLds {
     int2 *v;            // vertices relative to the origin; v[n..] repeat v[0]
     int4 *box;          // per 8-edge chunk: xmin, ymin, xmax, ymax
-    uint32_t *S;        // P only: net crossing sign per edge, two biased 16-bit halves a word
     int64_t *suf;       // Q only: suffix sums of the edges' cross products (see below)
 };
-
-// Crossing-sign sums are kept as 16-bit halves biased by 2^15 inside 32-bit
-// words (|S| <= kTileCap, so a half never wraps and never borrows from its
-// neighbour); one LDS atomic adds +-1 to either half.
-constexpr uint32_t kSBias = 0x80008000u;
-__device__ __forceinline__ void s_add(uint32_t *S, int e, int v)
-{
-    atomicAdd(&S[e >> 1], (uint32_t)v << (16 * (e & 1)));
-}
-__device__ __forceinline__ int s_get(const uint32_t *S, int e)
-{
-    return (int)((S[e >> 1] >> (16 * (e & 1))) & 0xffffu) - 0x8000;
-}
 
 // Tie-break class set of a shifted Q edge (c + delta, d + delta), f = d - c,
 // for orientations of points of P: a zero counts as positive when fy > 0, or
@@ -449,43 +434,6 @@ __device__ __forceinline__ bool member_edge(const int2 *v, int e, int2 a, int sh
     return flips_parity(v[e], v[e + 1], a, sh);
 }
 
-// P's membership sum: sum_e cr_e * w_e with w_e = w0 + s * (exclusive prefix
-// of S along the ring), s = Q's orientation; a per-lane partial.  Branch-free,
-// so the scan runs with every lane active.
-//
-// Q's sum needs no pass per pair: exchanging the order of summation,
-//   sum_f cr_f * (w0 + s' * sum_{f' < f} S_f') = w0 * A2Q + s' * sum_{f'} S_f' * Suf(f'),
-// with Suf(f') = sum_{f > f'} cr_f fixed by Q alone (staged once per query),
-// so every crossing on Q's edge f' adds its sign times Suf(f').
-//
-// Here the sum is split as w0 * A2P + s * T, T = sum_e cr_e * pre(e) with
-// pre(e) the exclusive prefix of S; the function returns T (a per-lane
-// partial) and K = pre(anchor) (uniform), so that a known membership at any
-// anchor vertex fixes w0 = w(anchor) - s * K.
-// Over a window of a longer ring: carry holds the crossing signs of the
-// edges before the window (in and out), K is set only when the anchor's
-// index (relative to the window) falls inside it, and crs gathers the
-// window's cross products (per-lane partial).
-__device__ double membership_term_window(RingLds P, int n, int anchor, int lane, int &carry, int &K, double &crs)
-{
-    double acc = 0.0;
-    for (int base = 0; base < n; base += 64) {
-        const int e = base + lane;
-        const bool live = e < n;
-        const int ee = live ? e : 0;
-        const int Se = live ? s_get(P.S, ee) : 0;
-        const int2 a = P.v[ee], b = P.v[ee + 1];
-        const double cr = __fma_rn((double)a.x, (double)b.y, -(double)b.x * (double)a.y);
-        const int incl = wave_incl_scan32(Se);
-        const int excl = carry + incl - Se;
-        acc += live ? cr * (double)excl : 0.0;
-        crs += live ? cr : 0.0;
-        if (anchor >= base && anchor < base + 64) K = __builtin_amdgcn_readlane(excl, anchor - base);
-        carry += __builtin_amdgcn_readlane(incl, 63);
-    }
-    return acc;
-}
-
 // Indices of a leftmost, a rightmost, a lowest and a highest vertex of Q
 // (rb: Q's MBR relative to the origin), by one wavefront.  A pair whose P
 // MBR leaves one of those sides of Q's MBR open anchors Q's memberships at
@@ -508,7 +456,10 @@ __device__ void q_extremes(RingLds Q, int m, int4 rb, int lane, int *ext)
 }
 
 // Q's suffix sums Suf(f) = A2Q - sum_{f' <= f} cr_f' (exact in 64-bit
-// integers), by one wavefront.
+// integers), by one wavefront.  They spare a pass per pair: exchanging the
+// order of summation,
+//   sum_f cr_f * (w0 + s' * sum_{f' < f} S_f') = w0 * A2Q + s' * sum_{f'} S_f' * Suf(f'),
+// every crossing on Q's edge f' adds its sign times Suf(f').
 __device__ int64_t q_suffix_sums(RingLds Q, int m, int64_t a2q, int lane, int64_t *suf, int64_t carry = 0)
 {
     for (int base = 0; base < m; base += 64) {
@@ -522,37 +473,6 @@ __device__ int64_t q_suffix_sums(RingLds Q, int m, int64_t a2q, int lane, int64_
         carry = (int64_t)dpp::readlane64((uint64_t)incl, 63);
     }
     return carry;
-}
-
-// Crossing contributions of buffered (e, f) pairs, 64 at a time with every
-// lane busy: the orientations are recomputed exactly as in the sweep, so the
-// signs and parameters are the ones that detected the crossing.
-__device__ void flush_crossings(RingLds P, RingLds Q, const uint32_t *buf, int count, int lane, int kq,
-                                double &accP, double &accQ, double &accM, double &accK)
-{
-    for (int k = lane; k < count; k += 64) {
-        const uint32_t ef = buf[k];
-        const int e = (int)(ef >> 16), f = (int)(ef & 0xffffu);
-        const int2 a = P.v[e], b = P.v[e + 1], c = Q.v[f], d = Q.v[f + 1];
-        const double ax = (double)a.x, ay = (double)a.y, bx = (double)b.x, by = (double)b.y;
-        const double cx = (double)c.x, cy = (double)c.y;
-        const double ex = bx - ax, ey = by - ay;
-        const double fx = (double)(d.x - c.x), fy = (double)(d.y - c.y);
-        const double rx = cx - ax, ry = cy - ay;
-        const double oc = __fma_rn(ex, ry, -(ey * rx));
-        const double oa = __fma_rn(fy, rx, -(fx * ry));
-        const double X = __fma_rn(ex, fy, -(ey * fx));
-        const double od = oc + X, ob = oa - X;
-        const bool p2 = od > p_edge_threshold(ex, ey);
-        const bool p4 = __builtin_amdgcn_class(ob, q_edge_class(d.x - c.x, d.y - c.y));
-        const double cre = __fma_rn(ax, by, -(bx * ay));
-        const double crf = __fma_rn(cx, fy, -(fx * cy));
-        accP += cre * (p4 ? 1.0 : -1.0) * (-ob) * rcp_refined(oa - ob);
-        accQ += crf * (p2 ? 1.0 : -1.0) * (-od) * rcp_refined(oc - od);
-        s_add(P.S, e, p4 ? 1 : -1);
-        accM += (p2 ? 1.0 : -1.0) * (double)Q.suf[f];
-        accK += f < kq ? (p2 ? 1.0 : -1.0) : 0.0;
-    }
 }
 
 // Masks of several comparisons are combined as scalars: combined as lane
@@ -782,10 +702,10 @@ constexpr int kWideListCap = 1 << 20;
 // staged polygon of kSplitFineP edges or more, else the shortest of 256, 512
 // and kWideCap that keeps the units within kMultiUnits), each walking Q's
 // windows, or, when Q has more than two windows, each (P window, Q window)
-// alone.  wide_meta finds the pair's own quantities once (areas, anchors,
-// Q's window carries), every unit writes its partial sums, all linear in the
-// crossing signs, and finish_split adds them in window order.  Up
-// to kMultiCap such pairs per call (the rest take all their windows on one
+// alone.  wide_meta finds the pair's own quantities once (areas, anchors, the
+// windows' carries) and every unit adds its crossings' terms to the pair's
+// sum, in the fixed point of k_refine's groups: whole numbers, in any order.
+// Up to kMultiCap such pairs per call (the rest take all their windows on one
 // wavefront).
 constexpr int kMultiCap = 4096;
 constexpr int kMultiUnits = 512;
@@ -798,7 +718,7 @@ struct SplitShape {
 };
 
 // The split of a pair whose staged polygon (P's role) has np edges and the
-// other nq; deterministic, so the wide kernel and the finish recompute it.
+// other nq; deterministic, so wide_meta and k_refine_wide recompute it.
 __device__ __forceinline__ int split_plen(int np, int qs)
 {
     return (np >= kSplitFineP && ((np + 127) >> 7) * qs <= kMultiUnits) ? 128
@@ -833,20 +753,18 @@ struct MultiPair {
     int64_t pa;
     int32_t n, q;
     int32_t units;        // counted down as they are done
+    int32_t fs;           // bits of the fixed point
+    unsigned long long sum;   // the units' terms (modulo 2^64)
     int32_t first;        // its first unit's place from the list's back
-    // the pair's own quantities, written by wide_meta for its units and
-    // the finish (P and Q in k_refine_wide's roles)
+    // the pair's own quantities, written by wide_meta for its units (P and
+    // Q in k_refine_wide's roles)
     int64_t a2p, a2q;     // exact doubled areas
     int32_t kp, kq;       // anchors (0 where a membership pass stands in; kp first holds the list entry)
     int32_t wkp, wkq;     // memberships of P's vertex 0 in Q, of Q's vertex 0 in P (0 when anchored)
 };
 
 struct MultiUnit {
-    double part;          // sp sq x (P window's membership term + crossing sums), summed over the wavefront
-    double cr;            // sum of the P window's cross products (first Q window's unit only)
-    int32_t stot;         // sum of the window's crossing signs
-    int32_t kloc;         // exclusive prefix of crossing signs at the anchor, if in this window
-    int64_t qpre;         // in: Q's cross-product sum before the unit's Q window (wide_meta)
+    int64_t ppre, qpre;   // P's and Q's cross-product sums before the unit's windows (wide_meta)
 };
 
 struct HeavyWs {
@@ -1133,7 +1051,7 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
             sQa2 = a2;
         }
     }
-    const RingLds Qs{sQv, sQbox, nullptr, nullptr};
+    const RingLds Qs{sQv, sQbox, nullptr};
     if (q_tiled) {
         // Q padded by one extra chunk: the all-padding chunk ncq fills empty
         // slots of a partial tile group
@@ -1158,7 +1076,7 @@ __global__ __launch_bounds__(256, 4) void k_refine(const int32_t *__restrict__ d
     }
     const int64_t a2q = sQa2;
     const GroupLds G{sPv[wave], sPre[wave], sPairOf[wave], sCon[wave], sAcc[wave]};
-    const RingLds Ps{sPv[wave], sPbox[wave], nullptr, nullptr};
+    const RingLds Ps{sPv[wave], sPbox[wave], nullptr};
     int32_t *const box_of = reinterpret_cast<int32_t *>(sCross[wave]), *const anchor_of = box_of + 4 * kGroup;
     unsigned long long st_tiled = 0, st_swept = 0, st_general = 0, st_disjoint = 0;
     for (int64_t cb = cs; cb < ce; cb += 64) {
@@ -1384,16 +1302,14 @@ __device__ __forceinline__ int2 ring_vertex(const int32_t *V, int m, int i, int6
 // memory rather than one per 64 vertices.
 constexpr int kPassU = 8;
 
-// One pass: the ring's MBR (absolute coordinates), twice its signed area
-// about the origin (as poly_area2) and the sum of the cross products of its
-// edges before edge `end`, the suffix-sum carry into a window that starts
-// there (exact in 64-bit integers).
-__device__ void ring_sums_global(const int32_t *V, int m, int64_t ox, int64_t oy, int end, int lane,
-                                 int32_t *mbr, int64_t &a2, int64_t &pre)
+// One pass: the ring's MBR (absolute coordinates) and twice its signed area
+// about the origin (as poly_area2, exact in 64-bit integers).
+__device__ void ring_sums_global(const int32_t *V, int m, int64_t ox, int64_t oy, int lane,
+                                 int32_t *mbr, int64_t &a2)
 {
     const int2 *W = reinterpret_cast<const int2 *>(V);
     int32_t mnx = INT32_MAX, mny = INT32_MAX, mxx = INT32_MIN, mxy = INT32_MIN;
-    int64_t a = 0, p = 0;
+    int64_t a = 0;
     for (int base = 0; base < m; base += 64 * kPassU) {
         int2 v[kPassU], w[kPassU];
 #pragma unroll
@@ -1410,15 +1326,12 @@ __device__ void ring_sums_global(const int32_t *V, int m, int64_t ox, int64_t oy
                 mny = min(mny, v[k].y); mxy = max(mxy, v[k].y);
                 const int64_t ax = (int64_t)v[k].x - ox, ay = (int64_t)v[k].y - oy;
                 const int64_t bx = (int64_t)w[k].x - ox, by = (int64_t)w[k].y - oy;
-                const int64_t c = (int64_t)((__int128)ax * by - (__int128)bx * ay);
-                a += c;
-                p += i < end ? c : 0;
+                a += (int64_t)((__int128)ax * by - (__int128)bx * ay);
             }
         }
     }
     mbr[0] = wmin(mnx); mbr[1] = wmin(mny); mbr[2] = wmax(mxx); mbr[3] = wmax(mxy);
     a2 = wave_sum_i64(a);
-    pre = wave_sum_i64(p);
 }
 
 // Membership of point a + sh*delta (relative coordinates) in a ring read from
@@ -1502,25 +1415,28 @@ __device__ int first_outside_global(const int32_t *V, int n, const int32_t *b, i
 
 // The quantities of a split pair that all its units share, found once per
 // pair by one workgroup (a unit used to find them itself, in four passes over
-// both whole rings read from memory, and the finish again): both rings' MBRs
-// and exact doubled areas, the anchors (P's first vertex strictly outside
-// Q's MBR, Q's extreme vertex outside P's MBR), the memberships of the ring
-// starts where there is no anchor, and Q's cross-product sum before each Q
-// window, written into the units' slots as their suffix-sum carry.  All are
-// exact integers, the same as the per-unit passes gave.  Rings of up to
+// both whole rings read from memory): both rings' MBRs and exact doubled
+// areas, the anchors (P's first vertex strictly outside Q's MBR, Q's extreme
+// vertex outside P's MBR), the memberships of the ring starts where there is
+// no anchor, and the rings' cross-product sums before each window, written
+// into the units' slots.  All are exact integers.  Rings of up to
 // kMetaThreads x kMetaU vertices take one round trip to memory a pass.  The
 // workgroup also writes the pair's unit entries at their places in the list.
 constexpr int kMetaThreads = 1024;
 constexpr int kMetaU = 8;
 
-__device__ void wide_meta(const int32_t *__restrict__ dxy, const int32_t *__restrict__ qxy,
+struct MetaLds {
+    unsigned long long qwin[kMultiUnits];   // Q's cross products per window of kWideCap edges
+    unsigned long long pwin[kMultiUnits];   // P's, per window of a unit
+    unsigned long long a[2];                // doubled areas of Q and P
+    int32_t box[8];                         // MBRs of Q and P: min x, min y, max x, max y
+    int32_t idx[5];                         // Q's extreme vertices, P's first vertex outside
+    int32_t odd[2];                         // crossings of the two membership passes
+};
+
+__device__ void wide_meta(MetaLds &L, const int32_t *__restrict__ dxy, const int32_t *__restrict__ qxy,
                           const int64_t *__restrict__ qoff, const HeavyWs &hw, int block, int blocks)
 {
-    __shared__ unsigned long long sWin[kMultiUnits];   // Q's cross products per window of kWideCap edges
-    __shared__ unsigned long long sA[2];               // doubled areas of Q and P
-    __shared__ int32_t sBox[8];                        // MBRs of Q and P: min x, min y, max x, max y
-    __shared__ int32_t sIdx[5];                        // Q's extreme vertices, P's first vertex outside
-    __shared__ int32_t sOdd[2];                        // crossings of the two membership passes
     const int tid = threadIdx.x, lane = tid & 63;
     const int64_t count = min((int64_t)hw.count[2], (int64_t)kMultiCap);
     const int64_t room = kWideListCap - min((int64_t)hw.count[1], (int64_t)kWideListCap);
@@ -1543,12 +1459,12 @@ __device__ void wide_meta(const int32_t *__restrict__ dxy, const int32_t *__rest
         const int2 o = QW[0];
         const SplitShape sh = split_shape(n, m);
         const int len = max(n, m);
-        for (int i = tid; i < kMultiUnits; i += kMetaThreads) sWin[i] = 0;
-        if (tid < 2) { sA[tid] = 0; sOdd[tid] = 0; }
-        if (tid < 8) sBox[tid] = (tid & 3) < 2 ? INT32_MAX : INT32_MIN;
-        if (tid < 5) sIdx[tid] = INT32_MAX;
+        for (int i = tid; i < kMultiUnits; i += kMetaThreads) L.qwin[i] = L.pwin[i] = 0;
+        if (tid < 2) { L.a[tid] = 0; L.odd[tid] = 0; }
+        if (tid < 8) L.box[tid] = (tid & 3) < 2 ? INT32_MAX : INT32_MIN;
+        if (tid < 5) L.idx[tid] = INT32_MAX;
         __syncthreads();
-        // MBRs, areas and Q's window sums (a wavefront's 64 edges lie in one window)
+        // MBRs, areas and the windows' sums (a wavefront's 64 edges lie in one window)
         {
             int32_t b[8] = {INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN, INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN};
             int64_t aq = 0, ap = 0;
@@ -1564,7 +1480,7 @@ __device__ void wide_meta(const int32_t *__restrict__ dxy, const int32_t *__rest
 #pragma unroll
                 for (int k = 0; k < kMetaU; k++) {
                     const int i = base + k * kMetaThreads + tid;
-                    int64_t cq = 0;
+                    int64_t cq = 0, cp = 0;
                     if (i < m) {
                         b[0] = min(b[0], qv[k].x); b[1] = min(b[1], qv[k].y);
                         b[2] = max(b[2], qv[k].x); b[3] = max(b[3], qv[k].y);
@@ -1573,13 +1489,18 @@ __device__ void wide_meta(const int32_t *__restrict__ dxy, const int32_t *__rest
                     if (i < n) {
                         b[4] = min(b[4], pv[k].x); b[5] = min(b[5], pv[k].y);
                         b[6] = max(b[6], pv[k].x); b[7] = max(b[7], pv[k].y);
-                        ap += (int64_t)(pv[k].x - o.x) * (pw[k].y - o.y) - (int64_t)(pw[k].x - o.x) * (pv[k].y - o.y);
+                        cp = (int64_t)(pv[k].x - o.x) * (pw[k].y - o.y) - (int64_t)(pw[k].x - o.x) * (pv[k].y - o.y);
                     }
                     aq += cq;
+                    ap += cp;
                     const int w0 = base + k * kMetaThreads + (tid & ~63);   // the wavefront's first edge
                     if (sh.qs > 1 && w0 < m) {
                         const int64_t ws = wave_sum_i64(cq);
-                        if (lane == 0) atomicAdd(&sWin[w0 / kWideCap], (unsigned long long)ws);
+                        if (lane == 0) atomicAdd(&L.qwin[w0 / kWideCap], (unsigned long long)ws);
+                    }
+                    if (w0 < n) {
+                        const int64_t ws = wave_sum_i64(cp);
+                        if (lane == 0) atomicAdd(&L.pwin[w0 / sh.plen], (unsigned long long)ws);
                     }
                 }
             }
@@ -1590,16 +1511,16 @@ __device__ void wide_meta(const int32_t *__restrict__ dxy, const int32_t *__rest
             if (lane == 0) {
 #pragma unroll
                 for (int j = 0; j < 8; j++) {
-                    if ((j & 3) < 2) atomicMin(&sBox[j], b[j]);
-                    else atomicMax(&sBox[j], b[j]);
+                    if ((j & 3) < 2) atomicMin(&L.box[j], b[j]);
+                    else atomicMax(&L.box[j], b[j]);
                 }
-                atomicAdd(&sA[0], (unsigned long long)aq);
-                atomicAdd(&sA[1], (unsigned long long)ap);
+                atomicAdd(&L.a[0], (unsigned long long)aq);
+                atomicAdd(&L.a[1], (unsigned long long)ap);
             }
         }
         __syncthreads();
-        const int32_t qm[4] = {sBox[0], sBox[1], sBox[2], sBox[3]}, pm[4] = {sBox[4], sBox[5], sBox[6], sBox[7]};
-        const int64_t a2q = (int64_t)sA[0], a2p = (int64_t)sA[1];
+        const int32_t qm[4] = {L.box[0], L.box[1], L.box[2], L.box[3]}, pm[4] = {L.box[4], L.box[5], L.box[6], L.box[7]};
+        const int64_t a2q = (int64_t)L.a[0], a2p = (int64_t)L.a[1];
         int kp = 0, kq = 0, wkp = 0, wkq = 0;
         if (a2p != 0 && a2q != 0) {
             // Q's extreme vertices (the first of each side) and P's first
@@ -1630,12 +1551,12 @@ __device__ void wide_meta(const int32_t *__restrict__ dxy, const int32_t *__rest
             for (int j = 0; j < 5; j++) e[j] = wmin(e[j]);
             if (lane == 0) {
 #pragma unroll
-                for (int j = 0; j < 5; j++) atomicMin(&sIdx[j], e[j]);
+                for (int j = 0; j < 5; j++) atomicMin(&L.idx[j], e[j]);
             }
             __syncthreads();
-            const int ext[4] = {sIdx[0], sIdx[1], sIdx[2], sIdx[3]};
+            const int ext[4] = {L.idx[0], L.idx[1], L.idx[2], L.idx[3]};
             kq = anchor_q(qm, pm, ext);
-            kp = sIdx[4] == INT32_MAX ? -1 : sIdx[4];
+            kp = L.idx[4] == INT32_MAX ? -1 : L.idx[4];
             if (kp < 0 || kq < 0) {
                 // without an anchor: P's vertex 0 (against Q + delta) and Q's
                 // vertex 0, the origin (plus delta, against P), by the
@@ -1661,25 +1582,28 @@ __device__ void wide_meta(const int32_t *__restrict__ dxy, const int32_t *__rest
                     }
                 }
                 const int cp = __popcll(__ballot(op)), cq = __popcll(__ballot(oq));
-                if (lane == 0) { atomicAdd(&sOdd[0], cp); atomicAdd(&sOdd[1], cq); }
+                if (lane == 0) { atomicAdd(&L.odd[0], cp); atomicAdd(&L.odd[1], cq); }
                 __syncthreads();
-                if (kp < 0) { wkp = sOdd[0] & 1; kp = 0; }
-                if (kq < 0) { wkq = sOdd[1] & 1; kq = 0; }
+                if (kp < 0) { wkp = L.odd[0] & 1; kp = 0; }
+                if (kq < 0) { wkq = L.odd[1] & 1; kq = 0; }
             }
         }
         if (tid == 0) {
             MultiPair &out = hw.multi[s];
             out.a2p = a2p; out.a2q = a2q; out.kp = kp; out.kq = kq; out.wkp = wkp; out.wkq = wkq;
+            out.fs = fixed_point_bits(make_int4(pm[0], pm[1], pm[2], pm[3]), make_int4(qm[0], qm[1], qm[2], qm[3]));
+            out.sum = 0;
             hw.wide[mp.kp].c = -1;
         }
         for (int u = tid; u < mp.units; u += kMetaThreads) {
-            const int qw = sh.qs > 1 ? u % sh.qs : 0;
-            int64_t pre = 0;
-            for (int j = 0; j < qw; j++) pre += (int64_t)sWin[j];
-            hw.units[s * kMultiUnits + u].qpre = pre;
+            const int pw = u / sh.qs, qw = u % sh.qs;
+            MultiUnit pre{0, 0};
+            for (int j = 0; j < pw; j++) pre.ppre += (int64_t)L.pwin[j];
+            for (int j = 0; j < qw; j++) pre.qpre += (int64_t)L.qwin[j];
+            hw.units[s * kMultiUnits + u] = pre;
             WidePair e;
             e.c = mp.c; e.pa = mp.pa; e.n = mp.n; e.q = mp.q;
-            e.pw = (int16_t)(u / sh.qs);
+            e.pw = (int16_t)pw;
             e.qw = (int16_t)(sh.qs == 1 ? -1 : qw);
             e.slot = (int32_t)s;
             hw.wide[kWideListCap - 1 - (mp.first + u)] = e;
@@ -1689,77 +1613,14 @@ __device__ void wide_meta(const int32_t *__restrict__ dxy, const int32_t *__rest
     }
 }
 
-// A split pair's value, by the wavefront that finished its last unit: the P
-// windows' sums (each the sum of its Q windows' units, one window a lane) with
-// the crossing signs of the earlier windows carried into each, added in a
-// fixed order (deterministic), then J.
-__device__ double finish_split(const int64_t *qoff, const HeavyWs &hw, int32_t s, int lane)
+// Cross products of P's window before each of its ncp chunks (lane = chunk),
+// from those before the window; returns those up to its end.  One wavefront.
+__device__ int64_t chunk_sums(RingLds P, int ncp, int64_t carry, int lane, int64_t *pre)
 {
-    const MultiPair mp = hw.multi[s];
-    // the roles of k_refine_wide; the pair's own quantities from wide_meta
-    const int mq = (int)(qoff[mp.q + 1] - qoff[mp.q]);
-    const bool swap = mp.n > kWideCap && mp.n > mq;
-    const int n = swap ? mq : mp.n, m = swap ? mp.n : mq;
-    const int64_t a2q = mp.a2q, a2p = mp.a2p;
-    double J = 0.0;
-    if (a2p != 0 && a2q != 0) {
-        const int kp = mp.kp, wkp = mp.wkp, wkq = mp.wkq;
-        const int sp = a2p > 0 ? 1 : -1, sq = a2q > 0 ? 1 : -1;
-        const SplitShape sh = split_shape(n, m);
-        const int pk = kp / sh.plen;
-        // lanes take the P windows, 64 at a time; the carry of crossing
-        // signs into each is a scan in window order
-        const int qs = sh.qs, npw = sh.units / qs;
-        const MultiUnit *U = hw.units + (int64_t)s * kMultiUnits;
-        double acc = 0.0;
-        int carry = 0, K = 0;
-        for (int base = 0; base < npw; base += 64) {
-            const int wdw = base + lane;
-            const bool live = wdw < npw;
-            double part = 0.0, cr = 0.0;
-            int stot = 0, kloc = 0;
-            if (live) {
-                cr = U[wdw * qs].cr;
-                for (int v = 0; v < qs; v++) {
-                    const MultiUnit x = U[wdw * qs + v];
-                    part += x.part;
-                    stot += x.stot;
-                    kloc += x.kloc;
-                }
-            }
-            const int incl = wave_incl_scan32(stot);
-            const int excl = carry + incl - stot;
-            acc += live ? part + (double)(sp * sq) * cr * (double)excl : 0.0;
-            if (pk >= base && pk < base + 64) K = __builtin_amdgcn_readlane(excl + kloc, pk - base);
-            carry += __builtin_amdgcn_readlane(incl, 63);
-        }
-        const double total = wave_sum(acc);
-        const double inter2 = total + (double)(sp * (wkp - sq * K)) * (double)a2p + (double)(sq * wkq) * (double)a2q;
-        J = jaccard_of(inter2, a2p, a2q);
-    }
-    return J;
-}
-
-// A pair of up to kWideCap edges a side by one wavefront, with the terms and
-// sums of k_refine's groups and of mid_pairs: whole numbers, so its
-// value is theirs bit for bit, whichever of them takes it.  pre: room for
-// P's cross products before each chunk.
-__device__ double fixed_pair(const int32_t *Pg, int n, const int32_t *Qg, int m, int64_t ox, int64_t oy,
-                             int fs, int kp, int kq, int wkp, int wkq, int64_t a2p, int64_t a2q, RingLds P,
-                             RingLds Q, int64_t *pre, uint16_t *list, uint32_t *units, uint32_t *xbuf, int lane,
-                             unsigned long long *swept)
-{
-    const int ncp = (n + 7) >> 3;
-    stage_window(Pg, n, 0, n, 8 * ncp + 1, ox, oy, P, lane);
-    stage_window(Qg, m, 0, m, 8 * ((m + 7) >> 3) + 9, ox, oy, Q, lane);
-    wave_lds_sync();
-    chunk_boxes_p<kWideCap / 8>(P, n, lane);
-    chunk_boxes(Q, m, lane, 64);
-    q_suffix_sums(Q, m, a2q, lane, Q.suf);
-    int64_t carry = 0;
     for (int c0 = 0; c0 < ncp; c0 += 64) {
         const int c = c0 + lane;
         int64_t own = 0;
+#pragma unroll
         for (int j = 0; j < 8; j++) {
             const int e = c < ncp ? 8 * c + j : 0;
             const int2 a = P.v[e], b = P.v[e + 1];
@@ -1767,34 +1628,24 @@ __device__ double fixed_pair(const int32_t *Pg, int n, const int32_t *Qg, int m,
         }
         own = c < ncp ? own : 0;
         const int64_t upto = carry + wave_incl_scan64(own);
-        if (c < ncp) pre[c + 1] = upto;
+        if (c < ncp) pre[c] = upto - own;
         carry = (int64_t)dpp::readlane64((uint64_t)upto, 63);
     }
-    if (lane == 0) pre[0] = 0;
-    wave_lds_sync();
-    uint64_t acc = 0;
-    tiled_accumulate<uint32_t, 16, 8, false, kCrossCap>(P, ncp, Q, m, lane, nullptr, list, units, xbuf, swept, [&](int count) {
-        for (int k = lane; k < count; k += 64) {
-            const uint32_t ef = xbuf[k];
-            const int e = (int)(ef >> 16), f = (int)(ef & 0xffffu);
-            acc += crossing_term(P.v + (e & ~7), e & 7, pre[e < kp ? 0 : ncp] - pre[e >> 3], Q.v[f], Q.v[f + 1],
-                                 Q.suf[f] - (f < kq ? a2q : 0), fs);
-        }
-    });
-    return group_jaccard((uint64_t)wave_sum_i64((int64_t)acc), wkp, wkq, a2p, a2q, fs);
+    return carry;
 }
 
-// One wavefront per deferred pair (workgroups of one wavefront, so four fit a
+// One wavefront per deferred pair (workgroups of one wavefront, so five fit a
 // CU's LDS), any sizes: both rings pass through LDS in windows of up to
 // kWideCap edges, P's windows in the outer loop and Q's in the inner one.
-// Every sum of the tiled form adds over Q's edges, and P's membership term
-// adds over P's edges once the crossing signs of the earlier windows are
-// carried in, so each (P window, Q window) adds its crossings, with Q's
-// suffix sums carried from window to window.  P is the data polygon, or the
-// query when the data polygon has more than kWideCap edges and more than the
-// query (so a polygon of at most kWideCap edges is staged once); exchanging
-// the roles translates the data polygon by delta instead of the query:
-// another consistent perturbation with the same limit area.
+// A crossing's term needs no more of the rings than its own windows and the
+// cross products before them, which are carried from window to window.  The
+// terms and the sums are those of k_refine's groups and of mid_pairs: whole
+// numbers, so that a pair's value is the same bit for bit, whichever of them
+// takes it.  P is the data polygon, or the query when the data polygon has more
+// than kWideCap edges and more than the query (so a polygon of at most kWideCap
+// edges is staged once); exchanging the roles translates the data polygon by
+// delta instead of the query: another consistent perturbation with the same
+// limit area.
 __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ dxy,
                                                     const int32_t *__restrict__ qxy,
                                                     const int64_t *__restrict__ qoff,
@@ -1805,11 +1656,10 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
     __shared__ int64_t sQsuf[kWideCap];
     __shared__ int2 sPv[kWideRing];
     __shared__ int4 sPbox[kWideCap / 8];
-    __shared__ uint32_t sPS[kWideCap / 2];
     __shared__ int64_t sPre[kWideCap / 8 + 1];
     __shared__ uint16_t sList[kListCap];
     __shared__ uint32_t sUnits[kUnitCap];
-    __shared__ uint32_t sCross[kCrossCap];
+    __shared__ uint32_t sCross[kGroupCross];
 
     const int lane = threadIdx.x;
     const int64_t norig = min((int64_t)hw.count[1], (int64_t)kWideListCap);
@@ -1842,19 +1692,19 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
         const int qfirst = w.qw < 0 ? 0 : w.qw * kWideCap;
         const int qend = w.qw < 0 ? m : min(m, qfirst + kWideCap);
         const int u = w.qw < 0 ? w.pw : w.pw * sh.qs + w.qw;   // a split pair's unit slot
-        int64_t a2q, a2p, qpre;
+        int64_t a2q, a2p, ppre = 0, qpre = 0;
         int kp = 0, kq = 0, wkp = 0, wkq = 0, fs = 0;
         if (w.pw >= 0) {
             // a split pair's unit: the pair's own quantities from wide_meta
-            // (its ring starts' memberships are the finish's)
             const MultiPair &mp = hw.multi[w.slot];
-            a2p = mp.a2p; a2q = mp.a2q; kp = mp.kp; kq = mp.kq;
-            qpre = hw.units[(int64_t)w.slot * kMultiUnits + u].qpre;
+            a2p = mp.a2p; a2q = mp.a2q; kp = mp.kp; kq = mp.kq; wkp = mp.wkp; wkq = mp.wkq; fs = mp.fs;
+            const MultiUnit pre = hw.units[(int64_t)w.slot * kMultiUnits + u];
+            ppre = pre.ppre;
+            qpre = pre.qpre;
         } else {
             int32_t qm[4], pm[4];
-            int64_t ppre;
-            ring_sums_global(Qg, m, ox, oy, 0, lane, qm, a2q, qpre);
-            ring_sums_global(Pg, n, ox, oy, 0, lane, pm, a2p, ppre);
+            ring_sums_global(Qg, m, ox, oy, lane, qm, a2q);
+            ring_sums_global(Pg, n, ox, oy, lane, pm, a2p);
             fs = fixed_point_bits(make_int4(pm[0], pm[1], pm[2], pm[3]), make_int4(qm[0], qm[1], qm[2], qm[3]));
             if (a2p != 0 && a2q != 0) {
                 // anchors: a vertex outside the other polygon's MBR has
@@ -1875,23 +1725,17 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
                 }
             }
         }
-        double J = 0.0;
-        MultiUnit unit{0.0, 0.0, 0, 0, 0};
-        if (a2p != 0 && a2q != 0 && max(n, m) <= kWideCap) {
-            J = fixed_pair(Pg, n, Qg, m, ox, oy, fs, kp, kq, wkp, wkq, a2p, a2q, RingLds{sPv, sPbox, nullptr, nullptr},
-                           RingLds{sQv, sQbox, nullptr, sQsuf}, sPre, sList, sUnits, sCross, lane, &st_swept);
-        } else if (a2p != 0 && a2q != 0) {
-            RingLds Qs{sQv, sQbox, nullptr, sQsuf};
-            RingLds Ps{sPv, sPbox, sPS, nullptr};
-            double accP = 0.0, accQ = 0.0, accM = 0.0, accK = 0.0, T = 0.0, crs = 0.0;
-            int pcarry = 0, K = 0;
+        uint64_t acc = 0;
+        if (a2p != 0 && a2q != 0) {
+            const RingLds Qs{sQv, sQbox, sQsuf}, Ps{sPv, sPbox, nullptr};
             const int pstep = w.pw < 0 ? kWideCap : sh.plen;
+            int64_t pcarry = ppre;
             for (int p0 = pfirst; p0 < pend; p0 += pstep) {
                 const int plen = min(pstep, pend - p0);
                 stage_window(Pg, n, p0, plen, 8 * ((plen + 7) >> 3) + 1, ox, oy, Ps, lane);
-                for (int j = lane; j < (plen + 1) >> 1; j += 64) Ps.S[j] = kSBias;
                 wave_lds_sync();
                 chunk_boxes_p<kWideCap / 8>(Ps, plen, lane);
+                pcarry = chunk_sums(Ps, (plen + 7) >> 3, pcarry, lane, sPre);
                 int64_t qcarry = qpre;
                 for (int w0 = qfirst; w0 < qend; w0 += kWideCap) {
                     const int len = min(kWideCap, m - w0);
@@ -1901,50 +1745,40 @@ __global__ __launch_bounds__(64) void k_refine_wide(const int32_t *__restrict__ 
                     chunk_boxes(Qs, len, lane, 64);
                     qcarry = q_suffix_sums(Qs, len, a2q, lane, sQsuf, qcarry);
                     wave_lds_sync();
-                    tiled_accumulate<uint32_t, 16, 8, false, kCrossCap>(
+                    tiled_accumulate<uint32_t, 16, 8, false, kGroupCross>(
                         Ps, (plen + 7) >> 3, Qs, len, lane, nullptr, sList, sUnits, sCross, &st_swept, [&](int count) {
-                            flush_crossings(Ps, Qs, sCross, count, lane, kq - w0, accP, accQ, accM, accK);
+                            if (lane < count) {
+                                const uint32_t ef = sCross[lane];
+                                const int e = (int)(ef >> 16), f = (int)(ef & 0xffffu);
+                                acc += crossing_term(sPv + (e & ~7), e & 7, (p0 + e < kp ? 0 : a2p) - sPre[e >> 3], sQv[f],
+                                                     sQv[f + 1], sQsuf[f] - (w0 + f < kq ? a2q : 0), fs);
+                            }
                         });
                     // every lane is done with the window before the next one
                     wave_lds_sync();
                 }
-                T += membership_term_window(Ps, plen, kp - p0, lane, pcarry, K, crs);
-                wave_lds_sync();
-            }
-            // T summed over P's windows, then the crossings' terms
-            const int sp = a2p > 0 ? 1 : -1, sq = a2q > 0 ? 1 : -1;
-            const double tot = wave_sum((double)(sp * sq) * (T + accP + accQ + accM - (double)a2q * accK));
-            if (w.pw < 0) {
-                const double inter2 = tot + (double)(sp * (wkp - sq * K)) * (double)a2p +
-                                      (double)(sq * wkq) * (double)a2q;
-                J = jaccard_of(inter2, a2p, a2q);
-            } else {
-                unit.part = tot;
-                // the P window's cross products are the same in each of its
-                // Q windows' units: the finish takes them from the first
-                const double cr = wave_sum(crs);
-                unit.cr = w.qw <= 0 ? cr : 0.0;
-                unit.stot = pcarry;
-                unit.kloc = K;
             }
         }
+        acc = (uint64_t)wave_sum_i64((int64_t)acc);
         st_pairs += (w.pw <= 0) & (w.qw <= 0);
-        if (w.pw < 0) {
-            if (lane == 0) cand_j[w.c] = J;
-        } else {
-            // the wavefront whose unit is the pair's last adds them up (all
-            // have been made visible by then)
-            int left = 0;
-            if (lane == 0) {
-                hw.units[(int64_t)w.slot * kMultiUnits + u] = unit;
-                __threadfence();
-                left = atomicSub(&hw.multi[w.slot].units, 1);
+        if (lane == 0) {
+            bool whole = true;
+            if (w.pw >= 0) {
+                // A unit adds its terms, then counts itself; whoever counts the
+                // last one finds the sum complete.  Both are additions at the
+                // device's own scope, and the count waits for the sum's
+                // returned value, so no caches are written back in between (a
+                // fence a unit cost 5 us: 15,000 pairs of 3,000 edges 9.9 ms).
+                unsigned long long before = __hip_atomic_fetch_add(&hw.multi[w.slot].sum, (unsigned long long)acc,
+                                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                int32_t one = 1;
+                asm volatile("; %1 has returned" : "+v"(one) : "v"(before) : "memory");
+                whole = __hip_atomic_fetch_sub(&hw.multi[w.slot].units, one, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT) == 1;
+                if (whole) acc = __hip_atomic_fetch_add(&hw.multi[w.slot].sum, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            if (__builtin_amdgcn_readfirstlane(left) == 1) {
-                __threadfence();
-                const double Js = finish_split(qoff, hw, w.slot, lane);
-                if (lane == 0) cand_j[w.c] = Js;
-            }
+            if (whole)
+                cand_j[w.c] = a2p != 0 && a2q != 0 ? group_jaccard(acc, wkp, wkq, a2p, a2q, fs) : 0.0;
         }
         // every lane is done with both rings before the next pair restages them
         wave_lds_sync();
@@ -2143,7 +1977,7 @@ __device__ void mid_pairs(MidLds &L, const int32_t *__restrict__ dxy, const int3
         if (a2p != 0 && a2q != 0) {
             const int kept = L.kept[0] + L.kept[1];
             const int b0 = kept * wave / kMidWaves, b1 = kept * (wave + 1) / kMidWaves;
-            const RingLds Q{L.qv, L.qbox, nullptr, nullptr}, P{L.pv, L.pbox + b0, nullptr, nullptr};
+            const RingLds Q{L.qv, L.qbox, nullptr}, P{L.pv, L.pbox + b0, nullptr};
             const GroupLds G{L.pv, L.pre, L.pair_of, &L.con, &L.acc};
             tiled_accumulate<uint32_t, 16, 9, true, kGroupCross>(
                 P, b1 - b0, Q, m, lane, L.cid + b0, L.list[wave], L.units[wave], L.cross[wave], &st_swept,
@@ -2173,17 +2007,18 @@ __global__ __launch_bounds__(kMetaThreads) void k_deferred(const int32_t *__rest
                                                          const int64_t *__restrict__ qoff,
                                                          double *__restrict__ cand_j, HeavyWs hw)
 {
-    __shared__ MidLds mid;
+    constexpr size_t kBytes = sizeof(MidLds) > sizeof(MetaLds) ? sizeof(MidLds) : sizeof(MetaLds);
+    __shared__ __align__(16) unsigned char lds[kBytes];
     const int block = (int)blockIdx.x;
     if (block < kMetaBlocks) {
-        wide_meta(dxy, qxy, qoff, hw, block, kMetaBlocks);
+        wide_meta(*reinterpret_cast<MetaLds *>(lds), dxy, qxy, qoff, hw, block, kMetaBlocks);
     } else if (block < 2 * kMetaBlocks) {
         constexpr int kWaves = kMetaThreads / 64;
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
         heavy_slices(dxy, qxy, cand_j, hw, (int64_t)(block - kMetaBlocks) * kWaves + wave,
                      (int64_t)kMetaBlocks * kWaves, threadIdx.x & 63);
     } else {
-        mid_pairs(mid, dxy, qxy, qoff, cand_j, hw, block);
+        mid_pairs(*reinterpret_cast<MidLds *>(lds), dxy, qxy, qoff, cand_j, hw, block);
     }
 }
 
@@ -2265,8 +2100,9 @@ polymh_status launch_refine(const polymh_polys *data, const polymh_polys *querie
     hipLaunchKernelGGL(k_deferred, dim3(3 * kMetaBlocks), dim3(kMetaThreads), 0, s, data->xy, queries->xy,
                        queries->offsets, cand_j, hw);
     if ((st = check_launch("refine: deferred pairs"))) return st;
-    // deferred wide tiled pairs: four one-wavefront workgroups per CU
-    hipLaunchKernelGGL(k_refine_wide, dim3(1024), dim3(64), 0, s, data->xy, queries->xy, queries->offsets, cand_j,
+    // deferred wide tiled pairs: the five one-wavefront workgroups a CU's LDS
+    // holds (15,000 pairs of 3,000 edges 6.6 ms, with four 8.0)
+    hipLaunchKernelGGL(k_refine_wide, dim3((unsigned)(5 * cu_count())), dim3(64), 0, s, data->xy, queries->xy, queries->offsets, cand_j,
                        hw, stats ? 1 : 0);
     if ((st = check_launch("refine: wide pairs"))) return st;
     if (!stats) return POLYMH_OK;

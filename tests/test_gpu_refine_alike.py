@@ -120,3 +120,22 @@ def test_more_large_pairs_than_the_list_holds(pm, orc):
     ids = np.arange((1 << 20) * 4 // 3 + 3000) % 4    # three of four go to the list
     got = _refine(pm, pm.to_device(ds), pm.to_device(qs), ids)
     assert np.all(np.abs(got - want[ids]) <= 1e-9 * want[ids] + 1e-12)
+
+
+@pytest.mark.parametrize("count", [1, 40, 2500])
+def test_units_of_split_pairs(pm, orc, count):
+    """Pairs split into units (from a few a call to more than 64 a wavefront):
+    each against the oracle, and the same bits however many there are; pairs
+    too wide for the split ones' arithmetic beside them."""
+    side = 1 << 24
+    data = _stars([3000, 1500, 5000], side, 0.2, 0.3, 41)
+    wide = np.rint(data[0].astype(float) * 5).astype(np.int64)      # beyond 2^26 across: split by slices
+    ds, qs = dg.from_list(data + [wide]), dg.from_list(_stars([2500], side, 0.2, 0.3, 42))
+    want = orc.jaccard_candidates(ds, qs, np.array([0, 4]), np.arange(4, dtype=np.int32))
+    assert (want[:3] > 0).all()
+    D, Q = pm.to_device(ds), pm.to_device(qs)
+    ids = np.concatenate([np.arange(count) % 3, np.full(min(count, 40), 3)])
+    got = _refine(pm, D, Q, ids)
+    assert np.all(np.abs(got - want[ids]) <= 1e-9 * want[ids] + 1e-12)
+    one = np.array([_refine(pm, D, Q, [i])[0] for i in range(4)])
+    assert np.array_equal(got, one[ids])
