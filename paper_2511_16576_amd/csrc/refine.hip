@@ -1817,12 +1817,11 @@ __device__ void heavy_slices(const int32_t *__restrict__ dxy, const int32_t *__r
             else edges_in_other_Q<false>(in, pm, lane, s, unused, slice, kHeavySlices);
         }
         s = wave_sum(s);
-        int done = 0;
-        if (lane == 0) {
-            hw.partial[(h * 2 + side) * kHeavySlices + slice] = s;
-            __threadfence();
-            done = atomicAdd(&hw.pairs[h].done, 1);
-        }
+        if (lane == 0) hw.partial[(h * 2 + side) * kHeavySlices + slice] = s;
+        __threadfence();
+        // every lane takes part (all but lane 0 with nothing), so that the
+        // result is not read across a divergent branch
+        const int done = atomicAdd(&hw.pairs[h].done, lane == 0 ? 1 : 0);
         if (__builtin_amdgcn_readfirstlane(done) == 2 * kHeavySlices - 1) {
             __threadfence();
             static_assert(kHeavySlices == 64, "a slice a lane");
