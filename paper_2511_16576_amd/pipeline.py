@@ -214,7 +214,10 @@ class QueryBatch:
         self.graph.launch()
 
     def result(self):
+        # the run's own stream, or, for a graph launched on another, the
+        # caller's: the flag is copied out at the run's end
         self.stream.synchronize()
+        torch.cuda.current_stream(self.overflow.device).synchronize()
         if int(self._overflow_host[0]):
             raise RuntimeError("candidate capacity exceeded; rebuild the batch with a larger cand_cap")
         return self.top_ids, self.top_j
