@@ -10,6 +10,8 @@
 // entries marks its polygons in that row.  Every way gives the same list.
 #include "internal.hpp"
 
+#include <mutex>
+
 namespace polymh {
 
 namespace {
@@ -841,17 +843,36 @@ inline bool use_row(int64_t nq, int64_t words)
     return words <= kRowMost && nq <= cu_count() * ((int64_t)(160 << 10) / (words * 4 + 6144));
 }
 
-// Lengths of every query's list into counts, and what k_emit and
-// k_sparse_emit read of them into the workspace.
-void lookup_counts(const uint64_t *skeys, const int32_t *sids, int64_t n_entries, int64_t words,
+// Lets k_mark_row have rows of any size that use_row gives it.  The setting is
+// the device's for the whole process, so it is the largest, made once: with
+// each call's own size, threads with data sets of different sizes could launch
+// by the other's.
+polymh_status allow_rows()
+{
+    static std::mutex mu;
+    static bool done[64] = {false};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
+        return set_error(POLYMH_EDEVICE, "query: no current device");
+    std::lock_guard<std::mutex> lk(mu);
+    if (done[dev]) return POLYMH_OK;
+    for (const void *f : {reinterpret_cast<const void *>(&k_mark_row<true, kRowTeam>),
+                          reinterpret_cast<const void *>(&k_mark_row<true, kRowThreads>)}) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRowMost * 4);
+        if (e != hipSuccess) return set_error(POLYMH_EDEVICE, "query: rows on chip: %s", hipGetErrorString(e));
+    }
+    done[dev] = true;
+    return POLYMH_OK;
+}
+
+// Lengths of every query's list into counts, and what k_emit reads of them into
+// the workspace.
+polymh_status lookup_counts(const uint64_t *skeys, const int32_t *sids, int64_t n_entries, int64_t words,
                    const uint64_t *qkeys, int64_t nq, int32_t b, const QueryWs &w, int64_t *counts, hipStream_t s)
 {
     if (use_row(nq, words)) {
         const bool team = nq <= cu_count();
-        if (words * 4 > 40 << 10)
-            (void)hipFuncSetAttribute(team ? reinterpret_cast<const void *>(&k_mark_row<true, kRowTeam>)
-                                           : reinterpret_cast<const void *>(&k_mark_row<true, kRowThreads>),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)words * 4);
+        if (const polymh_status st = words * 4 > 40 << 10 ? allow_rows() : POLYMH_OK) return st;
         if (team)
             hipLaunchKernelGGL((k_mark_row<true, kRowTeam>), dim3((unsigned)nq), dim3(kRowTeam), (size_t)words * 4, s,
                                skeys, sids, words > 0 ? n_entries : 0, qkeys, b, w.bitmap, words, counts,
@@ -860,7 +881,7 @@ void lookup_counts(const uint64_t *skeys, const int32_t *sids, int64_t n_entries
             hipLaunchKernelGGL((k_mark_row<true, kRowThreads>), dim3((unsigned)nq), dim3(kRowThreads),
                                (size_t)words * 4, s, skeys, sids, words > 0 ? n_entries : 0, qkeys, b, w.bitmap, words,
                                counts, (const int32_t *)nullptr);
-        return;
+        return POLYMH_OK;
     }
     hipLaunchKernelGGL(k_sparse, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, skeys, sids, n_entries,
                        qkeys, nq, b, w.dense, counts, w.bitmap, words);
@@ -870,6 +891,7 @@ void lookup_counts(const uint64_t *skeys, const int32_t *sids, int64_t n_entries
                        words);
     hipLaunchKernelGGL((k_mark_row<false, kRowThreads>), dim3((unsigned)nq), dim3(kRowThreads), 0, s, skeys, sids, n_entries, qkeys, b,
                        w.bitmap, words, counts, w.dense);
+    return POLYMH_OK;
 }
 
 void lookup_emit(int64_t words, int64_t nq, const QueryWs &w, int64_t *off, int32_t *ids, const int32_t *overflow,
@@ -893,7 +915,8 @@ polymh_status launch_query_capped(const uint64_t *skeys, const int32_t *sids, in
     if (!cv.ok)
         return set_error(POLYMH_ECAPACITY, "query_capped: workspace of %zu bytes, need %zu", ws_bytes, cv.used);
     if (nq > 0x7fffffffLL) return set_error(POLYMH_EINVAL, "query_capped: too many queries");
-    if (nq > 0) lookup_counts(skeys, sids, n_entries, words, qkeys, nq, b, w, cand_off, s);
+    if (nq > 0)
+        if (const polymh_status st = lookup_counts(skeys, sids, n_entries, words, qkeys, nq, b, w, cand_off, s)) return st;
     hipLaunchKernelGGL(k_offsets, dim3(1), dim3(1024), 0, s, cand_off, nq, cand_cap, overflow);
     if (nq > 0) lookup_emit(words, nq, w, cand_off, cand_ids, overflow, s);
     return check_launch("query_capped");
@@ -928,15 +951,14 @@ polymh_status launch_query(const uint64_t *skeys, const int32_t *sids, int64_t n
         return check_launch("query");
     }
     if (nq > 0x7fffffffLL) return set_error(POLYMH_EINVAL, "query: too many queries");
-    if (!cand_ids) {
-        lookup_counts(skeys, sids, n_entries, words, qkeys, nq, b, w, cand_off, s);
+    // with offsets from the first phase (the caller's), the lengths go to the
+    // workspace
+    int64_t *counts = cand_ids ? w.counts : cand_off;
+    if (const polymh_status st = lookup_counts(skeys, sids, n_entries, words, qkeys, nq, b, w, counts, s)) return st;
+    if (!cand_ids)
         hipLaunchKernelGGL(k_offsets, dim3(1), dim3(1024), 0, s, cand_off, nq, (int64_t)0, (int32_t *)nullptr);
-    } else {
-        // the offsets are the caller's from the first phase; the lengths go
-        // to the workspace
-        lookup_counts(skeys, sids, n_entries, words, qkeys, nq, b, w, w.counts, s);
+    else
         lookup_emit(words, nq, w, cand_off, cand_ids, nullptr, s);
-    }
     return check_launch("query");
 }
 
