@@ -6,10 +6,12 @@
 // entries mark it there (k_mark_row).  Else a query's same-band bucket
 // entries are gathered into its own bitmap row in memory (work in proportion
 // to its entries), then sorted and kept without repeats on chip (one wavefront
-// for up to kSparseCap entries, a block for up to kBigCap); a query with more
-// entries marks its polygons in that row.  Every way gives the same list.
+// for up to kSparseCap entries, where rows do not fit LDS a block for up to
+// kBigCap); a query with more entries marks its polygons in its row.  Every
+// way gives the same list.
 #include "internal.hpp"
 
+#include <algorithm>
 #include <mutex>
 
 namespace polymh {
@@ -80,15 +82,7 @@ __device__ __forceinline__ int64_t bucket_end(const uint64_t *__restrict__ skeys
     return a;
 }
 
-// The candidates of a query as a bitmap row, one workgroup per query: a thread
-// a band finds its bucket, the buckets' entries are spread over the threads
-// and mark their polygons, the bits are counted.  kLds: the row is built in
-// LDS and written out for k_emit; else it is built in place, and only for
-// the queries that the sparse passes left (dense).  Bound: the latency of the
-// searches' dependent reads.  100,000 polygons, 32 bands, 1,000 queries 53 us
-// for the whole lookup and 10,000 253, against 85 and 573 with a wavefront a
-// (query, band) and the rows cleared, marked and counted in memory.
-// The same searches by 16 lanes (a DPP row) with the same key.  A round reads
+// A key's bucket by 16 lanes (a DPP row) that all have the key.  A round reads
 // 16 keys about the interpolated place, the square root of the bracket's
 // length apart up to a quarter (a uniform key lies within half of it, about),
 // so that some 3 rounds of memory latency find the place instead of the 8
@@ -135,102 +129,121 @@ __device__ __forceinline__ Bucket bucket_by_row(const uint64_t *__restrict__ a, 
     return r;
 }
 
+// The candidates of a query as a bitmap row, a workgroup a query: a thread a
+// band finds its bucket (kRowTeam: 16 lanes a band), the buckets' entries are
+// spread over the threads and mark their polygons, the bits are counted.
+// kLds: the row is built in LDS and written out for k_emit, else in place.
+// dense: only the queries that the sparse passes left.  Bound: the latency of
+// the searches' dependent reads.  100,000 polygons, 32 bands, 1,000 queries 53
+// us for the whole lookup and 10,000 253, against 85 and 573 with a wavefront a
+// (query, band) and the rows cleared, marked and counted in memory.
 constexpr int kRowThreads = 256, kRowTeam = 1024;
 template <bool kLds, int kThreads>
 __global__ __launch_bounds__(kThreads) void k_mark_row(const uint64_t *__restrict__ skeys,
                                                           const int32_t *__restrict__ sids, int64_t n_entries,
-                                                          const uint64_t *__restrict__ qkeys, int32_t b,
+                                                          const uint64_t *__restrict__ qkeys, int64_t nq, int32_t b,
                                                           uint32_t *bitmap, int64_t words,
                                                           int64_t *__restrict__ counts,
                                                           const int32_t *__restrict__ dense)
 {
     extern __shared__ uint32_t s_row[];
     __shared__ int64_t s_base[kThreads + 1], s_lo[kThreads], s_w[kThreads / 64];
-    const int64_t q = blockIdx.x;
-    if (!kLds && !dense[q]) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    uint32_t *row = bitmap + q * words;
-    uint32_t *bits = kLds ? s_row : row;
-    for (int64_t i = tid; i < words; i += kThreads) bits[i] = 0u;
-    for (int32_t t0 = 0; t0 < b; t0 += kThreads) {
-        const int32_t t = t0 + tid;
-        int64_t lo = 0, hi = 0;
-        if constexpr (kThreads == kRowTeam) {
-            // few queries: the searches' latency is the launch's
-            const int l16 = tid & 15, row_shift = lane & 48, count = min(kThreads, b - t0);
-            for (int r = tid >> 4; r < count; r += kThreads / 16) {
-                const Bucket k = bucket_by_row(skeys, n_entries, qkeys[q * b + t0 + r], l16, row_shift);
-                if (l16 == 0) {
-                    s_lo[r] = k.lo;
-                    s_base[r] = k.hi - k.lo;
+    for (int64_t q = blockIdx.x; q < nq; q += gridDim.x) {
+        if (dense && !dense[q]) continue;
+        uint32_t *row = bitmap + q * words;
+        uint32_t *bits = kLds ? s_row : row;
+        for (int64_t i = tid; i < words; i += kThreads) bits[i] = 0u;
+        for (int32_t t0 = 0; t0 < b; t0 += kThreads) {
+            const int32_t t = t0 + tid;
+            int64_t lo = 0, hi = 0;
+            if constexpr (kThreads == kRowTeam) {
+                // few queries: the searches' latency is the launch's
+                const int l16 = tid & 15, row_shift = lane & 48, count = min(kThreads, b - t0);
+                for (int r = tid >> 4; r < count; r += kThreads / 16) {
+                    const Bucket k = bucket_by_row(skeys, n_entries, qkeys[q * b + t0 + r], l16, row_shift);
+                    if (l16 == 0) {
+                        s_lo[r] = k.lo;
+                        s_base[r] = k.hi - k.lo;
+                    }
+                }
+                __syncthreads();
+                if (t < b) {
+                    lo = s_lo[tid];
+                    hi = lo + s_base[tid];
+                }
+            } else if (t < b) {
+                const uint64_t key = qkeys[q * b + t];
+                lo = lower_bound_interp(skeys, n_entries, key);
+                hi = bucket_end(skeys, n_entries, key, lo);
+            }
+            const int64_t incl = wave_incl_scan64(hi - lo);
+            if (lane == 63) s_w[wave] = incl;
+            __syncthreads();
+            int64_t at = incl - (hi - lo);
+            for (int w = 0; w < wave; w++) at += s_w[w];
+            s_base[tid] = at;
+            s_lo[tid] = lo;
+            if (tid == kThreads - 1) s_base[kThreads] = at + (hi - lo);
+            __syncthreads();
+            const int64_t total = s_base[kThreads];
+            const int top = min(kThreads, b - t0) - 1;
+            constexpr int kU = 4;                   // entries in flight a thread
+            for (int64_t j0 = tid; j0 < total; j0 += kThreads * kU) {
+                int32_t ent[kU];
+                int band[kU];
+    #pragma unroll
+                for (int u = 0; u < kU; u++) {
+                    const int64_t j = j0 + kThreads * u;
+                    ent[u] = -1;
+                    band[u] = 0;
+                    if (j < total) {
+                        int l = 0, h = top;         // the last band with s_base[l] <= j
+                        while (l < h) {
+                            const int mid = (l + h + 1) >> 1;
+                            if (s_base[mid] <= j) l = mid;
+                            else h = mid - 1;
+                        }
+                        ent[u] = sids[s_lo[l] + (j - s_base[l])];   // entry p*b + t'
+                        band[u] = t0 + l;
+                    }
+                }
+    #pragma unroll
+                for (int u = 0; u < kU; u++) {
+                    const int32_t id = ent[u] >= 0 ? ent[u] / b : 0;
+                    if (ent[u] >= 0 && ent[u] - id * b == band[u]) atomicOr(&bits[id >> 5], 1u << (id & 31));
                 }
             }
             __syncthreads();
-            if (t < b) {
-                lo = s_lo[tid];
-                hi = lo + s_base[tid];
-            }
-        } else if (t < b) {
-            const uint64_t key = qkeys[q * b + t];
-            lo = lower_bound_interp(skeys, n_entries, key);
-            hi = bucket_end(skeys, n_entries, key, lo);
         }
-        const int64_t incl = wave_incl_scan64(hi - lo);
-        if (lane == 63) s_w[wave] = incl;
-        __syncthreads();
-        int64_t at = incl - (hi - lo);
-        for (int w = 0; w < wave; w++) at += s_w[w];
-        s_base[tid] = at;
-        s_lo[tid] = lo;
-        if (tid == kThreads - 1) s_base[kThreads] = at + (hi - lo);
-        __syncthreads();
-        const int64_t total = s_base[kThreads];
-        const int top = min(kThreads, b - t0) - 1;
-        constexpr int kU = 4;                   // entries in flight a thread
-        for (int64_t j0 = tid; j0 < total; j0 += kThreads * kU) {
-            int32_t ent[kU];
-            int band[kU];
-#pragma unroll
-            for (int u = 0; u < kU; u++) {
-                const int64_t j = j0 + kThreads * u;
-                ent[u] = -1;
-                band[u] = 0;
-                if (j < total) {
-                    int l = 0, h = top;         // the last band with s_base[l] <= j
-                    while (l < h) {
-                        const int mid = (l + h + 1) >> 1;
-                        if (s_base[mid] <= j) l = mid;
-                        else h = mid - 1;
-                    }
-                    ent[u] = sids[s_lo[l] + (j - s_base[l])];   // entry p*b + t'
-                    band[u] = t0 + l;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kU; u++) {
-                const int32_t id = ent[u] >= 0 ? ent[u] / b : 0;
-                if (ent[u] >= 0 && ent[u] - id * b == band[u]) atomicOr(&bits[id >> 5], 1u << (id & 31));
-            }
-        }
-        __syncthreads();
-    }
-    int64_t c = 0;
-    for (int64_t i = tid; i < words; i += kThreads) {
-        uint32_t v;
+        int64_t c = 0;
         if constexpr (kLds) {
-            v = s_row[i];
-            row[i] = v;
+            for (int64_t i = tid; i < words; i += kThreads) {
+                const uint32_t v = s_row[i];
+                row[i] = v;
+                c += __popc(v);
+            }
         } else {
-            v = __hip_atomic_load(&row[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            constexpr int kC = 8;                   // words in flight a thread
+            for (int64_t i0 = tid; i0 < words; i0 += kThreads * kC) {
+                uint32_t v[kC];
+#pragma unroll
+                for (int u = 0; u < kC; u++) {
+                    const int64_t i = i0 + kThreads * u;
+                    v[u] = __hip_atomic_load(&row[i < words ? i : i0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+#pragma unroll
+                for (int u = 0; u < kC; u++) c += i0 + kThreads * u < words ? __popc(v[u]) : 0;
+            }
         }
-        c += __popc(v);
-    }
-    c = wave_sum_i64(c);
-    if (lane == 0) s_w[wave] = c;
-    __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < kThreads / 64; w++) c += s_w[w];
-        counts[q] = c;
+        c = wave_sum_i64(c);
+        if (lane == 0) s_w[wave] = c;
+        __syncthreads();
+        if (tid == 0) {
+            for (int w = 1; w < kThreads / 64; w++) c += s_w[w];
+            counts[q] = c;
+        }
+        __syncthreads();
     }
 }
 
@@ -317,7 +330,7 @@ constexpr int kBigCap = 16384;
 // Gather pass, one wavefront per query (four per block): the query's
 // same-band bucket entries, in bucket order with repeats, written to the
 // start of its own bitmap row; raw[q] = their number.  A query with more
-// than min(kBigCap, words) entries gets dense[q] = 1 (the bitmap takes it).
+// than `cap` entries in its buckets gets dense[q] = 1 (the bitmap takes it).
 //
 // Lane t takes band t's key: an interpolation search gives its bucket's
 // first entry, a galloping search its end.  The bucket lengths' prefix
@@ -328,7 +341,7 @@ __global__ __launch_bounds__(256) void k_sparse(const uint64_t *__restrict__ ske
                                                 const int32_t *__restrict__ sids, int64_t n_entries,
                                                 const uint64_t *__restrict__ qkeys, int64_t nq, int32_t b,
                                                 int32_t *__restrict__ dense, int64_t *__restrict__ raw,
-                                                uint32_t *__restrict__ bitmap, int64_t words)
+                                                uint32_t *__restrict__ bitmap, int64_t words, int cap)
 {
     __shared__ int32_t sbase[4][65];     // exclusive prefix of the bucket lengths, then the total
     __shared__ int64_t slo[4][64];       // each lane's bucket start
@@ -336,7 +349,6 @@ __global__ __launch_bounds__(256) void k_sparse(const uint64_t *__restrict__ ske
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t q = (int64_t)blockIdx.x * 4 + wave;
     if (q >= nq) return;                       // wavefront-uniform; no block barriers below
-    const int cap = (int)(words < kBigCap ? words : kBigCap);
     int32_t *row = reinterpret_cast<int32_t *>(bitmap + q * words);
     int32_t *base = sbase[wave];
     int64_t *los = slo[wave];
@@ -369,6 +381,10 @@ __global__ __launch_bounds__(256) void k_sparse(const uint64_t *__restrict__ ske
         base[lane] = inc - len;
         los[lane] = lo;
         const int total = __shfl(inc, 63, 64);
+        if (cnt + total > cap) {               // wavefront-uniform
+            over = true;
+            break;
+        }
         if (lane == 63) base[64] = total;
         wave_lds_fence();
         // every entry of the 64 buckets, one per lane per step (band lane
@@ -376,7 +392,7 @@ __global__ __launch_bounds__(256) void k_sparse(const uint64_t *__restrict__ ske
         // kWalk steps are loaded before any is used, so the walk costs
         // total / (64 kWalk) round trips to memory
         constexpr int kWalk = 8;
-        for (int j00 = 0; j00 < total && !over; j00 += 64 * kWalk) {
+        for (int j00 = 0; j00 < total; j00 += 64 * kWalk) {
             int32_t ent[kWalk];
             int band[kWalk];
 #pragma unroll
@@ -401,10 +417,6 @@ __global__ __launch_bounds__(256) void k_sparse(const uint64_t *__restrict__ ske
                 const bool ok = ent[u] >= 0 && ent[u] - id * b == band[u];
                 const uint64_t om = __ballot(ok);
                 const int n_new = __popcll(om);
-                if (cnt + n_new > cap) {       // wavefront-uniform
-                    over = true;
-                    break;
-                }
                 const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(om >> 32),
                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)om, 0u));
                 if (ok) row[cnt + rank] = id;
@@ -837,10 +849,13 @@ constexpr int64_t kRowShort = 5120, kRowMost = 32768;
 static_assert(kRowShort >= kSparseCap, "a sparse list is kept in its query's bitmap row");
 static_assert(kBigCap <= 16384 && kSparseCap <= kBigCap, "list caps");
 
+// Rows of this many words that are on chip at once.
+inline int64_t rows_at_once(int64_t words) { return cu_count() * ((int64_t)(160 << 10) / (words * 4 + 6144)); }
+
 inline bool use_row(int64_t nq, int64_t words)
 {
     if (words <= kRowShort) return true;
-    return words <= kRowMost && nq <= cu_count() * ((int64_t)(160 << 10) / (words * 4 + 6144));
+    return words <= kRowMost && nq <= rows_at_once(words);
 }
 
 // Lets k_mark_row have rows of any size that use_row gives it.  The setting is
@@ -875,22 +890,47 @@ polymh_status lookup_counts(const uint64_t *skeys, const int32_t *sids, int64_t 
         if (const polymh_status st = words * 4 > 40 << 10 ? allow_rows() : POLYMH_OK) return st;
         if (team)
             hipLaunchKernelGGL((k_mark_row<true, kRowTeam>), dim3((unsigned)nq), dim3(kRowTeam), (size_t)words * 4, s,
-                               skeys, sids, words > 0 ? n_entries : 0, qkeys, b, w.bitmap, words, counts,
+                               skeys, sids, words > 0 ? n_entries : 0, qkeys, nq, b, w.bitmap, words, counts,
                                (const int32_t *)nullptr);
         else
             hipLaunchKernelGGL((k_mark_row<true, kRowThreads>), dim3((unsigned)nq), dim3(kRowThreads),
-                               (size_t)words * 4, s, skeys, sids, words > 0 ? n_entries : 0, qkeys, b, w.bitmap, words,
+                               (size_t)words * 4, s, skeys, sids, words > 0 ? n_entries : 0, qkeys, nq, b, w.bitmap, words,
                                counts, (const int32_t *)nullptr);
         return POLYMH_OK;
     }
+    // A list is sorted by a block while its row does not fit LDS (4 M polygons,
+    // lists of 4,800: 1,000 queries 407 us); else the row costs less (300,000
+    // polygons, 3,000 queries with lists of 4,800: 296 us, sorted 968; 1 M
+    // polygons 630 and 976).
+    const int cap = words > kRowMost ? kBigCap : kSparseCap;
     hipLaunchKernelGGL(k_sparse, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, skeys, sids, n_entries,
-                       qkeys, nq, b, w.dense, counts, w.bitmap, words);
+                       qkeys, nq, b, w.dense, counts, w.bitmap, words, (int)std::min<int64_t>(words, cap));
     hipLaunchKernelGGL(k_sparse_sort, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, w.dense, nq, counts,
                        w.bitmap, words);
-    hipLaunchKernelGGL(k_sparse_sort_big, dim3((unsigned)nq), dim3(1024), 0, s, w.dense, counts, w.bitmap,
+    if (cap > kSparseCap) hipLaunchKernelGGL(k_sparse_sort_big, dim3((unsigned)nq), dim3(1024), 0, s, w.dense, counts, w.bitmap,
                        words);
-    hipLaunchKernelGGL((k_mark_row<false, kRowThreads>), dim3((unsigned)nq), dim3(kRowThreads), 0, s, skeys, sids, n_entries, qkeys, b,
-                       w.bitmap, words, counts, w.dense);
+    // the queries that they left: rows on chip where they fit (as many
+    // workgroups as are there at once take them in turn), else in memory
+    if (words <= kRowMost) {
+        if (const polymh_status st = allow_rows()) return st;
+        const int64_t at_once = rows_at_once(words);
+        if (at_once <= cu_count())
+            hipLaunchKernelGGL((k_mark_row<true, kRowTeam>), dim3((unsigned)std::min(nq, at_once)), dim3(kRowTeam),
+                               (size_t)words * 4, s, skeys, sids, n_entries, qkeys, nq, b, w.bitmap, words, counts,
+                               w.dense);
+        else
+            hipLaunchKernelGGL((k_mark_row<true, kRowThreads>), dim3((unsigned)std::min(nq, at_once)),
+                               dim3(kRowThreads), (size_t)words * 4, s, skeys, sids, n_entries, qkeys, nq, b, w.bitmap,
+                               words, counts, w.dense);
+    } else if (nq <= 4 * cu_count()) {
+        // few workgroups a CU: 4 M polygons, a list of 32,000: 209 us, with 256
+        // threads 342
+        hipLaunchKernelGGL((k_mark_row<false, kRowTeam>), dim3((unsigned)nq), dim3(kRowTeam), 0, s, skeys, sids,
+                           n_entries, qkeys, nq, b, w.bitmap, words, counts, w.dense);
+    } else {
+        hipLaunchKernelGGL((k_mark_row<false, kRowThreads>), dim3((unsigned)nq), dim3(kRowThreads), 0, s, skeys, sids,
+                           n_entries, qkeys, nq, b, w.bitmap, words, counts, w.dense);
+    }
     return POLYMH_OK;
 }
 

@@ -59,3 +59,26 @@ def test_refinement_of_many_pairs_of_500_edges(pm):
     assert small <= 1.6 * large, (small, large)
     a, b = (pm.refine(D, Q, off, ids, ws=ws, n_cand=n)[:nq * per] for n in (nq * per, 1 << 18))
     assert torch.equal(a, b)
+
+
+def test_lookup_of_long_lists(pm):
+    """3,000 queries of some 4,800 entries each over 300,000 polygons, more than
+    run at once with their bitmaps on chip, against six calls of 500."""
+    import torch
+    n, b, nq = 300_000, 16, 3000
+    g = torch.Generator(device="cuda").manual_seed(4)
+    z = torch.randint(0, n // 300, (n, b), generator=g, device="cuda") * b + torch.arange(b, device="cuda")
+    z = (z ^ (z >> 30)) * -4658895280553007687
+    z = (z ^ (z >> 27)) * -7723592293110705685
+    z = z ^ (z >> 31)
+    sk, se = pm.index_build(z.contiguous())
+    qk = z[torch.randint(0, n, (nq,), generator=g, device="cuda")].contiguous()
+
+    def call(q):
+        off = torch.empty(q + 1, dtype=torch.int64, device="cuda")
+        ids = torch.empty(q * 6000, dtype=torch.int32, device="cuda")
+        flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+        ws = torch.empty(int(pm.lib().polymh_query_workspace_size(n, q)), dtype=torch.uint8, device="cuda")
+        return _us(lambda: pm.query_capped(sk, se, n, qk[:q], off, ids, flag, ws))
+    whole, part = call(nq), call(500)
+    assert whole <= 1.5 * 6 * part, (whole, part)
