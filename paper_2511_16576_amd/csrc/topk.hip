@@ -7,9 +7,9 @@
 // and goes on in the digit where the k-th best falls.  The entries left are
 // ranked by counting, for each, the ones before it.  Bound: the latency of
 // the steps, typically two counts, one gather and one ranking whatever k is,
-// where selecting one entry a round took k passes over the list: 64 lists of
-// 11,800 at k = 100 take 23 us (1,165 by rounds), 10,000 lists of about 600 at
-// k = 10 95 us (150 by rounds).
+// where selecting one entry a round takes k passes over the list: 64 lists of
+// 11,800 at k = 100 take 34 us (1,176 by rounds), 10,000 lists of 650 at
+// k = 10 85 us (157 by rounds).  Up to three or four entries go by rounds.
 #include "internal.hpp"
 
 #include <algorithm>
@@ -106,6 +106,17 @@ __global__ __launch_bounds__(1024) void k_topk(const int64_t *__restrict__ off, 
     top_j += q * k;
     const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
 
+    // The first few by rounds: 5,000 lists of 3,000 at k = 1 46 us (98 by
+    // digits, 276 if J takes 8 values), at k = 3 103 (98, 275), at k = 4 122
+    // (99, 278); one list of 100,000 37 and 86 us at k = 1 and 3 (113).  Short
+    // lists wait on the digits' steps rather than on memory and gain a little
+    // longer: 5,000 lists of 300 and of 500 at k = 4 49 and 52 us (65, 86), but
+    // at k = 8 83 and 87 (65, 86).
+    if (k <= 3 || (k == 4 && n <= 512)) {
+        select_by_rounds(ids, js, n, k, reinterpret_cast<double *>(s_mem), reinterpret_cast<int32_t *>(s_mem + nt),
+                         top_ids, top_j);
+        return;
+    }
     bool odd = n > INT32_MAX;
     int shift = 64, id_shift = 32;      // digits chosen so far end here
     uint64_t pre = 0;
@@ -124,7 +135,19 @@ __global__ __launch_bounds__(1024) void k_topk(const int64_t *__restrict__ off, 
             if (step == 0) odd |= !(fabs(j) <= DBL_MAX) || key == 1ull << 63 || id < 0;
             const bool in = on_id ? key == pre && (id_shift == 32 || (uint32_t)id >> id_shift == id_pre)
                                   : shift == 64 || key >> shift == pre;
-            if (in) atomicAdd(&s_bin[(uint32_t)((on_id ? (uint64_t)(uint32_t)id : key) >> lo) & mask], 1u);
+            // the lanes that share the first one's digit are counted together
+            // (many J are 0), the others one by one: 5,000 lists of 500 zeros
+            // at k = 100 129 us, 183 with every lane on its own; three turns
+            // of it cost random J more than they give
+            const uint32_t d = (uint32_t)((on_id ? (uint64_t)(uint32_t)id : key) >> lo) & mask;
+            uint64_t left = __ballot(in);
+            if (left != 0) {
+                const int first = __builtin_ctzll(left);
+                const uint64_t same = left & __ballot(d == (uint32_t)__builtin_amdgcn_readlane((int)d, first));
+                if (lane == first) atomicAdd(&s_bin[d], (uint32_t)__popcll(same));
+                left &= ~same;
+            }
+            if (__builtin_amdgcn_inverse_ballot_w64(left)) atomicAdd(&s_bin[d], 1u);
         }
         if (step == 0 ? __syncthreads_or(odd) : (__syncthreads(), 0)) {
             odd = true;

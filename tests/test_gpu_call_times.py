@@ -82,3 +82,28 @@ def test_lookup_of_long_lists(pm):
         return _us(lambda: pm.query_capped(sk, se, n, qk[:q], off, ids, flag, ws))
     whole, part = call(nq), call(500)
     assert whole <= 1.5 * 6 * part, (whole, part)
+
+
+def test_top_entry_of_equal_values(pm):
+    """The best of 5,000 lists of 3,000 that hold eight different J, against the
+    best ten: one pass over the lists, against the digits' counts."""
+    import torch
+    nq, n = 5000, 3000
+    g = torch.Generator(device="cuda").manual_seed(5)
+    js = torch.randint(0, 8, (nq * n,), generator=g, device="cuda").double() / 8
+    ids = torch.arange(n, dtype=torch.int32, device="cuda").repeat(nq)
+    off = torch.arange(nq + 1, dtype=torch.int64, device="cuda") * n
+    one, ten = _us(lambda: pm.topk(off, ids, js, 1)), _us(lambda: pm.topk(off, ids, js, 10))
+    assert one <= 0.5 * ten, (one, ten)
+
+
+def test_topk_of_zeros(pm):
+    """Lists whose J are all zero, against lists of random J."""
+    import torch
+    nq, n = 5000, 500
+    ids = torch.arange(n, dtype=torch.int32, device="cuda").repeat(nq)
+    off = torch.arange(nq + 1, dtype=torch.int64, device="cuda") * n
+    js = torch.rand(nq * n, generator=torch.Generator(device="cuda").manual_seed(6), dtype=torch.float64, device="cuda")
+    zero = _us(lambda: pm.topk(off, ids, js * 0, 100)) - _us(lambda: js * 0)
+    rand = _us(lambda: pm.topk(off, ids, js + 0, 100)) - _us(lambda: js + 0)
+    assert zero <= 1.7 * rand, (zero, rand)
