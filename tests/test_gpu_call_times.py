@@ -107,3 +107,12 @@ def test_topk_of_zeros(pm):
     zero = _us(lambda: pm.topk(off, ids, js * 0, 100)) - _us(lambda: js * 0)
     rand = _us(lambda: pm.topk(off, ids, js + 0, 100)) - _us(lambda: js + 0)
     assert zero <= 1.7 * rand, (zero, rand)
+
+
+def test_join_of_a_large_ring(pm):
+    """One ring of 300,000 vertices: copying it takes no longer than staging it,
+    which reads as much and computes besides."""
+    xy = _rings(1, 300_000, 1 << 24, 0.1, 0.2, 7)[0]
+    R, D = pm.rings_to_device(dg.from_rings([[xy]])), pm.to_device(dg.from_list([xy]))
+    join, prepare = _us(lambda: pm.join_rings(R)), _us(lambda: pm.prepare(D))
+    assert join <= prepare, (join, prepare)
