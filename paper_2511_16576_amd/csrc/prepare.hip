@@ -110,27 +110,30 @@ struct Staged {
 
 // MBR, twice the signed area (exact whenever |area2| < 2^63) and flags of
 // every polygon.  Bound: the latency of the chain offsets -> vertices ->
-// reductions, so four polygons share a wavefront, a 16-lane row each; one of
-// more than kRowMost vertices is taken by the whole wavefront afterwards (a
+// reductions, so `per` = 4 polygons share a wavefront, a 16-lane row each; one
+// of more than kRowMost vertices is taken by the whole wavefront afterwards (a
 // row alone would need 256 round trips for 8,192 vertices).  2 M polygons of
-// 22 vertices 358 us against 878 with a wavefront each.
+// 22 vertices 358 us against 878 with a wavefront each.  As long as the CUs
+// hold a wavefront for every polygon, each has its own (per = 1): four of
+// 300,000 vertices 1.07 ms, 3.92 one after another; 64 of 20,000 69 us, 225.
 constexpr int kRowMost = 128;
 __global__ __launch_bounds__(256) void k_prepare(const int32_t *__restrict__ xy,
                                                  const int64_t *__restrict__ off, int64_t n,
                                                  int32_t *__restrict__ mbr,
                                                  int64_t *__restrict__ area2,
-                                                 uint32_t *__restrict__ flags)
+                                                 uint32_t *__restrict__ flags, int per)
 {
     const int lane = threadIdx.x & 63, rl = lane & 15;
-    const int64_t step = ((int64_t)gridDim.x * blockDim.x) >> 4;
-    for (int64_t p0 = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * 4; p0 < n; p0 += step) {
+    const int64_t step = (((int64_t)gridDim.x * blockDim.x) >> 6) * per;
+    for (int64_t p0 = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * per; p0 < n; p0 += step) {
         const int64_t p = p0 + (lane >> 4);
-        const int64_t a = p < n ? off[p] : 0, b = p < n ? off[p + 1] : 0;
+        const bool in = (lane >> 4) < per && p < n;
+        const int64_t a = in ? off[p] : 0, b = in ? off[p + 1] : 0;
         const bool big = b - a > kRowMost;
         Staged s;
         if (b > a && !big) s.take<16, 2>(xy, a, b, rl);
         s.reduce_row();
-        if (p < n && !big && rl == 0) s.write(p, b - a, mbr, area2, flags);
+        if (in && !big && rl == 0) s.write(p, b - a, mbr, area2, flags);
         uint64_t todo = __ballot(big && rl == 0);
         while (todo) {
             const int r = __ffsll((unsigned long long)todo) - 1;
@@ -334,9 +337,9 @@ polymh_status launch_prepare(const int32_t *xy, const int64_t *off, int64_t n, i
                              int64_t *area2, uint32_t *flags, hipStream_t s)
 {
     if (n == 0) return POLYMH_OK;
-    // 16 polygons (rows of 16 lanes) per 256-thread block
-    hipLaunchKernelGGL(k_prepare, dim3(grid_for(n, 16, 1 << 16)), dim3(256), 0, s, xy, off, n, mbr,
-                       area2, flags);
+    const int per = n <= 16 * (int64_t)cu_count() ? 1 : 4;
+    hipLaunchKernelGGL(k_prepare, dim3(grid_for(n, 4 * per, 1 << 16)), dim3(256), 0, s, xy, off, n, mbr,
+                       area2, flags, per);
     return check_launch("prepare");
 }
 

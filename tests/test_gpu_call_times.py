@@ -116,3 +116,10 @@ def test_join_of_a_large_ring(pm):
     R, D = pm.rings_to_device(dg.from_rings([[xy]])), pm.to_device(dg.from_list([xy]))
     join, prepare = _us(lambda: pm.join_rings(R)), _us(lambda: pm.prepare(D))
     assert join <= prepare, (join, prepare)
+
+
+def test_prepare_of_a_few_large_rings(pm):
+    """Four rings of 300,000 vertices against one."""
+    rings = _rings(4, 300_000, 1 << 24, 0.1, 0.2, 8)
+    four, one = (_us(lambda: pm.prepare(D)) for D in (pm.to_device(dg.from_list(r)) for r in (rings, rings[:1])))
+    assert four <= 2 * one, (four, one)

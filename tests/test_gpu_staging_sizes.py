@@ -49,3 +49,19 @@ def test_join_of_sizes(which):
     torch.cuda.synchronize()
     assert np.array_equal(out_off.cpu().numpy(), off) and np.array_equal(out.cpu().numpy(), np.concatenate(want))
     assert int(bad) == int(any(m < 3 for m in rings))
+
+
+@pytest.mark.parametrize("which", range(6))
+def test_prepare_of_sizes(which):
+    from paper_2511_16576_amd import polymh as pm
+    pm.check_device()
+    n = _sets()[which]
+    rng = np.random.default_rng(which)
+    sizes = rng.choice([3, 16, 17, 127, 128, 129, 700], n)
+    polys = [rng.integers(-2**24, 2**24, (m, 2)) for m in sizes]
+    mbr, area2, flags = (t.cpu().numpy() for t in pm.prepare(pm.to_device(dg.from_list(polys))))
+    for p, q in enumerate(polys):
+        assert mbr[p].tolist() == [*q.min(0), *q.max(0)], p
+        x, y = q.T
+        assert area2[p] == int((x * np.roll(y, -1) - np.roll(x, -1) * y).sum()), p
+        assert flags[p] == 0, p
