@@ -60,23 +60,41 @@ struct BinArgs {
     int32_t cbits, csx;            // columns of a row: 2^cbits, that of offset o: o >> csx
     uint2 *range;                  // [groups][nchunks][rows][columns] first and past-the-end place
     uint32_t *cursor;              // [groups][nchunks][parts] counts, then next free place
+    int64_t list0;                 // k_bin_row's first (group, chunk)
 };
 
 constexpr int kBinSamples = 1 << kBinLog;
 
-// k_bin counts (PLACE false) or files (PLACE true) some hashes' samples of a
-// chunk by part: counted in LDS, one global atomic a part, and where they are
-// filed first ordered in LDS, so that a part's samples are written together.
-// 117 M samples take 0.2 ms to count, 0.5 to file by row and 0.65 by column
-// (k_bin_row), against 3.2 written one by one to the 4,096 cells.  The order
-// inside a part does not matter.
-template <bool POW2, bool PLACE>
+// State of hash h's stream, which sample j's numbers come from.
+__device__ __forceinline__ uint64_t stream_key(const BinArgs &A, int h)
+{
+    return mix64(A.seed + (uint64_t)(h + 1) * kGamma);
+}
+template <bool POW2>
+__device__ __forceinline__ uint2 sample_at(const BinArgs &A, uint64_t key, uint64_t j)
+{
+    const uint64_t r = mix64(key + (j + 1) * kGamma);
+    return make_uint2(lattice<POW2>((uint32_t)(r >> 32), A.wx, A.shx), lattice<POW2>((uint32_t)r, A.wy, A.shy));
+}
+
+enum BinTo { kCount = 0, kToRows = 1, kToCells = 2 };
+
+// k_bin counts or files some hashes' samples of a chunk by part: counted in
+// LDS, one global atomic a part, and where they are filed first ordered in
+// LDS, so that a part's samples are written together.  By row, only the four
+// bytes of hash and index are: k_bin_row draws the sample again, which costs
+// less than the eight bytes written and read.  117 M samples take 0.20 ms to
+// count, 0.28 to file by row and 0.40 by column (with the bytes 0.20, 0.53 and
+// 0.65), against 3.2 written one by one to the 4,096 cells.  The order inside
+// a part does not matter.
+template <bool POW2, BinTo TO>
 __global__ __launch_bounds__(1024) void k_bin(BinArgs A)
 {
     constexpr int kPer = kBinSamples / 1024;
+    constexpr bool PLACE = TO != kCount, XY = TO == kToCells;
     __shared__ uint32_t s_cnt[256], s_start[256];
     __shared__ uint32_t s_w[16];
-    __shared__ uint2 s_xy[PLACE ? kBinSamples : 1];
+    __shared__ uint2 s_xy[XY ? kBinSamples : 1];
     __shared__ uint32_t s_meta[PLACE ? kBinSamples : 1];
     __shared__ uint8_t s_part[PLACE ? kBinSamples : 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = blockIdx.x;
@@ -88,7 +106,8 @@ __global__ __launch_bounds__(1024) void k_bin(BinArgs A)
     const size_t gc = (size_t)g * A.nchunks + c;
     if (tid < 256) s_cnt[tid] = 0;
     __syncthreads();
-    uint32_t ox[kPer], oy[kPer], meta[kPer], rank[kPer];
+    uint2 o[kPer];
+    uint32_t meta[kPer], rank[kPer];
     int part[kPer];
 #pragma unroll
     for (int u = 0; u < kPer; u++) {
@@ -98,12 +117,10 @@ __global__ __launch_bounds__(1024) void k_bin(BinArgs A)
         const uint64_t j = ((uint64_t)c << A.lchunk) + i;
         part[u] = -1;
         if (h < A.k && j < A.horizon) {
-            const uint64_t r = mix64(mix64(A.seed + (uint64_t)(h + 1) * kGamma) + (j + 1) * kGamma);
-            ox[u] = lattice<POW2>((uint32_t)(r >> 32), A.wx, A.shx);
-            oy[u] = lattice<POW2>((uint32_t)r, A.wy, A.shy);
+            o[u] = sample_at<POW2>(A, stream_key(A, h), j);
             // 64-bit shifts: a 2^32-wide side with one cell shifts by 32
-            const int cy = (int)((uint64_t)oy[u] >> A.sby);
-            part[u] = A.by_row ? cy : cy << A.bits | (int)((uint64_t)ox[u] >> A.sbx);
+            const int cy = (int)((uint64_t)o[u].y >> A.sby);
+            part[u] = A.by_row ? cy : cy << A.bits | (int)((uint64_t)o[u].x >> A.sbx);
             meta[u] = (uint32_t)(h % kGroup) << 24 | i;
             rank[u] = atomicAdd(&s_cnt[part[u]], 1u);
         }
@@ -131,7 +148,7 @@ __global__ __launch_bounds__(1024) void k_bin(BinArgs A)
         for (int u = 0; u < kPer; u++) {
             if (part[u] >= 0) {
                 const uint32_t p = s_start[part[u]] + rank[u];
-                s_xy[p] = make_uint2(ox[u], oy[u]);
+                if (XY) s_xy[p] = o[u];
                 s_meta[p] = meta[u];
                 s_part[p] = (uint8_t)part[u];
             }
@@ -140,7 +157,7 @@ __global__ __launch_bounds__(1024) void k_bin(BinArgs A)
         const size_t base = gc * A.per;
         for (uint32_t e = tid; e < total; e += 1024) {
             const size_t p = base + s_cnt[s_part[e]] + e;
-            A.xy[p] = s_xy[e];
+            if (XY) A.xy[p] = s_xy[e];
             A.meta[p] = s_meta[e];
         }
     }
@@ -167,16 +184,18 @@ __global__ __launch_bounds__(256) void k_bin_scan(BinArgs A, int64_t lists)
     }
 }
 
-// One workgroup a (group, chunk, grid row): its samples by column, in place,
-// kPer a thread in registers and ordered in LDS before they are written.
+// One workgroup a (group, chunk, grid row): its samples by column, hash and
+// index in place, kPer a thread in registers and ordered in LDS before they
+// are written.
 // Columns are a quarter of a cell wide, so that a stretch ends near the MBR's
 // sides.  cursor holds the rows' ends by now.  A row of more samples than
 // the threads hold (the hashes spread them evenly: none) stays as it is, and
 // each of its columns is the whole row.
-template <int kPer>
+template <bool POW2, int kPer>
 __global__ __launch_bounds__(1024) void k_bin_row(BinArgs A)
 {
     constexpr uint32_t kMost = kPer * 1024;
+    __shared__ uint64_t s_key[kGroup];
     __shared__ uint2 s_xy[kMost];
     __shared__ uint32_t s_meta[kMost];
     __shared__ uint32_t s_cnt[256], s_w[16];
@@ -187,8 +206,13 @@ __global__ __launch_bounds__(1024) void k_bin_row(BinArgs A)
     uint2 *xy = A.xy + gc * A.per + e0;
     uint32_t *meta = A.meta + gc * A.per + e0;
     uint2 *range = A.range + (gc << (A.bits + A.cbits)) + (row << A.cbits);
+    const int64_t list = A.list0 + blockIdx.y, g = list / A.nchunks, c0 = (list - g * A.nchunks) << A.lchunk;
+    if (tid < kGroup) s_key[tid] = stream_key(A, (int)g * kGroup + tid);
+    __syncthreads();
+    auto sample = [&](uint32_t m) { return sample_at<POW2>(A, s_key[m >> 24], (uint64_t)c0 + (m & 0xffffffu)); };
     if (n > kMost) {
         if (tid < side) range[tid] = make_uint2(e0, e1);
+        for (uint32_t e = tid; e < n; e += 1024) xy[e] = sample(meta[e]);
         return;
     }
     uint2 o[kPer];
@@ -196,13 +220,10 @@ __global__ __launch_bounds__(1024) void k_bin_row(BinArgs A)
 #pragma unroll
     for (int u = 0; u < kPer; u++) {
         const uint32_t e = (uint32_t)(u * 1024 + tid);
-        o[u] = make_uint2(0u, 0u);
-        m[u] = 0;
-        if (e < n) {
-            o[u] = xy[e];
-            m[u] = meta[e];
-        }
+        m[u] = e < n ? meta[e] : 0u;
     }
+#pragma unroll
+    for (int u = 0; u < kPer; u++) o[u] = sample(m[u]);
     if (tid < 256) s_cnt[tid] = 0;
     __syncthreads();
 #pragma unroll
@@ -917,11 +938,12 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
                                              : (int64_t)L.k << (lchunk - kBinLog);
         const dim3 bgrid((unsigned)nchunks, (unsigned)ys);
         hipLaunchKernelGGL(k_zero_words, dim3(grid_for(lists * B.parts)), dim3(256), 0, s, w.cursor, lists * B.parts);
-        if (pow2) hipLaunchKernelGGL((k_bin<true, false>), bgrid, dim3(1024), 0, s, B);
-        else hipLaunchKernelGGL((k_bin<false, false>), bgrid, dim3(1024), 0, s, B);
+        hipLaunchKernelGGL((pow2 ? k_bin<true, kCount> : k_bin<false, kCount>), bgrid, dim3(1024), 0, s, B);
         hipLaunchKernelGGL(k_bin_scan, dim3((unsigned)((lists + 3) / 4)), dim3(256), 0, s, B, lists);
-        if (pow2) hipLaunchKernelGGL((k_bin<true, true>), bgrid, dim3(1024), 0, s, B);
-        else hipLaunchKernelGGL((k_bin<false, true>), bgrid, dim3(1024), 0, s, B);
+        if (B.by_row)
+            hipLaunchKernelGGL((pow2 ? k_bin<true, kToRows> : k_bin<false, kToRows>), bgrid, dim3(1024), 0, s, B);
+        else
+            hipLaunchKernelGGL((pow2 ? k_bin<true, kToCells> : k_bin<false, kToCells>), bgrid, dim3(1024), 0, s, B);
         // a row's samples, with room for what chance adds to them
         const double even = (double)B.per * std::ldexp(1.0, B.sby) / (double)wy;
         const bool narrow = even + 8.0 * std::sqrt(even) <= 5 * 1024;
@@ -932,8 +954,11 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
             R.range += l0 << (bits + B.cbits);
             R.cursor += l0 * B.parts;
             const dim3 rgrid(1u << bits, (unsigned)std::min<int64_t>(65535, lists - l0));
-            if (narrow) hipLaunchKernelGGL(k_bin_row<5>, rgrid, dim3(1024), 0, s, R);
-            else hipLaunchKernelGGL(k_bin_row<12>, rgrid, dim3(1024), 0, s, R);
+            R.list0 = l0;
+            if (narrow)
+                hipLaunchKernelGGL((pow2 ? k_bin_row<true, 5> : k_bin_row<false, 5>), rgrid, dim3(1024), 0, s, R);
+            else
+                hipLaunchKernelGGL((pow2 ? k_bin_row<true, 12> : k_bin_row<false, 12>), rgrid, dim3(1024), 0, s, R);
         }
     }
     polymh_status st = check_launch("sign_binned: bin");

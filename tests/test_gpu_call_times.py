@@ -123,3 +123,18 @@ def test_prepare_of_a_few_large_rings(pm):
     rings = _rings(4, 300_000, 1 << 24, 0.1, 0.2, 8)
     four, one = (_us(lambda: pm.prepare(D)) for D in (pm.to_device(dg.from_list(r)) for r in (rings, rings[:1])))
     assert four <= 2 * one, (four, one)
+
+
+def test_binning_of_samples(pm):
+    """Drawing 456,704 samples a hash, 256 hashes, and grouping them by cell,
+    against twelve bytes a sample written once."""
+    import torch
+    side, k, h = 1 << 24, 256, 456_704
+    rng = np.random.default_rng(9)
+    D = pm.to_device(dg.star_polygons(rng, [20] * 16, rng.integers(1 << 22, 3 << 22, (16, 2)), [2e6] * 16))
+    box = (0, 0, side - 1, side - 1)
+    ws = torch.empty(pm.sign_binned_workspace_size(16, k, 1 << 26, h, 6), dtype=torch.uint8, device="cuda")
+    first, again = (_us(lambda: pm.sign_binned(D, box, 0, k, 1 << 26, horizon=h, bin_bits=6, walk_ratio=0.0, ws=ws,
+                                               rebin=r)) for r in (True, False))
+    fill = _us(lambda: ws[:12 * k * h].fill_(1))
+    assert first - again <= 5.5 * fill, (first, again, fill)
