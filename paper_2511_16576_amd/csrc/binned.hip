@@ -39,7 +39,7 @@ constexpr int kQueue = 256;        // per-wavefront queue of membership tests
 constexpr int kGroup = 256;        // hashes a lookup workgroup at most
 constexpr int kBinLog = 13;        // log2 of the samples a workgroup of k_bin takes
 constexpr uint32_t kNone = 0xffffffffu;
-constexpr int kRound0 = 8;         // chunks of a lookup's first rounds
+constexpr int kRound0 = 8;         // chunks of a lookup's first rounds at most
 constexpr int kXcds = 8;           // workgroups are handed to the XCDs in turn
 
 struct BinArgs {
@@ -264,6 +264,8 @@ struct LookupArgs {
     const int64_t *off;
     const int32_t *mbr;
     const uint32_t *flags;
+    const int64_t *area2;
+    float need;                    // samples of a hash that hold the first hits, times the area
     const uint2 *bxy;              // the bins, see BinArgs
     const uint32_t *bmeta;
     const uint2 *brange;
@@ -452,9 +454,18 @@ __device__ __forceinline__ void take(const LookupArgs &A, const int4 *s_edges, c
 // the ranges' latency are paid once a round, the samples of settled hashes
 // read on the way cost one compare.  Every wavefront takes part; all
 // arguments but `active`, tid and lane are wavefront-uniform.
+// `need` samples a hash hold the first hits of all hashes of 31 workgroups in
+// 32, so the first round takes no more chunks than those fill.  Where they are
+// less than most of one chunk, and it is a long one (at most 64 hashes, one
+// wavefront), only they are tested at first; if a hash is then open, the chunk
+// is read again, whole.  3,000 large polygons at 4 hashes take 317 us, 535
+// without the bound; 100 of 75 edges at 16 hashes 162, 274 without it, 444
+// with longer chunks and rounds of kRound0 too.  With 128 hashes, whose chunk
+// is half as long, reading one twice costs more than that saves (3,000 large
+// polygons 1,450 us, 1,657 with it).
 template <int MODE>
 __device__ void lookup_polygon(const LookupArgs &A, const int4 *s_edges, const int32_t *pxy, int32_t n, Scan &S, int cx0,
-                               int cx1, int cy0, int cy1, bool active, int tid, int lane, int wave, int waves, int group)
+                               int cx1, int cy0, int cy1, bool active, int tid, int lane, int wave, int waves, int group, float need)
 {
     const int rows = cy1 - cy0 + 1;              // at most 64
     // chunks a round at most: a round's samples are counted in 26 bits, or,
@@ -462,8 +473,14 @@ __device__ void lookup_polygon(const LookupArgs &A, const int4 *s_edges, const i
     const int most = max(1, min(64 / rows, (int)((1u << 26) / A.per)));
     S.sub_shift = most > 1 ? 26 : 31;
     const int sub = lane / rows, row = (cy0 + lane % rows) << A.cbits;
-    int m = min(most, kRound0);
-    for (int c0 = 0; c0 < A.nchunks; c0 += m, m = min(most, max(kRound0, c0))) {
+    int m = min(most, max(1, (int)fminf(ceilf(ldexpf(need, -A.lchunk)), (float)kRound0)));
+    uint32_t bound = kNone;
+    if (waves == 1 && need < 0.75f * (float)(1u << A.lchunk)) {
+        bound = (uint32_t)need + 1;
+        S.s_best[tid] = bound;
+        __syncthreads();
+    }
+    for (int c0 = 0; c0 < A.nchunks;) {
         const size_t gc = (size_t)group * A.nchunks + c0;
         uint32_t e0 = 0, e1 = 0;
         if (sub < m && c0 + sub < A.nchunks) {
@@ -519,7 +536,16 @@ __device__ void lookup_polygon(const LookupArgs &A, const int4 *s_edges, const i
             wave_sync_lds();
         }
         __syncthreads();
-        if (!__syncthreads_or(active && S.s_best[tid] == kNone)) break;
+        const bool open = active && S.s_best[tid] == bound;
+        if (!__syncthreads_or(open)) break;
+        if (bound != kNone) {
+            if (open) S.s_best[tid] = kNone;
+            bound = kNone;
+            __syncthreads();
+        } else {
+            c0 += m;
+            m = min(most, max(kRound0, c0));
+        }
     }
 }
 
@@ -592,14 +618,16 @@ __global__ __launch_bounds__(256) void k_bin_lookup(LookupArgs A)
     for (int t = tid; t < kGroup; t += per) s_best[t] = kNone;
     __syncthreads();                 // the edges and the bests
     const int group = (int)(blockIdx.x % groups);
+    const float area = 0.5f * fabsf((float)A.area2[p]);
+    const float need = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(A.need / fmaxf(area, 0.5f))));
     if (mode == kTestRec)
-        lookup_polygon<kTestRec>(A, s_edges, pxy, n, S, cx0, cx1, cy0, cy1, active, tid, lane, wave, per >> 6, group);
+        lookup_polygon<kTestRec>(A, s_edges, pxy, n, S, cx0, cx1, cy0, cy1, active, tid, lane, wave, per >> 6, group, need);
     else if (mode == kTestLds)
-        lookup_polygon<kTestLds>(A, s_edges, pxy, n, S, cx0, cx1, cy0, cy1, active, tid, lane, wave, per >> 6, group);
+        lookup_polygon<kTestLds>(A, s_edges, pxy, n, S, cx0, cx1, cy0, cy1, active, tid, lane, wave, per >> 6, group, need);
     else if (mode == kTestStream)
-        lookup_polygon<kTestStream>(A, s_edges, pxy, n, S, cx0, cx1, cy0, cy1, active, tid, lane, wave, per >> 6, group);
+        lookup_polygon<kTestStream>(A, s_edges, pxy, n, S, cx0, cx1, cy0, cy1, active, tid, lane, wave, per >> 6, group, need);
     else
-        lookup_polygon<kTestWide>(A, s_edges, pxy, n, S, cx0, cx1, cy0, cy1, active, tid, lane, wave, per >> 6, group);
+        lookup_polygon<kTestWide>(A, s_edges, pxy, n, S, cx0, cx1, cy0, cy1, active, tid, lane, wave, per >> 6, group, need);
     const uint32_t best = active ? s_best[tid] : 0u;
     if (active) {
         if (best != kNone) out[i] = best + 1;
@@ -825,9 +853,12 @@ int grid_for(int64_t items)
 // Chunks of 256 to 1,024 samples a hash, a quarter of a sample per cell at
 // the finest grid, so that a settled hash is found so early; more where a
 // group has fewer than kGroup hashes, so that a chunk's cells hold enough of
-// them together to fill a wavefront's reads, or for a horizon of many chunks.
-// A grid row of a chunk then holds 4,096 samples where k_bin_row files it, or
-// half as many rows twice that.
+// them together to fill a wavefront's reads, or for a horizon of many chunks:
+// twice as many at 128 hashes, and from there on twice as many for every
+// quarter of them, as what is read past the first hits grows too (a lookup of
+// 16 hashes by 100 and 3,000 polygons takes 88 and 332 us, 111 and 364 with
+// twice as many for every half).  A grid row of a chunk then holds 4,096 samples at most
+// where k_bin_row files it, or half as many rows twice that.
 constexpr int64_t kMostChunks = 65535;
 
 int64_t chunks_of(uint32_t horizon, int lchunk) { return ((int64_t)horizon + ((int64_t)1 << lchunk) - 1) >> lchunk; }
@@ -840,7 +871,9 @@ bool horizon_fits(uint32_t horizon, int32_t bits)
 int chunk_log2(int32_t bits, int32_t k, uint32_t horizon)
 {
     int l = std::max(8, bits + 4);
-    for (int h = k; 2 * h <= kGroup; h *= 2) l++;
+    int halvings = 0;
+    for (int h = k; 2 * h <= kGroup; h *= 2) halvings++;
+    l += std::min(halvings, (halvings + 2) / 2);
     while (chunks_of(horizon, l) > kMostChunks) l++;
     return l;
 }
@@ -1001,6 +1034,8 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
     A.off = L.off;
     A.mbr = L.mbr;
     A.flags = L.flags;
+    A.area2 = area2;
+    A.need = (float)(std::log(32.0 * std::min(L.k, kGroup)) * (double)wx * (double)wy);
     A.bxy = w.xy;
     A.bmeta = w.meta;
     A.brange = w.range;

@@ -71,3 +71,21 @@ def test_large_launches(pm, n, box):
     for ratio in (0.0, 600.0):
         got = pm.sign_binned(D, box, 0, k, cap, horizon=4000, bin_bits=6, walk_ratio=ratio)
         assert torch.equal(got, walk), ratio
+
+
+@pytest.mark.parametrize("k", [1, 4, 64, 65])
+@pytest.mark.parametrize("frac", [0.02, 0.25, 1.0])
+def test_first_samples_alone(pm, k, frac):
+    """Polygons whose first hits are expected in the first samples of a chunk,
+    among them slivers that fill little of their MBR."""
+    import torch
+    side = 1 << 22
+    rng = np.random.default_rng([k, int(100 * frac)])
+    star = [dg.star_polygons(rng, [n], [[side // 2, side // 2]], [frac * side / 2]).xy for n in (3, 40, 300, 1500)]
+    sliver = [np.array([[0, 0], [side - 1, int(side * frac)], [side - 1, int(side * frac) + w]]) for w in (9, 900, 90_000)]
+    D = pm.to_device(dg.from_list(star + sliver))
+    box = (0, 0, side - 1, side - 1)
+    walk = pm.sign(D, box, 3, k, 1 << 18)
+    for bits in (3, 5, 6):
+        got = pm.sign_binned(D, box, 3, k, 1 << 18, horizon=1 << 18, bin_bits=bits, walk_ratio=0.0)
+        assert torch.equal(got, walk), bits

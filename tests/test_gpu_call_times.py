@@ -138,3 +138,22 @@ def test_binning_of_samples(pm):
                                                rebin=r)) for r in (True, False))
     fill = _us(lambda: ws[:12 * k * h].fill_(1))
     assert first - again <= 5.5 * fill, (first, again, fill)
+
+
+def test_lookup_of_few_hashes(pm):
+    """100 large polygons' lookups of 16 hashes against 256, which read many
+    samples at a time and so have fewer tested past their first hits."""
+    import torch
+    rng = np.random.default_rng(10)
+    box = (0, 0, (1 << 24) - 1, (1 << 24) - 1)
+    D = pm.to_device(dg.star_polygons(rng, rng.integers(40, 110, 100), rng.integers(3 << 20, 13 << 20, (100, 2)),
+                                      rng.uniform(0.02, 0.15, 100) * (1 << 24)))
+
+    def call(k):
+        h, b = pm.binned_params(D, box, k, 1 << 22, 0.0)
+        ws = torch.empty(pm.sign_binned_workspace_size(100, k, 1 << 22, h, b), dtype=torch.uint8, device="cuda")
+        sign = lambda r: pm.sign_binned(D, box, 0, k, 1 << 22, horizon=h, bin_bits=b, walk_ratio=0.0, ws=ws, rebin=r)
+        sign(True)
+        return _us(lambda: sign(False))
+    few, many = call(16), call(256)
+    assert few <= 0.75 * many, (few, many)
