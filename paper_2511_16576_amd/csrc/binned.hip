@@ -36,7 +36,7 @@ namespace {
 
 constexpr int kRecBatch = 128;      // points tested together against edges with their products
 constexpr int kQueue = 256;        // per-wavefront queue of membership tests
-constexpr int kGroup = 256;        // hashes a lookup workgroup at most
+constexpr int kGroup = 256;        // hashes a lookup workgroup at most, see group_hashes
 constexpr int kBinLog = 13;        // log2 of the samples a workgroup of k_bin takes
 constexpr uint32_t kNone = 0xffffffffu;
 constexpr int kRound0 = 8;         // chunks of a lookup's first rounds at most
@@ -45,6 +45,7 @@ constexpr int kXcds = 8;           // workgroups are handed to the XCDs in turn
 struct BinArgs {
     uint64_t seed;
     int32_t k;
+    int32_t hashes;                // of a group
     uint32_t horizon;              // samples per hash (j < horizon), <= cap
     int32_t nchunks;
     int32_t lchunk;                // chunk C = 2^lchunk samples
@@ -102,7 +103,7 @@ __global__ __launch_bounds__(1024) void k_bin(BinArgs A)
     const int lh = kBinLog - A.lchunk;
     const int h0 = lh >= 0 ? (int)blockIdx.y << lh : (int)(blockIdx.y >> -lh);
     const uint32_t i0 = lh >= 0 ? 0u : (blockIdx.y & ((1u << -lh) - 1)) << kBinLog;
-    const int g = h0 / kGroup;
+    const int g = h0 / A.hashes;
     const size_t gc = (size_t)g * A.nchunks + c;
     if (tid < 256) s_cnt[tid] = 0;
     __syncthreads();
@@ -121,7 +122,7 @@ __global__ __launch_bounds__(1024) void k_bin(BinArgs A)
             // 64-bit shifts: a 2^32-wide side with one cell shifts by 32
             const int cy = (int)((uint64_t)o[u].y >> A.sby);
             part[u] = A.by_row ? cy : cy << A.bits | (int)((uint64_t)o[u].x >> A.sbx);
-            meta[u] = (uint32_t)(h % kGroup) << 24 | i;
+            meta[u] = (uint32_t)(h - g * A.hashes) << 24 | i;
             rank[u] = atomicAdd(&s_cnt[part[u]], 1u);
         }
     }
@@ -207,7 +208,7 @@ __global__ __launch_bounds__(1024) void k_bin_row(BinArgs A)
     uint32_t *meta = A.meta + gc * A.per + e0;
     uint2 *range = A.range + (gc << (A.bits + A.cbits)) + (row << A.cbits);
     const int64_t list = A.list0 + blockIdx.y, g = list / A.nchunks, c0 = (list - g * A.nchunks) << A.lchunk;
-    if (tid < kGroup) s_key[tid] = stream_key(A, (int)g * kGroup + tid);
+    if (tid < kGroup) s_key[tid] = stream_key(A, (int)g * A.hashes + tid);
     __syncthreads();
     auto sample = [&](uint32_t m) { return sample_at<POW2>(A, s_key[m >> 24], (uint64_t)c0 + (m & 0xffffffu)); };
     if (n > kMost) {
@@ -272,6 +273,7 @@ struct LookupArgs {
     uint32_t per;
     uint32_t *sig;
     uint32_t *unresolved;          // [n] 1: a hash needs the walk, 2: the whole polygon is walked
+    int32_t hashes;                // of a group
     const int32_t *order;          // [n] polygons in the order their workgroups start
     int32_t by_place;              // the order is along the plane: a stretch of it an XCD
     int64_t n;
@@ -549,8 +551,8 @@ __device__ void lookup_polygon(const LookupArgs &A, const int4 *s_edges, const i
     }
 }
 
-// One workgroup of 64 * W threads (W = min(4, ceil(k / 64)) wavefronts) per
-// (polygon, group of 64 W hashes).
+// One workgroup per (polygon, group of hashes), with a thread a hash rounded up
+// to wavefronts.
 __global__ __launch_bounds__(256) void k_bin_lookup(LookupArgs A)
 {
     extern __shared__ int4 s_edges[];
@@ -559,7 +561,7 @@ __global__ __launch_bounds__(256) void k_bin_lookup(LookupArgs A)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int per = blockDim.x;
-    const int groups = (A.k + per - 1) / per;
+    const int groups = (A.k + A.hashes - 1) / A.hashes;
     // workgroups start in order of their index, index b on XCD b % kXcds
     int64_t at = blockIdx.x / groups;
     if (A.by_place) {
@@ -569,8 +571,8 @@ __global__ __launch_bounds__(256) void k_bin_lookup(LookupArgs A)
     }
     // read through a vector load, made uniform so that what follows is scalar
     const int64_t p = __builtin_amdgcn_readfirstlane(A.order[at]);
-    const int i = (int)(blockIdx.x % groups) * per + tid;
-    const bool active = i < A.k;
+    const int i = (int)(blockIdx.x % groups) * A.hashes + tid;
+    const bool active = tid < A.hashes && i < A.k;
     if (A.unresolved[p] & 2u) return;    // walked (uniform per workgroup, before any barrier)
     const int64_t a = (int64_t)dpp::readlane64((uint64_t)A.off[p], 0);
     const int32_t n = __builtin_amdgcn_readfirstlane((int32_t)(A.off[p + 1] - a));
@@ -868,14 +870,27 @@ bool horizon_fits(uint32_t horizon, int32_t bits)
     return chunks_of(horizon, std::min(12, std::max(8, 2 * bits))) <= kMostChunks;
 }
 
+int64_t hash_groups(int32_t k) { return (k + kGroup - 1) / kGroup; }
+
 int chunk_log2(int32_t bits, int32_t k, uint32_t horizon)
 {
     int l = std::max(8, bits + 4);
+    // (a little more than half, which k_bin_row's threads still hold, as half)
     int halvings = 0;
-    for (int h = k; 2 * h <= kGroup; h *= 2) halvings++;
+    for (int64_t h = (k + hash_groups(k) - 1) / hash_groups(k); 2 * h <= kGroup + kGroup / 16; h *= 2) halvings++;
     l += std::min(halvings, (halvings + 2) / 2);
     while (chunks_of(horizon, l) > kMostChunks) l++;
     return l;
+}
+
+// Hashes of a group: k spread evenly, whole workgroups of k_bin, so that one
+// hash more than a multiple of 256 does not cost the bins of 256.
+int group_hashes(int32_t k, int lchunk)
+{
+    const int64_t groups = hash_groups(k);
+    if (groups == 1) return k;
+    const int64_t step = (int64_t)1 << std::max(0, kBinLog - lchunk);
+    return (int)(((k + groups - 1) / groups + step - 1) / step * step);
 }
 
 // k_bin files straight by cell while its 8,192 samples leave 32 a cell.
@@ -885,7 +900,7 @@ int col_bits(int32_t bits, int lx) { return bits + (bins_by_row(bits) && lx >= b
 int64_t bin_parts(int32_t bits) { return (int64_t)1 << (bins_by_row(bits) ? bits : 2 * bits); }
 
 // Samples of a (group, chunk).
-int64_t group_samples(int32_t k, int lchunk) { return (int64_t)std::min(k, kGroup) << lchunk; }
+int64_t group_samples(int32_t k, int lchunk) { return (int64_t)group_hashes(k, lchunk) << lchunk; }
 
 struct BinnedWs {
     uint2 *xy;
@@ -901,7 +916,7 @@ BinnedWs carve_binned(Carve &c, int32_t k, uint32_t horizon, int32_t bits, int64
 {
     const int lchunk = chunk_log2(bits, k, horizon);
     const int64_t nchunks = chunks_of(horizon, lchunk);
-    const int64_t lists = (int64_t)((k + kGroup - 1) / kGroup) * nchunks, samples = lists * group_samples(k, lchunk);
+    const int64_t lists = hash_groups(k) * nchunks, samples = lists * group_samples(k, lchunk);
     const int64_t cells = (int64_t)1 << (2 * bits + (bins_by_row(bits) ? 2 : 0));
     BinnedWs w{};
     w.xy = c.take<uint2>((size_t)samples);
@@ -943,6 +958,7 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
     BinArgs B{};
     B.seed = L.seed;
     B.k = L.k;
+    B.hashes = group_hashes(L.k, lchunk);
     B.horizon = horizon;
     B.nchunks = (int32_t)nchunks;
     B.lchunk = lchunk;
@@ -966,7 +982,7 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
     // with the same arguments); the lookup clamps every stretch to its chunk,
     // so bins that are not there give wrong values, never a stray read
     if (rebin) {
-        const int64_t lists = (int64_t)((L.k + kGroup - 1) / kGroup) * nchunks;
+        const int64_t lists = hash_groups(L.k) * nchunks;
         const int64_t ys = lchunk <= kBinLog ? (L.k + (1 << (kBinLog - lchunk)) - 1) >> (kBinLog - lchunk)
                                              : (int64_t)L.k << (lchunk - kBinLog);
         const dim3 bgrid((unsigned)nchunks, (unsigned)ys);
@@ -996,9 +1012,8 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
     }
     polymh_status st = check_launch("sign_binned: bin");
     if (st) return st;
-    // one workgroup per (polygon, group of up to 256 hashes)
-    const int64_t waves = (L.k + 63) / 64 < 4 ? (L.k + 63) / 64 : 4;
-    const int64_t per = 64 * waves, groups = (L.k + per - 1) / per;
+    // one workgroup per (polygon, group of hashes)
+    const int64_t per = (B.hashes + 63) / 64 * 64, groups = hash_groups(L.k);
     const int64_t units = L.n * groups;
     const double walk_edges = (double)L.cfg.lds_edges;
     // the order and the cap on a lookup's tests serve small launches, where a
@@ -1035,7 +1050,7 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
     A.mbr = L.mbr;
     A.flags = L.flags;
     A.area2 = area2;
-    A.need = (float)(std::log(32.0 * std::min(L.k, kGroup)) * (double)wx * (double)wy);
+    A.need = (float)(std::log(32.0 * B.hashes) * (double)wx * (double)wy);
     A.bxy = w.xy;
     A.bmeta = w.meta;
     A.brange = w.range;
@@ -1043,6 +1058,7 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
     A.sig = L.sig;
     A.unresolved = w.unresolved;
     A.order = w.order;
+    A.hashes = B.hashes;
     A.by_place = ordered ? 0 : 1;
     A.n = L.n;
     A.k = L.k;
