@@ -204,12 +204,13 @@ polymh_status polymh_join_rings(const int32_t *xy, int64_t n_vertices, const int
 /* polymh_sign_binned -- the same signatures as polymh_sign, bit for bit,
  * computed from shared samples: every polygon reads the same point stream
  * per hash (Sec. 3.2's fixed-seed generators; Def. 2), so for every hash the
- * samples j < horizon are drawn once, in chunks of a few hundred, and each
- * chunk's samples of up to 256 hashes are grouped by cell of a 2^bin_bits x
- * 2^bin_bits grid over B.  A (polygon, hash) takes the smallest j whose
- * sample, in the cells under its MBR, is inside the polygon; units with no such sample below the horizon (and polygons
- * needing them) are walked as in polymh_sign.  Work per unit is then about
- * the samples that fall in its cells instead of the N_B / N_P draws of a
+ * samples j < horizon are drawn once, in chunks of 256 to 32,768,
+ * and each chunk's samples of up to 256 hashes are grouped by cell of a
+ * 2^bin_bits x 2^bin_bits grid over B.  A (polygon, hash) takes the smallest j
+ * whose sample, in the cells under its MBR, is inside the polygon; units with
+ * no such sample below the horizon (and polygons needing them) are walked as
+ * in polymh_sign.  Work per unit is then about the samples that fall in its
+ * cells instead of the N_B / N_P draws of a
  * walk (Thm. 2).
  *   horizon  samples drawn per hash (clamped to cap); a horizon of about 16
  *            times the largest N_B / N_P of the set leaves almost no walk.
@@ -224,8 +225,8 @@ polymh_status polymh_join_rings(const int32_t *xy, int64_t n_vertices, const int
  *            persistent form, at most 16 hashes a work item); lds_edges is
  *            also the lookup's edge cache (polygons beyond it are walked
  *            when walk_ratio > 0).
- *   ws       polymh_sign_binned_workspace_size(...) bytes: about
- *            13 * k * horizon bytes of binned samples.
+ *   ws       polymh_sign_binned_workspace_size(...) bytes: about 12.5 * k *
+ *            horizon bytes of binned samples (16 with one hash).
  * POLYMH_EINVAL for k > 65535, bin_bits outside 0..6, horizon < 1 or a
  * negative walk_ratio.
  * Stream-ordered. */

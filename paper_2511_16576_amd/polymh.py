@@ -337,8 +337,8 @@ def binned_params(polys: DevicePolys, box, k: int, cap: int, walk_ratio: float =
                   max_bytes: int = 1 << 31):
     """(horizon, bin_bits) for sign_binned from the set's shape: the horizon
     covers about 16 expected first-hit indices N_B / N_P (Thm. 2) of the
-    polygon at the 0.1% smallest area, within ``max_bytes`` of binned
-    samples; the grid side puts about two cells across the median MBR side
+    polygon at the 0.1% smallest area, as far as the binned samples fit in
+    ``max_bytes``; the grid side puts about two cells across the median MBR side
     of the polygons the lookup signs (|B| / area >= ``walk_ratio``).  A
     host-side choice: the signatures do not depend on it."""
     mbr, area2, _ = prepare(polys)
@@ -349,15 +349,25 @@ def binned_params(polys: DevicePolys, box, k: int, cap: int, walk_ratio: float =
     if a.size == 0:
         return min(cap, 256), 0
     p_small = max(float(np.quantile(a, 0.001)) / (wx * wy), 1e-12)
-    horizon = int(min(cap, 16.0 / p_small, max_bytes // (10 * k)))
-    horizon = max(256, (horizon + 255) // 256 * 256) if horizon < cap else cap
     m = mbr.double().cpu().numpy()
     binned = (a_all > 0) & (wx * wy >= walk_ratio * a_all)
     if binned.any():
         m = m[binned]
     side = float(np.median(np.maximum(m[:, 2] - m[:, 0], m[:, 3] - m[:, 1]) + 1.0))
     bits = int(np.clip(np.round(np.log2(max(wx, wy) / max(side, 1.0))) + 1, 0, 6))
-    return horizon, bits
+    return _binned_horizon(k, cap, bits, int(min(cap, 16.0 / p_small)), max_bytes), bits
+
+
+def _binned_horizon(k: int, cap: int, bits: int, horizon: int, max_bytes: int) -> int:
+    """The horizon in steps of 256 samples, or ``cap``, whose bins take at most
+    ``max_bytes`` (256 samples at least)."""
+    horizon = max(256, (horizon + 255) // 256 * 256) if horizon < cap else cap
+    while horizon > 256:
+        size = sign_binned_workspace_size(0, k, cap, horizon, bits)
+        if size <= max_bytes:
+            break
+        horizon = max(256, min(horizon - 1, horizon * max_bytes // size) // 256 * 256)
+    return horizon
 
 
 def binned_config(polys: DevicePolys) -> SignConfig:
