@@ -27,6 +27,8 @@
 // samples inside the polygon's MBR on edges straddling py, so each product is
 // bounded by the MBR's width * height; for sides below 2^26 the FP64 product
 // and fused multiply-add are exact.  Wider polygons use 128-bit integers.
+#include <algorithm>
+
 #include "internal.hpp"
 #include "sign_common.hpp"
 
@@ -292,14 +294,21 @@ int log2_exact(uint64_t w)
 // polygons are spread over the chip (at 10 polygons of 128 hashes 33 us
 // instead of 112 with a polygon an item, at 1,000 polygons 86 instead of
 // 256), a large set's edges are staged once (at 10,000 polygons 421 us with a
-// polygon an item, 457 with 32 hashes, at 100,000 3,840 and 4,350).
+// polygon an item, 457 with 32 hashes, at 100,000 3,840 and 4,350).  A
+// polygon's items are of one size: 3,000 polygons of 128 hashes with eight
+// wavefronts an item 176 us by 64 hashes, 234 by 96 and 32.
 int32_t sign_hash_block(const polymh_sign_config &c, int64_t n, int32_t k)
 {
     int64_t hb = c.hash_block;
     if (hb <= 0) {
-        hb = (n + cu_count() - 1) / cu_count() * (c.block_threads / 64);
+        const int64_t waves = c.block_threads / 64;
+        hb = (n + cu_count() - 1) / cu_count() * waves;
         const int64_t least = (n * k + (1 << 22) - 1) >> 22;  // a grid's limit is far
         if (hb < least) hb = least;
+        if (hb < k) {
+            const int64_t items = (k + hb - 1) / hb, even = (k + items - 1) / items;
+            hb = std::max(least, (even + waves - 1) / waves * waves);
+        }
     }
     return hb > k ? k : (int32_t)hb;
 }

@@ -157,3 +157,15 @@ def test_lookup_of_few_hashes(pm):
         return _us(lambda: sign(False))
     few, many = call(16), call(256)
     assert few <= 0.75 * many, (few, many)
+
+
+def test_signing_by_even_items(pm):
+    """3,000 polygons of 128 hashes in workgroups of 512: the library's choice of
+    hashes a work item against halves."""
+    rng = np.random.default_rng(11)
+    box = (0, 0, (1 << 24) - 1, (1 << 24) - 1)
+    D = pm.to_device(dg.star_polygons(rng, rng.integers(40, 110, 3000), rng.integers(3 << 20, 13 << 20, (3000, 2)),
+                                      rng.uniform(0.02, 0.15, 3000) * (1 << 24)))
+    auto, even = (_us(lambda: pm.sign(D, box, 0, 128, 1 << 22, config=pm.sign_config(block_threads=512, hash_block=h)))
+                  for h in (0, 64))
+    assert auto <= 1.15 * even, (auto, even)
