@@ -1,8 +1,8 @@
 """Launch-shape autotuner for the signing kernel.
 
-Times every candidate configuration (persistent or plain launch, workgroup
-size, hashes per work item, LDS edge capacity, samples per lane, blocks per
-CU) on a seeded sample of the workload with HIP events, checks that each
+Times every candidate configuration (longest polygons first or in their
+order, workgroup size, hashes per work item, LDS edge capacity, samples per
+lane, and where work items are popped from a queue, blocks per CU) on a seeded sample of the workload with HIP events, checks that each
 produces the same signatures as the default shape, and caches the fastest
 per workload fingerprint in a JSON file (POLYMH_TUNE_CACHE, default
 ~/.cache/polymh/sign_tune.json)."""
@@ -51,6 +51,20 @@ def _time(D, box, seed, k, cap, cfg, out, ws, reps):
     return e0.elapsed_time(e1) / reps
 
 
+def shapes(space, n: int, k: int):
+    """Every shape of the space that n polygons of k hashes launch differently:
+    blocks_per_cu counts where a persistent launch pops its work items from a
+    queue, which it does only if a grid of 2^32 threads cannot hold them."""
+    names = list(space)
+    for values in itertools.product(*(space[name] for name in names)):
+        c = dict(zip(names, values))
+        hb = c["hash_block"]
+        # left to the library, about 2^22 items at most
+        queued = c["persistent"] and hb > 0 and n * -(-k // min(hb, k)) > (2 ** 32 - 1) // c["block_threads"]
+        if queued or c["blocks_per_cu"] == space["blocks_per_cu"][0]:
+            yield c
+
+
 def tune_sign(polys, box, seed: int, k: int, cap: int, sample: int = 20000, reps: int = 3,
               space=None, use_cache: bool = True, log=None):
     """Best signing launch shape for this workload; returns (config, report)."""
@@ -73,10 +87,7 @@ def tune_sign(polys, box, seed: int, k: int, cap: int, sample: int = 20000, reps
     ref = pm.sign(D, box, seed, k, cap).clone()
     best, results = None, []
     ws = None
-    for values in itertools.product(*(space[n] for n in names)):
-        cfg_d = dict(zip(names, values))
-        if not cfg_d["persistent"] and cfg_d["blocks_per_cu"] != space["blocks_per_cu"][0]:
-            continue   # blocks_per_cu only shapes the persistent grid
+    for cfg_d in shapes(space, D.n, k):
         cfg = pm.sign_config(**cfg_d)
         need = pm.sign_workspace_size(D.n, cfg)
         if ws is None or ws.numel() < need:
