@@ -319,7 +319,7 @@ __global__ __launch_bounds__(kTileThreads) void k_mlp_back(int64_t tiles, int64_
 // tile a wavefront read from memory.
 constexpr int kGradRows = 64;                       // batch rows a step
 constexpr int kGradStride = kGradRows + 8;
-constexpr int kMaxSplit = 32;
+constexpr int kMaxSplit = 64;
 constexpr int64_t kW2Size = (int64_t)kHid * kHid, kW1Size = (int64_t)kHid * kIn;
 
 template <int N>
@@ -556,11 +556,25 @@ polymh_status launch_mlp_forward(const uint16_t *X, int64_t B, const float *para
 // partial sums of k_mlp_back and k_wgrad.
 constexpr int kMaxBack = 512;                    // workgroups of k_mlp_back at most
 
+// Steps of a split: at least two, and four rather than more than 32 splits
+// (8,192 rows 256 workgroups), until there are kMaxSplit, so that a partial sum
+// adds no more than 256 rows up to 16,384.
+int64_t split_steps(int64_t B)
+{
+    const int64_t steps = (B + kGradRows - 1) / kGradRows;
+    return std::max({(int64_t)2, std::min((int64_t)4, (steps + 31) / 32), (steps + kMaxSplit - 1) / kMaxSplit});
+}
+// The most splits of any batch up to B.
+int64_t most_splits(int64_t B)
+{
+    return std::min<int64_t>(kMaxSplit, std::max<int64_t>(32, (B + 4 * kGradRows - 1) / (4 * kGradRows)));
+}
+
 size_t mlp_backward_scratch_bytes(int64_t B)
 {
     return 2 * align_up((size_t)B * kHid * 2, 256) + align_up((size_t)kW2Size * 2, 256) +
            align_up((size_t)kMaxBack * kBackItems * 4, 256) +
-           align_up((size_t)kMaxSplit * (kW1Size + kW2Size) * 4, 256) + 256;
+           align_up((size_t)most_splits(B) * (kW1Size + kW2Size) * 4, 256) + 256;
 }
 
 polymh_status launch_mlp_backward(const uint16_t *X, int64_t B, const float *params,
@@ -581,9 +595,7 @@ polymh_status launch_mlp_backward(const uint16_t *X, int64_t B, const float *par
     hipLaunchKernelGGL(k_transpose_w2, dim3(64), dim3(256), 0, s, w2, w2t);
     hipLaunchKernelGGL(k_mlp_back, dim3(nback), dim3(kTileThreads), 0, s, tiles, B, params, w2t, a.z1, a.z2, a.h2,
                        label, a.y, dz1, dz2, bpart);
-    // at most kMaxSplit splits of a whole number of steps, at least two
-    const int64_t steps = (B + kGradRows - 1) / kGradRows;
-    const int64_t kc = std::max<int64_t>(2, (steps + kMaxSplit - 1) / kMaxSplit) * kGradRows;
+    const int64_t kc = split_steps(B) * kGradRows;
     const int nsplit = (int)((B + kc - 1) / kc);
     hipLaunchKernelGGL(k_wgrad, dim3(nsplit, kHid / 64, 2), dim3(256), 0, s, dz1, dz2,
                        reinterpret_cast<const __bf16 *>(X), a.h1, B, kc, wpart);
