@@ -619,8 +619,12 @@ polymh_status launch_index_build(const uint64_t *keys, int64_t n, int32_t b, voi
         return set_error(POLYMH_ECAPACITY, "index_build: workspace of %zu bytes, need %zu", ws_bytes, cv.used);
     B.tickets = B.hist + kDigits * kRadix;
     B.n_long = B.tickets + kDigits;
-    const bool in_place = reinterpret_cast<const char *>(keys) < reinterpret_cast<const char *>(sorted_keys + m) &&
-                          reinterpret_cast<const char *>(sorted_keys) < reinterpret_cast<const char *>(keys + m);
+    const auto meets = [&](const void *out, size_t bytes) {
+        const char *k = reinterpret_cast<const char *>(keys), *o = static_cast<const char *>(out);
+        return k < o + bytes && o < k + (size_t)m * sizeof(*keys);
+    };
+    const bool in_place = meets(sorted_keys, (size_t)m * sizeof(*sorted_keys)) ||
+                          meets(sorted_ids, (size_t)m * sizeof(*sorted_ids));
     const int cus = cu_count();
     auto grid = [](int64_t items, int64_t per, int64_t most) {
         int64_t g = (items + per - 1) / per;
