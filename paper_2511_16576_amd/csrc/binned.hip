@@ -20,7 +20,7 @@
 // are staged once in LDS and every membership test reads them as broadcasts;
 // samples inside the MBR are queued per wavefront and tested 64 at a time,
 // one point per lane.  Bound: VALU issue (about 70% busy).  2 M polygons of
-// 22 vertices at k = 256: 40 ms; 76 with bins a hash, lane = hash (64 places
+// 22 vertices at k = 256: 33 ms; 76 with bins a hash, lane = hash (64 places
 // of memory a read, and a wavefront as slow as the hash with most samples),
 // and 100 before the polygons were ordered along the plane.
 #include <algorithm>
@@ -39,7 +39,6 @@ constexpr int kQueue = 256;        // per-wavefront queue of membership tests
 constexpr int kGroup = 256;        // hashes a lookup workgroup at most, see group_hashes
 constexpr int kBinLog = 13;        // log2 of the samples a workgroup of k_bin takes
 constexpr uint32_t kNone = 0xffffffffu;
-constexpr int kRound0 = 8;         // chunks of a lookup's first rounds at most
 constexpr int kXcds = 8;           // workgroups are handed to the XCDs in turn
 
 struct BinArgs {
@@ -452,19 +451,21 @@ __device__ __forceinline__ void take(const LookupArgs &A, const int4 *s_edges, c
 // stretch of (chunk l / rows of the round, grid row l % rows), the
 // wavefronts take 64 samples at a time in turn.  After a round, a hash with a
 // hit is settled (all smaller indices have been seen); the workgroup is done
-// when all are.  Rounds grow, as what is left open shrinks: the barriers and
-// the ranges' latency are paid once a round, the samples of settled hashes
-// read on the way cost one compare.  Every wavefront takes part; all
+// when all are.  Rounds double what was read, as what is left open shrinks: the
+// barriers and the ranges' latency are paid once a round, the samples of
+// settled hashes read on the way cost one compare.  Every wavefront takes part; all
 // arguments but `active`, tid and lane are wavefront-uniform.
+//
 // `need` samples a hash hold the first hits of all hashes of 31 workgroups in
-// 32, so the first round takes no more chunks than those fill.  Where they are
-// less than most of one chunk, and it is a long one (at most 64 hashes, one
-// wavefront), only they are tested at first; if a hash is then open, the chunk
-// is read again, whole.  3,000 large polygons at 4 hashes take 317 us, 535
-// without the bound; 100 of 75 edges at 16 hashes 162, 274 without it, 444
-// with longer chunks and rounds of kRound0 too.  With 128 hashes, whose chunk
-// is half as long, reading one twice costs more than that saves (3,000 large
-// polygons 1,450 us, 1,657 with it).
+// 32, so the first round takes the chunks that those fill: 2 M polygons of 22
+// vertices 39.2 ms, 44.5 with eight chunks for all of them, 41.0 with eight at
+// most.  Where they are less than most of one chunk, and it is a long one (at
+// most 64 hashes, one wavefront), only they are tested at first; if a hash is
+// then open, the chunk is read again, whole.  3,000 large polygons at 4 hashes
+// take 317 us, 535 without the bound; 100 of 75 edges at 16 hashes 162, 274
+// without it, 444 with longer chunks and rounds of eight too.  With 128 hashes,
+// whose chunk is half as long, reading one twice costs more than that saves
+// (3,000 large polygons 1,450 us, 1,657 with it).
 template <int MODE>
 __device__ void lookup_polygon(const LookupArgs &A, const int4 *s_edges, const int32_t *pxy, int32_t n, Scan &S, int cx0,
                                int cx1, int cy0, int cy1, bool active, int tid, int lane, int wave, int waves, int group, float need)
@@ -475,7 +476,7 @@ __device__ void lookup_polygon(const LookupArgs &A, const int4 *s_edges, const i
     const int most = max(1, min(64 / rows, (int)((1u << 26) / A.per)));
     S.sub_shift = most > 1 ? 26 : 31;
     const int sub = lane / rows, row = (cy0 + lane % rows) << A.cbits;
-    int m = min(most, max(1, (int)fminf(ceilf(ldexpf(need, -A.lchunk)), (float)kRound0)));
+    int m = max(1, (int)fminf(ceilf(ldexpf(need, -A.lchunk)), (float)most));
     uint32_t bound = kNone;
     if (waves == 1 && need < 0.75f * (float)(1u << A.lchunk)) {
         bound = (uint32_t)need + 1;
@@ -546,7 +547,7 @@ __device__ void lookup_polygon(const LookupArgs &A, const int4 *s_edges, const i
             __syncthreads();
         } else {
             c0 += m;
-            m = min(most, max(kRound0, c0));
+            m = min(most, max(m, c0));
         }
     }
 }
@@ -681,8 +682,8 @@ __global__ __launch_bounds__(256) void k_order_count(const int64_t *__restrict__
 }
 
 // Dispatch order of a large launch: along the Z-order curve of the polygons'
-// MBR centres (64 x 64 cells), walked polygons last.  A (polygon, hash) unit
-// reads a few lines of that hash's bins; polygons of one place read the same
+// MBR centres (64 x 64 cells; walked polygons, whose workgroups return at once,
+// among the others).  A (polygon, hash) unit reads a few lines of that hash's bins; polygons of one place read the same
 // lines, and started together they find them in their XCD's L2.
 // A counting sort: a block counts its stretch of the polygons in LDS and adds
 // one number a cell to the totals (k_place_count), then reserves its range of
@@ -1023,8 +1024,8 @@ polymh_status launch_sign_binned(const SignLaunch &L, const int64_t *area2, uint
                        (double)wx * (double)wy, walk_ratio, walk_edges,
                        ordered ? kLookupTestCap : INFINITY, w.unresolved);
     hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t *>(w.count), (int64_t)1);
-    // the lookup's dispatch order (after the classification: walked polygons
-    // last), in small launches only
+    // the lookup's dispatch order (after the classification: in a small launch
+    // walked polygons last)
     hipLaunchKernelGGL(k_zero_words, dim3(kOrderCells / 256), dim3(256), 0, s,
                        reinterpret_cast<uint32_t *>(w.cell_counts), (int64_t)kOrderCells);
     if (ordered) {
