@@ -138,14 +138,15 @@ typedef struct {
                                  by a persistent launch where a grid could
                                  not hold them, or where their count is on
                                  the device); 0: in the order given.        */
-    int32_t block_threads;    /* 64..1024, multiple of 64                     */
+    int32_t block_threads;    /* 64..512, multiple of 64                      */
     int32_t hash_block;       /* hashes per work item (1..k; 0 = the library's
                                  choice: all k in large sets, fewer in small
                                  ones, to fill the device)                  */
     int32_t lds_edges;        /* polygons with more edges stream them from
                                  global memory instead of LDS (64..8192)     */
     int32_t samples_per_lane; /* 1 or 2 draws per lane per tile step          */
-    int32_t blocks_per_cu;    /* grid of a persistent launch / CU count       */
+    int32_t blocks_per_cu;    /* grid of a launch that pops its items from a
+                                 queue / CU count                           */
 } polymh_sign_config;
 
 void polymh_sign_default_config(polymh_sign_config *cfg_host);
@@ -222,7 +223,7 @@ polymh_status polymh_join_rings(const int32_t *xy, int64_t n_vertices, const int
  *            chunk's samples); 0 bins every polygon.  A few hundred suits
  *            the walk's cost per draw.  The signatures do not depend on it.
  *   cfg      as polymh_sign for the walk of the polygons left to it (its
- *            persistent form, at most 16 hashes a work item); lds_edges is
+ *            persistent form; 8 hashes a work item in a small launch); lds_edges is
  *            also the lookup's edge cache (polygons beyond it are walked
  *            when walk_ratio > 0).
  *   ws       polymh_sign_binned_workspace_size(...) bytes: about 12.5 * k *
@@ -369,7 +370,7 @@ polymh_status polymh_refine_stats(const polymh_polys *data, const polymh_polys *
  *   top_ids [nq][topk] int32 out, top_j [nq][topk] double out.
  *   1 <= topk <= 1024: meant for the K of a recall@K, not for sorting whole
  *   lists (a list is read about four times whatever topk is, topk times where
- *   it is 3 or 4 at most, where entries are given twice, and where a J is not
+ *   it is 4 at most, where entries are given twice, and where a J is not
  *   finite or is -0).  Stream-ordered.
  */
 polymh_status polymh_topk(const int64_t *cand_off, const int32_t *cand_ids, const double *cand_j,

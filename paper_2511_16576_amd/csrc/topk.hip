@@ -8,8 +8,11 @@
 // ranked by counting, for each, the ones before it.  Bound: the latency of
 // the steps, typically two counts, one gather and one ranking whatever k is,
 // where selecting one entry a round takes k passes over the list: 64 lists of
-// 11,800 at k = 100 take 34 us (1,176 by rounds), 10,000 lists of 650 at
-// k = 10 85 us (157 by rounds).  Up to three or four entries go by rounds.
+// 11,800 at k = 100 take 35 us (1,175 by rounds), 10,000 lists of 650 at
+// k = 10 88 us (157 by rounds).  Where a step leaves no entry out, the next one
+// starts at the highest bit in which they differ, so that equal J cost one
+// count rather than four: 5,000 lists of 3,000 at k = 10 103 us where all J are
+// equal and 163 where they take eight values (301 and 292 digit by digit).
 #include "internal.hpp"
 
 #include <algorithm>
@@ -98,6 +101,8 @@ __global__ __launch_bounds__(1024) void k_topk(const int64_t *__restrict__ off, 
     int32_t *s_id = reinterpret_cast<int32_t *>(s_mem + keep);    // [keep]
     uint32_t *s_bin = reinterpret_cast<uint32_t *>(s_id + keep);  // [kBins]
     __shared__ uint32_t s_wave[16], s_count, s_digit, s_below, s_in;
+    __shared__ int32_t s_id_most;
+    __shared__ unsigned long long s_and, s_or;
     const int64_t q = blockIdx.x;
     const int64_t a = off[q], n = off[q + 1] - a;
     ids += a;
@@ -106,24 +111,30 @@ __global__ __launch_bounds__(1024) void k_topk(const int64_t *__restrict__ off, 
     top_j += q * k;
     const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
 
-    // The first few by rounds: 5,000 lists of 3,000 at k = 1 46 us (98 by
-    // digits, 276 if J takes 8 values), at k = 3 103 (98, 275), at k = 4 122
-    // (99, 278); one list of 100,000 37 and 86 us at k = 1 and 3 (113).  Short
-    // lists wait on the digits' steps rather than on memory and gain a little
-    // longer: 5,000 lists of 300 and of 500 at k = 4 49 and 52 us (65, 86), but
-    // at k = 8 83 and 87 (65, 86).
-    if (k <= 3 || (k == 4 && n <= 512)) {
-        select_by_rounds(ids, js, n, k, reinterpret_cast<double *>(s_mem), reinterpret_cast<int32_t *>(s_mem + nt),
-                         top_ids, top_j);
-        return;
-    }
     bool odd = n > INT32_MAX;
     int shift = 64, id_shift = 32;      // digits chosen so far end here
-    uint64_t pre = 0;
-    uint32_t id_pre = 0, below = 0;
-    // s: bits of J from the top, then bits of the id
-    for (int step = 0; n > keep && step < 9; step++) {
-        const bool on_id = step >= 6;
+    uint64_t pre = 0, all_and = ~0ull, all_or = 0;
+    uint32_t id_pre = 0, below = 0, left_in = (uint32_t)n;
+    int32_t id_most = 0;
+    if (tid == 0) {
+        s_and = ~0ull;
+        s_or = 0;
+        s_id_most = 0;
+    }
+    // bits of J from the top, then bits of the id
+    while (n > keep) {
+        const bool first_step = shift == 64, on_id = shift == 0;
+        if (on_id && id_shift == 32) {
+            // the ids' own bits
+            id_most = wave_max32(id_most);
+            if (lane == 0) atomicMax(&s_id_most, id_most);
+            __syncthreads();
+            id_shift = 32 - __builtin_clz((uint32_t)s_id_most | 1u);
+        }
+        if (on_id && id_shift == 0) {   // more than `keep` copies of one entry
+            odd = true;
+            break;
+        }
         const int hi = on_id ? id_shift : shift, lo = hi > 11 ? hi - 11 : 0;
         const uint32_t mask = (1u << (hi - lo)) - 1;
         for (int b = tid; b < kBins; b += nt) s_bin[b] = 0;
@@ -132,9 +143,15 @@ __global__ __launch_bounds__(1024) void k_topk(const int64_t *__restrict__ off, 
             const double j = js[c];
             const int32_t id = ids[c];
             const uint64_t key = key_of(j);
-            if (step == 0) odd |= !(fabs(j) <= DBL_MAX) || key == 1ull << 63 || id < 0;
-            const bool in = on_id ? key == pre && (id_shift == 32 || (uint32_t)id >> id_shift == id_pre)
-                                  : shift == 64 || key >> shift == pre;
+            if (first_step) {
+                odd |= !(fabs(j) <= DBL_MAX) || key == 1ull << 63 || id < 0;
+                id_most = max(id_most, id);
+            }
+            const bool in = on_id ? key == pre && (uint32_t)id >> id_shift == id_pre : first_step || key >> shift == pre;
+            if (!on_id && in) {
+                all_and &= key;
+                all_or |= key;
+            }
             // the lanes that share the first one's digit are counted together
             // (many J are 0), the others one by one: 5,000 lists of 500 zeros
             // at k = 100 129 us, 183 with every lane on its own; three turns
@@ -149,7 +166,7 @@ __global__ __launch_bounds__(1024) void k_topk(const int64_t *__restrict__ off, 
             }
             if (__builtin_amdgcn_inverse_ballot_w64(left)) atomicAdd(&s_bin[d], 1u);
         }
-        if (step == 0 ? __syncthreads_or(odd) : (__syncthreads(), 0)) {
+        if (first_step ? __syncthreads_or(odd) : (__syncthreads(), 0)) {
             odd = true;
             break;
         }
@@ -173,15 +190,37 @@ __global__ __launch_bounds__(1024) void k_topk(const int64_t *__restrict__ off, 
         below = s_below;
         const uint32_t in = s_in;
         if (on_id) {
-            id_pre = (id_shift == 32 ? 0u : id_pre << (hi - lo)) | s_digit;
+            id_pre = id_pre << (hi - lo) | s_digit;
             id_shift = lo;
         } else {
-            pre = (shift == 64 ? 0ull : pre << (hi - lo)) | s_digit;
+            pre = (first_step ? 0ull : pre << (hi - lo)) | s_digit;
             shift = lo;
+            // none left out: on to the highest bit in which they differ
+            if (in == left_in && shift > 0) {
+                for (int o = 32; o > 0; o >>= 1) {
+                    all_and &= __shfl_xor(all_and, o, 64);
+                    all_or |= __shfl_xor(all_or, o, 64);
+                }
+                if (lane == 0) {
+                    atomicAnd(&s_and, all_and);
+                    atomicOr(&s_or, all_or);
+                }
+                __syncthreads();
+                const uint64_t differ = s_and ^ s_or;
+                shift = differ ? 64 - __builtin_clzll(differ) : 0;
+                pre = s_and >> shift;
+                __syncthreads();
+                if (tid == 0) {
+                    s_and = ~0ull;
+                    s_or = 0;
+                }
+            }
+            all_and = ~0ull;
+            all_or = 0;
+            left_in = in;
         }
         __syncthreads();
         if (below + in <= (uint32_t)keep) break;
-        odd = step == 8;                // more than `keep` copies of one entry
     }
     // the entries up to the chosen prefix
     if (tid == 0) s_count = 0;
@@ -230,6 +269,18 @@ __global__ __launch_bounds__(1024) void k_topk(const int64_t *__restrict__ off, 
                          top_ids, top_j);
 }
 
+// The first few entries by rounds alone (a kernel of its own, as the registers
+// and the LDS of the one above cost it a fifth).
+__global__ __launch_bounds__(1024) void k_topk_few(const int64_t *__restrict__ off, const int32_t *__restrict__ ids,
+                                                   const double *__restrict__ js, int32_t k,
+                                                   int32_t *__restrict__ top_ids, double *__restrict__ top_j)
+{
+    extern __shared__ uint64_t s_mem[];
+    const int64_t q = blockIdx.x, a = off[q], n = off[q + 1] - a;
+    select_by_rounds(ids + a, js + a, n, k, reinterpret_cast<double *>(s_mem),
+                     reinterpret_cast<int32_t *>(s_mem + blockDim.x), top_ids + q * k, top_j + q * k);
+}
+
 }  // namespace
 
 polymh_status launch_topk(const int64_t *off, const int32_t *ids, const double *js, int64_t nq,
@@ -239,7 +290,18 @@ polymh_status launch_topk(const int64_t *off, const int32_t *ids, const double *
     if (nq > 0x7fffffffLL) return set_error(POLYMH_EINVAL, "topk: too many queries");
     // few lists: each spread over a CU's SIMDs; many: more lists in flight
     const int threads = nq < 1024 ? 1024 : 256;
-    const int keep = std::max(256, 2 * k);
+    // up to four entries by rounds: 5,000 lists of 300 at k = 1, 2 and 4 take 22,
+    // 28 and 42 us (47 by digits), of 3,000 44, 71 and 122 (110); one of 100,000
+    // 38, 62 and 112 (119); at k = 6 digits win (47 against 52, 110 against 173)
+    if (k <= 4) {
+        hipLaunchKernelGGL(k_topk_few, dim3((unsigned)nq), dim3(threads), (size_t)threads * 12, s, off, ids, js, k, top_ids,
+                           top_j);
+        return check_launch("topk");
+    }
+    // ranking takes the square of what is kept: 5,000 lists of 200 and of 500 at
+    // k = 10 take 54 and 49 us with 128, 71 and 91 with 256; with 64, lists of
+    // few values need a step more (10,000 of 650 and eight values 140, 117 us)
+    const int keep = std::max(128, 2 * k);
     const size_t lds = std::max((size_t)keep * 12 + kBins * sizeof(uint32_t), (size_t)threads * 12);
     hipLaunchKernelGGL(k_topk, dim3((unsigned)nq), dim3(threads), lds, s, off, ids, js, k, keep, top_ids, top_j);
     return check_launch("topk");

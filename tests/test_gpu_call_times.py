@@ -109,6 +109,21 @@ def test_topk_of_zeros(pm):
     assert zero <= 1.7 * rand, (zero, rand)
 
 
+@pytest.mark.parametrize("values", [1, 8])
+def test_topk_of_few_values(pm, values):
+    """The best ten of 5,000 lists of 3,000 whose J take few values, against
+    lists of random J."""
+    import torch
+    nq, n = 5000, 3000
+    g = torch.Generator(device="cuda").manual_seed(12)
+    ids = torch.arange(n, dtype=torch.int32, device="cuda").repeat(nq)
+    off = torch.arange(nq + 1, dtype=torch.int64, device="cuda") * n
+    few = torch.randint(0, values, (nq * n,), generator=g, device="cuda").double() / values
+    rand = torch.rand(nq * n, generator=g, dtype=torch.float64, device="cuda")
+    a, b = (_us(lambda: pm.topk(off, ids, js, 10)) for js in (few, rand))
+    assert a <= 2.1 * b, (a, b)
+
+
 def test_join_of_a_large_ring(pm):
     """One ring of 300,000 vertices: copying it takes no longer than staging it,
     which reads as much and computes besides."""
