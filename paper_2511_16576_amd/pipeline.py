@@ -216,8 +216,12 @@ class QueryBatch:
     def result(self):
         # the run's own stream, or, for a graph launched on another, the
         # caller's: the flag is copied out at the run's end
-        self.stream.synchronize()
         torch.cuda.current_stream(self.overflow.device).synchronize()
+        return self._checked()
+
+    def _checked(self):
+        """The answer once the caller's stream is done."""
+        self.stream.synchronize()
         if int(self._overflow_host[0]):
             raise RuntimeError("candidate capacity exceeded; rebuild the batch with a larger cand_cap")
         return self.top_ids, self.top_j
@@ -355,7 +359,8 @@ class SplitBatch:
         self.graph.launch()
 
     def result(self):
-        res = [p.result() for p in self.parts]
+        torch.cuda.current_stream(self.parts[0].overflow.device).synchronize()
+        res = [p._checked() for p in self.parts]
         ids, js = torch.cat([r[0] for r in res]), torch.cat([r[1] for r in res])
         if self.perm is not None:
             # row r holds query perm[r]: back to the given order
