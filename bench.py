@@ -403,10 +403,9 @@ def bin_lookup_bytes(Q, qsig, box, horizon, bits, walk_ratio, lds_edges):
     wx, wy = float(box[2]) - box[0] + 1, float(box[3]) - box[1] + 1
     lx, ly = int(round(np.log2(wx))), int(round(np.log2(wy)))
     k = qsig.shape[1]
-    C = 2.0 ** max(8, bits + 4)
-    group = min(k, 256)
-    while 2 * group <= 256:                       # chunks of few hashes hold more samples
-        group, C = 2 * group, 2 * C
+    group = -(-k // -(-k // 256))
+    halvings = int(np.log2(272 // group)) if group <= 136 else 0
+    C = 2.0 ** (max(8, bits + 4) + min(halvings, (halvings + 2) // 2))    # chunks of few hashes hold more samples
     nchunks = np.ceil(horizon / C)
     area = np.abs(area2.astype(np.float64)) / 2
     n = (Q.offsets[1:] - Q.offsets[:-1]).cpu().numpy().astype(np.float64)
