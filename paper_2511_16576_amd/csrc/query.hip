@@ -133,116 +133,136 @@ __device__ __forceinline__ Bucket bucket_by_row(const uint64_t *__restrict__ a, 
 // band finds its bucket (kRowTeam: 16 lanes a band), the buckets' entries are
 // spread over the threads and mark their polygons, the bits are counted.
 // kLds: the row is built in LDS and written out for k_emit, else in place.
-// dense: only the queries that the sparse passes left.  Bound: the latency of
-// the searches' dependent reads.  100,000 polygons, 32 bands, 1,000 queries 53
+// Bound: the latency of the searches' dependent reads.  100,000 polygons, 32 bands, 1,000 queries 53
 // us for the whole lookup and 10,000 253, against 85 and 573 with a wavefront a
 // (query, band) and the rows cleared, marked and counted in memory.
 constexpr int kRowThreads = 256, kRowTeam = 1024;
 template <bool kLds, int kThreads>
-__global__ __launch_bounds__(kThreads) void k_mark_row(const uint64_t *__restrict__ skeys,
-                                                          const int32_t *__restrict__ sids, int64_t n_entries,
-                                                          const uint64_t *__restrict__ qkeys, int64_t nq, int32_t b,
-                                                          uint32_t *bitmap, int64_t words,
-                                                          int64_t *__restrict__ counts,
-                                                          const int32_t *__restrict__ dense)
+__device__ __forceinline__ void mark_row(const uint64_t *__restrict__ skeys, const int32_t *__restrict__ sids,
+                                         int64_t n_entries, const uint64_t *__restrict__ qkeys, int64_t q, int32_t b,
+                                         uint32_t *bitmap, int64_t words, int64_t *__restrict__ counts)
 {
     extern __shared__ uint32_t s_row[];
     __shared__ int64_t s_base[kThreads + 1], s_lo[kThreads], s_w[kThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int64_t q = blockIdx.x; q < nq; q += gridDim.x) {
-        if (dense && !dense[q]) continue;
-        uint32_t *row = bitmap + q * words;
-        uint32_t *bits = kLds ? s_row : row;
-        for (int64_t i = tid; i < words; i += kThreads) bits[i] = 0u;
-        for (int32_t t0 = 0; t0 < b; t0 += kThreads) {
-            const int32_t t = t0 + tid;
-            int64_t lo = 0, hi = 0;
-            if constexpr (kThreads == kRowTeam) {
-                // few queries: the searches' latency is the launch's
-                const int l16 = tid & 15, row_shift = lane & 48, count = min(kThreads, b - t0);
-                for (int r = tid >> 4; r < count; r += kThreads / 16) {
-                    const Bucket k = bucket_by_row(skeys, n_entries, qkeys[q * b + t0 + r], l16, row_shift);
-                    if (l16 == 0) {
-                        s_lo[r] = k.lo;
-                        s_base[r] = k.hi - k.lo;
-                    }
-                }
-                __syncthreads();
-                if (t < b) {
-                    lo = s_lo[tid];
-                    hi = lo + s_base[tid];
-                }
-            } else if (t < b) {
-                const uint64_t key = qkeys[q * b + t];
-                lo = lower_bound_interp(skeys, n_entries, key);
-                hi = bucket_end(skeys, n_entries, key, lo);
-            }
-            const int64_t incl = wave_incl_scan64(hi - lo);
-            if (lane == 63) s_w[wave] = incl;
-            __syncthreads();
-            int64_t at = incl - (hi - lo);
-            for (int w = 0; w < wave; w++) at += s_w[w];
-            s_base[tid] = at;
-            s_lo[tid] = lo;
-            if (tid == kThreads - 1) s_base[kThreads] = at + (hi - lo);
-            __syncthreads();
-            const int64_t total = s_base[kThreads];
-            const int top = min(kThreads, b - t0) - 1;
-            constexpr int kU = 4;                   // entries in flight a thread
-            for (int64_t j0 = tid; j0 < total; j0 += kThreads * kU) {
-                int32_t ent[kU];
-                int band[kU];
-    #pragma unroll
-                for (int u = 0; u < kU; u++) {
-                    const int64_t j = j0 + kThreads * u;
-                    ent[u] = -1;
-                    band[u] = 0;
-                    if (j < total) {
-                        int l = 0, h = top;         // the last band with s_base[l] <= j
-                        while (l < h) {
-                            const int mid = (l + h + 1) >> 1;
-                            if (s_base[mid] <= j) l = mid;
-                            else h = mid - 1;
-                        }
-                        ent[u] = sids[s_lo[l] + (j - s_base[l])];   // entry p*b + t'
-                        band[u] = t0 + l;
-                    }
-                }
-    #pragma unroll
-                for (int u = 0; u < kU; u++) {
-                    const int32_t id = ent[u] >= 0 ? ent[u] / b : 0;
-                    if (ent[u] >= 0 && ent[u] - id * b == band[u]) atomicOr(&bits[id >> 5], 1u << (id & 31));
+    uint32_t *row = bitmap + q * words;
+    uint32_t *bits = kLds ? s_row : row;
+    for (int64_t i = tid; i < words; i += kThreads) bits[i] = 0u;
+    for (int32_t t0 = 0; t0 < b; t0 += kThreads) {
+        const int32_t t = t0 + tid;
+        int64_t lo = 0, hi = 0;
+        if constexpr (kThreads == kRowTeam) {
+            // few queries: the searches' latency is the launch's
+            const int l16 = tid & 15, row_shift = lane & 48, count = min(kThreads, b - t0);
+            for (int r = tid >> 4; r < count; r += kThreads / 16) {
+                const Bucket k = bucket_by_row(skeys, n_entries, qkeys[q * b + t0 + r], l16, row_shift);
+                if (l16 == 0) {
+                    s_lo[r] = k.lo;
+                    s_base[r] = k.hi - k.lo;
                 }
             }
             __syncthreads();
+            if (t < b) {
+                lo = s_lo[tid];
+                hi = lo + s_base[tid];
+            }
+        } else if (t < b) {
+            const uint64_t key = qkeys[q * b + t];
+            lo = lower_bound_interp(skeys, n_entries, key);
+            hi = bucket_end(skeys, n_entries, key, lo);
         }
-        int64_t c = 0;
-        if constexpr (kLds) {
-            for (int64_t i = tid; i < words; i += kThreads) {
-                const uint32_t v = s_row[i];
-                row[i] = v;
-                c += __popc(v);
-            }
-        } else {
-            constexpr int kC = 8;                   // words in flight a thread
-            for (int64_t i0 = tid; i0 < words; i0 += kThreads * kC) {
-                uint32_t v[kC];
-#pragma unroll
-                for (int u = 0; u < kC; u++) {
-                    const int64_t i = i0 + kThreads * u;
-                    v[u] = __hip_atomic_load(&row[i < words ? i : i0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-#pragma unroll
-                for (int u = 0; u < kC; u++) c += i0 + kThreads * u < words ? __popc(v[u]) : 0;
-            }
-        }
-        c = wave_sum_i64(c);
-        if (lane == 0) s_w[wave] = c;
+        const int64_t incl = wave_incl_scan64(hi - lo);
+        if (lane == 63) s_w[wave] = incl;
         __syncthreads();
-        if (tid == 0) {
-            for (int w = 1; w < kThreads / 64; w++) c += s_w[w];
-            counts[q] = c;
+        int64_t at = incl - (hi - lo);
+        for (int w = 0; w < wave; w++) at += s_w[w];
+        s_base[tid] = at;
+        s_lo[tid] = lo;
+        if (tid == kThreads - 1) s_base[kThreads] = at + (hi - lo);
+        __syncthreads();
+        const int64_t total = s_base[kThreads];
+        const int top = min(kThreads, b - t0) - 1;
+        constexpr int kU = 4;                   // entries in flight a thread
+        for (int64_t j0 = tid; j0 < total; j0 += kThreads * kU) {
+            int32_t ent[kU];
+            int band[kU];
+#pragma unroll
+            for (int u = 0; u < kU; u++) {
+                const int64_t j = j0 + kThreads * u;
+                ent[u] = -1;
+                band[u] = 0;
+                if (j < total) {
+                    int l = 0, h = top;         // the last band with s_base[l] <= j
+                    while (l < h) {
+                        const int mid = (l + h + 1) >> 1;
+                        if (s_base[mid] <= j) l = mid;
+                        else h = mid - 1;
+                    }
+                    ent[u] = sids[s_lo[l] + (j - s_base[l])];   // entry p*b + t'
+                    band[u] = t0 + l;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kU; u++) {
+                const int32_t id = ent[u] >= 0 ? ent[u] / b : 0;
+                if (ent[u] >= 0 && ent[u] - id * b == band[u]) atomicOr(&bits[id >> 5], 1u << (id & 31));
+            }
         }
+        __syncthreads();
+    }
+    int64_t c = 0;
+    if constexpr (kLds) {
+        for (int64_t i = tid; i < words; i += kThreads) {
+            const uint32_t v = s_row[i];
+            row[i] = v;
+            c += __popc(v);
+        }
+    } else {
+        constexpr int kC = 8;                   // words in flight a thread
+        for (int64_t i0 = tid; i0 < words; i0 += kThreads * kC) {
+            uint32_t v[kC];
+#pragma unroll
+            for (int u = 0; u < kC; u++) {
+                const int64_t i = i0 + kThreads * u;
+                v[u] = __hip_atomic_load(&row[i < words ? i : i0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int u = 0; u < kC; u++) c += i0 + kThreads * u < words ? __popc(v[u]) : 0;
+        }
+    }
+    c = wave_sum_i64(c);
+    if (lane == 0) s_w[wave] = c;
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < kThreads / 64; w++) c += s_w[w];
+        counts[q] = c;
+    }
+}
+
+// Every query, a workgroup each, with rows in LDS.
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_mark_row(const uint64_t *__restrict__ skeys,
+                                                          const int32_t *__restrict__ sids, int64_t n_entries,
+                                                          const uint64_t *__restrict__ qkeys, int32_t b,
+                                                          uint32_t *bitmap, int64_t words,
+                                                          int64_t *__restrict__ counts)
+{
+    mark_row<true, kThreads>(skeys, sids, n_entries, qkeys, blockIdx.x, b, bitmap, words, counts);
+}
+
+// The queries that the sparse passes left (dense), taken in turn (a kernel of
+// its own: as one, the loop's registers cost the other a tenth).
+template <bool kLds, int kThreads>
+__global__ __launch_bounds__(kThreads) void k_mark_dense(const uint64_t *__restrict__ skeys,
+                                                         const int32_t *__restrict__ sids, int64_t n_entries,
+                                                         const uint64_t *__restrict__ qkeys, int64_t nq, int32_t b,
+                                                         uint32_t *bitmap, int64_t words,
+                                                         int64_t *__restrict__ counts,
+                                                         const int32_t *__restrict__ dense)
+{
+    for (int64_t q = blockIdx.x; q < nq; q += gridDim.x) {
+        if (!dense[q]) continue;
+        mark_row<kLds, kThreads>(skeys, sids, n_entries, qkeys, q, b, bitmap, words, counts);
         __syncthreads();
     }
 }
@@ -871,8 +891,10 @@ polymh_status allow_rows()
         return set_error(POLYMH_EDEVICE, "query: no current device");
     std::lock_guard<std::mutex> lk(mu);
     if (done[dev]) return POLYMH_OK;
-    for (const void *f : {reinterpret_cast<const void *>(&k_mark_row<true, kRowTeam>),
-                          reinterpret_cast<const void *>(&k_mark_row<true, kRowThreads>)}) {
+    for (const void *f : {reinterpret_cast<const void *>(&k_mark_row<kRowTeam>),
+                          reinterpret_cast<const void *>(&k_mark_row<kRowThreads>),
+                          reinterpret_cast<const void *>(&k_mark_dense<true, kRowTeam>),
+                          reinterpret_cast<const void *>(&k_mark_dense<true, kRowThreads>)}) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRowMost * 4);
         if (e != hipSuccess) return set_error(POLYMH_EDEVICE, "query: rows on chip: %s", hipGetErrorString(e));
     }
@@ -889,13 +911,12 @@ polymh_status lookup_counts(const uint64_t *skeys, const int32_t *sids, int64_t 
         const bool team = nq <= cu_count();
         if (const polymh_status st = words * 4 > 40 << 10 ? allow_rows() : POLYMH_OK) return st;
         if (team)
-            hipLaunchKernelGGL((k_mark_row<true, kRowTeam>), dim3((unsigned)nq), dim3(kRowTeam), (size_t)words * 4, s,
-                               skeys, sids, words > 0 ? n_entries : 0, qkeys, nq, b, w.bitmap, words, counts,
-                               (const int32_t *)nullptr);
+            hipLaunchKernelGGL((k_mark_row<kRowTeam>), dim3((unsigned)nq), dim3(kRowTeam), (size_t)words * 4, s,
+                               skeys, sids, words > 0 ? n_entries : 0, qkeys, b, w.bitmap, words, counts);
         else
-            hipLaunchKernelGGL((k_mark_row<true, kRowThreads>), dim3((unsigned)nq), dim3(kRowThreads),
-                               (size_t)words * 4, s, skeys, sids, words > 0 ? n_entries : 0, qkeys, nq, b, w.bitmap, words,
-                               counts, (const int32_t *)nullptr);
+            hipLaunchKernelGGL((k_mark_row<kRowThreads>), dim3((unsigned)nq), dim3(kRowThreads),
+                               (size_t)words * 4, s, skeys, sids, words > 0 ? n_entries : 0, qkeys, b, w.bitmap, words,
+                               counts);
         return POLYMH_OK;
     }
     // A list is sorted by a block while its row does not fit LDS (4 M polygons,
@@ -915,20 +936,20 @@ polymh_status lookup_counts(const uint64_t *skeys, const int32_t *sids, int64_t 
         if (const polymh_status st = allow_rows()) return st;
         const int64_t at_once = rows_at_once(words);
         if (at_once <= cu_count())
-            hipLaunchKernelGGL((k_mark_row<true, kRowTeam>), dim3((unsigned)std::min(nq, at_once)), dim3(kRowTeam),
+            hipLaunchKernelGGL((k_mark_dense<true, kRowTeam>), dim3((unsigned)std::min(nq, at_once)), dim3(kRowTeam),
                                (size_t)words * 4, s, skeys, sids, n_entries, qkeys, nq, b, w.bitmap, words, counts,
                                w.dense);
         else
-            hipLaunchKernelGGL((k_mark_row<true, kRowThreads>), dim3((unsigned)std::min(nq, at_once)),
+            hipLaunchKernelGGL((k_mark_dense<true, kRowThreads>), dim3((unsigned)std::min(nq, at_once)),
                                dim3(kRowThreads), (size_t)words * 4, s, skeys, sids, n_entries, qkeys, nq, b, w.bitmap,
                                words, counts, w.dense);
     } else if (nq <= 4 * cu_count()) {
         // few workgroups a CU: 4 M polygons, a list of 32,000: 209 us, with 256
         // threads 342
-        hipLaunchKernelGGL((k_mark_row<false, kRowTeam>), dim3((unsigned)nq), dim3(kRowTeam), 0, s, skeys, sids,
+        hipLaunchKernelGGL((k_mark_dense<false, kRowTeam>), dim3((unsigned)nq), dim3(kRowTeam), 0, s, skeys, sids,
                            n_entries, qkeys, nq, b, w.bitmap, words, counts, w.dense);
     } else {
-        hipLaunchKernelGGL((k_mark_row<false, kRowThreads>), dim3((unsigned)nq), dim3(kRowThreads), 0, s, skeys, sids,
+        hipLaunchKernelGGL((k_mark_dense<false, kRowThreads>), dim3((unsigned)nq), dim3(kRowThreads), 0, s, skeys, sids,
                            n_entries, qkeys, nq, b, w.bitmap, words, counts, w.dense);
     }
     return POLYMH_OK;
