@@ -169,10 +169,12 @@ def train(scorer: Scorer, sig, feats, left, right, label, epochs: int = 3, batch
 
 
 def predict_pairs(scorer: Scorer, lsig, lfeat, rsig, rfeat, li, ri, chunk: int = 1 << 18):
-    """Predicted J of every (li, ri) pair: by the fused inference where the
-    signatures and weights are 16-byte aligned (it reads them so; 200,000 pairs
-    172 us, 391 with the input rows and activations in memory), else in
-    chunks of `chunk` rows."""
+    """Predicted J of every (li, ri) pair.  The fused inference takes them all
+    in one launch, whatever `chunk` is, where the signatures and weights are
+    16-byte aligned (200,000 pairs 190 us, 390 with the input rows and
+    activations in memory).  Else, or with a `chunk` of 0 or less (an error, as
+    ever), `chunk` is the most rows whose inputs and activations are held in
+    memory at a time."""
     R = li.numel()
     if chunk > 0 and R > 0 and not any(t.data_ptr() % 16 for t in (lsig, rsig, scorer.wbf16)):
         return pm.mlp_predict_pairs(lsig, lfeat, rsig, rfeat, li, ri, scorer.params, scorer.wbf16)
