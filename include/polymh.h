@@ -291,8 +291,9 @@ polymh_status polymh_index_build(const uint64_t *keys, int64_t n, int32_t b, voi
  *   contents overwritten): a bitmap row of n_data bits per query plus two
  *   words per query.  Where that row fits on chip it is built there and
  *   written out; else a query's bucket entries are gathered into its row and
- *   sorted on chip, up to 16384 of them, and a query with more sets bits in
- *   its row (chosen by the sizes n_data and nq).  The lists are the same
+ *   sorted on chip, up to 4096 of them (16384 where a row does not fit the
+ *   chip), and a query with more sets bits in a row (chosen by the sizes
+ *   n_data and nq).  The lists are the same
  *   either way.  Stream-ordered except the
  *   capacity check above.
  */
